@@ -84,10 +84,19 @@ enum {
 /* Sweep schedules (see dp_eval_set_schedule). */
 enum {
   DP_SCHED_AUTO = 0,      /* the autotuned choice (default) */
-  DP_SCHED_LEVEL = 1,     /* one launch per level (an SP-only forward with
-                             few columns: one per two levels of fixed cells,
-                             the second level recomputing the pins the first
-                             drives; bit for bit the same results) */
+  DP_SCHED_LEVEL = 1,     /* launches in stream order: a simulation, and a
+                             sweep of many (net, column) pairs, one launch per
+                             level (an SP-only forward with few columns: one
+                             per two levels of fixed cells, the second level
+                             recomputing the pins the first drives); an
+                             SP-only or reverse sweep of at most 2^22 (net,
+                             column) pairs and 64 columns as one launch whose
+                             gates wait for their own inputs.  Bit for bit the
+                             same results.  Should such a wait give up (after
+                             seconds; it cannot while the device makes
+                             progress), that sweep's outputs are NaN and the
+                             eval's next host synchronization returns
+                             DP_E_HIP */
   DP_SCHED_GRAPH = 2,     /* the same launches captured once into HIP graphs,
                              one per forward sweep and one per reverse sweep
                              of dp_backward / dp_backward_columns (forward

@@ -274,10 +274,52 @@ dp_status grid_barrier(dp_eval *ev, dp::GridBarrier *out) {
   return DP_OK;
 }
 
+// --- dataflow sweeps (launch_sp_flow, launch_bwd_flow)
+// Allocate what the eval's dataflow sweeps need (once; before any capture).
+dp_status ensure_flow(dp_eval *ev) {
+  DP_TRY(ev->flow.alloc(dp::kFlowWords * sizeof(uint32_t)));
+  if (!ev->flow_report) {
+    void *p = nullptr;
+    DP_HIP_TRY(hipHostMalloc(&p, sizeof(uint32_t)));
+    ev->flow_report = static_cast<uint32_t *>(p);
+    *ev->flow_report = 0u;
+  }
+  return DP_OK;
+}
+
+// Whether a sweep over C columns of the eval runs as one dataflow launch
+// (once ensure_flow has run).
+bool flows(const dp_eval *ev, int32_t C) {
+  const dp_design *d = ev->d;
+  return ev->flow_report && ev->schedule != DP_SCHED_PERSISTENT &&
+         dp::flow_fits(view(d), d->depth, std::max(C, ev->B), d->n_edges);
+}
+
+// Every buffer of a reverse sweep over C columns (before any capture).
+dp_status ensure_reverse_buffers(dp_eval *ev, int32_t C) {
+  const dp_design *d = ev->d;
+  DP_TRY(ensure_flow(ev));
+  DP_TRY(ev->contrib.alloc(std::max<size_t>((size_t)d->n_edges * C * sizeof(float), 16)));
+  if (flows(ev, C)) {
+    DP_TRY(ev->seed.alloc(std::max<size_t>((size_t)d->n_nets * C * sizeof(float), 16)));
+    DP_TRY(ev->part.alloc(std::max<size_t>((size_t)ev->B * d->pins * d->n_gates * sizeof(float), 16)));
+  }
+  return DP_OK;
+}
+
+dp::FlowCtl flow_ctl(const dp_eval *ev) {
+  return dp::FlowCtl{ev->flow.as<uint32_t>(), ev->flow_report, 0, ev->d->ctx->n_cu};
+}
+
 // At a host synchronization of the eval (its stream idle): whether a
-// persistent sweep since the last check had a barrier wait give up.  Reads
-// and clears the report word.
+// persistent or dataflow sweep since the last check had a wait give up.
+// Reads and clears the report words.
 dp_status barrier_status(dp_eval *ev) {
+  if (ev->flow_report && *static_cast<volatile uint32_t *>(ev->flow_report) != 0u) {
+    *ev->flow_report = 0u;
+    return fail(DP_E_HIP, "a sweep's wait for its own results gave up; that sweep's outputs are NaN "
+                          "and not a result");
+  }
   if (!ev->barrier_pending) return DP_OK;
   uint32_t rep = 0;
   uint32_t *w = ev->barrier.as<uint32_t>() + dp::kBarrierReport;
@@ -294,7 +336,7 @@ dp_status barrier_status(dp_eval *ev) {
 // Synchronize the eval's stream when a persistent sweep is unchecked, then
 // report it (host-output calls end here).
 dp_status sync_and_check(dp_eval *ev) {
-  if (!ev->barrier_pending) return DP_OK;
+  if (!ev->barrier_pending && !ev->flow_report) return DP_OK;
   DP_HIP_TRY(hipStreamSynchronize(ev->stream()));
   return barrier_status(ev);
 }
@@ -330,7 +372,7 @@ int64_t sp_sweep_launches(const dp_design *d, int32_t B) {
 // Kernel launches of one forward sweep (what a captured graph would hold).
 int64_t forward_launches(const dp_eval *ev, const ChunkPlan *pl) {
   const int64_t depth = ev->d->depth + ev->d->split_levels;
-  if (!pl) return sp_sweep_launches(ev->d, ev->B) + 2;
+  if (!pl) return (flows(ev, ev->B) ? 2 : sp_sweep_launches(ev->d, ev->B)) + 2;
   return (int64_t)pl->n_groups * pl->n_chunks * (depth + 1) + 4 + (markov(ev) ? 1 : 0) +
          ev->d->cell_levels;  // the library cells' SP launches
 }
@@ -339,6 +381,7 @@ int64_t forward_launches(const dp_eval *ev, const ChunkPlan *pl) {
 dp_status ensure_forward_buffers(dp_eval *ev, const ChunkPlan *pl) {
   const dp_design *d = ev->d;
   const size_t nb = (size_t)d->n_nets * ev->B;
+  DP_TRY(ensure_flow(ev));
   if (ev->prm.mode == DP_HYBRID) DP_TRY(ev->beta.alloc(nb * sizeof(float)));
   const int32_t cols = ev->B * s_prime(ev);
   DP_TRY(ev->power_partial.alloc(
@@ -413,8 +456,15 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
     double bytes = 0.0;
     for (int32_t l = 1; l <= d->depth; ++l) bytes += sp_level_bytes(d, l, ev->B);
     SpanGuard sg(ev, SPAN_SP, bytes, prof && d->depth > 0,
-                 ev->schedule == DP_SCHED_PERSISTENT ? 1 : sp_sweep_launches(d, ev->B));
-    if (ev->schedule == DP_SCHED_PERSISTENT) {
+                 ev->schedule == DP_SCHED_PERSISTENT || flows(ev, ev->B)
+                     ? 1
+                     : sp_sweep_launches(d, ev->B));
+    if (flows(ev, ev->B)) {
+      const dp::FlowCtl ctl = flow_ctl(ev);
+      DP_HIP_TRY(dp::launch_sp_flow(
+          dp::SpFlow{g, sp, d->level_dev.as<int32_t>(), ev->B, d->depth}, d->max_level_width,
+          d->has_cell_gates, ctl, s));
+    } else if (ev->schedule == DP_SCHED_PERSISTENT) {
       dp::SpLevel lv{sp, ev->B, 0, 0};
       dp::GridBarrier bar;
       DP_TRY(grid_barrier(ev, &bar));
@@ -727,6 +777,15 @@ dp_status enqueue_backward(dp_eval *ev, const dp::BwdArgs &ba, float *dst) {
   const dp::GraphView g = view(d);
   double bwd_bytes = 0.0;
   for (int32_t l = d->depth; l >= 1; --l) bwd_bytes += bwd_level_bytes(d, l, ba.C);
+  if (flows(ev, ba.C)) {
+    const dp::FlowCtl ctl = flow_ctl(ev);
+    SpanGuard sg(ev, SPAN_BWD, bwd_bytes, ev->profiling && d->depth > 0, 1);
+    DP_HIP_TRY(dp::launch_bwd_flow(
+        dp::BwdFlow{g, ba, dst, ev->seed.as<float>(), ev->part.as<float>(),
+                    d->level_dev.as<int32_t>(), d->n_edges, d->depth},
+        std::max(d->max_level_width, d->n_pi), d->has_cell_gates, ctl, s));
+    return DP_OK;
+  }
   if (ev->schedule == DP_SCHED_PERSISTENT) {
     dp::GridBarrier bar;
     DP_TRY(grid_barrier(ev, &bar));
@@ -798,6 +857,7 @@ dp_eval::~dp_eval() {
   if (graph_bwd) (void)hipGraphExecDestroy(graph_bwd);
   if (graph_fb) (void)hipGraphExecDestroy(graph_fb);
   if (capture_stream_owned) (void)hipStreamDestroy(capture_stream_owned);
+  if (flow_report) (void)hipHostFree(flow_report);
   if (coop_stream) {
     (void)hipStreamSynchronize(coop_stream);
     (void)hipStreamDestroy(coop_stream);
@@ -839,8 +899,11 @@ dp_status dp_ctx_create(int32_t device, void *hip_stream, dp_ctx **out) {
     return fail(DP_E_INVALID, "dp_ctx_create: no device " + std::to_string(device));
   DP_HIP_TRY(hipSetDevice(device));
   DP_TRY(dp::static_scratch_init(device));  // once per device: dp_forward_static's scratch
+  int n_cu = 0;
+  DP_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device));
   auto *c = new dp_ctx();
   c->device = device;
+  c->n_cu = n_cu;
   if (hip_stream == (void *)hipStreamLegacy) {
     c->stream = nullptr;  // the null stream
   } else if (hip_stream) {
@@ -1333,7 +1396,7 @@ static dp_status run_backward(dp_eval *ev, const float *grad_power, int per_colu
     w = ev->w.as<float>();
   }
   if (dpi) {
-    DP_TRY(ev->contrib.alloc(std::max<size_t>((size_t)d->n_edges * C * sizeof(float), 16)));
+    DP_TRY(ensure_reverse_buffers(ev, C));
     const dp::BwdArgs ba = backward_args(ev, w, per_column, C);
     float *dst = dpi;
     const size_t bytes = (size_t)C * d->n_pi * sizeof(float);
@@ -1390,7 +1453,7 @@ dp_status dp_power_gradients(dp_eval *ev, float *dpower_dsp, float *score, int32
   DP_HIP_TRY(hipSetDevice(d->ctx->device));
   hipStream_t s = ev->stream();
   const int32_t B = ev->B;
-  DP_TRY(ev->contrib.alloc(std::max<size_t>((size_t)d->n_edges * B * sizeof(float), 16)));
+  DP_TRY(ensure_reverse_buffers(ev, B));
   DP_TRY(ev->pi_out.alloc(std::max<size_t>((size_t)B * d->n_pi * sizeof(float), 16)));
   DevBuf lam;
   DP_TRY(lam.alloc((size_t)B * d->n_nets * sizeof(float)));
@@ -1427,7 +1490,7 @@ dp_status dp_power_virus(dp_eval *ev, int32_t steps, double eta, uint8_t *v0, fl
   const int32_t B = ev->B;
   const size_t nb = (size_t)d->n_nets * B, pb = (size_t)d->n_pi * B;
   DP_TRY(ensure_forward_buffers(ev, nullptr));
-  DP_TRY(ev->contrib.alloc(std::max<size_t>((size_t)d->n_edges * B * sizeof(float), 16)));
+  DP_TRY(ensure_reverse_buffers(ev, B));
   DP_TRY(ev->pi_out.alloc(std::max<size_t>(pb * sizeof(float), 16)));
   // the proxy is the power without kappa: upstream weight 1 / kappa per column
   DP_TRY(ev->w.alloc(std::max<size_t>((size_t)B * sizeof(float), 16)));
@@ -1531,7 +1594,7 @@ dp_status dp_forward_backward_columns(dp_eval *ev, float *power, float *dpower_d
   hipStream_t s = ev->stream();
   DP_TRY(ensure_forward_buffers(ev, pl));
   const int32_t C = ev->B * s_prime(ev);
-  DP_TRY(ev->contrib.alloc(std::max<size_t>((size_t)d->n_edges * C * sizeof(float), 16)));
+  DP_TRY(ensure_reverse_buffers(ev, C));
   const size_t dpi_bytes = (size_t)C * d->n_pi * sizeof(float);
   float *dst = on_device ? dpower_dpi : nullptr;
   if (!dst) {  // host output, or none: the sweep writes the staging buffer
@@ -1971,7 +2034,7 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
     DP_TRY(ensure_forward_buffers(ev, hybrid(ev) ? &plans[i] : nullptr));
     cost[i] = forward_launches(ev, hybrid(ev) ? &plans[i] : nullptr);
     if (backward) {
-      DP_TRY(ev->contrib.alloc(std::max<size_t>((size_t)d->n_edges * ev->B * sizeof(float), 16)));
+      DP_TRY(ensure_reverse_buffers(ev, ev->B));
       DP_TRY(ev->pi_out.alloc(std::max<size_t>((size_t)ev->B * d->n_pi * sizeof(float), 16)));
       cost[i] += d->depth + d->split_levels + 1;
     }

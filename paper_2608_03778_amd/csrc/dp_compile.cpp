@@ -272,8 +272,8 @@ dp_status compile_design(dp_ctx *ctx, const dp_netlist *nl, int32_t n_cells,
   }
   // slot[j][g'] = where pin j of gate g' sits in its source net's fan-out
   // list: the reverse sweep writes a pin's contribution there, so a net sums
-  // one contiguous range
-  std::vector<int32_t> slot((size_t)pins_rows * G, 0);
+  // one contiguous range (-1: the gate has no such pin)
+  std::vector<int32_t> slot((size_t)pins_rows * G, -1);
   for (int64_t e = 0; e < n_edges; ++e) slot[rev_edge[e]] = (int32_t)e;
   d->lvl_pins.assign(depth + 1, 0);
   d->lvl_fanout.assign(depth + 1, 0);

@@ -45,9 +45,12 @@ struct dp_eval {
   dp::DevBuf barrier;        // persistent sweeps: grid-barrier words (dp::kBarrierAlloc)
   bool barrier_pending = false;      // a persistent sweep ran since the report word was read
   double barrier_limit_us = 1000.0;  // a barrier wait gives up after this long without progress
+  dp::DevBuf flow;                   // dataflow sweeps: control words (dp::kFlowWords)
+  uint32_t *flow_report = nullptr;   // pinned host word: a dataflow sweep's wait gave up
   // reverse state
   dp::DevBuf w;              // [B*S'] upstream weights
   dp::DevBuf contrib;        // [n_edges][C]
+  dp::DevBuf seed, part;     // dataflow reverse sweeps: seeds [C][n_nets], partials [B][pins][G]
   dp::DevBuf pi_out;         // [C][n_pi] staging for host outputs
   dp::DevBuf stage[8];       // host-output staging
   // A stream of its own (serving lanes); null = the context's stream.

@@ -74,6 +74,7 @@ uint64_t truth_table(const CellCode &cc);
 // destroyed in any order.
 struct dp_ctx {
   int device = 0;
+  int32_t n_cu = 0;               // compute units of the device
   hipStream_t stream = nullptr;   // stream calls enqueue on
   hipStream_t owned = nullptr;    // stream created by the library, if any
   std::atomic<int> refs{1};

@@ -23,7 +23,7 @@ struct GraphView {
   const int32_t *in;        // [pins][G] (unused pins alias pin 0)
   const int32_t *rev_ptr;   // [n_nets + 1]
   const int32_t *rev_edge;  // [n_edges]
-  const int32_t *slot;      // [pins][G] fan-out position of each pin
+  const int32_t *slot;      // [pins][G] fan-out position of each pin (-1: no such pin)
   const uint16_t *code;     // [n_cells][kCellMaxCode] library cells' stack code (op | arg << 8), padded
   const int32_t *cell;      // [n_cells][3]: code offset, length, inputs
   const uint64_t *tt;       // [n_cells] truth tables: bit m = output for input pattern m
@@ -286,6 +286,65 @@ hipError_t launch_sp_persistent(const GraphView &g, const SpLevel &lv, const int
 hipError_t launch_bwd_persistent(const GraphView &g, const BwdArgs &a, const int32_t *level_ptr,
                                  int32_t depth, int64_t max_items, float *pi_out,
                                  GridBarrier bar, hipStream_t s);
+// Dataflow sweeps (one launch per sweep, no level barrier; see the kernels):
+// each column by a team of workgroups of one XCD, after a launch that arms
+// the slots the sweep writes (the gate rows of sp; every entry of contrib)
+// and clears the control words.
+constexpr int kFlowDies = 8;       // XCDs that blocks are dealt to in turn
+constexpr int kFlowXcds = 16;      // values of the XCD id register
+constexpr int kFlowTeams = 8;      // teams per XCD at most
+constexpr int kFlowMaxCols = 64;   // columns of a sweep at most
+constexpr int kFlowLevels = 1024;  // depth + 2 of a design at most (the level table in LDS)
+constexpr int kFlowSlots = kFlowMaxCols + 1;  // columns one team may claim, and "none left"
+// control words: per team a line with its registration count and (16 words
+// on) its closed member count; the columns each team claimed, in order; the
+// next unclaimed column; the stop flag
+constexpr int kFlowReg = 0;
+constexpr int kFlowNext = kFlowReg + 32 * kFlowXcds * kFlowTeams;
+constexpr int kFlowStop = kFlowNext + 32;
+constexpr int kFlowClaims = kFlowStop + 32;
+constexpr int kFlowWords = kFlowClaims + kFlowXcds * kFlowTeams * kFlowSlots;
+struct FlowCtl {
+  uint32_t *words;    // device, [kFlowWords]
+  uint32_t *report;   // host-visible: set when a wait gave up
+  uint32_t expected;  // workgroups a team's leader waits for (set by the launcher)
+  int32_t n_cu;       // compute units of the device
+};
+// Whether a sweep of C columns is one for these kernels: within their 32-bit
+// offsets and tables, and few enough (net, column) pairs that its levels are
+// bound by latency.  Forward / reverse sweep by level launches against
+// dataflow, in us: 1M gates, 1 column 225 / 409 against 125 / 239, 4 columns
+// 235 / 517 against 172 / 328, 8 columns 238 / 532 against 243 / 521, 16
+// columns 245 / 546 against 487 / 1243; 117K gates, 16 columns 137 / 268
+// against 91 / 160, 32 columns 146 / 267 against 115 / 280, 64 columns
+// 156 / 269 against 237 / 463; 20K gates, 64 columns 95 / 147 against 73 / 84.
+constexpr int64_t kFlowMaxItems = 1 << 22;
+inline bool flow_fits(const GraphView &g, int32_t depth, int32_t C, int64_t n_edges) {
+  return C <= kFlowMaxCols && depth + 2 <= kFlowLevels && g.n_nets < (1 << 24) &&
+         (int64_t)g.n_nets * C <= kFlowMaxItems && n_edges < (1ll << 29);
+}
+struct SpFlow {
+  GraphView g;
+  float *sp;                 // [n_nets][B]
+  const int32_t *level_ptr;  // device copy of the level table
+  int32_t B, depth;
+};
+struct BwdFlow {
+  GraphView g;
+  BwdArgs a;                 // contrib here: [C][n_edges], each in fan-out order
+  float *pi_out;             // [C][n_pi]
+  float *seed;               // scratch [C][n_nets]: the nets' seeds
+  float *part;               // scratch [B][pins][G]: the gates' partial derivatives
+  const int32_t *level_ptr;
+  int64_t n_edges;
+  int32_t depth;
+};
+// widest: gates of the widest level; cells: the design holds library cells.
+hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl ctl, hipStream_t s);
+// The reverse levels and then the PI adjoints; widest also covers the PIs.
+hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl ctl,
+                           hipStream_t s);
+
 // dcap[ext n] = sum_{b,s} w[b][s] x[n][b] size_s(n) and dsize[s][ext g] =
 // sum_b w[b][s] x[out g][b] C_out g, with x = kappa beta TR_model
 // recomputed from SP and beta.

@@ -14,6 +14,7 @@
 // pairs, so every fan-in row is read as contiguous 1 KiB wave-wide accesses.
 
 #include <algorithm>
+#include <type_traits>
 
 #include "dp_kernels.h"
 
@@ -1878,6 +1879,612 @@ __global__ __launch_bounds__(kBlock) void k_bwd_persistent(GraphView g, BwdArgs 
     bwd_pi_item(g, a, pi_out, base + lane, lane, false, kSerialColumnsNoHeavy);
 }
 
+// ---------------------------------------------------------------- dataflow sweeps
+// A whole SP or reverse sweep in one launch and without a level barrier, each
+// query column by a team of workgroups of one XCD: every array slot that the
+// sweep will write holds kArmed (a NaN that no arithmetic here produces)
+// before the launch, a consumer polls the very slots that it reads until none
+// of them is armed, and a producer's store is all the signal there is.
+//
+// What bounds a sweep of few columns is the dependent chain of its levels.  A
+// level launch pays the launch boundary and, with the L2 dropped there, each
+// load round from beyond it: 2.3 us per SP level (two per launch) and 3.4 to
+// 4.3 us per reverse level.  Inside one XCD a value goes from a store to a
+// poll through the one L2 that its CUs share in 180 ns (measured; across XCDs
+// 520 ns, and only with stores that write through).  So a column never leaves
+// its XCD; further columns go to other teams.  SP and reverse sweep of one
+// column, in us: 2K gates 36 and 72 by level launches, 17 and 25 (with 2 and 5
+// for arming) here; 117K gates 132 and 235 against 47 and 86 (2 and 6); 1M
+// gates 234 and 439 against 117 and 229 (5 and 16).
+//
+// Membership: the workgroups of a team register; the first (the leader)
+// waits until the expected number has come, or briefly, and closes the list;
+// whoever registers later leaves.  Items are dealt to the members' waves by
+// rank, every wave takes its items in level order, and only running
+// workgroups are members, so each wait is for work that a running wave will
+// reach: nothing depends on how many workgroups fit on the device beside
+// other streams' work.  As a guard a wait that polls kFlowPolls times (seconds)
+// gives up: it raises the launch's stop flag, which ends every other wait at
+// once, and the host-visible report word, and what it could not compute
+// stays NaN.
+//
+// Polls are agent-scope loads: they go past the L1, which other CUs' stores
+// do not reach, to the L2, where plain stores of the same XCD land.
+//
+// A level is one short turn of a lone wave per SIMD, so its instructions
+// count as much as its latencies: addresses are 32-bit offsets from uniform
+// bases (launch_*_flow refuses larger arrays), and a column's seeds and
+// contributions are contiguous arrays of their own.
+constexpr uint32_t kArmed = 0xFFFFFFFFu;
+constexpr uint32_t kFlowPolls = 1u << 26;
+constexpr uint32_t kFlowClosed = 1u << 31;
+constexpr uint64_t kFlowJoinTicks = 500;  // 5 us of the 100 MHz counter
+constexpr int kFlowThreads = 512;         // threads per workgroup at most
+
+__device__ __forceinline__ bool is_armed(float v) { return __float_as_uint(v) == kArmed; }
+__device__ __forceinline__ float armed() { return __uint_as_float(kArmed); }
+__device__ __forceinline__ uint32_t flow_load(const uint32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Element access by a 32-bit byte offset from a uniform base.
+template <typename T>
+__device__ __forceinline__ T *flow_at(T *base, uint32_t bytes) {
+  using B = std::conditional_t<std::is_const_v<T>, const char, char>;
+  return reinterpret_cast<T *>(reinterpret_cast<B *>(base) + bytes);
+}
+__device__ __forceinline__ float flow_poll(const float *base, uint32_t bytes) {
+  return __hip_atomic_load(flow_at(base, bytes), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// A plain store that the compiler may not split, widen or move past a poll.
+__device__ __forceinline__ void flow_store(float *base, uint32_t bytes, float v) {
+  __hip_atomic_store(flow_at(base, bytes), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// One more poll of a wait: false when the wait has to end.
+__device__ __forceinline__ bool flow_again(const FlowCtl &ctl, uint32_t &polls) {
+  if ((++polls & 63u) != 0u) return true;
+  if (flow_load(ctl.words + kFlowStop) != 0u) return false;
+  if (polls < kFlowPolls) return true;
+  __hip_atomic_store(ctl.words + kFlowStop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(ctl.report, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  return false;
+}
+
+// This workgroup's place in its team.
+struct FlowSeat {
+  uint32_t team, rank, members;  // members == 0: not a member
+};
+
+// Blocks are dealt to the XCDs in turn, so block / kFlowDies counts an XCD's
+// blocks, `expected` of them to a team.  (Were they dealt otherwise, teams
+// would be smaller or larger, and still of one XCD each.)
+__device__ __forceinline__ FlowSeat flow_join(const FlowCtl &ctl) {
+  __shared__ FlowSeat seat;
+  if (threadIdx.x == 0) {
+    uint32_t x;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
+    const uint32_t sub = min(blockIdx.x / kFlowDies / ctl.expected, (uint32_t)kFlowTeams - 1);
+    const uint32_t team = (x & (kFlowXcds - 1)) * kFlowTeams + sub;
+    uint32_t *reg = ctl.words + kFlowReg + team * 32, *open = reg + 16;
+    const uint32_t r = __hip_atomic_fetch_add(reg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t n = 0;
+    if (r == 0) {
+      const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+      while (flow_load(reg) < ctl.expected && __builtin_amdgcn_s_memrealtime() - t0 < kFlowJoinTicks) {
+      }
+      n = __hip_atomic_fetch_or(reg, kFlowClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(open, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (!(r & kFlowClosed)) {
+      uint32_t polls = 0;
+      while ((n = flow_load(open)) == 0u && flow_again(ctl, polls)) {
+      }
+    }
+    seat = FlowSeat{team, r, n};
+  }
+  __syncthreads();
+  return FlowSeat{(uint32_t)__builtin_amdgcn_readfirstlane((int)seat.team),
+                  (uint32_t)__builtin_amdgcn_readfirstlane((int)seat.rank),
+                  (uint32_t)__builtin_amdgcn_readfirstlane((int)seat.members)};
+}
+
+// The k-th column of this team (claimed by its leader from the launch's
+// list), or -1 when the list is used up.  Uniform over the workgroup.
+__device__ __forceinline__ int32_t flow_claim(const FlowCtl &ctl, const FlowSeat &st, int32_t k,
+                                              int32_t n_cols) {
+  __shared__ int32_t col;
+  __syncthreads();  // every wave has read the previous one
+  if (threadIdx.x == 0) {
+    uint32_t *slot = ctl.words + kFlowClaims + st.team * kFlowSlots + k;
+    uint32_t v = 0;
+    if (st.rank == 0) {
+      const uint32_t t = __hip_atomic_fetch_add(ctl.words + kFlowNext, 1u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+      v = t < (uint32_t)n_cols ? t + 2u : 1u;  // 1: none left
+      __hip_atomic_store(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      uint32_t polls = 0;
+      while ((v = flow_load(slot)) == 0u && flow_again(ctl, polls)) {
+      }
+    }
+    col = (int32_t)v - 2;
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(col);
+}
+
+// A wave's walk over the 64-item blocks of a column's levels: block w, w + W,
+// ... of each level in turn, w counted across the members first, so a
+// level's blocks spread over as many CUs as there are.  The level table sits
+// in LDS.
+__shared__ int32_t flow_lv[kFlowLevels];
+
+struct FlowWalk {
+  int32_t w64, W64;   // 64 times this wave's index, 64 times the number of waves
+  int32_t n_pi, depth;
+};
+
+// A block of the walk: its first item is `base` of the n of level l, whose
+// first net is `net` (level 0: the PIs).  n == 0: past the end.
+struct FlowBlock {
+  int32_t l, net, n, base;
+};
+
+// Loads the level table into LDS; every thread calls it, before any claim.
+__device__ __forceinline__ FlowWalk flow_walk(const FlowSeat &st, const int32_t *level_ptr,
+                                              int32_t depth, int32_t n_pi) {
+  for (int32_t i = (int32_t)threadIdx.x; i < depth + 2; i += (int32_t)blockDim.x)
+    flow_lv[i] = level_ptr[i];
+  __syncthreads();
+  const int32_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  return FlowWalk{64 * (wave * (int32_t)st.members + (int32_t)st.rank),
+                  (int32_t)(blockDim.x * st.members), n_pi, depth};
+}
+
+// The first block at or after `q` that has items, levels ascending (DIR 1,
+// up to depth) or descending (DIR -1, down to the PIs).
+template <int DIR>
+__device__ __forceinline__ FlowBlock flow_settle(const FlowWalk &k, FlowBlock q) {
+  while (q.base >= q.n) {
+    if (q.l == (DIR > 0 ? k.depth : 0)) {
+      q.n = 0;
+      return q;
+    }
+    q.l += DIR;
+    const int32_t a = __builtin_amdgcn_readfirstlane(flow_lv[q.l]);  // (entry 0 is 0)
+    const int32_t b = __builtin_amdgcn_readfirstlane(flow_lv[q.l + 1]);
+    q.net = q.l > 0 ? k.n_pi + a : 0;
+    q.n = q.l > 0 ? b - a : k.n_pi;
+    q.base = k.w64;
+  }
+  return q;
+}
+template <int DIR>
+__device__ __forceinline__ FlowBlock flow_next(const FlowWalk &k, FlowBlock q) {
+  q.base += k.W64;
+  return flow_settle<DIR>(k, q);
+}
+
+// A lane's net of a block; lanes past the level's end get its last net, so
+// that what they load is in range, and are not active.
+struct FlowItem {
+  uint32_t net;
+  int32_t active;
+};
+__device__ __forceinline__ FlowItem flow_item(const FlowBlock &q) {
+  const int32_t at = q.base + (int32_t)(threadIdx.x & 63);
+  return FlowItem{(uint32_t)(q.net + min(at, q.n - 1)), at < q.n ? 1 : 0};
+}
+
+// The rows of a per-pin table at gate gi; rows past the design's widest gate
+// read its last row (a design has three rows at least).  Addresses without a
+// branch: a fetch must leave no value to be merged, or the wave would wait
+// for it on the spot.
+template <int N>
+__device__ __forceinline__ void flow_pins(const int32_t *tab, const GraphView &g, uint32_t gi,
+                                          uint32_t (&out)[N]) {
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+    out[j] = (uint32_t)*flow_at(tab + (int64_t)(j < 3 ? j : min(j, g.pins - 1)) * g.G, 4 * gi);
+}
+
+template <bool CELLS>
+constexpr int kFlowPins = CELLS ? kCellMaxIn : 3;
+
+// Byte offset of net's entry in an [n_nets][B] array, column col (both
+// below 2^24).
+__device__ __forceinline__ uint32_t flow_off(uint32_t net, int32_t B, int32_t col) {
+  return 4 * (__umul24(net, (uint32_t)B) + (uint32_t)col);
+}
+
+// ---- SP
+template <bool CELLS>
+struct SpFlowFetch {
+  int32_t op;
+  uint32_t pin[kFlowPins<CELLS>];
+};
+template <bool CELLS>
+__device__ __forceinline__ SpFlowFetch<CELLS> sp_flow_fetch(const GraphView &g, uint32_t gi) {
+  SpFlowFetch<CELLS> f;
+  f.op = *flow_at(g.op, gi);
+  flow_pins(g.in, g, gi, f.pin);
+  return f;
+}
+
+// What an item's rule reads: its pins' probabilities, polled until none is
+// armed.
+template <bool CELLS>
+struct SpFlowIn {
+  int32_t op;
+  int32_t ok;  // 0: the wait gave up
+  float v[kFlowPins<CELLS>];
+};
+template <bool CELLS>
+__device__ __forceinline__ SpFlowIn<CELLS> sp_flow_poll(const FlowCtl &ctl, const SpFlow &t,
+                                                        int32_t col, const FlowItem &it,
+                                                        const SpFlowFetch<CELLS> &f) {
+  constexpr int N = kFlowPins<CELLS>;
+  SpFlowIn<CELLS> x;
+  x.op = f.op;
+  x.ok = 1;
+  int n = arity_of(f.op);
+  if (CELLS && f.op >= kCellBase) n = t.g.cell[3 * (f.op - kCellBase) + 2];
+  if (!it.active) n = 0;
+  uint32_t at[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) at[j] = flow_off(f.pin[j], t.B, col);
+#pragma unroll
+  for (int j = 0; j < N; ++j) x.v[j] = j < n ? flow_poll(t.sp, at[j]) : 0.0f;
+  uint32_t polls = 0;
+  for (;;) {
+    bool wait = false;
+#pragma unroll
+    for (int j = 0; j < N; ++j) wait = wait || is_armed(x.v[j]);
+    if (!wait) break;
+    if (!flow_again(ctl, polls)) {
+      x.ok = 0;
+      break;
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if (is_armed(x.v[j])) x.v[j] = flow_poll(t.sp, at[j]);
+  }
+  return x;
+}
+
+template <bool CELLS>
+__device__ __forceinline__ void sp_flow_store(const SpFlow &t, int32_t col, const FlowItem &it,
+                                              const SpFlowIn<CELLS> &x) {
+  if (!it.active) return;
+  const uint32_t out = flow_off(it.net, t.B, col);
+  if constexpr (CELLS) {
+    if (x.op >= kCellBase) {
+      const LaneCode lc = lane_code(t.g, x.op);
+      f2 in[kCellMaxIn];
+#pragma unroll
+      for (int j = 0; j < kCellMaxIn; ++j) in[j] = sp_load(x.v[j]);
+      const float r = settle(cell_sp(lc, in));
+      flow_store(t.sp, out, x.ok ? r : armed());
+      return;
+    }
+  }
+  const int k = arity_of(x.op);
+  const f2 z = f2{0.0f, 1.0f};
+  const float r = settle(sp_rule(x.op, sp_load(x.v[0]), k > 1 ? sp_load(x.v[1]) : z,
+                                 k > 2 ? sp_load(x.v[2]) : z));
+  flow_store(t.sp, out, x.ok ? r : armed());
+}
+
+// Two blocks of the wave's walk are in hand at a time.  Vector loads return
+// in order, so a poll waits for whatever was issued before it: the fetch of
+// the next but one block goes out between this block's poll and its store,
+// where it overlaps the time the store takes to reach the next level.
+template <bool CELLS>
+__device__ __forceinline__ void sp_flow_column(const FlowCtl &ctl, const SpFlow &t,
+                                               const FlowWalk &k, int32_t col) {
+  const uint32_t n_pi = (uint32_t)t.g.n_pi;
+  using Fetch = SpFlowFetch<CELLS>;
+  FlowBlock q = flow_settle<1>(k, FlowBlock{0, 0, 0, 0});
+  if (q.n == 0) return;
+  FlowItem ia = flow_item(q);
+  Fetch fa = sp_flow_fetch<CELLS>(t.g, ia.net - n_pi);
+  q = flow_next<1>(k, q);
+  int left = q.n;  // nonzero: a block is in hand after the current one
+  FlowItem ib = q.n ? flow_item(q) : ia;
+  Fetch fb = sp_flow_fetch<CELLS>(t.g, ib.net - n_pi);
+  if (q.n) q = flow_next<1>(k, q);
+  auto turn = [&](FlowItem &i, Fetch &f) {  // false: that was the last block
+    const SpFlowIn<CELLS> x = sp_flow_poll<CELLS>(ctl, t, col, i, f);
+    const FlowItem it = i;
+    const bool more = left != 0;
+    i = q.n ? flow_item(q) : i;  // (past the end: the same block again)
+    f = sp_flow_fetch<CELLS>(t.g, i.net - n_pi);
+    left = q.n;
+    sp_flow_store<CELLS>(t, col, it, x);
+    if (q.n) q = flow_next<1>(k, q);
+    return more;
+  };
+  while (turn(ia, fa) && turn(ib, fb)) {
+  }
+}
+
+template <bool CELLS>
+__global__ __launch_bounds__(kFlowThreads) void k_sp_flow(FlowCtl ctl, SpFlow t) {
+  const FlowSeat st = flow_join(ctl);
+  if (st.members == 0) return;
+  const FlowWalk k = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi);
+  for (int32_t i = 0; i < kFlowSlots; ++i) {
+    const int32_t col = flow_claim(ctl, st, i, t.B);
+    if (col < 0) return;
+    sp_flow_column<CELLS>(ctl, t, k, col);
+  }
+}
+
+// ---- reverse: levels depth .. 1, then the PIs (level 0)
+// The sweep's chain takes only what has to wait: a launch of the whole chip
+// before it (k_bwd_arm) forms every net's seed and every gate's partial
+// derivatives, which no level waits for, so an item loads one run of values
+// in place of its net's probability, beta, capacitance and sizes and its
+// fan-in's probabilities (random lines that one XCD would fetch alone) and
+// takes no cell rule.
+template <int N>
+struct BwdFlowFetch {
+  uint32_t e0, e1;  // the net's fan-out range
+  int32_t slot[N];  // -1: no such pin
+  float d[N];       // partial derivatives
+  float seed, beta;
+};
+
+// What is uniform over a column.
+struct BwdFlowCol {
+  int32_t c, b;             // reverse column and its SP column
+  const float *seed;        // [n_nets]
+  const float *part;        // [pins][G]
+  float *contrib;           // [n_edges]
+  __amdgpu_buffer_rsrc_t contrib_rsrc;
+};
+
+template <int N>
+__device__ __forceinline__ BwdFlowFetch<N> bwd_flow_fetch(const BwdFlow &t, const BwdFlowCol &u,
+                                                          const FlowItem &i) {
+  const GraphView &g = t.g;
+  const BwdArgs &a = t.a;
+  BwdFlowFetch<N> f;
+  // a PI reads gate 0's rows and ignores them
+  const uint32_t g4 = 4 * (uint32_t)max((int32_t)i.net - g.n_pi, 0), n4 = 4 * i.net;
+  f.e0 = (uint32_t)*flow_at(g.rev_ptr, n4);
+  f.e1 = (uint32_t)*flow_at(g.rev_ptr + 1, n4);
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const int64_t row = (int64_t)(j < 3 ? j : min(j, g.pins - 1)) * g.G;
+    f.slot[j] = *flow_at(g.slot + row, g4);
+    f.d[j] = *flow_at(u.part + row, g4);
+  }
+  f.seed = *flow_at(u.seed, n4);
+  // STE alone takes the net's beta here; otherwise the seed again, unused
+  const bool ste = a.ste && a.beta;
+  f.beta = *flow_at(ste ? a.beta : u.seed,
+                    ste && !a.beta_shared ? flow_off(i.net, a.B, u.b) : n4);
+  return f;
+}
+
+// The eight entries from e on, in two 16-byte loads past the L1 (entries
+// beyond the array read as zero), until none of the first m (any m <= 8, or
+// more for all) is armed; then their sum in entry order, as strand_fold.
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+constexpr int kBufferSc1 = 16;  // cache policy of a buffer load: agent scope
+__device__ __forceinline__ float flow_strand(const FlowCtl &ctl, const BwdFlowCol &u, uint32_t e,
+                                             int32_t m, int32_t &ok) {
+  float v[kStrand];
+  uint32_t polls = 0;
+  for (;;) {
+    const u4 lo = __builtin_amdgcn_raw_buffer_load_b128(u.contrib_rsrc, (int)(4 * e), 0, kBufferSc1);
+    const u4 hi =
+        __builtin_amdgcn_raw_buffer_load_b128(u.contrib_rsrc, (int)(4 * e + 16), 0, kBufferSc1);
+    asm volatile("" ::: "memory");  // each round loads again
+    uint32_t worst = 0;
+#pragma unroll
+    for (int i = 0; i < kStrand; ++i) {
+      const uint32_t b = i < m ? (i < 4 ? lo[i] : hi[i - 4]) : 0u;
+      v[i] = __uint_as_float(b);
+      worst = max(worst, b);  // kArmed is the largest
+    }
+    if (worst != kArmed) break;
+    if (!flow_again(ctl, polls)) {
+      ok = 0;
+      break;
+    }
+  }
+  return strand_fold(v, m);
+}
+
+// The canonical sum of a net's contributions (strands of kStrand, their sums
+// in order).  Lane by lane while every net of the wave has at most
+// kFlowSerial entries left; the longer ranges (one net in a thousand) take
+// the whole wave, one strand per lane.  Every lane of the wave calls it.
+constexpr int32_t kFlowSerial = 32;
+__device__ __forceinline__ float flow_pull(const FlowCtl &ctl, const BwdFlowCol &u, uint32_t e0,
+                                           int32_t n, int lane, int32_t &ok) {
+  float acc = 0.0f;
+  const bool heavy = n > kFlowSerial;
+  const int32_t mine = heavy ? 0 : n;
+  for (int32_t s = 0; __ballot(s < mine); s += kStrand)
+    if (s < mine) {
+      const float sum = flow_strand(ctl, u, e0 + (uint32_t)s, mine - s, ok);
+      acc = s == 0 ? sum : acc + sum;
+    }
+  for (uint64_t hh = __ballot(heavy); hh; hh &= hh - 1) {
+    const int h = __builtin_ctzll(hh);
+    const uint32_t h0 = (uint32_t)__builtin_amdgcn_readlane((int)e0, h);
+    const int32_t hn = __builtin_amdgcn_readlane(n, h);
+    const int32_t strands = (hn + kStrand - 1) / kStrand;
+    float total = 0.0f;
+    for (int32_t base = 0; base < strands; base += 64) {
+      const int32_t j = base + lane;
+      float v = 0.0f;
+      if (j < strands) v = flow_strand(ctl, u, h0 + (uint32_t)(j * kStrand), hn - j * kStrand, ok);
+      const int32_t vb = __float_as_int(v), m = min(64, strands - base);
+      for (int32_t t = 0; t < m; ++t) {
+        const float x = __int_as_float(__builtin_amdgcn_readlane(vb, t));
+        total = (base == 0 && t == 0) ? x : total + x;
+      }
+    }
+    if (lane == h) acc = total;
+  }
+  return acc;
+}
+
+// The end of an item whose contributions are summed: its adjoint, and what
+// it leaves on its fan-in slots (a gate) or the gradient (a PI).
+template <int N>
+__device__ __forceinline__ void bwd_flow_store(const BwdFlow &t, const BwdFlowCol &u, bool gate,
+                                               int32_t ok, const FlowItem &it,
+                                               const BwdFlowFetch<N> &f, float pulled) {
+  const BwdArgs &a = t.a;
+  if (!it.active) return;
+  float lam = f.seed + pulled;
+  if (a.ste && a.beta) lam *= f.beta;
+  if (!ok) lam = armed();
+  if (!gate && a.fixed && a.fixed[it.net]) lam = 0.0f;  // excluded from the gradients
+  if (a.lam) a.lam[(int64_t)u.c * (a.n_pi + a.G) + it.net] = lam;
+  if (!gate) {
+    t.pi_out[(int64_t)u.c * a.n_pi + it.net] = lam;
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+    if ((j < 3 || j < t.g.pins) && f.slot[j] >= 0)
+      flow_store(u.contrib, 4 * (uint32_t)f.slot[j], lam * f.d[j]);
+}
+
+// As sp_flow_column: the fetch of the next but one block goes out between a
+// block's pull and its stores.
+template <int N>
+__device__ __forceinline__ void bwd_flow_column(const FlowCtl &ctl, const BwdFlow &t,
+                                                const FlowWalk &k, int32_t c) {
+  using Fetch = BwdFlowFetch<N>;
+  BwdFlowCol u;
+  u.c = c;
+  u.b = c / t.a.cdiv;
+  u.seed = t.seed + (int64_t)c * t.g.n_nets;
+  u.part = t.part + (int64_t)u.b * t.g.pins * t.g.G;
+  u.contrib = t.a.contrib + (int64_t)c * t.n_edges;
+  u.contrib_rsrc = __builtin_amdgcn_make_buffer_rsrc(u.contrib, 0, (int)(4 * t.n_edges), 0x00020000);
+  FlowBlock q = flow_settle<-1>(k, FlowBlock{t.depth + 1, 0, 0, 0});
+  if (q.n == 0) return;
+  // (a level holds gates only, or the PIs only: the kind is uniform)
+  bool ga = q.l > 0;
+  FlowItem ia = flow_item(q);
+  Fetch fa = bwd_flow_fetch<N>(t, u, ia);
+  q = flow_next<-1>(k, q);
+  int left = q.n;  // nonzero: a block is in hand after the current one
+  bool gb = q.n ? q.l > 0 : ga;
+  FlowItem ib = q.n ? flow_item(q) : ia;
+  Fetch fb = bwd_flow_fetch<N>(t, u, ib);
+  if (q.n) q = flow_next<-1>(k, q);
+  const int lane = (int)(threadIdx.x & 63);
+  int32_t ok = 1;
+  auto turn = [&](bool &gate_, FlowItem &i, Fetch &fetched) {
+    const float pulled = flow_pull(ctl, u, fetched.e0,
+                                   i.active ? (int32_t)(fetched.e1 - fetched.e0) : 0, lane, ok);
+    const bool gate = gate_, more = left != 0;
+    const FlowItem it = i;
+    const Fetch f = fetched;
+    gate_ = q.n ? q.l > 0 : gate_;
+    i = q.n ? flow_item(q) : i;  // (past the end: the same block again)
+    fetched = bwd_flow_fetch<N>(t, u, i);
+    left = q.n;
+    bwd_flow_store<N>(t, u, gate, ok, it, f, pulled);
+    if (q.n) q = flow_next<-1>(k, q);
+    return more;
+  };
+  while (turn(ga, ia, fa) && turn(gb, ib, fb)) {
+  }
+}
+
+template <bool CELLS>
+__global__ __launch_bounds__(kFlowThreads) void k_bwd_flow(FlowCtl ctl, BwdFlow t) {
+  const FlowSeat st = flow_join(ctl);
+  if (st.members == 0) return;
+  const FlowWalk k = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi);
+  for (int32_t i = 0; i < kFlowSlots; ++i) {
+    const int32_t c = flow_claim(ctl, st, i, t.a.C);
+    if (c < 0) return;
+    bwd_flow_column<kFlowPins<CELLS>>(ctl, t, k, c);
+  }
+}
+
+// Arms the n slots a sweep will write and clears its control words.  Four
+// dwords per thread, each wave-wide store one contiguous run.
+constexpr int kArmPer = 4;
+__device__ __forceinline__ void flow_arm(uint32_t *p, int64_t n, uint32_t *words, int32_t n_words,
+                                         uint32_t block) {
+  const int64_t i0 = (int64_t)block * (kBlock * kArmPer) + threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < kArmPer; ++k) {
+    const int64_t i = i0 + k * kBlock;
+    if (i < n)
+      p[i] = kArmed;
+    else if (i - n < n_words)
+      words[i - n] = 0u;
+  }
+}
+__global__ __launch_bounds__(kBlock) void k_flow_arm(uint32_t *p, int64_t n, uint32_t *words) {
+  flow_arm(p, n, words, kFlowWords, blockIdx.x);
+}
+
+// Before a reverse sweep, in three runs of blocks: arms the contributions,
+// writes every net's seed [C][n_nets], and every gate's partial derivatives
+// [B][pins][G].
+template <bool CELLS>
+__global__ __launch_bounds__(kBlock) void k_bwd_arm(BwdFlow t, uint32_t *words, uint32_t arm_blocks,
+                                                    uint32_t seed_blocks) {
+  const GraphView &g = t.g;
+  const BwdArgs &a = t.a;
+  if (blockIdx.x < arm_blocks) {
+    flow_arm(reinterpret_cast<uint32_t *>(a.contrib), t.n_edges * a.C, words, kFlowWords, blockIdx.x);
+    return;
+  }
+  if (blockIdx.x < arm_blocks + seed_blocks) {
+    const int64_t idx = (int64_t)(blockIdx.x - arm_blocks) * kBlock + threadIdx.x;
+    if (idx >= (int64_t)g.n_nets * a.C) return;
+    const int32_t c = (int32_t)(idx / g.n_nets), net = (int32_t)(idx - (int64_t)c * g.n_nets);
+    const int32_t b = c / a.cdiv;
+    const float beta = a.beta ? a.beta[a.beta_shared ? (int64_t)net : (int64_t)net * a.B + b] : 1.0f;
+    t.seed[idx] = seed_of(a, net, c, b, sp_load(a.sp[(int64_t)net * a.B + b]), beta, a.cap[net]);
+    return;
+  }
+  const int64_t idx = (int64_t)(blockIdx.x - arm_blocks - seed_blocks) * kBlock + threadIdx.x;
+  if (idx >= (int64_t)g.G * a.B) return;
+  const int32_t b = (int32_t)(idx / g.G), gi = (int32_t)(idx - (int64_t)b * g.G);
+  constexpr int N = kFlowPins<CELLS>;
+  const int op = g.op[gi];
+  int32_t pin[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) pin[j] = pin_row(g.in, g, j)[gi];
+  float *part = t.part + (int64_t)b * g.pins * g.G + gi;
+  f2 x[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) x[j] = sp_load(a.sp[(int64_t)pin[j] * a.B + b]);
+  if constexpr (CELLS) {
+    if (op >= kCellBase) {
+      const LaneCode lc = lane_code(g, op);
+      float d[kCellMaxIn];
+      cell_partials(lc, x, d);
+#pragma unroll
+      for (int j = 0; j < kCellMaxIn; ++j)
+        if (j < lc.nin) part[(int64_t)j * g.G] = d[j];
+      return;
+    }
+  }
+  const int k = arity_of(op);
+  const f2 z = f2{0.0f, 1.0f};
+  float d0, d1, d2;
+  sp_partials(op, x[0], k > 1 ? x[1] : z, k > 2 ? x[2] : z, d0, d1, d2);
+  part[0] = d0;
+  if (k > 1) part[g.G] = d1;
+  if (k > 2) part[2 * (int64_t)g.G] = d2;
+}
+
 // dP/dC_n = sum_{b,s} w[b][s] kappa beta TR_model s_s(drv n);
 // dP/ds[s][g] = sum_b w[b][s] kappa beta TR_model C of g's output net.
 // x = kappa beta TR_model of net n in column b, recomputed as the forward's
@@ -2388,6 +2995,70 @@ hipError_t launch_bwd_persistent(const GraphView &g, const BwdArgs &a, const int
   GridBarrier gb = bar;
   void *args[] = {&gv, &ba, &lp, &d, &po, &gb};
   return hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(kBlock), args, 0, s);
+}
+
+// Workgroups of a dataflow sweep over C columns: a team gets enough waves for
+// the widest level (64 items each) on as many of an XCD's CUs as there are
+// waves, then more waves per workgroup; columns beyond one per XCD get teams
+// of their own while the waves stay resident together, and queue after that.
+// Blocks go to the XCDs in turn.
+constexpr int64_t kFlowWavesPerCu = 16;
+static void flow_shape(FlowCtl *ctl, int64_t widest, int32_t C, unsigned *grid, unsigned *threads) {
+  const int64_t cus = std::max<int64_t>(1, ctl->n_cu / kFlowDies);
+  const int64_t waves = std::max<int64_t>(1, (widest + 63) / 64);
+  int64_t m = std::min(waves, cus);
+  int64_t wpb = (waves + m - 1) / m;
+  if (wpb > kFlowThreads / 64) {  // a second workgroup per CU
+    wpb = kFlowThreads / 64;
+    m = std::min((waves + wpb - 1) / wpb, 2 * cus);
+  }
+  const int64_t fit = std::max<int64_t>(1, cus * kFlowWavesPerCu / (m * wpb));
+  const int64_t teams = std::min<int64_t>({fit, kFlowTeams, (C + kFlowDies - 1) / kFlowDies});
+  ctl->expected = (uint32_t)m;
+  *grid = (unsigned)(m * kFlowDies * teams);
+  *threads = (unsigned)(64 * wpb);
+}
+
+hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl ctl, hipStream_t s) {
+  if (t.depth <= 0 || t.B <= 0) return hipSuccess;
+  if (!ctl.words || !ctl.report || !flow_fits(t.g, t.depth, t.B, 0)) return hipErrorInvalidValue;
+  const int64_t slots = (int64_t)t.g.G * t.B;  // the gate rows of sp
+  const int64_t ab = (slots + kFlowWords + kBlock * kArmPer - 1) / (kBlock * kArmPer);
+  k_flow_arm<<<(unsigned)ab, kBlock, 0, s>>>(
+      reinterpret_cast<uint32_t *>(t.sp + (int64_t)t.g.n_pi * t.B), slots, ctl.words);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  unsigned grid, threads;
+  flow_shape(&ctl, widest, t.B, &grid, &threads);
+  if (cells)
+    k_sp_flow<true><<<grid, threads, 0, s>>>(ctl, t);
+  else
+    k_sp_flow<false><<<grid, threads, 0, s>>>(ctl, t);
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl ctl,
+                           hipStream_t s) {
+  if (t.a.C <= 0 || t.g.n_nets <= 0) return hipSuccess;
+  if (!ctl.words || !ctl.report || !t.seed || !t.part || !flow_fits(t.g, t.depth, t.a.C, t.n_edges))
+    return hipErrorInvalidValue;
+  const int64_t slots = t.n_edges * t.a.C;
+  const int64_t ab = (slots + kFlowWords + kBlock * kArmPer - 1) / (kBlock * kArmPer);
+  const int64_t sb = ((int64_t)t.g.n_nets * t.a.C + kBlock - 1) / kBlock;
+  const int64_t blocks = ab + sb + ((int64_t)t.g.G * t.a.B + kBlock - 1) / kBlock;
+  if (cells)
+    k_bwd_arm<true><<<(unsigned)blocks, kBlock, 0, s>>>(t, ctl.words, (uint32_t)ab, (uint32_t)sb);
+  else
+    k_bwd_arm<false><<<(unsigned)blocks, kBlock, 0, s>>>(t, ctl.words, (uint32_t)ab, (uint32_t)sb);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  unsigned grid, threads;
+  flow_shape(&ctl, widest, t.a.C, &grid, &threads);
+  if (cells)
+    k_bwd_flow<true><<<grid, threads, 0, s>>>(ctl, t);
+  else
+    k_bwd_flow<false><<<grid, threads, 0, s>>>(ctl, t);
+  return hipGetLastError();
 }
 
 hipError_t launch_grad_export(const GradExportArgs &a, hipStream_t s) {

@@ -140,6 +140,10 @@ hipError_t hipFree(void *ptr) {
   return hipSuccess;
 }
 hipError_t hipHostMalloc(void **ptr, size_t size, unsigned int) { return hipMalloc(ptr, size); }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) {
+  *v = 256;
+  return hipSuccess;
+}
 hipError_t hipHostFree(void *ptr) { return hipFree(ptr); }
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
   if (s && s->cap) {
@@ -571,6 +575,43 @@ hipError_t launch_bwd_persistent(const GraphView &g, const BwdArgs &a, const int
   wr(bar.words, kBarrierWords);
   rd(bar.words + kBarrierReport, 1);
   return launch_bwd_pi(g, a, pi_out, s, nullptr, kNoHeavyCheck);  // its own PI pass
+}
+// Dataflow sweeps: the control words, the report word and every extent of
+// the single-level launches they replace.
+static void flow_ctl_ok(const FlowCtl &c) {
+  wr(c.words, kFlowWords);
+  rd(c.report, 1);
+}
+static void flow_levels_ok(const GraphView &g, const int32_t *level_ptr, int32_t depth,
+                           int64_t widest, bool cells) {
+  rd(level_ptr, depth + 2);
+  for (int32_t l = 1; l <= depth; ++l) {
+    if (level_ptr[l + 1] - level_ptr[l] > widest) fatal("level wider than its sweep");
+    for (int32_t i = level_ptr[l]; i < level_ptr[l + 1]; ++i)
+      if (!cells && g.op[i] >= kCellBase) fatal("library cell in a fixed-cell sweep");
+  }
+}
+hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl ctl,
+                          hipStream_t stream_) {
+  Scope sc_(stream_);
+  flow_ctl_ok(ctl);
+  if (!flow_fits(t.g, t.depth, t.B, 0)) fatal("dataflow sweep out of its range");
+  flow_levels_ok(t.g, t.level_ptr, t.depth, widest, cells);
+  wr(t.sp, (int64_t)t.g.n_nets * t.B);
+  return hipSuccess;
+}
+hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl ctl,
+                           hipStream_t stream_) {
+  Scope sc_(stream_);
+  flow_ctl_ok(ctl);
+  if (!flow_fits(t.g, t.depth, t.a.C, t.n_edges)) fatal("dataflow sweep out of its range");
+  if (t.g.n_pi > widest) fatal("startpoints wider than their sweep");
+  if (t.n_edges != n_edges_of(t.g)) fatal("edge count of a reverse sweep");
+  flow_levels_ok(t.g, t.level_ptr, t.depth, widest, cells);
+  wr(t.seed, (int64_t)t.g.n_nets * t.a.C);
+  wr(t.part, (int64_t)t.a.B * t.g.pins * t.g.G);
+  launch_bwd_level(t.g, t.a, 0, 0, false, stream_, nullptr, kNoHeavyCheck);  // its extents
+  return launch_bwd_pi(t.g, t.a, t.pi_out, stream_, nullptr, kNoHeavyCheck);
 }
 hipError_t launch_sp_multi(const SpSeg *segs, int32_t n_segs, uint32_t blocks, bool cells,
                            hipStream_t st) {
