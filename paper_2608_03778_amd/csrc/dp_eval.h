@@ -23,7 +23,7 @@ struct dp_eval {
   dp::DevBuf sp;             // [n_nets][B]
   dp::DevBuf cap;            // [n_nets] internal
   dp::DevBuf cap_stage;      // [n_nets] caller numbering
-  dp::DevBuf size;           // [S][G] internal gate order
+  dp::DevBuf size;           // [G][S] internal gate order
   dp::DevBuf size_stage;     // [S][G] caller gate order
   dp::DevBuf beta_frozen;    // [n_nets][B]
   dp::DevBuf beta_stage;     // [B][n_nets]

@@ -86,7 +86,7 @@ hipError_t launch_gather_nets_f32(const float *src_ext, const int32_t *int2ext, 
 // [B][n_nets] caller numbering -> [n_nets][B] internal.
 hipError_t launch_import_cols_f32(const float *src, const int32_t *int2ext, float *dst,
                                   int32_t n_nets, int32_t B, hipStream_t s);
-// Sizes [S][G] caller gate numbering -> [S][G] internal gate order.
+// Sizes [S][G] caller gate numbering -> [G][S] internal gate order.
 hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, float *dst, int32_t n_pi,
                                int32_t G, int32_t S, hipStream_t s);
 
@@ -154,7 +154,7 @@ struct PowerArgs {
   const uint32_t *tog;              // [n_nets][B] toggle counts (hybrid), or null
   const float *beta_frozen;         // [n_nets][B], [n_nets] when beta_shared, or null
   int32_t beta_shared;              // one frozen beta for every column
-  const float *cap, *size;          // cap [n_nets] internal; size [S][G] internal or null
+  const float *cap, *size;          // cap [n_nets] internal; size [G][S] internal or null
   int64_t T;                        // simulated words (hybrid)
   float kappa, beta_min, beta_max;
   int32_t mode;                     // DP_MODELED, DP_HYBRID, DP_FROZEN_BETA
@@ -181,7 +181,7 @@ struct BwdArgs {
   const float *beta;          // [n_nets][B], [n_nets] when beta_shared, or null (beta = 1)
   const float *cap;           // [n_nets] internal
   const float *w;             // [B][S'] (null = 1)
-  const float *size;          // [S][G] internal, or null (all 1)
+  const float *size;          // [G][S] internal, or null (all 1)
   float *contrib;             // [n_edges][C], in fan-out (reader) order
   float *lam;                 // [C][n_nets] internal: every net's adjoint, or null
   const uint8_t *fixed;       // [n_pi]: nonzero = excluded from the gradients (0), or null
@@ -355,7 +355,7 @@ struct GradExportArgs {
   float kappa;
   const float *cap;           // [n_nets]
   const float *w;             // [B][S'] or null
-  const float *size;          // [S][G] internal or null
+  const float *size;          // [G][S] internal or null
   const int32_t *int2ext;
   int32_t n_pi, n_nets, G, B, S;
   int32_t paired;             // column b uses size row b

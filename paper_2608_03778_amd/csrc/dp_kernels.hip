@@ -316,14 +316,33 @@ __global__ __launch_bounds__(kBlock) void k_import_cols(const float *__restrict_
   dst[idx] = src[(int64_t)b * n_nets + int2ext[n]];
 }
 
+// Sizes [S][G] in caller gate order -> [G][S] in internal order: the kernels
+// that read them have a net's size vectors in consecutive lanes (with [S][G]
+// the per-(b, s) reverse level read 64 lines per wave for its sizes alone).
+// A block takes 64 gates x 32 size vectors through LDS: gathers along a row of
+// the caller's array, stores along a row of the result.
+constexpr int32_t kSizeGates = 64, kSizeVecs = 32;
 __global__ __launch_bounds__(kBlock) void k_import_sizes(const float *__restrict__ src,
                                                           const int32_t *__restrict__ int2ext,
                                                           float *__restrict__ dst, int32_t n_pi,
                                                           int32_t G, int32_t S) {
-  int64_t idx = gidx();
-  if (idx >= (int64_t)G * S) return;
-  int32_t s = (int32_t)(idx / G), g = (int32_t)(idx - (int64_t)s * G);
-  dst[idx] = src[(int64_t)s * G + (int2ext[n_pi + g] - n_pi)];
+  __shared__ float tile[kSizeGates][kSizeVecs + 1];
+  const int32_t g_tiles = (G + kSizeGates - 1) / kSizeGates;
+  const int32_t g0 = (int32_t)(blockIdx.x % g_tiles) * kSizeGates;
+  const int32_t s0 = (int32_t)(blockIdx.x / g_tiles) * kSizeVecs;
+  const int32_t gl = (int32_t)threadIdx.x & 63, sl = (int32_t)threadIdx.x >> 6;
+  if (g0 + gl < G) {
+    const int32_t e = int2ext[n_pi + g0 + gl] - n_pi;
+#pragma unroll
+    for (int k = 0; k < kSizeVecs / kWavesPerBlock; ++k) {
+      const int32_t s = s0 + sl + k * kWavesPerBlock;
+      if (s < S) tile[gl][sl + k * kWavesPerBlock] = src[(int64_t)s * G + e];
+    }
+  }
+  __syncthreads();
+  const int32_t ns = min(kSizeVecs, S - s0), ng = min(kSizeGates, G - g0);
+  for (int32_t i = (int32_t)threadIdx.x; i < ng * ns; i += kBlock)
+    dst[(int64_t)(g0 + i / ns) * S + s0 + i % ns] = tile[i / ns][i % ns];
 }
 
 // ---------------------------------------------------------------- SP level
@@ -1046,7 +1065,7 @@ __global__ __launch_bounds__(kPowerThreads) void k_power_sp(PowerArgs a, int32_t
         if constexpr (MODE == 1) aux[k] = a.tog[idx];
         if constexpr (MODE == 2)
           aux[k] = __float_as_uint(a.beta_frozen[a.beta_shared ? (int64_t)n : idx]);
-        sv[k] = (sized && n >= a.n_pi) ? a.size[(int64_t)b * a.G + max(n - a.n_pi, 0)] : 1.0f;
+        sv[k] = (sized && n >= a.n_pi) ? a.size[(int64_t)max(n - a.n_pi, 0) * a.S + b] : 1.0f;
       }
 #pragma unroll
       for (int k = 0; k < kPowerBatch; ++k) {
@@ -1089,71 +1108,112 @@ __device__ __forceinline__ double block_sum_d(double v, double *lds) {
 }
 
 // Many size vectors (S > 0, not paired): P[b][s] = sum_n X[n][b] Y[n][s]
-// with X[n][b] = kappa beta TR_model and Y[n][s] = C_n s_s(drv n) is a small dense product
-// (B x N) (N x S).  A block owns a 32 x 64 (b, s) tile and one slab of nets;
-// X and Y slabs are staged through LDS and each thread accumulates 8 outputs
-// in double.  Partials [slab][b][s] are summed over slabs in a fixed order.
-constexpr int32_t kTileB = 32, kTileS = 64, kSlabNets = 2048, kStage = 64;
+// with X[n][b] = kappa beta TR_model and Y[n][s] = C_n s_s(drv n), both
+// float, their products and sums in double: a (B x N)(N x S) contraction on
+// the FP64 matrix cores.  A wave takes a slab of nets and MB x MS tiles of 16
+// columns b and 16 size vectors s; it loads both operands straight from
+// memory (16 consecutive b, or s, of four consecutive nets per load), sixteen
+// nets' loads in flight, so the operands need no LDS.  Partials
+// [slab][b][s] are summed over slabs in a fixed order.  The slab's length
+// depends on the net count alone: about 256 slabs, so that a small (b, s)
+// face still fills the chip (50K nets, 8 x 4: 330 us on 25 blocks of a 32 x 64
+// tile staged through LDS, vector FP64).
+typedef double d4 __attribute__((ext_vector_type(4)));
+inline int32_t power_slab(int32_t n_nets) {
+  return std::min(2048, std::max(64, (n_nets / 256 + 63) / 64 * 64));
+}
 
-__global__ __launch_bounds__(kBlock) void k_power_tiled(PowerArgs a, int32_t n_slabs) {
-  __shared__ float xs[kStage][kTileB];
-  __shared__ float ys[kStage][kTileS + 1];
-  const int32_t tiles_s = (a.S + kTileS - 1) / kTileS;
-  const int32_t tile = blockIdx.x % tiles_s;
-  const int32_t rest = blockIdx.x / tiles_s;
-  const int32_t tiles_b = (a.B + kTileB - 1) / kTileB;
-  const int32_t tb = rest % tiles_b;
-  const int32_t slab = rest / tiles_b;
-  const int32_t b0 = tb * kTileB, s0 = tile * kTileS;
-  const int32_t n_lo = slab * kSlabNets, n_hi = min(n_lo + kSlabNets, a.n_nets);
-  const int tid = threadIdx.x;
-  const int bl = tid % kTileB;          // this thread's b
-  const int sg = tid / kTileB;          // 8 groups of 8 s values
-  double acc[8];
+template <int MB, int MS>
+__global__ __launch_bounds__(kBlock) void k_power_mfma(PowerArgs a, const float *beta,
+                                                       int32_t beta_shared, int32_t n_slabs,
+                                                       int32_t slab_nets) {
+  constexpr int U = 4;  // steps of four nets in flight
+  const int32_t tiles_s = (a.S + 16 * MS - 1) / (16 * MS);
+  const int32_t tiles_b = (a.B + 16 * MB - 1) / (16 * MB);
+  const int32_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t task = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+  if (task >= (int64_t)n_slabs * tiles_b * tiles_s) return;
+  const int32_t ts = (int32_t)(task % tiles_s);
+  const int32_t rest = (int32_t)(task / tiles_s);
+  const int32_t tb = rest % tiles_b, slab = rest / tiles_b;
+  const int32_t n_lo = slab * slab_nets, n_hi = min(n_lo + slab_nets, a.n_nets);
+  const int32_t i = (int32_t)threadIdx.x & 15, kk = ((int32_t)threadIdx.x >> 4) & 3;
+  int32_t b[MB], s[MS];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) acc[j] = 0.0;
-  for (int32_t base = n_lo; base < n_hi; base += kStage) {
-    // stage X[n][b0..b0+31] (x = kappa beta TR_model from SP and beta) and
-    // Y[n][s0..s0+63] for kStage nets
-    for (int e = tid; e < kStage * kTileB; e += kBlock) {
-      const int cb = e % kTileB, r = e / kTileB;  // consecutive lanes walk columns
-      const int32_t n = base + r, b = b0 + cb;
-      float x = 0.0f;
-      if (n < n_hi && b < a.B) {
-        const int64_t idx = (int64_t)n * a.B + b;
-        const f2 pq = sp_load(a.sp[idx]);
+  for (int m = 0; m < MB; ++m) b[m] = tb * 16 * MB + 16 * m + i;
+#pragma unroll
+  for (int m = 0; m < MS; ++m) s[m] = ts * 16 * MS + 16 * m + i;
+  const bool gates = a.G > 0;
+  d4 acc[MB][MS];
+#pragma unroll
+  for (int p = 0; p < MB; ++p)
+#pragma unroll
+    for (int q = 0; q < MS; ++q) acc[p][q] = d4{0.0, 0.0, 0.0, 0.0};
+  for (int32_t base = n_lo; base < n_hi; base += 4 * U) {
+    float v[U][MB], bt[U][MB], sz[U][MS], cap[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {  // every load at a valid address
+      const int32_t n = min(base + 4 * u + kk, n_hi - 1);
+      cap[u] = a.cap[n];
+#pragma unroll
+      for (int m = 0; m < MB; ++m) {
+        const int64_t idx = (int64_t)n * a.B + min(b[m], a.B - 1);
+        v[u][m] = a.sp[idx];
+        bt[u][m] = beta ? beta[beta_shared ? (int64_t)n : idx] : 1.0f;
+      }
+#pragma unroll
+      for (int m = 0; m < MS; ++m)
+        sz[u][m] = gates ? a.size[(int64_t)max(n - a.n_pi, 0) * a.S + min(s[m], a.S - 1)] : 1.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t n = base + 4 * u + kk;
+      double x[MB], y[MS];
+#pragma unroll
+      for (int m = 0; m < MB; ++m) {
+        const f2 pq = sp_load(v[u][m]);
         const float tm = 2.0f * pq.x * pq.y;
-        const float beta = a.mode == 1 ? a.beta[idx] : beta_of(a, idx, n, tm);
-        x = a.kappa * beta * tm;
+        x[m] = n < n_hi && b[m] < a.B ? (double)(a.kappa * bt[u][m] * tm) : 0.0;
       }
-      xs[r][cb] = x;
-    }
-    for (int e = tid; e < kStage * kTileS; e += kBlock) {
-      const int cs = e / kStage, r = e % kStage;  // consecutive lanes walk nets
-      const int32_t n = base + r, s = s0 + cs;
-      float y = 0.0f;
-      if (n < n_hi && s < a.S) {
-        const float sz = n >= a.n_pi ? a.size[(int64_t)s * a.G + (n - a.n_pi)] : 1.0f;
-        y = a.cap[n] * sz;
-      }
-      ys[r][cs] = y;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int r = 0; r < kStage; ++r) {
-      const double x = (double)xs[r][bl];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] = fma(x, (double)ys[r][sg * 8 + j], acc[j]);
+      for (int m = 0; m < MS; ++m)
+        y[m] = n < n_hi && s[m] < a.S ? (double)(cap[u] * (n >= a.n_pi ? sz[u][m] : 1.0f)) : 0.0;
+#pragma unroll
+      for (int p = 0; p < MB; ++p)
+#pragma unroll
+        for (int q = 0; q < MS; ++q)
+          acc[p][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[p], y[q], acc[p][q], 0, 0, 0);
     }
-    __syncthreads();
   }
-  const int32_t b = b0 + bl;
-  if (b < a.B)
+  // register r of a tile holds row 4 r + lane / 16, column lane % 16
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int32_t s = s0 + sg * 8 + j;
-      if (s < a.S) a.partial[((int64_t)slab * a.B + b) * a.S + s] = acc[j];
+  for (int p = 0; p < MB; ++p)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int32_t bb = tb * 16 * MB + 16 * p + 4 * r + kk;
+#pragma unroll
+      for (int q = 0; q < MS; ++q)
+        if (bb < a.B && s[q] < a.S) a.partial[((int64_t)slab * a.B + bb) * a.S + s[q]] = acc[p][q][r];
     }
+}
+
+// The slabs' partials of 16 (b, s) results per block: thread (k, c) sums
+// slabs k, k + 16, ... of result c in order, then a fixed order over k.
+__global__ __launch_bounds__(kBlock) void k_power_slabs(const double *__restrict__ partial,
+                                                        int32_t n_slabs, int32_t n_cols,
+                                                        float *power) {
+  __shared__ double lds[16][16];
+  const int32_t c = (int32_t)threadIdx.x & 15, k = (int32_t)threadIdx.x >> 4;
+  const int32_t col = min((int32_t)blockIdx.x * 16 + c, n_cols - 1);
+  double acc = 0.0;
+#pragma unroll 4
+  for (int32_t j = k; j < n_slabs; j += 16) acc += partial[(int64_t)j * n_cols + col];
+  lds[k][c] = acc;
+  __syncthreads();
+  if (k != 0 || (int32_t)blockIdx.x * 16 + c >= n_cols) return;
+  double r = lds[0][c];
+  for (int32_t j = 1; j < 16; ++j) r += lds[j][c];
+  power[col] = (float)r;
 }
 
 // One block per column: thread t sums chunks t, t + 256, ... in order, then
@@ -1182,19 +1242,19 @@ __device__ __forceinline__ float seed_of(const BwdArgs &a, int32_t n, int32_t c,
   if (a.per_column) {
     const int32_t s = c - b * a.cdiv;
     const float w = a.w ? a.w[c] : 1.0f;
-    const float sz = gate ? a.size[(int64_t)s * a.G + g] : 1.0f;
+    const float sz = gate ? a.size[g * a.S + s] : 1.0f;
     return base * w * sz;
   }
   if (a.paired) {
     const float w = a.w ? a.w[b] : 1.0f;
-    const float sz = gate ? a.size[(int64_t)b * a.G + g] : 1.0f;
+    const float sz = gate ? a.size[g * a.S + b] : 1.0f;
     return base * (w * sz);
   }
   const int32_t Sp = a.S > 0 ? a.S : 1;
   float ws = 0.0f;
   for (int32_t s = 0; s < Sp; ++s) {
     const float w = a.w ? a.w[(int64_t)b * Sp + s] : 1.0f;
-    const float sz = gate ? a.size[(int64_t)s * a.G + g] : 1.0f;
+    const float sz = gate ? a.size[g * a.S + s] : 1.0f;
     ws = fmaf(w, sz, ws);
   }
   return base * ws;
@@ -2519,7 +2579,7 @@ __global__ __launch_bounds__(kCapRows) void k_grad_cap(GradExportArgs a) {
     for (int32_t s = 0; s < Sp; ++s) {
       const int32_t row = a.paired ? b : s;
       const float w = a.w ? a.w[(int64_t)b * Sp + s] : 1.0f;
-      const float sz = gate ? a.size[(int64_t)row * a.G + (n - a.n_pi)] : 1.0f;
+      const float sz = gate ? a.size[(n - a.n_pi) * a.S + row] : 1.0f;
       ws = fmaf(w, sz, ws);
     }
     return ws;
@@ -2582,7 +2642,7 @@ __global__ __launch_bounds__(kBlock) void k_grad_cap_narrow(GradExportArgs a) {
     for (int32_t s = 0; s < Sp; ++s) {
       const int32_t row = a.paired ? b : s;
       const float w = a.w ? a.w[(int64_t)b * Sp + s] : 1.0f;
-      const float sz = gate ? a.size[(int64_t)row * a.G + (n - a.n_pi)] : 1.0f;
+      const float sz = gate ? a.size[(n - a.n_pi) * a.S + row] : 1.0f;
       ws = fmaf(w, sz, ws);
     }
     acc += (double)x_of(a, n, b) * (double)ws;
@@ -2658,10 +2718,11 @@ hipError_t launch_import_cols_f32(const float *src, const int32_t *int2ext, floa
 
 hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, float *dst, int32_t n_pi,
                                int32_t G, int32_t S, hipStream_t s) {
-  const int64_t n = (int64_t)G * S;
-  if (n <= 0) return hipSuccess;
-  if (too_big(n)) return hipErrorInvalidValue;
-  k_import_sizes<<<blocks_for(n), kBlock, 0, s>>>(src, int2ext, dst, n_pi, G, S);
+  if ((int64_t)G * S <= 0) return hipSuccess;
+  const int64_t blocks = (int64_t)((G + kSizeGates - 1) / kSizeGates) *
+                         ((S + kSizeVecs - 1) / kSizeVecs);
+  if (blocks > kMaxBlocks) return hipErrorInvalidValue;
+  k_import_sizes<<<(unsigned)blocks, kBlock, 0, s>>>(src, int2ext, dst, n_pi, G, S);
   return hipGetLastError();
 }
 
@@ -2840,7 +2901,10 @@ int32_t power_chunks(int32_t n_nets) {
 int32_t power_partial_doubles(int32_t n_nets, int32_t B, int32_t S, int32_t paired) {
   const int64_t cols = (int64_t)B * ((S > 0 && !paired) ? S : 1);
   int64_t slabs = power_chunks(n_nets);
-  if (S > 0 && !paired) slabs = std::max<int64_t>(slabs, (n_nets + kSlabNets - 1) / kSlabNets);
+  if (S > 0 && !paired && n_nets > 0) {
+    const int32_t len = power_slab(n_nets);
+    slabs = std::max<int64_t>(slabs, (n_nets + len - 1) / len);
+  }
   return (int32_t)(slabs * cols);
 }
 
@@ -2855,16 +2919,25 @@ hipError_t launch_power(const PowerArgs &a, hipStream_t s) {
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-    const int32_t n_slabs = (a.n_nets + kSlabNets - 1) / kSlabNets;
-    const int64_t blocks = (int64_t)n_slabs * ((a.B + kTileB - 1) / kTileB) *
-                           ((a.S + kTileS - 1) / kTileS);
+    const int32_t len = power_slab(a.n_nets), n_slabs = (a.n_nets + len - 1) / len;
+    const float *beta = a.mode == 1 ? a.beta : a.mode == 2 ? a.beta_frozen : nullptr;
+    const int32_t shared = a.mode == 2 ? a.beta_shared : 0;
+    // two tiles a side where there are that many columns: each operand loaded
+    // feeds two products
+    const int mb = a.B > 16 ? 2 : 1, ms = a.S > 16 ? 2 : 1;
+    const int64_t tasks = (int64_t)n_slabs * ((a.B + 16 * mb - 1) / (16 * mb)) *
+                          ((a.S + 16 * ms - 1) / (16 * ms));
+    const int64_t blocks = (tasks + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks > kMaxBlocks) return hipErrorInvalidValue;
-    k_power_tiled<<<(unsigned)blocks, kBlock, 0, s>>>(a, n_slabs);
+    using K = void (*)(PowerArgs, const float *, int32_t, int32_t, int32_t);
+    static const K table[2][2] = {{k_power_mfma<1, 1>, k_power_mfma<1, 2>},
+                                  {k_power_mfma<2, 1>, k_power_mfma<2, 2>}};
+    hipLaunchKernelGGL(table[mb - 1][ms - 1], dim3((unsigned)blocks), dim3(kBlock), 0, s, a, beta,
+                       shared, n_slabs, len);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    PowerArgs f = a;
-    f.n_chunks = n_slabs;
-    k_power_final<<<(unsigned)n_cols, kBlock, 0, s>>>(f, n_cols);
+    k_power_slabs<<<(unsigned)((n_cols + 15) / 16), kBlock, 0, s>>>(a.partial, n_slabs, n_cols,
+                                                                   a.power);
     return hipGetLastError();
   }
   if (a.mode == 1 && !a.beta) return hipErrorInvalidValue;

@@ -337,7 +337,8 @@ void rd_graph(const dp::GraphView &g, int32_t g0, int32_t n, bool cells) {
 }  // namespace
 
 namespace dp {
-constexpr int32_t kPowerChunk = 2048, kSlabNets = 2048;
+constexpr int32_t kPowerChunk = 2048;
+static int32_t power_slab(int32_t n) { return std::min(2048, std::max(64, (n / 256 + 63) / 64 * 64)); }
 
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t stream_) {
   Scope sc_(stream_);
@@ -488,7 +489,8 @@ int32_t power_chunks(int32_t n_nets) {
 int32_t power_partial_doubles(int32_t n_nets, int32_t B, int32_t S, int32_t paired) {
   const int64_t cols = (int64_t)B * ((S > 0 && !paired) ? S : 1);
   int64_t slabs = power_chunks(n_nets);
-  if (S > 0 && !paired) slabs = std::max<int64_t>(slabs, (n_nets + kSlabNets - 1) / kSlabNets);
+  if (S > 0 && !paired && n_nets > 0)
+    slabs = std::max<int64_t>(slabs, (n_nets + power_slab(n_nets) - 1) / power_slab(n_nets));
   return (int32_t)(slabs * cols);
 }
 hipError_t launch_power(const PowerArgs &a, hipStream_t stream_) {
