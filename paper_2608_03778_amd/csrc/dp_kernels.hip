@@ -676,14 +676,21 @@ __global__ __launch_bounds__(kSimBlock) void k_sim_level(GraphView g, ChunkView 
 // ---------------------------------------------------------------- stimulus
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds of
 // (c0,c1,c2,c3) -> (hi(M1 c2)^c1^k0, lo(M1 c2), hi(M0 c0)^c3^k1, lo(M0 c0)),
-// key bumped by the Weyl constants between rounds.
+// key bumped by the Weyl constants between rounds.  The words are bound by
+// vector issue: a round is two full products and two three-operand xors
+// (v_bitop3_b32, truth table 0x96; as pairs of v_xor_b32 a call is 60
+// instructions in place of 40; with the shifts below the 1M-gate design's
+// 8,192 x 1,024 words take 200 us, 253 before).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * c.x;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * c.z;
-    c = make_uint4((uint32_t)(p1 >> 32) ^ c.y ^ k0, (uint32_t)p1,
-                   (uint32_t)(p0 >> 32) ^ c.w ^ k1, (uint32_t)p0);
+    c = make_uint4(xor3((uint32_t)(p1 >> 32), c.y, k0), (uint32_t)p1,
+                   xor3((uint32_t)(p0 >> 32), c.w, k1), (uint32_t)p0);
     k0 += 0x9E3779B9u;
     k1 += 0xBB67AE85u;
   }
@@ -698,21 +705,65 @@ __device__ __forceinline__ uint64_t prob_threshold(float p) {
   return (uint64_t)v;
 }
 
+// A bit u < threshold for a threshold up to 2^32 (all, which 32 bits cannot
+// hold, as a mask).
+struct BitThreshold {
+  uint32_t t;
+  uint64_t all;  // ~0: every bit is one
+};
+__device__ __forceinline__ BitThreshold bit_threshold(uint64_t thr) {
+  return BitThreshold{(uint32_t)thr, thr >> 32 ? ~0ull : 0ull};
+}
+
+// Shifts the bit u < t into h from below: a compare and an add with carry
+// (left to the compiler it is a compare, a select, a shift and an or).
+// UNI: t is wave-uniform.
+template <bool UNI>
+__device__ __forceinline__ void shift_in(uint32_t &h, uint32_t u, uint32_t t) {
+  if constexpr (UNI)
+    asm("v_cmp_gt_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+        : "+v"(h) : "v"(u), "s"(t) : "vcc");
+  else
+    asm("v_cmp_gt_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+        : "+v"(h) : "v"(u), "v"(t) : "vcc");
+}
+
 // Word t of PI i: i.i.d. Bernoulli(p) lanes, the temporal-independence case
 // of the Markov stimulus of Sec. III-C; lane j = 4q + l is 1 iff lane l of
-// Philox(t, i, q, 0; seed) is below the threshold.
-__device__ __forceinline__ uint64_t stim_word(uint32_t pi, int64_t t, uint64_t thr, uint32_t k0,
-                                              uint32_t k1) {
-  uint64_t w = 0;
-#pragma unroll 4
-  for (uint32_t q = 0; q < 16; ++q) {
-    const uint4 u = philox4x32_10(make_uint4((uint32_t)t, pi, q, 0u), k0, k1);
-    const uint64_t bits = (uint64_t)((uint64_t)u.x < thr) | ((uint64_t)((uint64_t)u.y < thr) << 1) |
-                          ((uint64_t)((uint64_t)u.z < thr) << 2) |
-                          ((uint64_t)((uint64_t)u.w < thr) << 3);
-    w |= bits << (4 * q);
+// Philox(t, i, q, 0; seed) is below the threshold.  The uniforms do not
+// depend on the column, so one draw serves NT thresholds (query columns);
+// the words are shifted in from their last lane on.
+template <bool UNI, int NT>
+__device__ __forceinline__ void stim_words(uint32_t pi, uint32_t t, const BitThreshold (&thr)[NT],
+                                           uint32_t k0, uint32_t k1, uint64_t (&w)[NT]) {
+#pragma unroll
+  for (int half = 1; half >= 0; --half) {
+    uint32_t h[NT];
+#pragma unroll
+    for (int c = 0; c < NT; ++c) h[c] = 0;
+#pragma unroll 2
+    for (int q = 7; q >= 0; --q) {
+      const uint4 u = philox4x32_10(make_uint4(t, pi, (uint32_t)(8 * half + q), 0u), k0, k1);
+#pragma unroll
+      for (int c = 0; c < NT; ++c) {
+        shift_in<UNI>(h[c], u.w, thr[c].t);
+        shift_in<UNI>(h[c], u.z, thr[c].t);
+        shift_in<UNI>(h[c], u.y, thr[c].t);
+        shift_in<UNI>(h[c], u.x, thr[c].t);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < NT; ++c)
+      w[c] = half ? (uint64_t)h[c] << 32 : (w[c] | h[c]) | thr[c].all;
   }
-  return w;
+}
+
+// The same word with the wave's lanes in place of its bits: lane j draws bit
+// j (one call where stim_words takes sixteen).
+__device__ __forceinline__ uint32_t stim_lane(uint32_t pi, uint32_t t, uint32_t k0, uint32_t k1) {
+  const uint32_t j = threadIdx.x & 63;
+  const uint4 u = philox4x32_10(make_uint4(t, pi, j >> 2, 0u), k0, k1);
+  return (j & 2) ? ((j & 1) ? u.w : u.z) : ((j & 1) ? u.y : u.x);
 }
 
 // ---------------------------------------------------------------- paired SP levels
@@ -860,8 +911,9 @@ __global__ __launch_bounds__(kBlock) void k_markov_words(const float *__restrict
   const float p = sp_load(sp[(int64_t)i * B + b]).x;
   double rise, stay;
   markov_probs(p, tau[(int64_t)b * n_pi + i], rise, stay);
-  const uint64_t thr_p = prob_threshold(p), thr_rise = threshold_d(rise),
-                 thr_stay = threshold_d(stay);
+  const BitThreshold thr_p = bit_threshold(prob_threshold(p)),
+                     thr_rise = bit_threshold(threshold_d(rise)),
+                     thr_stay = bit_threshold(threshold_d(stay));
   const uint32_t si = stream ? (uint32_t)stream[i] : (uint32_t)i;
   uint64_t *orow = out + row * T;
   const BitMap id = BitMap{~0ull, 0ull};
@@ -874,20 +926,10 @@ __global__ __launch_bounds__(kBlock) void k_markov_words(const float *__restrict
       const int64_t t = t0 + (int64_t)lane * kMarkovK + k;
       m[k] = id;
       if (t < T) {
-        const uint64_t ts = t == 0 ? thr_p : thr_stay, tr = t == 0 ? thr_p : thr_rise;
-        uint64_t ms = 0, mu = 0;
-        for (uint32_t q = 0; q < 16; ++q) {
-          const uint4 u = philox4x32_10(make_uint4((uint32_t)t, si, q, 0u), k0, k1);
-          const uint64_t s4 = (uint64_t)((uint64_t)u.x < ts) | ((uint64_t)((uint64_t)u.y < ts) << 1) |
-                              ((uint64_t)((uint64_t)u.z < ts) << 2) |
-                              ((uint64_t)((uint64_t)u.w < ts) << 3);
-          const uint64_t u4 = (uint64_t)((uint64_t)u.x < tr) | ((uint64_t)((uint64_t)u.y < tr) << 1) |
-                              ((uint64_t)((uint64_t)u.z < tr) << 2) |
-                              ((uint64_t)((uint64_t)u.w < tr) << 3);
-          ms |= s4 << (4 * q);
-          mu |= u4 << (4 * q);
-        }
-        m[k] = BitMap{ms, mu};
+        const BitThreshold thr[2] = {t == 0 ? thr_p : thr_stay, t == 0 ? thr_p : thr_rise};
+        uint64_t w[2];
+        stim_words<false>(si, (uint32_t)t, thr, k0, k1, w);
+        m[k] = BitMap{w[0], w[1]};
       }
       f = bitmap_then(f, m[k]);
     }
@@ -908,7 +950,11 @@ __global__ __launch_bounds__(kBlock) void k_markov_words(const float *__restrict
   }
 }
 
-template <int ITERS>
+// PI rows of NC query columns at a time: one draw of uniforms serves them all
+// (32 columns of the 117K-gate sizing sweep, 2,048 PIs x 1,024 words: 1,775 us
+// with a draw per column, 430 us with one per eight).
+// STIM: explicit words (NC 1).
+template <int ITERS, int NC, bool STIM>
 __global__ __launch_bounds__(kBlock) void k_stimulus(int32_t n_pi, ChunkView c, CountView cnt,
                                                      const float *__restrict__ p_rows,
                                                      const uint64_t *__restrict__ stim, int64_t T,
@@ -918,47 +964,86 @@ __global__ __launch_bounds__(kBlock) void k_stimulus(int32_t n_pi, ChunkView c, 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int64_t task = (int64_t)blockIdx.x * kWavesPerBlock + wave;
-  // tasks: (column, PI, run of word pairs), column outermost
-  const int64_t per_col = (int64_t)n_pi * waves_per_row;
-  if (task >= per_col * c.n_cols) return;
-  const int32_t lc = (int32_t)(task / per_col);
-  const int64_t rest = task - (int64_t)lc * per_col;
+  // tasks: (column group, PI, run of word pairs), group outermost
+  const int64_t per_grp = (int64_t)n_pi * waves_per_row;
+  if (task >= per_grp * ((c.n_cols + NC - 1) / NC)) return;
+  const int32_t grp = (int32_t)(task / per_grp);
+  const int64_t rest = task - (int64_t)grp * per_grp;
   const int32_t i = (int32_t)(rest / waves_per_row);
   const int32_t seg = (int32_t)(rest - (int64_t)i * waves_per_row);
-  const int32_t col = cnt.col + lc;
-  const uint64_t thr = prob_threshold(sp_load(p_rows[(int64_t)i * cnt.B + col]).x);
-  const uint64_t *srow = stim ? stim + ((int64_t)lc * n_pi + i) * T : nullptr;
+  const int32_t lc0 = grp * NC, cols = min(NC, c.n_cols - lc0);
   const uint32_t si = stream ? (uint32_t)stream[i] : (uint32_t)i;  // shared stream
-  auto word = [&](int64_t u) -> uint64_t {
+  BitThreshold thr[NC];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const BitThreshold b = bit_threshold(prob_threshold(
+        sp_load(p_rows[(int64_t)i * cnt.B + cnt.col + lc0 + min(k, cols - 1)]).x));
+    thr[k].t = (uint32_t)__builtin_amdgcn_readfirstlane((int)b.t);
+    thr[k].all = __builtin_amdgcn_readfirstlane((int)b.all) ? ~0ull : 0ull;
+  }
+  const uint64_t *srow = STIM ? stim + ((int64_t)lc0 * n_pi + i) * T : nullptr;
+  // every column's word u of the chunk (cycles outside the run: zero)
+  auto words = [&](int64_t u, uint64_t (&w)[NC]) {
     const int64_t t = c.t_first + u;
-    if (t < 0 || t >= T) return 0;
-    return srow ? srow[t] : stim_word(si, t, thr, k0, k1);
-  };
-  uint64_t *out = c.W + (int64_t)lc * c.col_stride + (int64_t)i * c.pitch;
-  const int32_t p_begin = seg * 64 * ITERS;
-  uint64_t carry = p_begin > 0 ? word(2 * (int64_t)p_begin - 1) : 0;
-  uint32_t ones = 0, togs = 0;
-  for (int it = 0; it < ITERS; ++it) {
-    const int32_t p = p_begin + it * 64 + lane;
-    w2 y = w2{0, 0};
-    if (p < c.pairs) {
-      y.x = word(2 * (int64_t)p);
-      y.y = word(2 * (int64_t)p + 1);
+    const bool in = t >= 0 && t < T;
+    if constexpr (STIM) {
+      w[0] = in ? srow[t] : 0;
+    } else {
+      stim_words<true>(si, (uint32_t)t, thr, k0, k1, w);
+      if (!in)
+#pragma unroll
+        for (int k = 0; k < NC; ++k) w[k] = 0;
     }
-    uint64_t prev = __shfl_up(y.y, 1u);
-    if (lane == 0) prev = carry;
-    carry = __shfl(y.y, 63);
-    if (p < c.pairs) {
-      reinterpret_cast<w2 *>(out)[p] = y;
-      count_pair(c, p, y, prev, ones, togs);
+  };
+  uint64_t *out = c.W + (int64_t)lc0 * c.col_stride + (int64_t)i * c.pitch;
+  const int32_t p_begin = seg * 64 * ITERS;
+  uint64_t carry[NC];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) carry[k] = 0;
+  if (p_begin > 0) {  // the word before the run
+    const int64_t t = c.t_first + 2 * (int64_t)p_begin - 1;
+    if (t >= 0 && t < T) {
+      if constexpr (STIM) {
+        carry[0] = srow[t];
+      } else {
+        const uint32_t u = stim_lane(si, (uint32_t)t, k0, k1);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) carry[k] = __ballot(u < thr[k].t) | thr[k].all;
+      }
     }
   }
-  ones = wave_sum(ones);
-  togs = wave_sum(togs);
-  if (lane == 0) {
-    const int64_t o = (int64_t)i * cnt.B + col;
-    if (ones) atomicAdd(cnt.ones + o, ones);
-    if (togs) atomicAdd(cnt.tog + o, togs);
+  uint32_t ones[NC], togs[NC];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) ones[k] = togs[k] = 0;
+  for (int it = 0; it < ITERS; ++it) {
+    const int32_t p = p_begin + it * 64 + lane;
+    uint64_t x[NC], y[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) x[k] = y[k] = 0;
+    if (p < c.pairs) {
+      words(2 * (int64_t)p, x);
+      words(2 * (int64_t)p + 1, y);
+    }
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      uint64_t prev = __shfl_up(y[k], 1u);
+      if (lane == 0) prev = carry[k];
+      carry[k] = __shfl(y[k], 63);
+      if (p < c.pairs && k < cols) {
+        const w2 v = w2{x[k], y[k]};
+        reinterpret_cast<w2 *>(out + k * c.col_stride)[p] = v;
+        count_pair(c, p, v, prev, ones[k], togs[k]);
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const uint32_t o1 = wave_sum(ones[k]), t1 = wave_sum(togs[k]);
+    if (lane == 0 && k < cols) {
+      const int64_t o = (int64_t)i * cnt.B + cnt.col + lc0 + k;
+      if (o1) atomicAdd(cnt.ones + o, o1);
+      if (t1) atomicAdd(cnt.tog + o, t1);
+    }
   }
 }
 
@@ -2817,16 +2902,24 @@ hipError_t launch_stimulus(const GraphView &g, const ChunkView &c, const CountVi
   if (c.n_cols <= 0) return hipSuccess;
   const int iters = tune.iters;
   const int32_t wpr = waves_per_row(c, iters);
-  const int64_t tasks = (int64_t)g.n_pi * wpr * c.n_cols;
+  // columns per draw: as many as there are, up to eight (a lane's registers:
+  // 101 at eight, four waves a SIMD)
+  const int nc = stim || c.n_cols == 1 ? 1 : c.n_cols == 2 ? 2 : c.n_cols <= 4 ? 4 : 8;
+  const int64_t tasks = (int64_t)g.n_pi * wpr * ((c.n_cols + nc - 1) / nc);
   if ((tasks + kWavesPerBlock - 1) / kWavesPerBlock > kMaxBlocks) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)((tasks + kWavesPerBlock - 1) / kWavesPerBlock);
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-  switch (iters) {
-    case 1: k_stimulus<1><<<grid, kBlock, 0, s>>>(g.n_pi, c, cnt, p_col, stim, T, stream, k0, k1, wpr); break;
-    case 2: k_stimulus<2><<<grid, kBlock, 0, s>>>(g.n_pi, c, cnt, p_col, stim, T, stream, k0, k1, wpr); break;
-    case 4: k_stimulus<4><<<grid, kBlock, 0, s>>>(g.n_pi, c, cnt, p_col, stim, T, stream, k0, k1, wpr); break;
-    default: k_stimulus<8><<<grid, kBlock, 0, s>>>(g.n_pi, c, cnt, p_col, stim, T, stream, k0, k1, wpr); break;
-  }
+  using K = void (*)(int32_t, ChunkView, CountView, const float *, const uint64_t *, int64_t,
+                     const int32_t *, uint32_t, uint32_t, int32_t);
+#define DP_STIM_ROW(NC, STIM) \
+  { k_stimulus<1, NC, STIM>, k_stimulus<2, NC, STIM>, k_stimulus<4, NC, STIM>, k_stimulus<8, NC, STIM> }
+  static const K table[5][4] = {DP_STIM_ROW(1, true), DP_STIM_ROW(1, false), DP_STIM_ROW(2, false),
+                                DP_STIM_ROW(4, false), DP_STIM_ROW(8, false)};
+#undef DP_STIM_ROW
+  const int row = stim ? 0 : nc == 1 ? 1 : nc == 2 ? 2 : nc == 4 ? 3 : 4;
+  const int col = iters == 1 ? 0 : iters == 2 ? 1 : iters == 4 ? 2 : 3;
+  hipLaunchKernelGGL(table[row][col], dim3(grid), dim3(kBlock), 0, s, g.n_pi, c, cnt, p_col, stim,
+                     T, stream, k0, k1, wpr);
   return hipGetLastError();
 }
 
