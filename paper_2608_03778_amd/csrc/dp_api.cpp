@@ -291,7 +291,7 @@ dp_status ensure_flow(dp_eval *ev) {
 // (once ensure_flow has run).
 bool flows(const dp_eval *ev, int32_t C) {
   const dp_design *d = ev->d;
-  return ev->flow_report && ev->schedule != DP_SCHED_PERSISTENT &&
+  return ev->flow.ptr && ev->schedule != DP_SCHED_PERSISTENT &&
          dp::flow_fits(view(d), d->depth, std::max(C, ev->B), d->n_edges);
 }
 
@@ -315,11 +315,7 @@ dp::FlowCtl flow_ctl(const dp_eval *ev) {
 // persistent or dataflow sweep since the last check had a wait give up.
 // Reads and clears the report words.
 dp_status barrier_status(dp_eval *ev) {
-  if (ev->flow_report && *static_cast<volatile uint32_t *>(ev->flow_report) != 0u) {
-    *ev->flow_report = 0u;
-    return fail(DP_E_HIP, "a sweep's wait for its own results gave up; that sweep's outputs are NaN "
-                          "and not a result");
-  }
+  DP_TRY(dp::flow_status(ev));
   if (!ev->barrier_pending) return DP_OK;
   uint32_t rep = 0;
   uint32_t *w = ev->barrier.as<uint32_t>() + dp::kBarrierReport;
@@ -848,6 +844,12 @@ dp_status reverse_sweep(dp_eval *ev, const dp::BwdArgs &ba, float *dst) {
 }  // namespace
 
 namespace dp {
+dp_status flow_status(dp_eval *ev) {
+  if (!ev->flow_report || *static_cast<volatile uint32_t *>(ev->flow_report) == 0u) return DP_OK;
+  *ev->flow_report = 0u;
+  return fail(DP_E_HIP, "a sweep's wait for its own results gave up; that sweep's outputs are NaN "
+                        "and not a result");
+}
 dp_status params_ok(const dp_params *p) { return check_params(p); }
 double kappa(const dp_params &p) { return kappa_of(p); }
 }  // namespace dp
@@ -1756,6 +1758,76 @@ dp_status MergedTables::launch_reverse(const BwdSeg *dev, hipStream_t s) const {
   return DP_OK;
 }
 
+bool FlowTables::fits(const MergedTables::Lane *lanes, int32_t n) {
+  int64_t jobs = 0, items = 0;
+  for (int32_t j = 0; j < n; ++j) {
+    const dp_eval *ev = lanes[j].ev;
+    if (!flows(ev, ev->B) || (lanes[j].backward && !ev->part.ptr)) return false;
+    jobs += ev->B;
+    items += (int64_t)ev->d->n_nets * ev->B;
+  }
+  return n > 0 && jobs <= kFlowMaxJobs && items <= kFlowMultiItems;
+}
+
+void FlowTables::build(const MergedTables::Lane *lanes, int32_t n) {
+  fs.clear();
+  bs.clear();
+  f_jobs = b_jobs = 0;
+  f_blocks = b_blocks = 0;
+  f_widest = b_widest = 1;
+  cells = false;
+  ctl = flow_ctl(lanes[0].ev);
+  std::vector<int32_t> order(n);
+  for (int32_t j = 0; j < n; ++j) order[j] = j;
+  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+    return lanes[x].ev->d->n_nets > lanes[y].ev->d->n_nets;
+  });
+  for (int32_t j : order) {
+    dp_eval *ev = lanes[j].ev;
+    const dp_design *d = ev->d;
+    cells = cells || d->has_cell_gates;
+    SpFlowSeg f{};
+    f.t = SpFlow{view(d), ev->sp.as<float>(), d->level_dev.as<int32_t>(), ev->B, d->depth};
+    f.job0 = f_jobs;
+    f.block0 = f_blocks;
+    f_jobs += ev->B;
+    f_blocks += flow_arm_blocks(f.t, fs.empty());
+    f_widest = std::max<int64_t>(f_widest, d->max_level_width);
+    fs.push_back(f);
+    if (!lanes[j].backward) continue;
+    BwdFlowSeg b{};
+    b.t = BwdFlow{view(d), backward_args(ev, nullptr, 0, ev->B), ev->pi_out.as<float>(),
+                  ev->seed.as<float>(), ev->part.as<float>(), d->level_dev.as<int32_t>(),
+                  d->n_edges, d->depth};
+    b.job0 = b_jobs;
+    b.block0 = b_blocks;
+    b_jobs += ev->B;
+    b_blocks += flow_arm_blocks(b.t, bs.empty(), &b.arm_blocks, &b.seed_blocks);
+    b_widest = std::max<int64_t>(b_widest, std::max(d->max_level_width, d->n_pi));
+    bs.push_back(b);
+  }
+}
+
+size_t FlowTables::bwd_offset() const {
+  return (fs.size() * sizeof(SpFlowSeg) + 255) & ~(size_t)255;
+}
+size_t FlowTables::bytes() const {
+  return std::max<size_t>(bwd_offset() + bs.size() * sizeof(BwdFlowSeg), 256);
+}
+void FlowTables::pack(void *host) const {
+  if (!fs.empty()) std::memcpy(host, fs.data(), fs.size() * sizeof(SpFlowSeg));
+  if (!bs.empty())
+    std::memcpy((char *)host + bwd_offset(), bs.data(), bs.size() * sizeof(BwdFlowSeg));
+}
+dp_status FlowTables::launch_forward(const SpFlowSeg *dev, hipStream_t s) const {
+  DP_HIP_TRY(launch_sp_flow_multi(dev, (int32_t)fs.size(), f_jobs, f_blocks, f_widest, cells, ctl, s));
+  return DP_OK;
+}
+dp_status FlowTables::launch_reverse(const BwdFlowSeg *dev, hipStream_t s) const {
+  DP_HIP_TRY(launch_bwd_flow_multi(dev, (int32_t)bs.size(), b_jobs, b_blocks, b_widest, cells, ctl, s));
+  return DP_OK;
+}
+
 }  // namespace dp
 
 struct GroupPool {
@@ -1812,6 +1884,8 @@ struct dp_group {
   // their device copy (forward segments, then reverse at tab_dev_bwd).
   std::vector<int32_t> merged;      // eval indices
   dp::MergedTables tab;
+  dp::FlowTables flow;       // in place of tab where the evals' sweeps fit
+  bool use_flow = false;
   dp::DevBuf tab_dev;
   size_t tab_dev_bwd = 0;
   bool have_tables = false;
@@ -1861,15 +1935,26 @@ void assign_branches(dp_group *g, const std::vector<int64_t> &cost) {
 // Fork from `origin` into the branches, enqueue each eval's forward (and
 // reverse) sweep on its branch with per-level launches, join back.
 // Segment tables of the merged level launches (host work, one upload).
-dp_status build_merged_tables(dp_group *g) {
+dp_status build_merged_tables(dp_group *g, bool backward) {
   std::vector<dp::MergedTables::Lane> lanes;
-  for (int32_t i : g->merged) lanes.push_back({g->evs[i], true});
-  g->tab.build(lanes.data(), (int32_t)lanes.size());
-  g->tab_dev_bwd = g->tab.bwd_offset();
-  DP_TRY(g->tab_dev.alloc(g->tab.bytes()));
-  std::vector<char> host(g->tab.bytes());
-  g->tab.pack(host.data());
-  DP_HIP_TRY(hipMemcpy(g->tab_dev.ptr, host.data(), host.size(), hipMemcpyHostToDevice));
+  for (int32_t i : g->merged) lanes.push_back({g->evs[i], backward});
+  std::vector<char> host;
+  auto upload = [&](const auto &tab) -> dp_status {
+    g->tab_dev_bwd = tab.bwd_offset();
+    DP_TRY(g->tab_dev.alloc(tab.bytes()));
+    host.resize(tab.bytes());
+    tab.pack(host.data());
+    DP_HIP_TRY(hipMemcpy(g->tab_dev.ptr, host.data(), host.size(), hipMemcpyHostToDevice));
+    return DP_OK;
+  };
+  if (g->use_flow) {
+    g->flow.build(lanes.data(), (int32_t)lanes.size());
+    DP_TRY(upload(g->flow));
+  } else {
+    for (auto &l : lanes) l.backward = true;
+    g->tab.build(lanes.data(), (int32_t)lanes.size());
+    DP_TRY(upload(g->tab));
+  }
   g->have_tables = true;
   return DP_OK;
 }
@@ -1879,9 +1964,11 @@ dp_status build_merged_tables(dp_group *g) {
 // eval's PI adjoints.
 dp_status enqueue_merged(dp_group *g, hipStream_t origin, bool backward) {
   if (g->merged.empty()) return DP_OK;
-  const dp::SpSeg *fs = g->tab_dev.as<dp::SpSeg>();
-  const auto *bs = reinterpret_cast<const dp::BwdSeg *>((char *)g->tab_dev.ptr + g->tab_dev_bwd);
-  DP_TRY(g->tab.launch_forward(fs, origin));
+  const char *bwd_tab = (const char *)g->tab_dev.ptr + g->tab_dev_bwd;
+  if (g->use_flow)
+    DP_TRY(g->flow.launch_forward(g->tab_dev.as<dp::SpFlowSeg>(), origin));
+  else
+    DP_TRY(g->tab.launch_forward(g->tab_dev.as<dp::SpSeg>(), origin));
   for (int32_t i : g->merged) {
     dp_eval *ev = g->evs[i];
     ev->branch = origin;
@@ -1890,7 +1977,9 @@ dp_status enqueue_merged(dp_group *g, hipStream_t origin, bool backward) {
     DP_TRY(st);
   }
   if (!backward) return DP_OK;
-  DP_TRY(g->tab.launch_reverse(bs, origin));
+  if (g->use_flow)  // the PIs' adjoints included
+    return g->flow.launch_reverse(reinterpret_cast<const dp::BwdFlowSeg *>(bwd_tab), origin);
+  DP_TRY(g->tab.launch_reverse(reinterpret_cast<const dp::BwdSeg *>(bwd_tab), origin));
   for (int32_t i : g->merged) {
     dp_eval *ev = g->evs[i];
     const dp::HeavySpan hp = dp::heavy_pis(ev->d);
@@ -2044,6 +2133,8 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
     mix(graph_key(ev, hybrid(ev) ? &plans[i] : nullptr));
     ev->schedule = sched;
     mix((uint64_t)(uintptr_t)ev->contrib.ptr);
+    mix((uint64_t)(uintptr_t)ev->part.ptr);
+    mix((uint64_t)(uintptr_t)ev->seed.ptr);
     mix((uint64_t)(uintptr_t)ev->pi_out.ptr);
     mix((uint64_t)(uintptr_t)(ev->have_fixed ? ev->fixed.ptr : nullptr));
     mix((uint64_t)ev->B);
@@ -2062,8 +2153,11 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
     }
   if (!g->merged.empty()) {
     std::vector<dp::MergedTables::Lane> lanes;
-    for (int32_t i : g->merged) lanes.push_back({g->evs[i], true});
-    const int64_t per_sweep = dp::MergedTables::level_launches(lanes.data(), (int32_t)lanes.size());
+    for (int32_t i : g->merged) lanes.push_back({g->evs[i], backward != 0});
+    g->use_flow = dp::FlowTables::fits(lanes.data(), (int32_t)lanes.size());
+    mix((uint64_t)g->use_flow);
+    const int64_t per_sweep =
+        g->use_flow ? 2 : dp::MergedTables::level_launches(lanes.data(), (int32_t)lanes.size());
     launches += per_sweep * (backward ? 2 : 1) + (int64_t)g->merged.size() * (backward ? 4 : 3);
   }
   const int32_t want = g->max_branches > 0 ? g->max_branches : kGroupBranches;
@@ -2080,7 +2174,7 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
   } restore{g, all};
   if (g->tables_key != key || !g->have_tables) {
     DP_HIP_TRY(hipStreamSynchronize(s));  // no run reads the old tables
-    DP_TRY(build_merged_tables(g));
+    DP_TRY(build_merged_tables(g, backward != 0));
     g->tables_key = key;
   }
   if (g->use_graph && launches <= kMaxGraphLaunches) {
@@ -2127,7 +2221,10 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
       host_out = host_out || !on_device;
     }
   }
-  if (host_out) DP_HIP_TRY(hipStreamSynchronize(s));
+  if (host_out) {
+    DP_HIP_TRY(hipStreamSynchronize(s));
+    for (int32_t i : g->merged) DP_TRY(barrier_status(g->evs[i]));
+  }
   return DP_OK;
 }
 
@@ -2163,8 +2260,19 @@ size_t lane_bytes(const dp_design *d, int32_t capacity) {
   return (size_t)capacity * per_col + 8 * nn;
 }
 
+size_t lane_flow_bytes(const dp_design *d, int32_t capacity) {
+  return (size_t)capacity * 4 * ((size_t)d->n_nets + (size_t)d->pins * d->n_gates) +
+         kFlowWords * sizeof(uint32_t);
+}
+
+void lane_drop_flow(dp_eval *ev) {
+  ev->seed.release();
+  ev->part.release();
+  ev->flow.release();
+}
+
 dp_status lane_create(dp_design *d, int32_t capacity, const dp_params *prm, hipStream_t stream,
-                      const float *cap_int, const float *beta_int, dp_eval **out) {
+                      const float *cap_int, const float *beta_int, bool flow, dp_eval **out) {
   DP_TRY(check_params(prm));
   if (prm->mode == DP_HYBRID) return fail(DP_E_UNSUPPORTED, "serving lanes run DP_MODELED or DP_FROZEN_BETA");
   auto *ev = new dp_eval();
@@ -2191,6 +2299,11 @@ dp_status lane_create(dp_design *d, int32_t capacity, const dp_params *prm, hipS
   A(ev->contrib, (size_t)d->n_edges * capacity * 4);
   A(ev->pi_out, (size_t)capacity * d->n_pi * 4);
   if (beta_int) A(ev->beta_frozen, nn * 4);
+  if (flow) {
+    A(ev->seed, nn * capacity * 4);
+    A(ev->part, (size_t)capacity * d->pins * d->n_gates * 4);
+    if (st == DP_OK) st = ensure_flow(ev);
+  }
   if (st != DP_OK) {
     delete ev;
     return st;
@@ -2290,8 +2403,13 @@ dp_status lanes_run_merged(const LaneJob *jobs, int32_t n_jobs, hipStream_t s,
     any_backward = any_backward || jobs[j].backward;
   }
   MergedTables tab;
-  tab.build(lanes.data(), n_jobs);
-  const size_t bytes = tab.bytes();
+  FlowTables flow;
+  const bool use_flow = FlowTables::fits(lanes.data(), n_jobs);
+  if (use_flow)
+    flow.build(lanes.data(), n_jobs);
+  else
+    tab.build(lanes.data(), n_jobs);
+  const size_t bytes = use_flow ? flow.bytes() : tab.bytes();
   if (bytes > sc->cap) {
     if (sc->host) (void)hipHostFree(sc->host);
     sc->host = nullptr;
@@ -2300,11 +2418,14 @@ dp_status lanes_run_merged(const LaneJob *jobs, int32_t n_jobs, hipStream_t s,
     DP_TRY(sc->dev.alloc(bytes));
     sc->cap = bytes;
   }
-  tab.pack(sc->host);
+  use_flow ? flow.pack(sc->host) : tab.pack(sc->host);
   DP_HIP_TRY(hipMemcpyAsync(sc->dev.ptr, sc->host, bytes, hipMemcpyHostToDevice, s));
-  const SpSeg *fd = sc->dev.as<SpSeg>();
-  const BwdSeg *bd = reinterpret_cast<const BwdSeg *>((char *)sc->dev.ptr + tab.bwd_offset());
-  DP_TRY(tab.launch_forward(fd, s));
+  const char *bwd_tab =
+      (const char *)sc->dev.ptr + (use_flow ? flow.bwd_offset() : tab.bwd_offset());
+  if (use_flow)
+    DP_TRY(flow.launch_forward(sc->dev.as<SpFlowSeg>(), s));
+  else
+    DP_TRY(tab.launch_forward(sc->dev.as<SpSeg>(), s));
   for (int32_t j = 0; j < n_jobs; ++j) {
     dp_eval *ev = jobs[j].ev;
     ev->branch = s;
@@ -2315,14 +2436,18 @@ dp_status lanes_run_merged(const LaneJob *jobs, int32_t n_jobs, hipStream_t s,
                               hipMemcpyDeviceToHost, s));
   }
   if (!any_backward) return DP_OK;
-  DP_TRY(tab.launch_reverse(bd, s));
+  if (use_flow)
+    DP_TRY(flow.launch_reverse(reinterpret_cast<const BwdFlowSeg *>(bwd_tab), s));
+  else
+    DP_TRY(tab.launch_reverse(reinterpret_cast<const BwdSeg *>(bwd_tab), s));
   for (int32_t j = 0; j < n_jobs; ++j) {
     if (!jobs[j].backward) continue;
     dp_eval *ev = jobs[j].ev;
     const dp_design *d = ev->d;
     const HeavySpan hp = heavy_pis(d);
-    DP_HIP_TRY(launch_bwd_pi(view(d), backward_args(ev, nullptr, 0, ev->B),
-                             ev->pi_out.as<float>(), s, hp.gates, hp.n));
+    if (!use_flow)  // (the dataflow sweep ends with the PIs)
+      DP_HIP_TRY(launch_bwd_pi(view(d), backward_args(ev, nullptr, 0, ev->B),
+                               ev->pi_out.as<float>(), s, hp.gates, hp.n));
     if (jobs[j].dpi && d->n_pi > 0)
       DP_HIP_TRY(hipMemcpyAsync(jobs[j].dpi, ev->pi_out.ptr, (size_t)jobs[j].n * d->n_pi * 4,
                                 hipMemcpyDeviceToHost, s));

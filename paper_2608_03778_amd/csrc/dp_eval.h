@@ -96,8 +96,13 @@ namespace dp {
 // validation or host synchronisation.  Implemented in dp_api.cpp.
 //   cap_int:   [n_nets] internal-order capacitances (device)
 //   beta_int:  [n_nets] internal-order frozen beta (device) or null
+//   flow:      also allocate what its dataflow sweeps need
 dp_status lane_create(dp_design *d, int32_t capacity, const dp_params *prm, hipStream_t stream,
-                      const float *cap_int, const float *beta_int, dp_eval **out);
+                      const float *cap_int, const float *beta_int, bool flow, dp_eval **out);
+// Device bytes of what `flow` adds, and giving them back (the lane idle): its
+// sweeps then run as merged level launches.
+size_t lane_flow_bytes(const dp_design *d, int32_t capacity);
+void lane_drop_flow(dp_eval *ev);
 // Enqueue one batch of n columns: p [n][n_pi] and sizes [n][n_gates] (caller
 // gate order, or null) in pinned host memory; outputs power [n] and, when
 // backward, dP/dp [n][n_pi] into pinned host memory.
@@ -167,6 +172,33 @@ struct MergedTables {
   dp_status launch_forward(const SpSeg *dev, hipStream_t s) const;
   dp_status launch_reverse(const BwdSeg *dev, hipStream_t s) const;
 };
+
+// Segment tables of dataflow sweeps over several evals (design groups and
+// serving steps), the largest designs' columns first in the claim order.
+struct FlowTables {
+  std::vector<SpFlowSeg> fs;
+  std::vector<BwdFlowSeg> bs;
+  int32_t f_jobs = 0, b_jobs = 0;
+  uint32_t f_blocks = 0, b_blocks = 0;
+  int64_t f_widest = 1, b_widest = 1;
+  bool cells = false;
+  FlowCtl ctl{};  // the first eval's
+  // Whether these evals' sweeps go this way: each is one for the dataflow
+  // kernels, its reverse buffers are there where it wants gradients, and
+  // together they are within the launches' limits.
+  static bool fits(const MergedTables::Lane *lanes, int32_t n);
+  void build(const MergedTables::Lane *lanes, int32_t n);
+  // Packed layout: forward segments, then the reverse ones at bwd_offset().
+  size_t bwd_offset() const;
+  size_t bytes() const;
+  void pack(void *host) const;
+  dp_status launch_forward(const SpFlowSeg *dev, hipStream_t s) const;
+  dp_status launch_reverse(const BwdFlowSeg *dev, hipStream_t s) const;
+};
+
+// Whether a dataflow sweep of the eval gave up since the last check (its
+// stream idle): a failure status, once.
+dp_status flow_status(dp_eval *ev);
 
 // Hybrid calibration at probability p_all for every PI: beta [n_nets] in
 // internal order into beta_int (device), on the context's stream.

@@ -319,6 +319,9 @@ struct FlowCtl {
 // against 91 / 160, 32 columns 146 / 267 against 115 / 280, 64 columns
 // 156 / 269 against 237 / 463; 20K gates, 64 columns 95 / 147 against 73 / 84.
 constexpr int64_t kFlowMaxItems = 1 << 22;
+// Jobs and (net, column) pairs of a sweep over several designs.
+constexpr int32_t kFlowMaxJobs = kFlowMaxCols;
+constexpr int64_t kFlowMultiItems = 2 * kFlowMaxItems;
 inline bool flow_fits(const GraphView &g, int32_t depth, int32_t C, int64_t n_edges) {
   return C <= kFlowMaxCols && depth + 2 <= kFlowLevels && g.n_nets < (1 << 24) &&
          (int64_t)g.n_nets * C <= kFlowMaxItems && n_edges < (1ll << 29);
@@ -339,6 +342,31 @@ struct BwdFlow {
   int64_t n_edges;
   int32_t depth;
 };
+// Several designs in one sweep: segment k's columns are the jobs [job0_k,
+// job0_{k+1}) that the teams claim, and its arming takes the blocks from
+// block0 on (both ascending, the first 0).
+struct SpFlowSeg {
+  SpFlow t;
+  int32_t job0;
+  uint32_t block0;
+};
+struct BwdFlowSeg {
+  BwdFlow t;
+  int32_t job0;
+  uint32_t block0, arm_blocks, seed_blocks;  // arming: contributions, then seeds, then partials
+};
+// Blocks that arm a segment (clears: the one that also clears the control
+// words, which is the first).
+uint32_t flow_arm_blocks(const SpFlow &t, bool clears);
+uint32_t flow_arm_blocks(const BwdFlow &t, bool clears, uint32_t *arm_blocks, uint32_t *seed_blocks);
+// segs: device table of n_segs; jobs: columns of all segments; blocks: arming
+// blocks of all segments; widest: over all segments.
+hipError_t launch_sp_flow_multi(const SpFlowSeg *segs, int32_t n_segs, int32_t jobs,
+                                uint32_t blocks, int64_t widest, bool cells, FlowCtl ctl,
+                                hipStream_t s);
+hipError_t launch_bwd_flow_multi(const BwdFlowSeg *segs, int32_t n_segs, int32_t jobs,
+                                 uint32_t blocks, int64_t widest, bool cells, FlowCtl ctl,
+                                 hipStream_t s);
 // widest: gates of the widest level; cells: the design holds library cells.
 hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl ctl, hipStream_t s);
 // The reverse levels and then the PI adjoints; widest also covers the PIs.

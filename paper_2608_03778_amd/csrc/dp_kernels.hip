@@ -2364,6 +2364,67 @@ __global__ __launch_bounds__(kFlowThreads) void k_sp_flow(FlowCtl ctl, SpFlow t)
   }
 }
 
+// A pointer read from a table, as one to global memory (loads through it are
+// then global loads, not flat ones, whose waits also cover LDS).
+template <typename T>
+__device__ __forceinline__ T *global_ptr(T *p) {
+  return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
+}
+__device__ __forceinline__ GraphView global_view(GraphView g) {
+  g.op = global_ptr(g.op);
+  g.in = global_ptr(g.in);
+  g.rev_ptr = global_ptr(g.rev_ptr);
+  g.slot = global_ptr(g.slot);
+  g.code = global_ptr(g.code);
+  g.cell = global_ptr(g.cell);
+  return g;
+}
+__device__ __forceinline__ SpFlow global_view(SpFlow t) {
+  t.g = global_view(t.g);
+  t.sp = global_ptr(t.sp);
+  t.level_ptr = global_ptr(t.level_ptr);
+  return t;
+}
+__device__ __forceinline__ BwdFlow global_view(BwdFlow t) {
+  t.g = global_view(t.g);
+  t.a.sp = global_ptr(t.a.sp);
+  t.a.beta = global_ptr(t.a.beta);
+  t.a.cap = global_ptr(t.a.cap);
+  t.a.w = global_ptr(t.a.w);
+  t.a.size = global_ptr(t.a.size);
+  t.a.contrib = global_ptr(t.a.contrib);
+  t.a.lam = global_ptr(t.a.lam);
+  t.a.fixed = global_ptr(t.a.fixed);
+  t.pi_out = global_ptr(t.pi_out);
+  t.seed = global_ptr(t.seed);
+  t.part = global_ptr(t.part);
+  t.level_ptr = global_ptr(t.level_ptr);
+  return t;
+}
+// The segment of a job, and of an arming block (uniform: a short scalar scan).
+template <class Seg>
+__device__ __forceinline__ int32_t seg_of_job(const Seg *__restrict__ segs, int32_t n, int32_t job) {
+  int32_t k = 0;
+  while (k + 1 < n && segs[k + 1].job0 <= job) ++k;
+  return k;
+}
+
+template <bool CELLS>
+__global__ __launch_bounds__(kFlowThreads) void k_sp_flow_multi(FlowCtl ctl,
+                                                                const SpFlowSeg *__restrict__ segs,
+                                                                int32_t n_segs, int32_t jobs) {
+  const FlowSeat st = flow_join(ctl);
+  if (st.members == 0) return;
+  for (int32_t i = 0; i < kFlowSlots; ++i) {
+    const int32_t job = flow_claim(ctl, st, i, jobs);
+    if (job < 0) return;
+    const int32_t k = seg_of_job(segs, n_segs, job);
+    const SpFlow t = global_view(segs[k].t);
+    const FlowWalk w = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi);
+    if (t.depth > 0) sp_flow_column<CELLS>(ctl, t, w, job - segs[k].job0);
+  }
+}
+
 // ---- reverse: levels depth .. 1, then the PIs (level 0)
 // The sweep's chain takes only what has to wait: a launch of the whole chip
 // before it (k_bwd_arm) forms every net's seed and every gate's partial
@@ -2558,6 +2619,21 @@ __global__ __launch_bounds__(kFlowThreads) void k_bwd_flow(FlowCtl ctl, BwdFlow 
   }
 }
 
+template <bool CELLS>
+__global__ __launch_bounds__(kFlowThreads) void k_bwd_flow_multi(
+    FlowCtl ctl, const BwdFlowSeg *__restrict__ segs, int32_t n_segs, int32_t jobs) {
+  const FlowSeat st = flow_join(ctl);
+  if (st.members == 0) return;
+  for (int32_t i = 0; i < kFlowSlots; ++i) {
+    const int32_t job = flow_claim(ctl, st, i, jobs);
+    if (job < 0) return;
+    const int32_t k = seg_of_job(segs, n_segs, job);
+    const BwdFlow t = global_view(segs[k].t);
+    const FlowWalk w = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi);
+    bwd_flow_column<kFlowPins<CELLS>>(ctl, t, w, job - segs[k].job0);
+  }
+}
+
 // Arms the n slots a sweep will write and clears its control words.  Four
 // dwords per thread, each wave-wide store one contiguous run.
 constexpr int kArmPer = 4;
@@ -2581,16 +2657,16 @@ __global__ __launch_bounds__(kBlock) void k_flow_arm(uint32_t *p, int64_t n, uin
 // writes every net's seed [C][n_nets], and every gate's partial derivatives
 // [B][pins][G].
 template <bool CELLS>
-__global__ __launch_bounds__(kBlock) void k_bwd_arm(BwdFlow t, uint32_t *words, uint32_t arm_blocks,
-                                                    uint32_t seed_blocks) {
+__device__ __forceinline__ void bwd_arm(const BwdFlow &t, uint32_t *words, int32_t n_words,
+                                        uint32_t block, uint32_t arm_blocks, uint32_t seed_blocks) {
   const GraphView &g = t.g;
   const BwdArgs &a = t.a;
-  if (blockIdx.x < arm_blocks) {
-    flow_arm(reinterpret_cast<uint32_t *>(a.contrib), t.n_edges * a.C, words, kFlowWords, blockIdx.x);
+  if (block < arm_blocks) {
+    flow_arm(reinterpret_cast<uint32_t *>(a.contrib), t.n_edges * a.C, words, n_words, block);
     return;
   }
-  if (blockIdx.x < arm_blocks + seed_blocks) {
-    const int64_t idx = (int64_t)(blockIdx.x - arm_blocks) * kBlock + threadIdx.x;
+  if (block < arm_blocks + seed_blocks) {
+    const int64_t idx = (int64_t)(block - arm_blocks) * kBlock + threadIdx.x;
     if (idx >= (int64_t)g.n_nets * a.C) return;
     const int32_t c = (int32_t)(idx / g.n_nets), net = (int32_t)(idx - (int64_t)c * g.n_nets);
     const int32_t b = c / a.cdiv;
@@ -2598,7 +2674,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_arm(BwdFlow t, uint32_t *words, 
     t.seed[idx] = seed_of(a, net, c, b, sp_load(a.sp[(int64_t)net * a.B + b]), beta, a.cap[net]);
     return;
   }
-  const int64_t idx = (int64_t)(blockIdx.x - arm_blocks - seed_blocks) * kBlock + threadIdx.x;
+  const int64_t idx = (int64_t)(block - arm_blocks - seed_blocks) * kBlock + threadIdx.x;
   if (idx >= (int64_t)g.G * a.B) return;
   const int32_t b = (int32_t)(idx / g.G), gi = (int32_t)(idx - (int64_t)b * g.G);
   constexpr int N = kFlowPins<CELLS>;
@@ -2628,6 +2704,29 @@ __global__ __launch_bounds__(kBlock) void k_bwd_arm(BwdFlow t, uint32_t *words, 
   part[0] = d0;
   if (k > 1) part[g.G] = d1;
   if (k > 2) part[2 * (int64_t)g.G] = d2;
+}
+template <bool CELLS>
+__global__ __launch_bounds__(kBlock) void k_bwd_arm(BwdFlow t, uint32_t *words, uint32_t arm_blocks,
+                                                    uint32_t seed_blocks) {
+  bwd_arm<CELLS>(t, words, kFlowWords, blockIdx.x, arm_blocks, seed_blocks);
+}
+
+// The same for the segments of a sweep over several designs; the first
+// segment's blocks clear the control words.
+__global__ __launch_bounds__(kBlock) void k_flow_arm_multi(const SpFlowSeg *__restrict__ segs,
+                                                           int32_t n_segs, uint32_t *words) {
+  const int32_t k = seg_of(segs, n_segs);
+  const SpFlow t = global_view(segs[k].t);
+  flow_arm(reinterpret_cast<uint32_t *>(t.sp + (int64_t)t.g.n_pi * t.B), (int64_t)t.g.G * t.B, words,
+           k == 0 ? kFlowWords : 0, blockIdx.x - segs[k].block0);
+}
+template <bool CELLS>
+__global__ __launch_bounds__(kBlock) void k_bwd_arm_multi(const BwdFlowSeg *__restrict__ segs,
+                                                          int32_t n_segs, uint32_t *words) {
+  const int32_t k = seg_of(segs, n_segs);
+  const BwdFlow t = global_view(segs[k].t);
+  bwd_arm<CELLS>(t, words, k == 0 ? kFlowWords : 0, blockIdx.x - segs[k].block0,
+                 segs[k].arm_blocks, segs[k].seed_blocks);
 }
 
 // dP/dC_n = sum_{b,s} w[b][s] kappa beta TR_model s_s(drv n);
@@ -3185,13 +3284,24 @@ static void flow_shape(FlowCtl *ctl, int64_t widest, int32_t C, unsigned *grid, 
   *threads = (unsigned)(64 * wpb);
 }
 
+static int64_t fill_blocks(int64_t slots, bool clears) {
+  return (slots + (clears ? kFlowWords : 0) + kBlock * kArmPer - 1) / (kBlock * kArmPer);
+}
+uint32_t flow_arm_blocks(const SpFlow &t, bool clears) {
+  return (uint32_t)fill_blocks((int64_t)t.g.G * t.B, clears);
+}
+uint32_t flow_arm_blocks(const BwdFlow &t, bool clears, uint32_t *arm_blocks,
+                         uint32_t *seed_blocks) {
+  *arm_blocks = (uint32_t)fill_blocks(t.n_edges * t.a.C, clears);
+  *seed_blocks = blocks_for((int64_t)t.g.n_nets * t.a.C);
+  return *arm_blocks + *seed_blocks + blocks_for((int64_t)t.g.G * t.a.B);
+}
+
 hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl ctl, hipStream_t s) {
   if (t.depth <= 0 || t.B <= 0) return hipSuccess;
   if (!ctl.words || !ctl.report || !flow_fits(t.g, t.depth, t.B, 0)) return hipErrorInvalidValue;
-  const int64_t slots = (int64_t)t.g.G * t.B;  // the gate rows of sp
-  const int64_t ab = (slots + kFlowWords + kBlock * kArmPer - 1) / (kBlock * kArmPer);
-  k_flow_arm<<<(unsigned)ab, kBlock, 0, s>>>(
-      reinterpret_cast<uint32_t *>(t.sp + (int64_t)t.g.n_pi * t.B), slots, ctl.words);
+  k_flow_arm<<<flow_arm_blocks(t, true), kBlock, 0, s>>>(
+      reinterpret_cast<uint32_t *>(t.sp + (int64_t)t.g.n_pi * t.B), (int64_t)t.g.G * t.B, ctl.words);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   unsigned grid, threads;
@@ -3208,14 +3318,12 @@ hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl
   if (t.a.C <= 0 || t.g.n_nets <= 0) return hipSuccess;
   if (!ctl.words || !ctl.report || !t.seed || !t.part || !flow_fits(t.g, t.depth, t.a.C, t.n_edges))
     return hipErrorInvalidValue;
-  const int64_t slots = t.n_edges * t.a.C;
-  const int64_t ab = (slots + kFlowWords + kBlock * kArmPer - 1) / (kBlock * kArmPer);
-  const int64_t sb = ((int64_t)t.g.n_nets * t.a.C + kBlock - 1) / kBlock;
-  const int64_t blocks = ab + sb + ((int64_t)t.g.G * t.a.B + kBlock - 1) / kBlock;
+  uint32_t ab, sb;
+  const uint32_t blocks = flow_arm_blocks(t, true, &ab, &sb);
   if (cells)
-    k_bwd_arm<true><<<(unsigned)blocks, kBlock, 0, s>>>(t, ctl.words, (uint32_t)ab, (uint32_t)sb);
+    k_bwd_arm<true><<<blocks, kBlock, 0, s>>>(t, ctl.words, ab, sb);
   else
-    k_bwd_arm<false><<<(unsigned)blocks, kBlock, 0, s>>>(t, ctl.words, (uint32_t)ab, (uint32_t)sb);
+    k_bwd_arm<false><<<blocks, kBlock, 0, s>>>(t, ctl.words, ab, sb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   unsigned grid, threads;
@@ -3224,6 +3332,43 @@ hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl
     k_bwd_flow<true><<<grid, threads, 0, s>>>(ctl, t);
   else
     k_bwd_flow<false><<<grid, threads, 0, s>>>(ctl, t);
+  return hipGetLastError();
+}
+
+hipError_t launch_sp_flow_multi(const SpFlowSeg *segs, int32_t n_segs, int32_t jobs,
+                                uint32_t blocks, int64_t widest, bool cells, FlowCtl ctl,
+                                hipStream_t s) {
+  if (n_segs <= 0 || jobs <= 0) return hipSuccess;
+  if (!ctl.words || !ctl.report || jobs > kFlowMaxJobs || blocks == 0) return hipErrorInvalidValue;
+  k_flow_arm_multi<<<blocks, kBlock, 0, s>>>(segs, n_segs, ctl.words);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  unsigned grid, threads;
+  flow_shape(&ctl, widest, jobs, &grid, &threads);
+  if (cells)
+    k_sp_flow_multi<true><<<grid, threads, 0, s>>>(ctl, segs, n_segs, jobs);
+  else
+    k_sp_flow_multi<false><<<grid, threads, 0, s>>>(ctl, segs, n_segs, jobs);
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_flow_multi(const BwdFlowSeg *segs, int32_t n_segs, int32_t jobs,
+                                 uint32_t blocks, int64_t widest, bool cells, FlowCtl ctl,
+                                 hipStream_t s) {
+  if (n_segs <= 0 || jobs <= 0) return hipSuccess;
+  if (!ctl.words || !ctl.report || jobs > kFlowMaxJobs || blocks == 0) return hipErrorInvalidValue;
+  if (cells)
+    k_bwd_arm_multi<true><<<blocks, kBlock, 0, s>>>(segs, n_segs, ctl.words);
+  else
+    k_bwd_arm_multi<false><<<blocks, kBlock, 0, s>>>(segs, n_segs, ctl.words);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  unsigned grid, threads;
+  flow_shape(&ctl, widest, jobs, &grid, &threads);
+  if (cells)
+    k_bwd_flow_multi<true><<<grid, threads, 0, s>>>(ctl, segs, n_segs, jobs);
+  else
+    k_bwd_flow_multi<false><<<grid, threads, 0, s>>>(ctl, segs, n_segs, jobs);
   return hipGetLastError();
 }
 

@@ -60,7 +60,8 @@ struct Lane {
   bool busy = false;
   std::vector<Request *> batch;
   float *pin_p = nullptr, *pin_size = nullptr, *pin_power = nullptr, *pin_dpi = nullptr;
-  size_t bytes = 0;
+  size_t bytes = 0;       // device bytes, those of flow_bytes included
+  size_t flow_bytes = 0;  // of its dataflow sweeps' buffers (0: it has none)
 };
 
 // One device step in flight: its stream, completion event, the merged
@@ -121,20 +122,39 @@ Lane *make_lane(dp_server *s, int32_t design, int32_t cap) {
             hipHostMalloc((void **)&l->pin_size, std::max<size_t>((size_t)cap * d->n_gates * 4, 16)) == hipSuccess &&
             hipHostMalloc((void **)&l->pin_power, (size_t)cap * 4) == hipSuccess &&
             hipHostMalloc((void **)&l->pin_dpi, std::max<size_t>((size_t)cap * d->n_pi * 4, 16)) == hipSuccess;
+  // the dataflow sweeps' buffers come out of what the budget has left, and are
+  // given back before any query waits for memory (trim_flow)
+  const size_t base = dp::lane_bytes(d, cap), extra = dp::lane_flow_bytes(d, cap);
+  const bool flow = s->used + base + extra <= s->budget;
   if (ok)
     ok = dp::lane_create(de->d, cap, &de->prm, l->stream, de->cap_int.as<float>(),
-                         de->frozen ? de->beta_int.as<float>() : nullptr, &l->ev) == DP_OK;
+                         de->frozen ? de->beta_int.as<float>() : nullptr, flow, &l->ev) == DP_OK;
   if (!ok) {
     (void)hipGetLastError();
     destroy_lane(l);
     return nullptr;
   }
-  l->bytes = dp::lane_bytes(d, cap);
+  l->flow_bytes = flow ? extra : 0;
+  l->bytes = base + l->flow_bytes;
   s->lanes.push_back(l);
   s->used += l->bytes;
   s->st.lanes_created++;
   s->st.peak_slot_bytes = std::max<int64_t>(s->st.peak_slot_bytes, (int64_t)s->used);
   return l;
+}
+
+// Give back idle lanes' dataflow buffers until `need` bytes fit (caller holds
+// mu): those lanes' sweeps run as merged level launches from then on.
+bool trim_flow(dp_server *s, size_t need) {
+  for (Lane *l : s->lanes) {
+    if (s->used + need <= s->budget) break;
+    if (l->busy || l->flow_bytes == 0) continue;
+    dp::lane_drop_flow(l->ev);
+    s->used -= l->flow_bytes;
+    l->bytes -= l->flow_bytes;
+    l->flow_bytes = 0;
+  }
+  return s->used + need <= s->budget;
 }
 
 // Free idle lanes of other designs until `need` bytes fit (caller holds mu).
@@ -243,10 +263,14 @@ void launch_step(dp_server *s, Step *st, const std::vector<Lane *> &ready) {
   s->st.device_steps++;
 }
 
-void finish_lane(dp_server *s, Lane *l, Clock::time_point now) {
+void finish_lane(dp_server *s, Lane *l, Clock::time_point now, dp_status rc) {
   const dp_design *d = s->designs[l->design]->d;
   for (size_t b = 0; b < l->batch.size(); ++b) {
     Request *r = l->batch[b];
+    if (rc != DP_OK) {
+      r->status = rc;
+      r->error = std::string("server step: ") + dp_last_error();
+    }
     if (r->out_power) *r->out_power = l->pin_power[b];
     if (r->out_dpi && r->kind == DP_Q_FWD_BWD)
       std::memcpy(r->out_dpi, l->pin_dpi + b * (size_t)d->n_pi, (size_t)d->n_pi * 4);
@@ -260,7 +284,12 @@ void finish_lane(dp_server *s, Lane *l, Clock::time_point now) {
 
 void finish_step(dp_server *s, Step *st) {
   const auto now = Clock::now();
-  for (Lane *l : st->lanes) finish_lane(s, l, now);
+  dp_status rc = DP_OK;  // a dataflow sweep that gave up fails the step's queries
+  for (Lane *l : st->lanes) {
+    const dp_status one = dp::flow_status(l->ev);
+    if (one != DP_OK) rc = one;
+  }
+  for (Lane *l : st->lanes) finish_lane(s, l, now, rc);
   st->lanes.clear();
   st->busy = false;
   if (--s->inflight == 0)
@@ -293,6 +322,7 @@ void admit(dp_server *s) {
       while (c2 < cap) c2 <<= 1;
       cap = std::min(c2, s->max_batch);
       while (cap > 1 && dp::lane_bytes(d, cap) > s->budget) cap >>= 1;
+      trim_flow(s, dp::lane_bytes(d, cap));
       // under memory pressure a smaller lane that fits what is free now is
       // preferred to freeing other designs' idle lanes: a lane costs
       // allocations to create, which freeing throws away

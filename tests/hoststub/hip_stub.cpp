@@ -615,6 +615,46 @@ hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl
   launch_bwd_level(t.g, t.a, 0, 0, false, stream_, nullptr, kNoHeavyCheck);  // its extents
   return launch_bwd_pi(t.g, t.a, t.pi_out, stream_, nullptr, kNoHeavyCheck);
 }
+// Several designs: each segment's own launch, its jobs and arming blocks in a
+// row.  (The counts need only be consistent between the two sides.)
+uint32_t flow_arm_blocks(const SpFlow &t, bool clears) { return (uint32_t)(t.g.G + clears); }
+uint32_t flow_arm_blocks(const BwdFlow &t, bool clears, uint32_t *arm, uint32_t *seed) {
+  *arm = (uint32_t)(t.n_edges + clears);
+  *seed = (uint32_t)t.g.n_nets;
+  return *arm + *seed + (uint32_t)t.g.G;
+}
+hipError_t launch_sp_flow_multi(const SpFlowSeg *segs, int32_t n_segs, int32_t jobs,
+                                uint32_t blocks, int64_t widest, bool cells, FlowCtl ctl,
+                                hipStream_t stream_) {
+  Scope sc_(stream_);
+  int32_t job = 0;
+  uint32_t block = 0;
+  for (int32_t k = 0; k < n_segs; ++k) {
+    if (segs[k].job0 != job || segs[k].block0 != block) fatal("dataflow segments out of order");
+    job += segs[k].t.B;
+    block += flow_arm_blocks(segs[k].t, k == 0);
+    launch_sp_flow(segs[k].t, widest, cells, ctl, stream_);
+  }
+  if (job != jobs || jobs > kFlowMaxJobs || block != blocks) fatal("dataflow segments' totals");
+  return hipSuccess;
+}
+hipError_t launch_bwd_flow_multi(const BwdFlowSeg *segs, int32_t n_segs, int32_t jobs,
+                                 uint32_t blocks, int64_t widest, bool cells, FlowCtl ctl,
+                                 hipStream_t stream_) {
+  Scope sc_(stream_);
+  int32_t job = 0;
+  uint32_t block = 0;
+  for (int32_t k = 0; k < n_segs; ++k) {
+    uint32_t arm, seed;
+    if (segs[k].job0 != job || segs[k].block0 != block) fatal("dataflow segments out of order");
+    job += segs[k].t.a.C;
+    block += flow_arm_blocks(segs[k].t, k == 0, &arm, &seed);
+    if (arm != segs[k].arm_blocks || seed != segs[k].seed_blocks) fatal("arming blocks");
+    launch_bwd_flow(segs[k].t, widest, cells, ctl, stream_);
+  }
+  if (job != jobs || jobs > kFlowMaxJobs || block != blocks) fatal("dataflow segments' totals");
+  return hipSuccess;
+}
 hipError_t launch_sp_multi(const SpSeg *segs, int32_t n_segs, uint32_t blocks, bool cells,
                            hipStream_t st) {
   Scope sc_(st);

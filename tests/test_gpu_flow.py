@@ -157,3 +157,60 @@ def test_flow_library_cells(ctx):
         f, adj = oracle_column(o, p[b], cap)
         assert np.abs(r["sp"][b] - f["sp"]).max() <= SP_ABS
         assert_grad_close(r["dpi"][b], adj["dpi"], "dP/dp")
+
+
+@pytest.mark.parametrize("budget", [100_000, 200_000, 1 << 26])
+def test_server_with_and_without_room_for_flow_buffers(ctx, budget):
+    """Lanes whose dataflow buffers fit the budget, and lanes that run merged
+    level launches for want of them, give the same bits."""
+    say(f"server budget {budget}")
+    nls = [synth.random_dag(synth.DagSpec(3000, 64, 12), 41),
+           synth.random_dag(synth.DagSpec(1500, 40, 9), 42)]
+    caps = [synth.net_caps(nl.n_nets, 43) for nl in nls]
+    srv = api.Server(ctx, budget, max_batch=8, max_inflight=4)
+    ids = [srv.add_design(api.Design(ctx, nl), c, mode=L.DP_MODELED) for nl, c in zip(nls, caps)]
+    tickets = []
+    for k in range(24):
+        i = k % 2
+        p = synth.pi_probs(nls[i].n_pi, 50 + k)[0]
+        size = synth.cell_sizes(nls[i].n_gates, 80 + k)[0]
+        tickets.append((i, p, size, srv.submit(ids[i], p, size, backward=k % 3 == 0)))
+    for i, p, size, t in tickets:
+        power, dpi, _ = srv.wait(t)
+        ev = api.Eval(api.Design(ctx, nls[i]), 1, 1)
+        ev.set_pi_prob(p[None])
+        ev.set_caps(caps[i])
+        ev.set_cell_sizes(size[None])
+        ev.set_schedule(L.DP_SCHED_PERSISTENT)
+        ref = ev.forward(("power",))["power"][0, 0]
+        assert abs(power - ref) <= 1e-6 * abs(ref)  # paired sizes sum in another order
+        if dpi is not None:
+            np.testing.assert_array_equal(dpi, ev.backward(want=("dpi",))["dpi"][0])
+    srv.close()
+
+
+def test_group_beyond_one_sweep(ctx):
+    """A group of more (net, column) jobs than one dataflow sweep takes runs
+    merged level launches; both match each eval alone."""
+    say("groups of 40 and of 80 columns")
+    nls = [synth.random_dag(synth.DagSpec(900 * (k + 1), 30 + k, 7 + 2 * k), 60 + k) for k in range(4)]
+    for cols in (10, 20):
+        evs = []
+        for k, nl in enumerate(nls):
+            ev = api.Eval(api.Design(ctx, nl), cols)
+            ev.set_pi_prob(synth.pi_probs(nl.n_pi, 70 + k, batch=cols))
+            ev.set_caps(synth.net_caps(nl.n_nets, 71))
+            evs.append(ev)
+        for graph in (True, False):
+            g = api.Group(ctx, evs)
+            g.configure(use_graph=graph)
+            for backward in (False, True, True):
+                res = g.run(("sp", "power"), backward=backward)
+            for ev, r in zip(evs, res):
+                ev.set_schedule(L.DP_SCHED_PERSISTENT)
+                ref = ev.forward(("sp", "power"))
+                ref.update(ev.backward(want=("dpi",)))
+                ev.set_schedule(L.DP_SCHED_AUTO)
+                for k in r:
+                    np.testing.assert_array_equal(r[k], ref[k], err_msg=k)
+            g.close()
