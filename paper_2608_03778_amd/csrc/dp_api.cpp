@@ -295,10 +295,23 @@ bool flows(const dp_eval *ev, int32_t C) {
          dp::flow_fits(view(d), d->depth, std::max(C, ev->B), d->n_edges);
 }
 
+// Whether the per-(b, s) reverse sweep over C columns runs in adjoints
+// (launch_bwd_wide_level): from 16 size vectors, which then share an entry's
+// partial derivative.
+constexpr int32_t kWideSizes = 16;
+bool wide_reverse(const dp_eval *ev, int32_t C, int per_column) {
+  return per_column && s_prime(ev) >= kWideSizes && ev->schedule != DP_SCHED_PERSISTENT &&
+         !flows(ev, C);
+}
+
 // Every buffer of a reverse sweep over C columns (before any capture).
-dp_status ensure_reverse_buffers(dp_eval *ev, int32_t C) {
+dp_status ensure_reverse_buffers(dp_eval *ev, int32_t C, int per_column = 0) {
   const dp_design *d = ev->d;
   DP_TRY(ensure_flow(ev));
+  if (wide_reverse(ev, C, per_column)) {  // contrib holds the adjoints
+    DP_TRY(ev->contrib.alloc(std::max<size_t>((size_t)d->n_nets * C * sizeof(float), 16)));
+    return ev->part.alloc(std::max<size_t>((size_t)d->n_edges * ev->B * sizeof(float), 16));
+  }
   DP_TRY(ev->contrib.alloc(std::max<size_t>((size_t)d->n_edges * C * sizeof(float), 16)));
   if (flows(ev, C)) {
     DP_TRY(ev->seed.alloc(std::max<size_t>((size_t)d->n_nets * C * sizeof(float), 16)));
@@ -782,6 +795,20 @@ dp_status enqueue_backward(dp_eval *ev, const dp::BwdArgs &ba, float *dst) {
         std::max(d->max_level_width, d->n_pi), d->has_cell_gates, ctl, s));
     return DP_OK;
   }
+  if (wide_reverse(ev, ba.C, ba.per_column) && !ba.lam) {
+    float *lam = ev->contrib.as<float>(), *part = ev->part.as<float>();
+    SpanGuard sg(ev, SPAN_BWD, bwd_bytes, ev->profiling && d->depth > 0, d->depth);
+    DP_HIP_TRY(dp::launch_edge_partials(g, ba.sp, ba.B, d->has_cell_gates, part, s));
+    for (int32_t l = d->depth; l >= 1; --l) {
+      const int32_t g0 = d->level_ptr[l], n = d->level_ptr[l + 1] - g0;
+      const dp::HeavySpan hs = dp::heavy_span(d, g0, n);
+      DP_HIP_TRY(dp::launch_bwd_wide_level(g, ba, part, lam, d->n_pi + g0, n, s, hs.gates, hs.n));
+    }
+    const dp::HeavySpan hp = dp::heavy_pis(d);
+    DP_HIP_TRY(dp::launch_bwd_wide_level(g, ba, part, lam, 0, d->n_pi, s, hp.gates, hp.n));
+    DP_HIP_TRY(dp::launch_bwd_wide_out(lam, d->n_pi, ba.C, dst, s));
+    return DP_OK;
+  }
   if (ev->schedule == DP_SCHED_PERSISTENT) {
     dp::GridBarrier bar;
     DP_TRY(grid_barrier(ev, &bar));
@@ -813,6 +840,7 @@ uint64_t reverse_key(const dp_eval *ev, const dp::BwdArgs &ba, const float *dst)
   for (const void *ptr : {(const void *)ba.sp, (const void *)ba.beta, (const void *)ba.cap,
                           (const void *)ba.w, (const void *)ba.size, (const void *)ba.contrib,
                           (const void *)ba.lam, (const void *)ba.fixed, (const void *)dst,
+                          (const void *)ev->part.ptr, (const void *)ev->seed.ptr,
                           (const void *)ev->stream()})
     mix((uint64_t)(uintptr_t)ptr);
   uint32_t kb;
@@ -829,7 +857,7 @@ uint64_t reverse_key(const dp_eval *ev, const dp::BwdArgs &ba, const float *dst)
 // replayed, otherwise enqueued launch by launch.
 dp_status reverse_sweep(dp_eval *ev, const dp::BwdArgs &ba, float *dst) {
   const dp_design *d = ev->d;
-  const int64_t launches = (int64_t)d->depth + d->split_levels + 1;
+  const int64_t launches = (int64_t)d->depth + d->split_levels + 3;
   if (ev->schedule != DP_SCHED_GRAPH || ev->profiling || launches > kMaxGraphLaunches)
     return enqueue_backward(ev, ba, dst);
   const uint64_t k = reverse_key(ev, ba, dst);
@@ -1398,7 +1426,7 @@ static dp_status run_backward(dp_eval *ev, const float *grad_power, int per_colu
     w = ev->w.as<float>();
   }
   if (dpi) {
-    DP_TRY(ensure_reverse_buffers(ev, C));
+    DP_TRY(ensure_reverse_buffers(ev, C, per_column));
     const dp::BwdArgs ba = backward_args(ev, w, per_column, C);
     float *dst = dpi;
     const size_t bytes = (size_t)C * d->n_pi * sizeof(float);
@@ -1564,7 +1592,7 @@ dp_status dp_forward_backward_columns(dp_eval *ev, float *power, float *dpower_d
   ChunkPlan plan;
   if (hyb) plan = plan_chunks(ev);
   const ChunkPlan *pl = hyb ? &plan : nullptr;
-  const int64_t launches = forward_launches(ev, pl) + d->depth + d->split_levels + 1;
+  const int64_t launches = forward_launches(ev, pl) + d->depth + d->split_levels + 3;
   if (ev->schedule != DP_SCHED_GRAPH || ev->profiling || launches > kMaxGraphLaunches) {
     DP_TRY(dp_forward(ev, nullptr));
     if (power) {
@@ -1596,7 +1624,7 @@ dp_status dp_forward_backward_columns(dp_eval *ev, float *power, float *dpower_d
   hipStream_t s = ev->stream();
   DP_TRY(ensure_forward_buffers(ev, pl));
   const int32_t C = ev->B * s_prime(ev);
-  DP_TRY(ensure_reverse_buffers(ev, C));
+  DP_TRY(ensure_reverse_buffers(ev, C, 1));
   const size_t dpi_bytes = (size_t)C * d->n_pi * sizeof(float);
   float *dst = on_device ? dpower_dpi : nullptr;
   if (!dst) {  // host output, or none: the sweep writes the staging buffer

@@ -242,7 +242,7 @@ dp_status compile_design(dp_ctx *ctx, const dp_netlist *nl, int32_t n_cells,
   d->h_op.resize(G);
   d->h_arity_prefix.assign(G + 1, 0);
   std::vector<int32_t> in((size_t)pins_rows * G, 0);
-  std::vector<int32_t> rev_ptr(n_nets + 1, 0), rev_edge(n_edges);
+  std::vector<int32_t> rev_ptr(n_nets + 1, 0);
   for (int32_t gi = 0; gi < G; ++gi) {
     int32_t g = gate_of[gi];
     d->h_op[gi] = (uint8_t)internal_op(nl->op[g]);
@@ -259,22 +259,23 @@ dp_status compile_design(dp_ctx *ctx, const dp_netlist *nl, int32_t n_cells,
     for (int32_t j = 0; j < k; ++j) ++rev_ptr[in[(size_t)j * G + gi] + 1];
   }
   for (int32_t n = 0; n < n_nets; ++n) rev_ptr[n + 1] += rev_ptr[n];
+  // fan-out lists in ascending order of the reading gate, then its pin: a fixed
+  // order for the reverse sums.  rev_net: the reader's output net of each
+  // entry.  slot[j][g'] = where pin j of gate g' sits in its source net's list:
+  // the reverse sweep writes a pin's contribution there, so a net sums one
+  // contiguous range (-1: the gate has no such pin).
+  std::vector<int32_t> slot((size_t)pins_rows * G, -1), rev_net(n_edges);
   {
-    // ascending internal gate, then pin: a fixed order for the reverse sums
     std::vector<int32_t> fill(rev_ptr.begin(), rev_ptr.end() - 1);
     for (int32_t gi = 0; gi < G; ++gi) {
       int32_t k = d->h_arity_prefix[gi + 1] - d->h_arity_prefix[gi];
       for (int32_t j = 0; j < k; ++j) {
-        int32_t src = in[(size_t)j * G + gi];
-        rev_edge[fill[src]++] = j * G + gi;
+        const int32_t e = fill[in[(size_t)j * G + gi]]++;
+        slot[(size_t)j * G + gi] = e;
+        rev_net[e] = n_pi + gi;
       }
     }
   }
-  // slot[j][g'] = where pin j of gate g' sits in its source net's fan-out
-  // list: the reverse sweep writes a pin's contribution there, so a net sums
-  // one contiguous range (-1: the gate has no such pin)
-  std::vector<int32_t> slot((size_t)pins_rows * G, -1);
-  for (int64_t e = 0; e < n_edges; ++e) slot[rev_edge[e]] = (int32_t)e;
   d->lvl_pins.assign(depth + 1, 0);
   d->lvl_fanout.assign(depth + 1, 0);
   d->lvl_read.assign(depth + 1, 0);
@@ -329,7 +330,7 @@ dp_status compile_design(dp_ctx *ctx, const dp_netlist *nl, int32_t n_cells,
       (st = upload(d->tt, tt, s)) != DP_OK || (st = upload(d->arity, arity, s)) != DP_OK ||
       (st = upload(d->op, d->h_op, s)) != DP_OK || (st = upload(d->in, in, s)) != DP_OK ||
       (st = upload(d->rev_ptr, rev_ptr, s)) != DP_OK ||
-      (st = upload(d->rev_edge, rev_edge, s)) != DP_OK ||
+      (st = upload(d->rev_net, rev_net, s)) != DP_OK ||
       (st = upload(d->slot, slot, s)) != DP_OK ||
       (st = upload(d->level_dev, d->level_ptr, s)) != DP_OK ||
       (st = upload(d->int2ext, d->h_int2ext, s)) != DP_OK ||
@@ -344,7 +345,7 @@ dp_status compile_design(dp_ctx *ctx, const dp_netlist *nl, int32_t n_cells,
     delete d;
     return fail(DP_E_HIP, std::string("dp_compile: upload failed: ") + hipGetErrorString(e));
   }
-  d->device_bytes = (int64_t)(d->op.bytes + d->in.bytes + d->rev_ptr.bytes + d->rev_edge.bytes +
+  d->device_bytes = (int64_t)(d->op.bytes + d->in.bytes + d->rev_ptr.bytes + d->rev_net.bytes +
                               d->slot.bytes + d->int2ext.bytes + d->ext2int.bytes +
                               d->code.bytes + d->cell.bytes + d->tt.bytes + d->arity.bytes + d->heavy.bytes +
                               d->heavy_pi.bytes);

@@ -49,8 +49,10 @@ struct dp_eval {
   uint32_t *flow_report = nullptr;   // pinned host word: a dataflow sweep's wait gave up
   // reverse state
   dp::DevBuf w;              // [B*S'] upstream weights
-  dp::DevBuf contrib;        // [n_edges][C]
-  dp::DevBuf seed, part;     // dataflow reverse sweeps: seeds [C][n_nets], partials [B][pins][G]
+  dp::DevBuf contrib;        // [n_edges][C] contributions, or [n_nets][C] adjoints
+  // dataflow reverse sweeps: seeds [C][n_nets], partials [B][pins][G]; the
+  // per-(b, s) sweep in adjoints: partials [n_edges][B] (adjoints in contrib)
+  dp::DevBuf seed, part;
   dp::DevBuf pi_out;         // [C][n_pi] staging for host outputs
   dp::DevBuf stage[8];       // host-output staging
   // A stream of its own (serving lanes); null = the context's stream.

@@ -116,7 +116,7 @@ struct dp_design {
   dp::DevBuf op;        // uint8 [n_gates]
   dp::DevBuf in;        // int32 [pins][n_gates] input net of pin j (SoA)
   dp::DevBuf rev_ptr;   // int32 [n_nets + 1] fan-out list offsets
-  dp::DevBuf rev_edge;  // int32 [n_edges] fan-out edges, id = j * n_gates + g'
+  dp::DevBuf rev_net;   // int32 [n_edges] fan-out lists: the reader's output net
   dp::DevBuf slot;      // int32 [pins][n_gates] position of pin (g', j) in its source's fan-out list
   dp::DevBuf code;      // uint16: the library cells' stack code, concatenated
   dp::DevBuf cell;      // int32 [n_cells][3]: code offset, length, inputs
@@ -140,7 +140,7 @@ inline GraphView design_view(const dp_design *d) {
   g.op = d->op.as<uint8_t>();
   g.in = d->in.as<int32_t>();
   g.rev_ptr = d->rev_ptr.as<int32_t>();
-  g.rev_edge = d->rev_edge.as<int32_t>();
+  g.rev_net = d->rev_net.as<int32_t>();
   g.slot = d->slot.as<int32_t>();
   g.code = d->code.as<uint16_t>();
   g.cell = d->cell.as<int32_t>();

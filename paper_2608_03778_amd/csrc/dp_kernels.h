@@ -22,7 +22,7 @@ struct GraphView {
   const uint8_t *op;        // [G]
   const int32_t *in;        // [pins][G] (unused pins alias pin 0)
   const int32_t *rev_ptr;   // [n_nets + 1]
-  const int32_t *rev_edge;  // [n_edges]
+  const int32_t *rev_net;   // [n_edges] reader's output net of each fan-out entry
   const int32_t *slot;      // [pins][G] fan-out position of each pin (-1: no such pin)
   const uint16_t *code;     // [n_cells][kCellMaxCode] library cells' stack code (op | arg << 8), padded
   const int32_t *cell;      // [n_cells][3]: code offset, length, inputs
@@ -197,6 +197,20 @@ constexpr int32_t kHeavyPull = 32;
 hipError_t launch_bwd_level(const GraphView &g, const BwdArgs &a, int32_t g0, int32_t n,
                             bool cells, hipStream_t s, const int32_t *heavy = nullptr,
                             int32_t n_heavy = 0);
+// The per-(b, s) reverse sweep with many size vectors, in adjoints instead of
+// contributions: a net's adjoint is its seed plus, over its fan-out entries,
+// the reader's adjoint times the entry's partial derivative, which the size
+// vectors of one b share.  lam [n_nets][C]; part [n_edges][B].
+// launch_edge_partials fills part; then launch_bwd_wide_level per level
+// (net0: its first net; heavy: as launch_bwd_level) and for the PIs (net0 0),
+// and launch_bwd_wide_out writes out [C][n_pi].
+hipError_t launch_edge_partials(const GraphView &g, const float *sp, int32_t B, bool cells,
+                                float *part, hipStream_t s);
+hipError_t launch_bwd_wide_level(const GraphView &g, const BwdArgs &a, const float *part, float *lam,
+                                 int32_t net0, int32_t n, hipStream_t s, const int32_t *heavy,
+                                 int32_t n_heavy);
+hipError_t launch_bwd_wide_out(const float *lam, int32_t n_pi, int32_t C, float *out, hipStream_t s);
+
 // PI adjoints -> out[c][n_pi].
 // heavy[0, n_heavy): every PI with more than kHeavyPull fan-out entries
 // (ascending), pulled by cooperative workgroups at kSerialColumns columns or

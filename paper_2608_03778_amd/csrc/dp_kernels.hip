@@ -319,17 +319,24 @@ __global__ __launch_bounds__(kBlock) void k_import_cols(const float *__restrict_
 // Sizes [S][G] in caller gate order -> [G][S] in internal order: the kernels
 // that read them have a net's size vectors in consecutive lanes (with [S][G]
 // the per-(b, s) reverse level read 64 lines per wave for its sizes alone).
-// A block takes 64 gates x 32 size vectors through LDS: gathers along a row of
-// the caller's array, stores along a row of the result.
-constexpr int32_t kSizeGates = 64, kSizeVecs = 32;
+// A block takes 64 gates x 8 size vectors through LDS: gathers along a row of
+// the caller's array, stores along a row of the result.  With many vectors a
+// group of eight stays with one XCD, whose L2 holds its rows while all gates
+// gather from them (117K gates x 256: 368 us with groups of 32 anywhere).
+constexpr int32_t kSizeGates = 64, kSizeVecs = 8;
+constexpr int32_t kSizeXcds = 8;
 __global__ __launch_bounds__(kBlock) void k_import_sizes(const float *__restrict__ src,
                                                           const int32_t *__restrict__ int2ext,
                                                           float *__restrict__ dst, int32_t n_pi,
                                                           int32_t G, int32_t S) {
   __shared__ float tile[kSizeGates][kSizeVecs + 1];
   const int32_t g_tiles = (G + kSizeGates - 1) / kSizeGates;
-  const int32_t g0 = (int32_t)(blockIdx.x % g_tiles) * kSizeGates;
-  const int32_t s0 = (int32_t)(blockIdx.x / g_tiles) * kSizeVecs;
+  const int32_t groups = (S + kSizeVecs - 1) / kSizeVecs;
+  const int32_t ways = groups >= kSizeXcds ? kSizeXcds : 1;  // blocks go to the XCDs in turn
+  const int32_t slot = (int32_t)blockIdx.x / ways;
+  const int32_t g0 = (slot % g_tiles) * kSizeGates;
+  const int32_t s0 = (slot / g_tiles * ways + (int32_t)blockIdx.x % ways) * kSizeVecs;
+  if (s0 >= S) return;
   const int32_t gl = (int32_t)threadIdx.x & 63, sl = (int32_t)threadIdx.x >> 6;
   if (g0 + gl < G) {
     const int32_t e = int2ext[n_pi + g0 + gl] - n_pi;
@@ -1317,9 +1324,12 @@ __global__ __launch_bounds__(kBlock) void k_power_final(PowerArgs a, int32_t n_c
 // Local adjoint seed of net n in reverse column c (SP column b): the
 // derivative of the net's own power term, kappa C 2 (1 - 2P) (Eq. 2 and
 // Eq. 7), times beta (unless STE), the upstream weight and the driver's size
-// factor (per column, paired, or summed over the size vectors).
+// factor (per column, paired, or summed over the size vectors).  Rounded as it
+// stands (no product of it is fused into the sum that the caller adds it to),
+// so that a sweep which stores seeds has the same bits.
 __device__ __forceinline__ float seed_of(const BwdArgs &a, int32_t n, int32_t c, int32_t b,
                                          f2 pq, float beta, float cap) {
+#pragma clang fp contract(off)
   const float local = a.kappa * cap * 2.0f * (pq.y - pq.x);
   const float base = a.ste ? local : beta * local;
   const bool gate = n >= a.n_pi && a.size;
@@ -1780,6 +1790,184 @@ __global__ __launch_bounds__(kBlock) void k_bwd_pi(GraphView g, BwdArgs a, float
   }
   bwd_pi_item(g, a, out, (blockIdx.x - heavy_blocks) * kBlock + threadIdx.x, threadIdx.x & 63,
               n_heavy > 0);
+}
+
+// ---------------------------------------------------------------- many size vectors
+// The per-(b, s) reverse sweep in adjoints: lam[n][c] = seed + sum over the
+// net's fan-out entries of lam[reader][c] part[entry][b], the products rounded
+// before the sum and summed as pull_sum does, so the results are those of the
+// contributions bit for bit.  At 8,192 columns the contribution form was bound
+// by vector issue (a lane per (gate, column) took some 250 instructions: 129 us
+// per level of 1,950 gates for 255 MB); here a wave has one net, so its
+// structure and branches are scalar, a lane has VEC columns, and a net's row
+// is written once instead of once per pin.
+//
+// Partial derivative of every fan-out entry, [n_edges][B].
+template <bool CELLS>
+__global__ __launch_bounds__(kBlock) void k_edge_partials(GraphView g, const float *__restrict__ sp,
+                                                          int32_t B, float *__restrict__ part) {
+  const int64_t idx = gidx();
+  if (idx >= (int64_t)g.G * B) return;
+  const int32_t gi = (int32_t)(idx / B), b = (int32_t)(idx - (int64_t)gi * B);
+  constexpr int N = CELLS ? kCellMaxIn : 3;
+  const int op = g.op[gi];
+  int32_t pin[N], slot[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    pin[j] = pin_row(g.in, g, j)[gi];
+    slot[j] = pin_row(g.slot, g, j)[gi];
+  }
+  f2 x[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) x[j] = sp_load(sp[(int64_t)pin[j] * B + b]);
+  if constexpr (CELLS) {
+    if (op >= kCellBase) {
+      const LaneCode lc = lane_code(g, op);
+      float d[kCellMaxIn];
+      cell_partials(lc, x, d);
+#pragma unroll
+      for (int j = 0; j < kCellMaxIn; ++j)
+        if (j < lc.nin) part[(int64_t)slot[j] * B + b] = d[j];
+      return;
+    }
+  }
+  const int k = arity_of(op);
+  const f2 z = f2{0.0f, 1.0f};
+  float d0, d1, d2;
+  sp_partials(op, x[0], k > 1 ? x[1] : z, k > 2 ? x[2] : z, d0, d1, d2);
+  part[(int64_t)slot[0] * B + b] = d0;
+  if (k > 1) part[(int64_t)slot[1] * B + b] = d1;
+  if (k > 2) part[(int64_t)slot[2] * B + b] = d2;
+}
+
+// A product that is rounded before whatever is added to it.
+__device__ __forceinline__ float mul_rounded(float x, float y) {
+#pragma clang fp contract(off)
+  return x * y;
+}
+
+// VEC consecutive columns of a row.
+template <int VEC>
+struct RowPart {
+  float v[VEC];
+};
+template <int VEC>
+__device__ __forceinline__ RowPart<VEC> row_load(const float *p) {
+  RowPart<VEC> r;
+  if constexpr (VEC == 4) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const f4 x = *reinterpret_cast<const f4 *>(p);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r.v[k] = x[k];
+  } else {
+    r.v[0] = *p;
+  }
+  return r;
+}
+template <int VEC>
+__device__ __forceinline__ void row_store(float *p, const RowPart<VEC> &r) {
+  if constexpr (VEC == 4) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    *reinterpret_cast<f4 *>(p) = f4{r.v[0], r.v[1], r.v[2], r.v[3]};
+  } else {
+    *p = r.v[0];
+  }
+}
+
+// One wave per (net, 64 VEC columns), the column segments innermost.  The
+// first heavy_waves waves take the level's nets of long fan-out ranges, whose
+// rows take many load rounds, so that they start first.
+template <int VEC>
+__global__ __launch_bounds__(kBlock) void k_bwd_wide(GraphView g, BwdArgs a,
+                                                     const float *__restrict__ part, float *lam,
+                                                     int32_t net0, int32_t n, int32_t segs,
+                                                     const int32_t *__restrict__ heavy,
+                                                     int32_t n_heavy) {
+  const int32_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t task = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+  const int32_t at = (int32_t)(task / segs), seg = (int32_t)(task - (int64_t)at * segs);
+  if (at >= n_heavy + n) return;
+  const bool is_heavy = at < n_heavy;
+  int32_t net = net0 + (at - n_heavy);
+  if (is_heavy) net = (net0 ? g.n_pi : 0) + heavy[at];
+  net = __builtin_amdgcn_readfirstlane(net);
+  const int32_t e0 = __builtin_amdgcn_readfirstlane(g.rev_ptr[net]);
+  const int32_t len = __builtin_amdgcn_readfirstlane(g.rev_ptr[net + 1]) - e0;
+  if (!is_heavy && n_heavy > 0 && len > kHeavyPull) return;
+  const int32_t c0 = (seg * 64 + ((int32_t)threadIdx.x & 63)) * VEC;
+  const bool active = c0 < a.C;  // (VEC divides C)
+  const int32_t c = active ? c0 : 0, b = c / a.cdiv, s = c - b * a.cdiv;
+  // the seed's values, and the pull's first strand, go out together
+  const f2 pq = sp_load(a.sp[(int64_t)net * a.B + b]);
+  const float beta = a.beta ? a.beta[a.beta_shared ? (int64_t)net : (int64_t)net * a.B + b] : 1.0f;
+  const float cap = a.cap[net];
+  const bool gate = net >= a.n_pi && a.size;
+  RowPart<VEC> sz, w;
+#pragma unroll
+  for (int k = 0; k < VEC; ++k) sz.v[k] = w.v[k] = 1.0f;
+  if (gate) sz = row_load<VEC>(a.size + (int64_t)(net - a.n_pi) * a.S + s);
+  if (a.w) w = row_load<VEC>(a.w + c);
+  RowPart<VEC> acc;
+#pragma unroll
+  for (int k = 0; k < VEC; ++k) acc.v[k] = 0.0f;
+  for (int32_t st = 0; st < len; st += kStrand) {
+    const int32_t m = min(kStrand, len - st), e = e0 + st;
+    RowPart<VEC> x[kStrand];
+    float d[kStrand];
+#pragma unroll
+    for (int i = 0; i < kStrand; ++i) {
+      if (i < m) {  // (uniform)
+        const int32_t r = __builtin_amdgcn_readfirstlane(g.rev_net[e + i]);
+        x[i] = row_load<VEC>(lam + (int64_t)r * a.C + c);
+        d[i] = part[(int64_t)(e + i) * a.B + b];
+      }
+    }
+    RowPart<VEC> sum;
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) sum.v[k] = mul_rounded(x[0].v[k], d[0]);
+#pragma unroll
+    for (int i = 1; i < kStrand; ++i) {
+      if (i < m) {
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) sum.v[k] += mul_rounded(x[i].v[k], d[i]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) acc.v[k] = st == 0 ? sum.v[k] : acc.v[k] + sum.v[k];
+  }
+  // the seed as seed_of forms it
+  const float local = a.kappa * cap * 2.0f * (pq.y - pq.x);
+  const float base = a.ste ? local : beta * local;
+  const bool fixed = net < a.n_pi && a.fixed && a.fixed[net];
+  RowPart<VEC> out;
+#pragma unroll
+  for (int k = 0; k < VEC; ++k) {
+    float l = mul_rounded(mul_rounded(base, w.v[k]), sz.v[k]) + acc.v[k];
+    if (a.ste) l *= beta;
+    out.v[k] = fixed ? 0.0f : l;  // excluded from the gradients
+  }
+  if (active) row_store<VEC>(lam + (int64_t)net * a.C + c, out);
+}
+
+// lam rows of the PIs [n_pi][C] -> out [C][n_pi], 64 x 64 through LDS (written
+// straight, a wave's 64 values go to 64 lines).
+__global__ __launch_bounds__(kBlock) void k_bwd_wide_out(const float *__restrict__ lam, int32_t n_pi,
+                                                         int32_t C, float *__restrict__ out) {
+  __shared__ float tile[64][65];
+  const int32_t ct = (C + 63) / 64;
+  const int32_t c0 = (int32_t)(blockIdx.x % ct) * 64, i0 = (int32_t)(blockIdx.x / ct) * 64;
+  const int32_t x = (int32_t)threadIdx.x & 63, y = (int32_t)threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int32_t i = i0 + y + 4 * k;
+    if (i < n_pi && c0 + x < C) tile[y + 4 * k][x] = lam[(int64_t)i * C + c0 + x];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int32_t cc = c0 + y + 4 * k;
+    if (cc < C && i0 + x < n_pi) out[(int64_t)cc * n_pi + i0 + x] = tile[x][y + 4 * k];
+  }
 }
 
 // ---------------------------------------------------------------- adjoints and scores
@@ -2903,8 +3091,9 @@ hipError_t launch_import_cols_f32(const float *src, const int32_t *int2ext, floa
 hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, float *dst, int32_t n_pi,
                                int32_t G, int32_t S, hipStream_t s) {
   if ((int64_t)G * S <= 0) return hipSuccess;
-  const int64_t blocks = (int64_t)((G + kSizeGates - 1) / kSizeGates) *
-                         ((S + kSizeVecs - 1) / kSizeVecs);
+  const int64_t groups = (S + kSizeVecs - 1) / kSizeVecs;
+  const int64_t rounds = groups >= kSizeXcds ? (groups + kSizeXcds - 1) / kSizeXcds * kSizeXcds : groups;
+  const int64_t blocks = (int64_t)((G + kSizeGates - 1) / kSizeGates) * rounds;
   if (blocks > kMaxBlocks) return hipErrorInvalidValue;
   k_import_sizes<<<(unsigned)blocks, kBlock, 0, s>>>(src, int2ext, dst, n_pi, G, S);
   return hipGetLastError();
@@ -3181,6 +3370,44 @@ hipError_t launch_bwd_level(const GraphView &g, const BwdArgs &a, int32_t g0, in
     k_bwd_level<false, false><<<level_grid(items), level_block(items), 0, s>>>(g, a, g0, n,
                                                                               nullptr, 0, 0);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_edge_partials(const GraphView &g, const float *sp, int32_t B, bool cells,
+                                float *part, hipStream_t s) {
+  const int64_t n = (int64_t)g.G * B;
+  if (n <= 0) return hipSuccess;
+  if (too_big(n)) return hipErrorInvalidValue;
+  if (cells)
+    k_edge_partials<true><<<blocks_for(n), kBlock, 0, s>>>(g, sp, B, part);
+  else
+    k_edge_partials<false><<<blocks_for(n), kBlock, 0, s>>>(g, sp, B, part);
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_wide_level(const GraphView &g, const BwdArgs &a, const float *part, float *lam,
+                                 int32_t net0, int32_t n, hipStream_t s, const int32_t *heavy,
+                                 int32_t n_heavy) {
+  if (n <= 0 || a.C <= 0) return hipSuccess;
+  if (n_heavy < 0 || (n_heavy > 0 && !heavy) || !part || !lam || !a.per_column || a.lam)
+    return hipErrorInvalidValue;
+  // four columns a lane where their rows are whole 16-byte pieces of one b
+  const bool vec = a.C >= 256 && a.C % 4 == 0 && a.cdiv % 4 == 0;
+  const int32_t span = vec ? 256 : 64, segs = (a.C + span - 1) / span;
+  const int64_t blocks = ((int64_t)(n + n_heavy) * segs + kWavesPerBlock - 1) / kWavesPerBlock;
+  if (blocks > kMaxBlocks) return hipErrorInvalidValue;
+  if (vec)
+    k_bwd_wide<4><<<(unsigned)blocks, kBlock, 0, s>>>(g, a, part, lam, net0, n, segs, heavy, n_heavy);
+  else
+    k_bwd_wide<1><<<(unsigned)blocks, kBlock, 0, s>>>(g, a, part, lam, net0, n, segs, heavy, n_heavy);
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_wide_out(const float *lam, int32_t n_pi, int32_t C, float *out, hipStream_t s) {
+  if (n_pi <= 0 || C <= 0) return hipSuccess;
+  const int64_t blocks = (int64_t)((n_pi + 63) / 64) * ((C + 63) / 64);
+  if (blocks > kMaxBlocks) return hipErrorInvalidValue;
+  k_bwd_wide_out<<<(unsigned)blocks, kBlock, 0, s>>>(lam, n_pi, C, out);
   return hipGetLastError();
 }
 

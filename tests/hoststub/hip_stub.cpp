@@ -541,6 +541,43 @@ hipError_t launch_bwd_level(const GraphView &g, const BwdArgs &a, int32_t g0, in
   if ((int64_t)a.C > (int64_t)a.B * a.cdiv) { std::fprintf(stderr, "STUB: C > B*cdiv\n"); std::abort(); }
   return hipSuccess;
 }
+hipError_t launch_edge_partials(const GraphView &g, const float *sp, int32_t B, bool cells,
+                                float *part, hipStream_t stream_) {
+  Scope sc_(stream_);
+  for (int32_t i = 0; i < g.G; ++i)
+    if (!cells && g.op[i] >= kCellBase) fatal("library cell in a fixed-cell launch");
+  rd(sp, (int64_t)g.n_nets * B);
+  wr(part, CONTRIB_ELEMS(g) * B);
+  return hipSuccess;
+}
+hipError_t launch_bwd_wide_level(const GraphView &g, const BwdArgs &a, const float *part, float *lam,
+                                 int32_t net0, int32_t n, hipStream_t stream_, const int32_t *heavy,
+                                 int32_t n_heavy) {
+  Scope sc_(stream_);
+  if (!a.per_column || a.lam || net0 < 0 || net0 + n > g.n_nets) fatal("wide reverse range");
+  if (net0 != 0 && net0 < g.n_pi) fatal("wide reverse range over PIs and gates");
+  int32_t k = 0;  // the heavy list: gates, or PIs, of the range
+  for (int32_t i = net0; i < net0 + n; ++i) {
+    if (g.rev_ptr[i + 1] - g.rev_ptr[i] <= dp::kHeavyPull) continue;
+    if (k >= n_heavy || heavy[k] != (net0 ? i - g.n_pi : i)) fatal("heavy list of the wide sweep");
+    ++k;
+  }
+  if (k != n_heavy) fatal("heavy list of the wide sweep");
+  rd(g.rev_net, n_edges_of(g));
+  rd(part, CONTRIB_ELEMS(g) * a.B);
+  rd(a.sp, (int64_t)g.n_nets * a.B);
+  if (a.size) rd(a.size, (int64_t)a.S * a.G);
+  if (a.beta) rd(a.beta, a.beta_shared ? (int64_t)g.n_nets : (int64_t)g.n_nets * a.B);
+  wr(lam, (int64_t)g.n_nets * a.C);
+  return hipSuccess;
+}
+hipError_t launch_bwd_wide_out(const float *lam, int32_t n_pi, int32_t C, float *out,
+                               hipStream_t stream_) {
+  Scope sc_(stream_);
+  rd(lam, (int64_t)n_pi * C);
+  wr(out, (int64_t)C * n_pi);
+  return hipSuccess;
+}
 hipError_t launch_bwd_pi(const GraphView &g, const BwdArgs &a, float *out, hipStream_t stream_,
                          const int32_t *heavy, int32_t n_heavy) {
   Scope sc_(stream_);

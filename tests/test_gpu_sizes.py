@@ -56,3 +56,53 @@ def oracle_adjoint(o, f, cap, size, beta, mode, adj):
     if mode != "frozen":
         return adj["dpi"]
     return o.adjoint(f["sp"], beta, cap, size)["dpi"]
+
+
+# column counts that take one and four columns a lane, b crossing a lane's
+# and a wave's columns; nets of more than 32 readers among them
+@pytest.mark.parametrize("gates,pis,depth,B,S,mode,cells,ste", [
+    (3000, 90, 9, 8, 64, "modeled", False, False), (3000, 90, 9, 5, 100, "hybrid", False, True),
+    (3000, 90, 9, 3, 33, "hybrid", True, False), (12_000, 300, 6, 3, 256, "modeled", False, False),
+    (300, 70, 3, 16, 17, "modeled", False, False)])
+def test_reverse_of_many_size_vectors(gates, pis, depth, B, S, mode, cells, ste):
+    """The sweep in adjoints is bit for bit the one in contributions (the
+    persistent schedule's), alone and in one graph with the forward, and a
+    column's gradient does not depend on the others."""
+    say(f"many sizes, reverse: {gates} gates, B={B}, S={S}, {mode}, cells {cells}, ste {ste}")
+    ops = tuple(range(9)) + (tuple(synth.CELL_BASE + c for c in range(9)) if cells else ())
+    nl = synth.random_dag(synth.DagSpec(gates, pis, depth, ops=ops, fo_mean=3.0, fo_cap=256,
+                                        cells=synth.LIBRARY if cells else ()), 22)
+    d = api.Design(api.Context(0), nl)
+    p, cap = synth.pi_probs(pis, 1, batch=B), synth.net_caps(nl.n_nets, 2)
+    size = np.random.default_rng(3).uniform(0.3, 4.0, (S, nl.n_gates)).astype(np.float32)
+    fixed = (np.arange(pis) % 7 == 0).astype(np.uint8)
+
+    def make(bs, ss, sched):
+        ev = api.Eval(d, len(bs), len(ss), n_sim=64 * 8, seed=2,
+                      mode=L.DP_HYBRID if mode == "hybrid" else L.DP_MODELED,
+                      beta_grad=L.DP_BETA_STE if ste else L.DP_BETA_LOCAL)
+        ev.set_pi_prob(p[bs])
+        ev.set_caps(cap)
+        ev.set_cell_sizes(size[ss])
+        ev.set_pi_fixed(fixed)
+        ev.set_schedule(sched)
+        return ev
+    every = (list(range(B)), list(range(S)))
+    ev = make(*every, L.DP_SCHED_AUTO)
+    ev.forward(("power",))
+    dpi = ev.backward_columns()
+    np.testing.assert_array_equal(ev.backward_columns(), dpi)
+    ev = make(*every, L.DP_SCHED_GRAPH)
+    for _ in range(3):
+        _, g = ev.forward_backward_columns()
+        np.testing.assert_array_equal(g, dpi)
+    if not cells:
+        ev = make(*every, L.DP_SCHED_PERSISTENT)
+        ev.forward(("power",))
+        np.testing.assert_array_equal(ev.backward_columns(), dpi)
+    ev = make([0, B - 1], [1, S - 1], L.DP_SCHED_AUTO)
+    ev.forward(("power",))
+    np.testing.assert_array_equal(ev.backward_columns(), dpi[np.ix_([0, B - 1], [1, S - 1])])
+    o = oracle.Netlist.of(nl)
+    f, adj = oracle_column(o, p[B - 1], cap, size[S - 1], mode=mode, n_words=8, seed=2, ste=ste)
+    assert_grad_close(dpi[B - 1, S - 1], np.where(fixed, 0.0, adj["dpi"]), "dP/dp")
