@@ -180,13 +180,50 @@ struct ChunkPlan {
   int32_t halo = 0, n_chunks = 0;
   int32_t cols = 1;      // query columns per launch
   int32_t n_groups = 1;  // column groups, ceil(B / cols)
+  // word tiles (launch_sim_flow) instead: words per tile (0: level launches),
+  // tiles per column, teams' buffers
+  int32_t tile = 0, n_tiles = 0, n_bufs = 0;
 };
 
 int32_t n_sim_streams(const dp_eval *ev) { return ev->sim_streams > 0 ? ev->sim_streams : 1; }
 
+bool flows(const dp_eval *ev, int32_t C);
+
+// Whether the simulation runs in word tiles, and in which: with chunks, streams
+// and columns left automatic, fixed cells only, and the SP sweep a dataflow
+// launch of its own.  Up to 24 tiles are a round of the teams; of the pitches
+// that stay within it the narrowest (a level's turns grow with the pitch),
+// and 64 words up to 32 tiles.  Beyond, and beyond 2^28 words over all nets
+// and columns, the level launches' longer rows are the faster ones (forward,
+// us, tiles against levels: 2K gates x 1280 words 105 / 123, x 5120 184 / 167;
+// 117K x 257 271 / 424, x 1024 638 / 691; 300K x 1024 1516 / 1368; 1M x 257
+// 1670 / 1966), as they are where fewer than 16 tiles leave XCDs without work
+// in levels of more than 8192 gates (1M x 64: 899 / 817).
+constexpr int64_t kTileMaxWords = 1ll << 28;
+constexpr int32_t kTileTeams = 24, kTileWide = 8192;
+void plan_tiles(const dp_eval *ev, ChunkPlan *c) {
+  const dp_design *d = ev->d;
+  if (ev->words_per_chunk > 0 || ev->sim_streams > 1 || ev->sim_cols > 0 ||
+      d->has_cell_gates || d->depth < 1 || !flows(ev, ev->B) || c->T > kTileMaxWords / d->n_nets / ev->B)
+    return;
+  for (int32_t pitch : {16, 32, 64}) {
+    const int64_t tiles = (c->T + pitch - 1) / pitch * ev->B;
+    if (tiles > (pitch < 64 ? kTileTeams : dp::kSimBufs)) continue;
+    if (tiles < 16 && d->max_level_width > kTileWide) return;
+    if (!dp::sim_fits(view(d), d->depth, ev->B, pitch, c->T)) return;
+    c->n_chunks = 1;  // of the level launches in its place
+    c->tile = pitch;
+    c->n_tiles = (int32_t)(tiles / ev->B);
+    c->n_bufs = (int32_t)tiles;
+    return;
+  }
+}
+
 ChunkPlan plan_chunks(const dp_eval *ev) {
   ChunkPlan c;
   c.T = n_words(ev->prm);
+  plan_tiles(ev, &c);
+  if (c.tile) return c;
   // words per net that fit one stream's share of the budget, over all the
   // columns of its buffer
   const int64_t row_budget = std::max<int64_t>(
@@ -378,10 +415,11 @@ int64_t sp_sweep_launches(const dp_design *d, int32_t B) {
   return n;
 }
 
-// Kernel launches of one forward sweep (what a captured graph would hold).
+// Kernel launches of one forward sweep in level launches (what a captured
+// graph holds at most).
 int64_t forward_launches(const dp_eval *ev, const ChunkPlan *pl) {
   const int64_t depth = ev->d->depth + ev->d->split_levels;
-  if (!pl) return (flows(ev, ev->B) ? 2 : sp_sweep_launches(ev->d, ev->B)) + 2;
+  if (!pl) return sp_sweep_launches(ev->d, ev->B) + 2;
   return (int64_t)pl->n_groups * pl->n_chunks * (depth + 1) + 4 + (markov(ev) ? 1 : 0) +
          ev->d->cell_levels;  // the library cells' SP launches
 }
@@ -400,6 +438,14 @@ dp_status ensure_forward_buffers(dp_eval *ev, const ChunkPlan *pl) {
   if (pl) {
     DP_TRY(ev->ones.alloc(nb * sizeof(uint32_t)));
     DP_TRY(ev->tog.alloc(nb * sizeof(uint32_t)));
+    if (pl->tile) {
+      DP_TRY(ev->sim_ctl.alloc(dp::kSimWords * sizeof(uint32_t)));
+      DP_TRY(ev->words.alloc((size_t)pl->n_bufs * d->n_nets * pl->tile * sizeof(uint64_t)));
+      DP_TRY(ev->tiles.alloc((size_t)pl->n_tiles * nb * (2 * sizeof(uint64_t) + sizeof(uint32_t))));
+      if (!ev->have_stim)
+        DP_TRY(ev->mstim.alloc(std::max<size_t>((size_t)ev->B * d->n_pi * pl->T * sizeof(uint64_t), 16)));
+      return DP_OK;
+    }
     const int32_t L = n_sim_streams(ev);
     DP_TRY(ev->words.alloc((size_t)L * pl->cols * d->n_nets * pl->pitch * sizeof(uint64_t)));
     if (markov(ev))
@@ -461,7 +507,7 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
   const dp::GraphView g = view(d);
   const bool prof = ev->profiling;
   float *sp = ev->sp.as<float>();
-  if (!pl) {  // modeled (or frozen-beta) sweep: one span over all level launches
+  if (!pl || pl->tile) {  // modeled (or frozen-beta) sweep: one span over all level launches
     double bytes = 0.0;
     for (int32_t l = 1; l <= d->depth; ++l) bytes += sp_level_bytes(d, l, ev->B);
     SpanGuard sg(ev, SPAN_SP, bytes, prof && d->depth > 0,
@@ -497,7 +543,32 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
         ++l;
       }
     }
-  } else {
+  }
+  if (pl && pl->tile) {
+    const int32_t *streams = ev->have_streams ? ev->streams.as<int32_t>() : nullptr;
+    const uint64_t *stim = ev->have_stim ? ev->stim.as<uint64_t>() : ev->mstim.as<uint64_t>();
+    if (!ev->have_stim) {
+      SpanGuard sg(ev, SPAN_STIM, 0.0, prof, 1);
+      if (markov(ev))
+        DP_HIP_TRY(dp::launch_markov_words(sp, ev->tau.as<float>(), streams, d->n_pi, ev->B, pl->T,
+                                           ev->prm.seed, ev->mstim.as<uint64_t>(), s));
+      else
+        DP_HIP_TRY(dp::launch_stim_words(sp, streams, d->n_pi, ev->B, pl->T, ev->prm.seed,
+                                         ev->mstim.as<uint64_t>(), s));
+    }
+    double bytes = 0.0;
+    for (int32_t l = 1; l <= d->depth; ++l)
+      bytes += sim_level_bytes(d, l, pl->T, ev->B, ev->B, false);
+    SpanGuard sg(ev, SPAN_SIM, bytes, prof, 1);
+    uint64_t *edge = ev->tiles.as<uint64_t>();
+    const size_t n = (size_t)pl->n_tiles * d->n_nets * ev->B;
+    const dp::SimFlow t{g, d->level_dev.as<int32_t>(), stim, ev->words.as<uint64_t>(),
+                        reinterpret_cast<uint32_t *>(edge + 2 * n), edge, pl->T, d->depth, ev->B,
+                        pl->tile, pl->n_tiles, pl->n_bufs};
+    dp::FlowCtl ctl = flow_ctl(ev);
+    ctl.words = ev->sim_ctl.as<uint32_t>();
+    DP_HIP_TRY(dp::launch_sim_flow(t, ctl, sp, ev->ones.as<uint32_t>(), ev->tog.as<uint32_t>(), s));
+  } else if (pl) {
     const size_t nb = (size_t)d->n_nets * ev->B;
     DP_HIP_TRY(dp::launch_fill_u32(ev->ones.as<uint32_t>(), (int64_t)nb, 0u, s));
     DP_HIP_TRY(dp::launch_fill_u32(ev->tog.as<uint32_t>(), (int64_t)nb, 0u, s));
@@ -704,6 +775,9 @@ uint64_t graph_key(const dp_eval *ev, const ChunkPlan *pl) {
   mix((uint64_t)ev->beta_shared);
   if (pl) {
     mix((uint64_t)pl->Tc);
+    mix((uint64_t)pl->tile);
+    mix((uint64_t)pl->n_bufs);
+    mix((uint64_t)(uintptr_t)ev->tiles.ptr);
     mix((uint64_t)pl->cols);
     mix((uint64_t)pick_iters(ev, *pl));
     mix((uint64_t)n_sim_streams(ev));
@@ -1242,7 +1316,16 @@ dp_status dp_eval_autotune(dp_eval *ev, int32_t reps, int32_t with_backward, dou
   std::vector<Cand> cands;
   const int64_t T = n_words(ev->prm);
   if (hybrid(ev)) {
-    const int64_t chunks[3] = {0, (T / 2 + 1) & ~1ll, (T / 4 + 1) & ~1ll};
+    DP_TRY(ensure_flow(ev));
+    // automatic chunks on one stream may be word tiles; whole rows in level
+    // launches are then a chunk of T words
+    ev->words_per_chunk = ev->sim_streams = 0;
+    const bool tiles = plan_chunks(ev).tile > 0;
+    ev->words_per_chunk = c0;
+    ev->sim_streams = l0;
+    if (tiles)
+      for (int32_t sc : {DP_SCHED_LEVEL, DP_SCHED_GRAPH}) cands.push_back({sc, 1, 0, 1});
+    const int64_t chunks[3] = {tiles ? T : 0, (T / 2 + 1) & ~1ll, (T / 4 + 1) & ~1ll};
     for (int k = 0; k < 3; ++k) {
       if (k > 0 && chunks[k] < 128) continue;
       for (int32_t lanes : {1, 2, 4}) {
@@ -1387,6 +1470,7 @@ dp_status dp_forward(dp_eval *ev, const dp_fwd_out *out) {
     return fail(DP_E_STATE, "dp_forward: the explicit stimulus is shorter than n_sim/64 words");
   DP_HIP_TRY(hipSetDevice(d->ctx->device));
   hipStream_t s = ev->stream();
+  DP_TRY(ensure_flow(ev));
   ChunkPlan plan;
   if (hyb) plan = plan_chunks(ev);
   const ChunkPlan *pl = hyb ? &plan : nullptr;
@@ -1589,6 +1673,8 @@ dp_status dp_forward_backward_columns(dp_eval *ev, float *power, float *dpower_d
   // the schedules that capture: the whole pair of sweeps as one graph;
   // otherwise the two calls as they are
   const bool hyb = hybrid(ev);
+  DP_HIP_TRY(hipSetDevice(d->ctx->device));
+  DP_TRY(ensure_flow(ev));
   ChunkPlan plan;
   if (hyb) plan = plan_chunks(ev);
   const ChunkPlan *pl = hyb ? &plan : nullptr;
@@ -2147,6 +2233,7 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
     if (hybrid(ev) && ev->have_stim &&
         ev->stim.bytes < (size_t)ev->B * d->n_pi * n_words(ev->prm) * sizeof(uint64_t))
       return fail(DP_E_STATE, "dp_group_run: an explicit stimulus is too short");
+    DP_TRY(ensure_flow(ev));
     if (hybrid(ev)) plans[i] = plan_chunks(ev);
     DP_TRY(ensure_forward_buffers(ev, hybrid(ev) ? &plans[i] : nullptr));
     cost[i] = forward_launches(ev, hybrid(ev) ? &plans[i] : nullptr);

@@ -36,7 +36,9 @@ struct dp_eval {
        have_stim = false, have_tau = false, have_streams = false, have_fixed = false;
   uint64_t inputs_version = 1, fwd_version = 0;
   // forward state
-  dp::DevBuf words;          // simulation chunk [n_nets][pitch]
+  dp::DevBuf words;          // simulation chunk [n_nets][pitch], or the teams' tiles
+  dp::DevBuf sim_ctl;        // word tiles: control words (dp::kSimWords)
+  dp::DevBuf tiles;          // word tiles: first and last words, counts per (tile, net)
   dp::DevBuf ones, tog;      // [n_nets][B]
   dp::DevBuf beta;           // [n_nets][B] computed beta (hybrid mode only)
   dp::DevBuf power_partial;  // [chunks][B*S'] double

@@ -387,6 +387,47 @@ hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl c
 hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl ctl,
                            hipStream_t s);
 
+// The simulation in word tiles (see the kernels): a tile is `pitch` words of
+// one column, all levels by one team of workgroups of one XCD; fixed cells
+// only.  Control words: a line per (XCD, team) with its registration; the
+// next team buffer, the next tile, the stop flag; per buffer a line with its
+// team's claimed tile and one per member for the level flags.
+constexpr int kSimTeams = 4;      // teams per XCD at most
+constexpr int kSimMembers = 32;   // workgroups per team at most
+constexpr int kSimBufs = kFlowDies * kSimTeams;
+constexpr int kSimReg = 0;
+constexpr int kSimNextBuf = kSimReg + 32 * kFlowXcds * kSimTeams;
+constexpr int kSimNextTile = kSimNextBuf + 32;
+constexpr int kSimStop = kSimNextTile + 32;
+constexpr int kSimClaim = kSimStop + 32;
+constexpr int kSimFlags = kSimClaim + 32 * kSimBufs;
+constexpr int kSimWords = kSimFlags + 32 * kSimBufs * kSimMembers;
+struct SimFlow {
+  GraphView g;
+  const int32_t *level_ptr;
+  const uint64_t *stim;  // [B][n_pi][T] the PIs' words
+  uint64_t *W;           // [n_bufs][n_nets][pitch] the teams' rows
+  uint32_t *cnt;         // [B][n_chunks][n_nets] counts, ones | toggles << 16
+  uint64_t *edge;        // [B][n_chunks][n_nets][2] first and last word
+  int64_t T;
+  int32_t depth, B;
+  int32_t pitch, n_chunks;  // words per tile (16, 32 or 64), tiles per column
+  int32_t n_bufs;           // teams that work at once
+};
+// Whether a simulation is within the kernels' 32-bit offsets and tables.
+inline bool sim_fits(const GraphView &g, int32_t depth, int32_t B, int32_t pitch, int64_t T) {
+  return depth >= 1 && depth + 2 <= kFlowLevels && (pitch == 16 || pitch == 32 || pitch == 64) &&
+         (int64_t)g.n_nets * pitch < (1ll << 29) && g.n_nets < (1 << 27) &&
+         (T + pitch - 1) / pitch < 65535 / B;
+}
+hipError_t launch_stim_words(const float *sp /* stored SP [n_pi][B] */, const int32_t *stream,
+                             int32_t n_pi, int32_t B, int64_t T, uint64_t seed, uint64_t *out,
+                             hipStream_t s);
+// ctl.words: [kSimWords].  Writes ones and tog [n_nets][B]; a simulation that
+// gives up leaves NaN in sp.
+hipError_t launch_sim_flow(const SimFlow &t, FlowCtl ctl, float *sp, uint32_t *ones, uint32_t *tog,
+                           hipStream_t s);
+
 // dcap[ext n] = sum_{b,s} w[b][s] x[n][b] size_s(n) and dsize[s][ext g] =
 // sum_b w[b][s] x[out g][b] C_out g, with x = kappa beta TR_model
 // recomputed from SP and beta.

@@ -2274,11 +2274,11 @@ __device__ __forceinline__ void flow_store(float *base, uint32_t bytes, float v)
 }
 
 // One more poll of a wait: false when the wait has to end.
-__device__ __forceinline__ bool flow_again(const FlowCtl &ctl, uint32_t &polls) {
+__device__ __forceinline__ bool flow_again(const FlowCtl &ctl, int stop, uint32_t &polls) {
   if ((++polls & 63u) != 0u) return true;
-  if (flow_load(ctl.words + kFlowStop) != 0u) return false;
+  if (flow_load(ctl.words + stop) != 0u) return false;
   if (polls < kFlowPolls) return true;
-  __hip_atomic_store(ctl.words + kFlowStop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(ctl.words + stop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(ctl.report, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   return false;
 }
@@ -2309,7 +2309,7 @@ __device__ __forceinline__ FlowSeat flow_join(const FlowCtl &ctl) {
       __hip_atomic_store(open, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else if (!(r & kFlowClosed)) {
       uint32_t polls = 0;
-      while ((n = flow_load(open)) == 0u && flow_again(ctl, polls)) {
+      while ((n = flow_load(open)) == 0u && flow_again(ctl, kFlowStop, polls)) {
       }
     }
     seat = FlowSeat{team, r, n};
@@ -2336,7 +2336,7 @@ __device__ __forceinline__ int32_t flow_claim(const FlowCtl &ctl, const FlowSeat
       __hip_atomic_store(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
       uint32_t polls = 0;
-      while ((v = flow_load(slot)) == 0u && flow_again(ctl, polls)) {
+      while ((v = flow_load(slot)) == 0u && flow_again(ctl, kFlowStop, polls)) {
       }
     }
     col = (int32_t)v - 2;
@@ -2473,7 +2473,7 @@ __device__ __forceinline__ SpFlowIn<CELLS> sp_flow_poll(const FlowCtl &ctl, cons
 #pragma unroll
     for (int j = 0; j < N; ++j) wait = wait || is_armed(x.v[j]);
     if (!wait) break;
-    if (!flow_again(ctl, polls)) {
+    if (!flow_again(ctl, kFlowStop, polls)) {
       x.ok = 0;
       break;
     }
@@ -2683,7 +2683,7 @@ __device__ __forceinline__ float flow_strand(const FlowCtl &ctl, const BwdFlowCo
       worst = max(worst, b);  // kArmed is the largest
     }
     if (worst != kArmed) break;
-    if (!flow_again(ctl, polls)) {
+    if (!flow_again(ctl, kFlowStop, polls)) {
       ok = 0;
       break;
     }
@@ -2915,6 +2915,362 @@ __global__ __launch_bounds__(kBlock) void k_bwd_arm_multi(const BwdFlowSeg *__re
   const BwdFlow t = global_view(segs[k].t);
   bwd_arm<CELLS>(t, words, k == 0 ? kFlowWords : 0, blockIdx.x - segs[k].block0,
                  segs[k].arm_blocks, segs[k].seed_blocks);
+}
+
+// ---------------------------------------------------------------- word tiles
+// The simulation of one query column's `pitch` consecutive words of cycles (a
+// tile), all levels in one launch, by a team of one XCD: cycles are
+// independent, so a tile needs nothing from another but the word before it,
+// whose toggle the count kernel adds at the end.  Short simulations were
+// bound by their chain of level launches (5.5 to 6.8 us each for a level of
+// 0.3 to 4 MB); inside an XCD a level costs its barrier (0.7 us), the drain
+// of its stores and a turn of row loads, pin 0's from the XCD's own L2, and
+// other teams' tiles fill the waits.  50K gates x 45 levels, 5 columns of 64
+// words: 277 -> 110 us; 117K gates x 60 levels, 257 words: 408 -> 190 us
+// (3.2 us a level, about half of it the fabric's: half of the row reads are of
+// older levels and miss the L2, and every row is evicted).
+//
+// Rows are [net][pitch] words of the team's own buffer, whole cache lines:
+// 16 words (2 * LPG) while that gives no more tiles than teams, as a turn of
+// the workgroup then covers the most gates.  LPG lanes take one gate's row, a
+// pair of words each, so a wave takes 64 / LPG consecutive gates (sorted by
+// cell: mostly one cell).  Row loads go past the L1, which other CUs' stores
+// do not reach.  Rows are stored before the workgroup's flag; a level's last
+// counts are left for the wait after it.  Loading older levels' rows before
+// the wait, or the next turn's during a turn, was slower (432 to 510 against
+// 438 us for the second case's whole pass): the waits are of the memory.
+//
+// A tile leaves per net its counts (packed, ones low) and its first and last
+// word; k_sim_counts adds them up over the chunks with the toggles between
+// chunks.
+struct SimSeat {
+  uint32_t buf, rank, members;  // members == 0: not a member
+};
+
+__device__ __forceinline__ SimSeat sim_join(const FlowCtl &ctl, uint32_t n_bufs) {
+  __shared__ SimSeat seat;
+  if (threadIdx.x == 0) {
+    uint32_t x;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
+    const uint32_t sub = min(blockIdx.x / kFlowDies / ctl.expected, (uint32_t)kSimTeams - 1);
+    uint32_t *reg = ctl.words + kSimReg + ((x & (kFlowXcds - 1)) * kSimTeams + sub) * 32;
+    uint32_t *open = reg + 16;
+    const uint32_t r = __hip_atomic_fetch_add(reg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t v = 0;  // members | (buffer + 1) << 8
+    if (r == 0) {
+      const uint32_t buf = __hip_atomic_fetch_add(ctl.words + kSimNextBuf, 1u, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+      const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+      while (flow_load(reg) < ctl.expected && __builtin_amdgcn_s_memrealtime() - t0 < kFlowJoinTicks) {
+      }
+      const uint32_t n = __hip_atomic_fetch_or(reg, kFlowClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      v = min(n, (uint32_t)kSimMembers) | (buf + 1) << 8;
+      __hip_atomic_store(open, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (!(r & kFlowClosed)) {
+      uint32_t polls = 0;
+      while ((v = flow_load(open)) == 0u && flow_again(ctl, kSimStop, polls)) {
+      }
+    }
+    const uint32_t buf = (v >> 8) - 1, members = v & 255u;
+    // a team without a buffer, or a workgroup beyond a team's flags, leaves
+    seat = SimSeat{buf, r, v != 0u && buf < n_bufs && r < members ? members : 0u};
+  }
+  __syncthreads();
+  return SimSeat{(uint32_t)__builtin_amdgcn_readfirstlane((int)seat.buf),
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)seat.rank),
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)seat.members)};
+}
+
+// The team's barrier in two halves.  Arrive: this workgroup's stores so far
+// are in the L2, which its flag (a line of its own) tells.
+__device__ __forceinline__ void sim_arrive(const FlowCtl &ctl, const SimSeat &st, uint32_t epoch) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(ctl.words + kSimFlags + (st.buf * kSimMembers + st.rank) * 32, epoch,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// Wait: every member has arrived.  The first wave reads all flags.  False (in
+// the whole workgroup) when the wait gave up.
+__device__ __forceinline__ bool sim_wait(const FlowCtl &ctl, const SimSeat &st, uint32_t epoch) {
+  __shared__ int32_t go;
+  if (threadIdx.x < 64) {
+    const uint32_t *flags = ctl.words + kSimFlags + st.buf * kSimMembers * 32;
+    uint32_t polls = 0;
+    int32_t ok = 1;
+    for (;;) {
+      const uint32_t v = threadIdx.x < st.members ? flow_load(flags + threadIdx.x * 32) : epoch;
+      if (__all((int32_t)(v - epoch) >= 0)) break;
+      if (!__any(flow_again(ctl, kSimStop, polls))) {
+        ok = 0;
+        break;
+      }
+    }
+    if (threadIdx.x == 0) go = ok;
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(go) != 0;
+}
+
+// The team's k-th tile, or -1 when the list is used up.  (One word: a member
+// that has not read it yet is still before the next level's barrier, which
+// the leader cannot pass.)
+__device__ __forceinline__ int32_t sim_claim(const FlowCtl &ctl, const SimSeat &st, uint32_t k,
+                                             int32_t n_tiles) {
+  __shared__ int32_t tile;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t *slot = ctl.words + kSimClaim + st.buf * 32;  // sequence k + 1, tile + 1 (0: none left)
+    uint32_t v = 0;
+    if (st.rank == 0) {
+      const uint32_t t = __hip_atomic_fetch_add(ctl.words + kSimNextTile, 1u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+      v = (k + 1) << 16 | (t < (uint32_t)n_tiles ? t + 1 : 0u);
+      __hip_atomic_store(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      uint32_t polls = 0;
+      while ((v = flow_load(slot)) >> 16 != k + 1)
+        if (!flow_again(ctl, kSimStop, polls)) {
+          v = 0;
+          break;
+        }
+    }
+    tile = (int32_t)(v & 0xffffu) - 1;
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(tile);
+}
+
+// Sum over the LPG lanes of a gate; the gate's last lane has it.
+template <int LPG>
+__device__ __forceinline__ uint32_t row_sum(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
+  if constexpr (LPG > 8) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+  if constexpr (LPG > 16) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+  return v;
+}
+
+// The previous lane's value (a gate's first lane does not use it).
+template <int LPG>
+__device__ __forceinline__ uint64_t prev_lane(uint64_t v) {
+  constexpr int ctrl = LPG <= 16 ? 0x111 : 0x138;  // row_shr:1, wave_shr:1
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, ctrl, 0xf, 0xf, true);
+  const uint32_t hi =
+      (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), ctrl, 0xf, 0xf, true);
+  return (uint64_t)hi << 32 | lo;
+}
+
+// What is uniform over a tile.
+struct SimTile {
+  __amdgpu_buffer_rsrc_t rows;  // the team's buffer
+  uint32_t *cnt;                // [n_nets]
+  uint64_t *edge;               // [n_nets][2]
+  int32_t nw;                   // words of the chunk
+};
+
+// A gate's (or PI's) words, two per lane.
+struct SimWords {
+  uint64_t y0, y1;
+  uint32_t net;
+  bool valid;
+};
+template <int LPG>
+__device__ __forceinline__ void sim_store(const SimTile &t, const SimWords &w, bool keep) {
+  const uint32_t l = threadIdx.x & (LPG - 1);
+  if (w.valid && keep && 2 * (int32_t)l < t.nw) {
+    const u4 v = u4{(uint32_t)w.y0, (uint32_t)(w.y0 >> 32), (uint32_t)w.y1, (uint32_t)(w.y1 >> 32)};
+    __builtin_amdgcn_raw_buffer_store_b128(v, t.rows, (int)(w.net * (LPG * 16u) + 16u * l), 0, 0);
+  }
+}
+// Its counts and its first and last word.
+template <int LPG>
+__device__ __forceinline__ void sim_count(const SimTile &t, const SimWords &w) {
+  const uint64_t y0 = w.y0, y1 = w.y1;
+  const uint32_t net = w.net;
+  const int32_t l = (int32_t)threadIdx.x & (LPG - 1), u0 = 2 * l;
+  const bool in0 = u0 < t.nw, in1 = u0 + 1 < t.nw;
+  const uint64_t prev = prev_lane<LPG>(y1);
+  uint32_t ones = 0, togs = 0;
+  if (in0) {
+    ones = __popcll(y0);
+    if (l) togs = __popcll(y0 ^ prev);
+  }
+  if (in1) {
+    ones += __popcll(y1);
+    togs += __popcll(y0 ^ y1);
+  }
+  const uint32_t sum = row_sum<LPG>(togs << 16 | ones);
+  if (!w.valid) return;
+  if (l == LPG - 1) *flow_at(t.cnt, 4 * net) = sum;
+  if (l == 0) *flow_at(t.edge, 16 * net) = y0;
+  if (u0 == ((t.nw - 1) & ~1)) *flow_at(t.edge + 1, 16 * net) = in1 ? y1 : y0;
+}
+
+struct SimFlowFetch {
+  int32_t op;
+  uint32_t pin[3];
+  int32_t e0, e1;
+};
+__device__ __forceinline__ SimFlowFetch sim_flow_fetch(const GraphView &g, uint32_t gi) {
+  SimFlowFetch f;
+  f.op = *flow_at(g.op, gi);
+  flow_pins(g.in, g, gi, f.pin);
+  f.e0 = *flow_at(g.rev_ptr + g.n_pi, 4 * gi);
+  f.e1 = *flow_at(g.rev_ptr + g.n_pi + 1, 4 * gi);
+  return f;
+}
+
+template <int LPG>
+__device__ __forceinline__ u4 sim_row(const SimTile &t, uint32_t net, uint32_t l16) {
+  return __builtin_amdgcn_raw_buffer_load_b128(t.rows, (int)(net * (LPG * 16u) + l16), 0, kBufferSc1);
+}
+
+template <int LPG>
+__global__ __launch_bounds__(kFlowThreads) void k_sim_flow(FlowCtl ctl, SimFlow t) {
+  const SimSeat st = sim_join(ctl, (uint32_t)t.n_bufs);
+  if (st.members == 0) return;
+  for (int32_t i = (int32_t)threadIdx.x; i < t.depth + 2; i += (int32_t)blockDim.x)
+    flow_lv[i] = t.level_ptr[i];
+  __syncthreads();
+  constexpr int GP = 64 / LPG;  // gates of a wave
+  constexpr int32_t pitch = 2 * LPG;
+  const GraphView &g = t.g;
+  const int32_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int32_t first = GP * (wave * (int32_t)st.members + (int32_t)st.rank);
+  const int32_t step = GP * (int32_t)((blockDim.x >> 6) * st.members);
+  const int32_t sub = ((int32_t)threadIdx.x & 63) / LPG;
+  const uint32_t l = threadIdx.x & (LPG - 1), l16 = 16 * l;
+  SimTile tile;
+  tile.rows = __builtin_amdgcn_make_buffer_rsrc(t.W + (int64_t)st.buf * g.n_nets * pitch, 0,
+                                                (int)((uint32_t)g.n_nets * (pitch * 8u)), 0x00020000);
+  uint32_t epoch = 0;
+  for (uint32_t k = 0;; ++k) {
+    const int32_t id = sim_claim(ctl, st, k, t.n_chunks * t.B);
+    if (id < 0) return;
+    const int32_t b = id / t.n_chunks;
+    const int64_t t0 = (int64_t)(id - b * t.n_chunks) * pitch;
+    tile.nw = (int32_t)min<int64_t>(pitch, t.T - t0);
+    tile.cnt = t.cnt + (int64_t)id * g.n_nets;
+    tile.edge = t.edge + (int64_t)id * g.n_nets * 2;
+    // the PIs' rows
+    for (int32_t base = first; base < g.n_pi; base += step) {
+      const int32_t i = min(base + sub, g.n_pi - 1);
+      const uint64_t *row = t.stim + ((int64_t)b * g.n_pi + i) * t.T + t0;
+      const int32_t u0 = 2 * (int32_t)l;
+      const SimWords w{u0 < tile.nw ? row[u0] : 0, u0 + 1 < tile.nw ? row[u0 + 1] : 0, (uint32_t)i,
+                       base + sub < g.n_pi};
+      sim_store<LPG>(tile, w, true);
+      sim_count<LPG>(tile, w);
+    }
+    sim_arrive(ctl, st, ++epoch);
+    SimWords last{0, 0, 0, false};
+    for (int32_t lv = 1; lv <= t.depth; ++lv) {
+      const int32_t g0 = __builtin_amdgcn_readfirstlane(flow_lv[lv]);
+      const int32_t n = __builtin_amdgcn_readfirstlane(flow_lv[lv + 1]) - g0;
+      // while the other members arrive: the first gates' structure, and the
+      // counts of the level before's last ones
+      SimFlowFetch f = sim_flow_fetch(g, (uint32_t)(g0 + min(first + sub, n - 1)));
+      sim_count<LPG>(tile, last);
+      last.valid = false;
+      if (!sim_wait(ctl, st, epoch)) return;
+      for (int32_t base = first; base < n; base += step) {
+        if (base != first) sim_count<LPG>(tile, last);
+        const SimFlowFetch c = f;
+        last.net = (uint32_t)(g.n_pi + g0 + min(base + sub, n - 1));
+        last.valid = base + sub < n;
+        const int k3 = arity_of(c.op);
+        u4 x0 = sim_row<LPG>(tile, c.pin[0], l16), x1 = u4{0, 0, 0, 0}, x2 = x1;
+        if (k3 > 1) x1 = sim_row<LPG>(tile, c.pin[1], l16);
+        if (k3 > 2) x2 = sim_row<LPG>(tile, c.pin[2], l16);
+        if (base + step < n) f = sim_flow_fetch(g, (uint32_t)(g0 + min(base + step + sub, n - 1)));
+        const uint64_t a0 = (uint64_t)x0[1] << 32 | x0[0], a1 = (uint64_t)x0[3] << 32 | x0[2];
+        const uint64_t b0 = (uint64_t)x1[1] << 32 | x1[0], b1 = (uint64_t)x1[3] << 32 | x1[2];
+        const uint64_t c0 = (uint64_t)x2[1] << 32 | x2[0], c1 = (uint64_t)x2[3] << 32 | x2[2];
+        uint64_t y0, y1;
+        switch (c.op) {
+#define DP_SIM_CASE(OP) case OP: y0 = cell_bits<OP>(a0, b0, c0); y1 = cell_bits<OP>(a1, b1, c1); break
+          DP_SIM_CASE(INV);
+          DP_SIM_CASE(BUF);
+          DP_SIM_CASE(AND2);
+          DP_SIM_CASE(OR2);
+          DP_SIM_CASE(NAND2);
+          DP_SIM_CASE(NOR2);
+          DP_SIM_CASE(XOR2);
+          DP_SIM_CASE(AOI21);
+#undef DP_SIM_CASE
+          default: y0 = cell_bits<MUX2>(a0, b0, c0); y1 = cell_bits<MUX2>(a1, b1, c1); break;
+        }
+        last.y0 = y0;
+        last.y1 = y1;
+        sim_store<LPG>(tile, last, c.e1 > c.e0);
+      }
+      sim_arrive(ctl, st, ++epoch);
+    }
+    sim_count<LPG>(tile, last);
+    // the next tile rewrites the rows that this one's last levels read
+    if (!sim_wait(ctl, st, epoch)) return;
+  }
+}
+
+// Counts [n_nets][B] of all chunks, the toggles between chunks among them.  A
+// simulation that gave up (stop) leaves NaN probabilities, so that nothing
+// computed from its counts can pass for a result.
+__global__ __launch_bounds__(kBlock) void k_sim_counts(SimFlow t, const uint32_t *stop, float *sp,
+                                                       uint32_t *ones, uint32_t *tog) {
+  const int64_t idx = gidx();
+  if (idx >= (int64_t)t.g.n_nets * t.B) return;
+  const int32_t b = (int32_t)(idx / t.g.n_nets), net = (int32_t)(idx - (int64_t)b * t.g.n_nets);
+  const int64_t o = (int64_t)net * t.B + b;
+  uint32_t n1 = 0, nt = 0;
+  uint64_t last = 0;
+#pragma unroll 4
+  for (int32_t k = 0; k < t.n_chunks; ++k) {
+    const int64_t at = ((int64_t)b * t.n_chunks + k) * t.g.n_nets + net;
+    const uint32_t v = t.cnt[at];
+    const w2 e = reinterpret_cast<const w2 *>(t.edge)[at];
+    n1 += v & 0xffffu;
+    nt += v >> 16;
+    if (k) nt += __popcll(last ^ e.x);
+    last = e.y;
+  }
+  ones[o] = n1;
+  tog[o] = nt;
+  if (*stop) sp[o] = __builtin_nanf("");
+}
+
+// Words [B][n_pi][T] of the independent stimulus: a wave takes 64 cycles of one
+// PI for NC columns.
+template <int NC>
+__global__ __launch_bounds__(kBlock) void k_stim_words(const float *__restrict__ sp,
+                                                       const int32_t *__restrict__ stream,
+                                                       int32_t n_pi, int32_t B, int64_t T,
+                                                       uint32_t k0, uint32_t k1,
+                                                       uint64_t *__restrict__ out) {
+  const int32_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t task = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+  const int64_t runs = (T + 63) / 64, per_grp = runs * n_pi;
+  if (task >= per_grp * ((B + NC - 1) / NC)) return;
+  const int32_t grp = (int32_t)(task / per_grp);
+  const int64_t rest = task - grp * per_grp;
+  const int32_t i = (int32_t)(rest / runs);
+  const int64_t t = (rest - (int64_t)i * runs) * 64 + (threadIdx.x & 63);
+  const int32_t b0 = grp * NC, cols = min(NC, B - b0);
+  BitThreshold thr[NC];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const BitThreshold x = bit_threshold(prob_threshold(
+        sp_load(sp[(int64_t)i * B + b0 + min(k, cols - 1)]).x));
+    thr[k].t = (uint32_t)__builtin_amdgcn_readfirstlane((int)x.t);
+    thr[k].all = __builtin_amdgcn_readfirstlane((int)x.all) ? ~0ull : 0ull;
+  }
+  uint64_t w[NC];
+  stim_words<true>(stream ? (uint32_t)stream[i] : (uint32_t)i, (uint32_t)t, thr, k0, k1, w);
+  if (t < T)
+#pragma unroll
+    for (int k = 0; k < NC; ++k)
+      if (k < cols) out[((int64_t)(b0 + k) * n_pi + i) * T + t] = w[k];
 }
 
 // dP/dC_n = sum_{b,s} w[b][s] kappa beta TR_model s_s(drv n);
@@ -3596,6 +3952,46 @@ hipError_t launch_bwd_flow_multi(const BwdFlowSeg *segs, int32_t n_segs, int32_t
     k_bwd_flow_multi<true><<<grid, threads, 0, s>>>(ctl, segs, n_segs, jobs);
   else
     k_bwd_flow_multi<false><<<grid, threads, 0, s>>>(ctl, segs, n_segs, jobs);
+  return hipGetLastError();
+}
+
+hipError_t launch_stim_words(const float *sp, const int32_t *stream, int32_t n_pi, int32_t B,
+                             int64_t T, uint64_t seed, uint64_t *out, hipStream_t s) {
+  if (n_pi <= 0 || B <= 0 || T <= 0) return hipSuccess;
+  const int nc = B == 1 ? 1 : B == 2 ? 2 : B <= 4 ? 4 : 8;
+  const int64_t tasks = (T + 63) / 64 * n_pi * ((B + nc - 1) / nc);
+  const int64_t blocks = (tasks + kWavesPerBlock - 1) / kWavesPerBlock;
+  if (blocks > kMaxBlocks) return hipErrorInvalidValue;
+  using K = void (*)(const float *, const int32_t *, int32_t, int32_t, int64_t, uint32_t, uint32_t,
+                     uint64_t *);
+  const K kern = nc == 1 ? k_stim_words<1> : nc == 2 ? k_stim_words<2>
+                 : nc == 4 ? k_stim_words<4> : k_stim_words<8>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kBlock), 0, s, sp, stream, n_pi, B, T,
+                     (uint32_t)seed, (uint32_t)(seed >> 32), out);
+  return hipGetLastError();
+}
+
+hipError_t launch_sim_flow(const SimFlow &t, FlowCtl ctl, float *sp, uint32_t *ones, uint32_t *tog,
+                           hipStream_t s) {
+  const int64_t nb = (int64_t)t.g.n_nets * t.B;
+  if (nb <= 0 || t.T <= 0) return hipSuccess;
+  if (!ctl.words || !ctl.report || !sim_fits(t.g, t.depth, t.B, t.pitch, t.T) ||
+      t.n_chunks != (t.T + t.pitch - 1) / t.pitch || t.n_bufs < 1 || t.n_bufs > kSimBufs)
+    return hipErrorInvalidValue;
+  k_fill_u32<<<blocks_for(kSimWords), kBlock, 0, s>>>(ctl.words, kSimWords, 0u);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int64_t cus = std::min<int64_t>(kSimMembers, std::max<int64_t>(1, ctl.n_cu / kFlowDies));
+  ctl.expected = (uint32_t)cus;
+  const unsigned grid = (unsigned)(cus * kFlowDies * ((t.n_bufs + kFlowDies - 1) / kFlowDies));
+  switch (t.pitch) {
+    case 16: k_sim_flow<8><<<grid, kFlowThreads, 0, s>>>(ctl, t); break;
+    case 32: k_sim_flow<16><<<grid, kFlowThreads, 0, s>>>(ctl, t); break;
+    default: k_sim_flow<32><<<grid, kFlowThreads, 0, s>>>(ctl, t); break;
+  }
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_sim_counts<<<blocks_for(nb), kBlock, 0, s>>>(t, ctl.words + kSimStop, sp, ones, tog);
   return hipGetLastError();
 }
 

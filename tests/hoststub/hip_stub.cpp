@@ -424,6 +424,14 @@ hipError_t launch_markov_words(const float *sp, const float *tau, const int32_t 
   wr(out, (int64_t)n_pi * B * T);
   return hipSuccess;
 }
+hipError_t launch_stim_words(const float *sp, const int32_t *stream, int32_t n_pi, int32_t B,
+                             int64_t T, uint64_t, uint64_t *out, hipStream_t stream_) {
+  Scope sc_(stream_);
+  rd(sp, (int64_t)n_pi * B);
+  if (stream) rd(stream, n_pi);
+  wr(out, (int64_t)n_pi * B * T);
+  return hipSuccess;
+}
 hipError_t launch_stimulus(const GraphView &g, const ChunkView &c, const CountView &cnt,
                            const float *p_col, const uint64_t *stim, int64_t T,
                            const int32_t *stream, uint64_t, const SimTune &, hipStream_t stream_) {
@@ -637,6 +645,24 @@ hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl c
   if (!flow_fits(t.g, t.depth, t.B, 0)) fatal("dataflow sweep out of its range");
   flow_levels_ok(t.g, t.level_ptr, t.depth, widest, cells);
   wr(t.sp, (int64_t)t.g.n_nets * t.B);
+  return hipSuccess;
+}
+hipError_t launch_sim_flow(const SimFlow &t, FlowCtl ctl, float *sp, uint32_t *ones, uint32_t *tog,
+                           hipStream_t stream_) {
+  Scope sc_(stream_);
+  if (!sim_fits(t.g, t.depth, t.B, t.pitch, t.T) || t.n_bufs < 1 || t.n_bufs > kSimBufs ||
+      t.n_chunks != (t.T + t.pitch - 1) / t.pitch || !ctl.report || ctl.n_cu < 1)
+    fatal("word tiles out of their range");
+  const int64_t tiles = (int64_t)t.B * t.n_chunks * t.g.n_nets, nb = (int64_t)t.g.n_nets * t.B;
+  wr(ctl.words, kSimWords);
+  rd(t.level_ptr, t.depth + 2);
+  rd(t.stim, (int64_t)t.B * t.g.n_pi * t.T);
+  wr(t.W, (int64_t)t.n_bufs * t.g.n_nets * t.pitch);
+  wr(t.cnt, tiles);
+  wr(t.edge, 2 * tiles);
+  wr(sp, nb);
+  wr(ones, nb);
+  wr(tog, nb);
   return hipSuccess;
 }
 hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl ctl,
