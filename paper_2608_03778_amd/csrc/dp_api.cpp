@@ -190,21 +190,22 @@ int32_t n_sim_streams(const dp_eval *ev) { return ev->sim_streams > 0 ? ev->sim_
 bool flows(const dp_eval *ev, int32_t C);
 
 // Whether the simulation runs in word tiles, and in which: with chunks, streams
-// and columns left automatic, fixed cells only, and the SP sweep a dataflow
-// launch of its own.  Up to 24 tiles are a round of the teams; of the pitches
+// and columns left automatic and the SP sweep a dataflow launch of its own.  Up to 24 tiles are a round of the teams; of the pitches
 // that stay within it the narrowest (a level's turns grow with the pitch),
 // and 64 words up to 32 tiles.  Beyond, and beyond 2^28 words over all nets
 // and columns, the level launches' longer rows are the faster ones (forward,
 // us, tiles against levels: 2K gates x 1280 words 105 / 123, x 5120 184 / 167;
 // 117K x 257 271 / 424, x 1024 638 / 691; 300K x 1024 1516 / 1368; 1M x 257
 // 1670 / 1966), as they are where fewer than 16 tiles leave XCDs without work
-// in levels of more than 8192 gates (1M x 64: 899 / 817).
+// in levels of more than 8192 gates (1M x 64: 899 / 817).  Half library cells,
+// 300K x 256, with the reverse sweep: 1074 / 1914.  (Their kernel's registers
+// leave room for 24 teams.)
 constexpr int64_t kTileMaxWords = 1ll << 28;
 constexpr int32_t kTileTeams = 24, kTileWide = 8192;
 void plan_tiles(const dp_eval *ev, ChunkPlan *c) {
   const dp_design *d = ev->d;
   if (ev->words_per_chunk > 0 || ev->sim_streams > 1 || ev->sim_cols > 0 ||
-      d->has_cell_gates || d->depth < 1 || !flows(ev, ev->B) || c->T > kTileMaxWords / d->n_nets / ev->B)
+      d->depth < 1 || !flows(ev, ev->B) || c->T > kTileMaxWords / d->n_nets / ev->B)
     return;
   for (int32_t pitch : {16, 32, 64}) {
     const int64_t tiles = (c->T + pitch - 1) / pitch * ev->B;
@@ -214,7 +215,7 @@ void plan_tiles(const dp_eval *ev, ChunkPlan *c) {
     c->n_chunks = 1;  // of the level launches in its place
     c->tile = pitch;
     c->n_tiles = (int32_t)(tiles / ev->B);
-    c->n_bufs = (int32_t)tiles;
+    c->n_bufs = std::min((int32_t)tiles, d->has_cell_gates ? kTileTeams : dp::kSimBufs);
     return;
   }
 }
@@ -567,7 +568,7 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
                         pl->tile, pl->n_tiles, pl->n_bufs};
     dp::FlowCtl ctl = flow_ctl(ev);
     ctl.words = ev->sim_ctl.as<uint32_t>();
-    DP_HIP_TRY(dp::launch_sim_flow(t, ctl, sp, ev->ones.as<uint32_t>(), ev->tog.as<uint32_t>(), s));
+    DP_HIP_TRY(dp::launch_sim_flow(t, d->has_cell_gates, ctl, sp, ev->ones.as<uint32_t>(), ev->tog.as<uint32_t>(), s));
   } else if (pl) {
     const size_t nb = (size_t)d->n_nets * ev->B;
     DP_HIP_TRY(dp::launch_fill_u32(ev->ones.as<uint32_t>(), (int64_t)nb, 0u, s));

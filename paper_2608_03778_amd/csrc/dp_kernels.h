@@ -388,8 +388,7 @@ hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl
                            hipStream_t s);
 
 // The simulation in word tiles (see the kernels): a tile is `pitch` words of
-// one column, all levels by one team of workgroups of one XCD; fixed cells
-// only.  Control words: a line per (XCD, team) with its registration; the
+// one column, all levels by one team of workgroups of one XCD.  Control words: a line per (XCD, team) with its registration; the
 // next team buffer, the next tile, the stop flag; per buffer a line with its
 // team's claimed tile and one per member for the level flags.
 constexpr int kSimTeams = 4;      // teams per XCD at most
@@ -425,8 +424,8 @@ hipError_t launch_stim_words(const float *sp /* stored SP [n_pi][B] */, const in
                              hipStream_t s);
 // ctl.words: [kSimWords].  Writes ones and tog [n_nets][B]; a simulation that
 // gives up leaves NaN in sp.
-hipError_t launch_sim_flow(const SimFlow &t, FlowCtl ctl, float *sp, uint32_t *ones, uint32_t *tog,
-                           hipStream_t s);
+hipError_t launch_sim_flow(const SimFlow &t, bool cells, FlowCtl ctl, float *sp, uint32_t *ones,
+                           uint32_t *tog, hipStream_t s);
 
 // dcap[ext n] = sum_{b,s} w[b][s] x[n][b] size_s(n) and dsize[s][ext g] =
 // sum_b w[b][s] x[out g][b] C_out g, with x = kappa beta TR_model

@@ -398,7 +398,6 @@ __device__ __forceinline__ void sp_item(const GraphView &g, const SpLevel &lv, u
     float r[kCellMaxIn];
 #pragma unroll
     for (int k = 0; k < kCellMaxIn; ++k) r[k] = k < g.pins ? sp[(int64_t)pin[k] * B + b] : 0.0f;
-    const LaneCode lc = lane_code(g, op);
     f2 x[kCellMaxIn];
 #pragma unroll
     for (int k = 0; k < kCellMaxIn; ++k) x[k] = k < g.pins ? sp_load(r[k]) : f2{0.0f, 1.0f};
@@ -2491,7 +2490,6 @@ __device__ __forceinline__ void sp_flow_store(const SpFlow &t, int32_t col, cons
   const uint32_t out = flow_off(it.net, t.B, col);
   if constexpr (CELLS) {
     if (x.op >= kCellBase) {
-      const LaneCode lc = lane_code(t.g, x.op);
       f2 in[kCellMaxIn];
 #pragma unroll
       for (int j = 0; j < kCellMaxIn; ++j) in[j] = sp_load(x.v[j]);
@@ -3108,14 +3106,18 @@ __device__ __forceinline__ void sim_count(const SimTile &t, const SimWords &w) {
   if (u0 == ((t.nw - 1) & ~1)) *flow_at(t.edge + 1, 16 * net) = in1 ? y1 : y0;
 }
 
+template <bool CELLS>
 struct SimFlowFetch {
-  int32_t op;
-  uint32_t pin[3];
+  int32_t op, k;  // cell, its inputs
+  uint32_t pin[kFlowPins<CELLS>];
   int32_t e0, e1;
 };
-__device__ __forceinline__ SimFlowFetch sim_flow_fetch(const GraphView &g, uint32_t gi) {
-  SimFlowFetch f;
+template <bool CELLS>
+__device__ __forceinline__ SimFlowFetch<CELLS> sim_flow_fetch(const GraphView &g, uint32_t gi) {
+  SimFlowFetch<CELLS> f;
   f.op = *flow_at(g.op, gi);
+  if constexpr (CELLS) f.k = *flow_at(g.arity, gi);
+  else f.k = arity_of(f.op);
   flow_pins(g.in, g, gi, f.pin);
   f.e0 = *flow_at(g.rev_ptr + g.n_pi, 4 * gi);
   f.e1 = *flow_at(g.rev_ptr + g.n_pi + 1, 4 * gi);
@@ -3123,11 +3125,57 @@ __device__ __forceinline__ SimFlowFetch sim_flow_fetch(const GraphView &g, uint3
 }
 
 template <int LPG>
-__device__ __forceinline__ u4 sim_row(const SimTile &t, uint32_t net, uint32_t l16) {
-  return __builtin_amdgcn_raw_buffer_load_b128(t.rows, (int)(net * (LPG * 16u) + l16), 0, kBufferSc1);
+__device__ __forceinline__ w2 sim_row(const SimTile &t, uint32_t net, uint32_t l16) {
+  const u4 v = __builtin_amdgcn_raw_buffer_load_b128(t.rows, (int)(net * (LPG * 16u) + l16), 0, kBufferSc1);
+  return w2{(uint64_t)v[1] << 32 | v[0], (uint64_t)v[3] << 32 | v[2]};
+}
+// A library cell's function from its truth table, as tt_eval, with a table
+// per lane: a leaf's mask is one sign-extending bit extract.
+template <int N>
+__device__ __forceinline__ w2 tt_lane(const w2 *x, uint32_t lo, uint32_t hi, int base) {
+  if constexpr (N == 0) {
+    const int32_t m = __builtin_amdgcn_sbfe((int32_t)(base < 32 ? lo : hi), base & 31, 1);
+    const uint64_t v = (uint64_t)(uint32_t)m << 32 | (uint32_t)m;
+    return w2{v, v};
+  } else {
+    const w2 a = tt_lane<N - 1>(x, lo, hi, base), b = tt_lane<N - 1>(x, lo, hi, base + (1 << (N - 1)));
+    return w2{(x[N - 1].x & b.x) | (~x[N - 1].x & a.x), (x[N - 1].y & b.y) | (~x[N - 1].y & a.y)};
+  }
+}
+template <int N>
+__device__ __forceinline__ w2 sim_cell(const w2 (&x)[N], const SimFlowFetch<N == kCellMaxIn> &f, uint64_t tt) {
+  switch (f.op) {
+#define DP_SIM_CASE(OP) \
+  case OP: return w2{cell_bits<OP>(x[0].x, x[1].x, x[2].x), cell_bits<OP>(x[0].y, x[1].y, x[2].y)}
+    DP_SIM_CASE(INV);
+    DP_SIM_CASE(BUF);
+    DP_SIM_CASE(AND2);
+    DP_SIM_CASE(OR2);
+    DP_SIM_CASE(NAND2);
+    DP_SIM_CASE(NOR2);
+    DP_SIM_CASE(XOR2);
+    DP_SIM_CASE(AOI21);
+    default: break;
+  }
+  if constexpr (N == kCellMaxIn)
+    if (f.op >= kCellBase) {
+      const uint32_t lo = (uint32_t)tt, hi = (uint32_t)(tt >> 32);
+      switch (f.k) {
+        case 1: return tt_lane<1>(x, lo, hi, 0);
+        case 2: return tt_lane<2>(x, lo, hi, 0);
+        case 3: return tt_lane<3>(x, lo, hi, 0);
+        case 4: return tt_lane<4>(x, lo, hi, 0);
+        case 5: return tt_lane<5>(x, lo, hi, 0);
+        default: return tt_lane<6>(x, lo, hi, 0);
+      }
+    }
+  switch (MUX2) {
+    DP_SIM_CASE(MUX2);
+#undef DP_SIM_CASE
+  }
 }
 
-template <int LPG>
+template <int LPG, bool CELLS>
 __global__ __launch_bounds__(kFlowThreads) void k_sim_flow(FlowCtl ctl, SimFlow t) {
   const SimSeat st = sim_join(ctl, (uint32_t)t.n_bufs);
   if (st.members == 0) return;
@@ -3171,39 +3219,26 @@ __global__ __launch_bounds__(kFlowThreads) void k_sim_flow(FlowCtl ctl, SimFlow 
       const int32_t n = __builtin_amdgcn_readfirstlane(flow_lv[lv + 1]) - g0;
       // while the other members arrive: the first gates' structure, and the
       // counts of the level before's last ones
-      SimFlowFetch f = sim_flow_fetch(g, (uint32_t)(g0 + min(first + sub, n - 1)));
+      SimFlowFetch<CELLS> f = sim_flow_fetch<CELLS>(g, (uint32_t)(g0 + min(first + sub, n - 1)));
       sim_count<LPG>(tile, last);
       last.valid = false;
       if (!sim_wait(ctl, st, epoch)) return;
       for (int32_t base = first; base < n; base += step) {
         if (base != first) sim_count<LPG>(tile, last);
-        const SimFlowFetch c = f;
+        const SimFlowFetch<CELLS> c = f;
         last.net = (uint32_t)(g.n_pi + g0 + min(base + sub, n - 1));
         last.valid = base + sub < n;
-        const int k3 = arity_of(c.op);
-        u4 x0 = sim_row<LPG>(tile, c.pin[0], l16), x1 = u4{0, 0, 0, 0}, x2 = x1;
-        if (k3 > 1) x1 = sim_row<LPG>(tile, c.pin[1], l16);
-        if (k3 > 2) x2 = sim_row<LPG>(tile, c.pin[2], l16);
-        if (base + step < n) f = sim_flow_fetch(g, (uint32_t)(g0 + min(base + step + sub, n - 1)));
-        const uint64_t a0 = (uint64_t)x0[1] << 32 | x0[0], a1 = (uint64_t)x0[3] << 32 | x0[2];
-        const uint64_t b0 = (uint64_t)x1[1] << 32 | x1[0], b1 = (uint64_t)x1[3] << 32 | x1[2];
-        const uint64_t c0 = (uint64_t)x2[1] << 32 | x2[0], c1 = (uint64_t)x2[3] << 32 | x2[2];
-        uint64_t y0, y1;
-        switch (c.op) {
-#define DP_SIM_CASE(OP) case OP: y0 = cell_bits<OP>(a0, b0, c0); y1 = cell_bits<OP>(a1, b1, c1); break
-          DP_SIM_CASE(INV);
-          DP_SIM_CASE(BUF);
-          DP_SIM_CASE(AND2);
-          DP_SIM_CASE(OR2);
-          DP_SIM_CASE(NAND2);
-          DP_SIM_CASE(NOR2);
-          DP_SIM_CASE(XOR2);
-          DP_SIM_CASE(AOI21);
-#undef DP_SIM_CASE
-          default: y0 = cell_bits<MUX2>(a0, b0, c0); y1 = cell_bits<MUX2>(a1, b1, c1); break;
-        }
-        last.y0 = y0;
-        last.y1 = y1;
+        w2 x[kFlowPins<CELLS>];
+        x[0] = sim_row<LPG>(tile, c.pin[0], l16);
+#pragma unroll
+        for (int j = 1; j < kFlowPins<CELLS>; ++j)
+          x[j] = c.k > j ? sim_row<LPG>(tile, c.pin[j], l16) : w2{0, 0};
+        uint64_t tt = 0;
+        if constexpr (CELLS) tt = *flow_at(g.tt, 8 * (uint32_t)max(c.op - kCellBase, 0));
+        if (base + step < n) f = sim_flow_fetch<CELLS>(g, (uint32_t)(g0 + min(base + step + sub, n - 1)));
+        const w2 y = sim_cell(x, c, tt);
+        last.y0 = y.x;
+        last.y1 = y.y;
         sim_store<LPG>(tile, last, c.e1 > c.e0);
       }
       sim_arrive(ctl, st, ++epoch);
@@ -3971,8 +4006,8 @@ hipError_t launch_stim_words(const float *sp, const int32_t *stream, int32_t n_p
   return hipGetLastError();
 }
 
-hipError_t launch_sim_flow(const SimFlow &t, FlowCtl ctl, float *sp, uint32_t *ones, uint32_t *tog,
-                           hipStream_t s) {
+hipError_t launch_sim_flow(const SimFlow &t, bool cells, FlowCtl ctl, float *sp, uint32_t *ones,
+                           uint32_t *tog, hipStream_t s) {
   const int64_t nb = (int64_t)t.g.n_nets * t.B;
   if (nb <= 0 || t.T <= 0) return hipSuccess;
   if (!ctl.words || !ctl.report || !sim_fits(t.g, t.depth, t.B, t.pitch, t.T) ||
@@ -3984,11 +4019,11 @@ hipError_t launch_sim_flow(const SimFlow &t, FlowCtl ctl, float *sp, uint32_t *o
   const int64_t cus = std::min<int64_t>(kSimMembers, std::max<int64_t>(1, ctl.n_cu / kFlowDies));
   ctl.expected = (uint32_t)cus;
   const unsigned grid = (unsigned)(cus * kFlowDies * ((t.n_bufs + kFlowDies - 1) / kFlowDies));
-  switch (t.pitch) {
-    case 16: k_sim_flow<8><<<grid, kFlowThreads, 0, s>>>(ctl, t); break;
-    case 32: k_sim_flow<16><<<grid, kFlowThreads, 0, s>>>(ctl, t); break;
-    default: k_sim_flow<32><<<grid, kFlowThreads, 0, s>>>(ctl, t); break;
-  }
+  using K = void (*)(FlowCtl, SimFlow);
+  K kern = cells ? k_sim_flow<32, true> : k_sim_flow<32, false>;
+  if (t.pitch == 16) kern = cells ? k_sim_flow<8, true> : k_sim_flow<8, false>;
+  if (t.pitch == 32) kern = cells ? k_sim_flow<16, true> : k_sim_flow<16, false>;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(kFlowThreads), 0, s, ctl, t);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   k_sim_counts<<<blocks_for(nb), kBlock, 0, s>>>(t, ctl.words + kSimStop, sp, ones, tog);

@@ -647,8 +647,8 @@ hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl c
   wr(t.sp, (int64_t)t.g.n_nets * t.B);
   return hipSuccess;
 }
-hipError_t launch_sim_flow(const SimFlow &t, FlowCtl ctl, float *sp, uint32_t *ones, uint32_t *tog,
-                           hipStream_t stream_) {
+hipError_t launch_sim_flow(const SimFlow &t, bool, FlowCtl ctl, float *sp, uint32_t *ones,
+                           uint32_t *tog, hipStream_t stream_) {
   Scope sc_(stream_);
   if (!sim_fits(t.g, t.depth, t.B, t.pitch, t.T) || t.n_bufs < 1 || t.n_bufs > kSimBufs ||
       t.n_chunks != (t.T + t.pitch - 1) / t.pitch || !ctl.report || ctl.n_cu < 1)

@@ -1,7 +1,7 @@
 """The simulation in word tiles (all levels in one launch, each tile by one
 team of workgroups): counts bit for bit the level launches' and the oracle's,
 at words around the pitches (16, 32, 64) and the tile limits, level widths
-below and beyond a team's turn, and each form of stimulus."""
+below and beyond a team's turn, each form of stimulus, and library cells."""
 from __future__ import annotations
 
 import numpy as np
@@ -10,7 +10,7 @@ import pytest
 import oracle
 from paper_2608_03778_amd import _lib as L
 from paper_2608_03778_amd import api, synth
-from tests.gpu_helpers import say
+from tests.gpu_helpers import SP_ABS, say
 
 pytestmark = pytest.mark.gpu
 FIELDS = ("ones", "toggles", "sp", "beta", "power")
@@ -83,3 +83,29 @@ def test_tiles_with_each_stimulus(ctx, form, B, T):
     ref.set_schedule(L.DP_SCHED_LEVEL, T)
     want = ref.forward(FIELDS)
     _same(_eval(d, nl, B, T, **kw).forward(FIELDS), want, form)
+
+
+# NOTs of inputs, constants, results and NOTs; chains that wait two deep and
+# deeper; each input count
+ODD_CELLS = ("!(!A)", "1^A", "!(0|A)", "A&!B", "!(!A&!B)", "A^(B|!C)", "A&(B|(C^!D))",
+             "!(A&B)^(C|D)&E", "A|(B&(C|(D&(E|F))))", "(A^B)&(C^D)|!(E^F)")
+
+
+@pytest.mark.parametrize("pis,gates,depth,B,T", [(40, 900, 1, 1, 16), (30, 4000, 12, 2, 70),
+                                                 (30, 2000, 9, 1, 700)])
+def test_tiles_of_library_cells(ctx, pis, gates, depth, B, T):
+    say(f"word tiles of library cells: {gates} gates, depth {depth}, B={B}, T={T}")
+    ops = tuple(range(9)) + tuple(synth.CELL_BASE + c for c in range(len(ODD_CELLS)))
+    nl = synth.random_dag(synth.DagSpec(gates, pis, depth, ops=ops, cells=ODD_CELLS), 46)
+    d = api.Design(ctx, nl)
+    ref = _eval(d, nl, B, T)
+    ref.set_schedule(L.DP_SCHED_LEVEL, T)
+    want = ref.forward(FIELDS)
+    _same(_eval(d, nl, B, T).forward(FIELDS), want, "tiles")
+    p, cap = synth.pi_probs(pis, 41, batch=B), synth.net_caps(nl.n_nets, 42)
+    for b in range(B):
+        f = oracle.Netlist.of(nl).forward(p[b], cap, hybrid=True, n_words=T,
+                                          pi_words=oracle.stimulus_model(p[b], 9, T))
+        np.testing.assert_array_equal(want["ones"][b].astype(np.uint64), f["ones"])
+        np.testing.assert_array_equal(want["toggles"][b].astype(np.uint64), f["toggles"])
+        np.testing.assert_allclose(want["sp"][b], f["sp"], atol=SP_ABS, rtol=0)
