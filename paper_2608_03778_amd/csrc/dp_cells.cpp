@@ -187,6 +187,36 @@ int fixed_op_of(const CellCode &cc) {
   return -1;
 }
 
+std::vector<uint16_t> cell_rule(const CellCode &c) {
+  std::vector<uint16_t> r(kCellRule, 0);
+  size_t n = 4;  // the next step's word
+  for (const uint16_t w : c.code) {
+    const int op = w & 0xff;
+    if (op == kCellNot) {  // of the last step's value
+      uint16_t &last = r[n - 1];
+      last ^= (last & kRuleKind) == kRulePush ? kRuleInputNot : kRuleNot;
+    } else if (op == kCellIn) {
+      r[n++] = (uint16_t)(kRulePush | (w >> 8));
+    } else if (op == kCellZero || op == kCellOne) {
+      r[n++] = (uint16_t)(kRuleConst | (op == kCellOne ? kRuleNot : 0));
+    } else {
+      uint16_t &last = r[n - 1];
+      const uint16_t what = (uint16_t)((op - kCellAnd) << kRuleOp);
+      if ((last & kRuleKind) == kRulePush) last |= (uint16_t)(kRuleWithInput | what);
+      else r[n++] = (uint16_t)(kRuleWithLast | what);
+    }
+  }
+  int live = 0, most = 0;
+  for (size_t i = 4; i < n; ++i) {
+    const int kind = r[i] & kRuleKind;
+    if (kind == kRulePush || kind == kRuleConst) most = std::max(most, live++);
+    else if (kind == kRuleWithLast) --live;
+  }
+  r[0] = (uint16_t)(n - 4);
+  r[1] = (uint16_t)most;
+  return r;
+}
+
 // The code run on 64 lanes at once, lane m carrying input pattern m.
 uint64_t truth_table(const CellCode &cc) {
   uint64_t in[kCellMaxIn];

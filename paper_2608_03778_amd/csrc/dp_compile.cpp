@@ -313,6 +313,7 @@ dp_status compile_design(dp_ctx *ctx, const dp_netlist *nl, int32_t n_cells,
   std::vector<uint16_t> code((size_t)std::max(n_logic, 1) * kCellMaxCode, 0);
   std::vector<int32_t> cell_tab(3 * (size_t)std::max(n_logic, 1), 0);
   std::vector<uint64_t> tt((size_t)std::max(n_logic, 1), 0);
+  std::vector<uint16_t> rule((size_t)std::max(n_logic, 1) * kCellRule, 0);
   for (int32_t id = 0; id < n_logic; ++id) {
     const CellCode &cc = lib[logic_cell[id]];
     cell_tab[3 * id] = id * kCellMaxCode;
@@ -320,6 +321,8 @@ dp_status compile_design(dp_ctx *ctx, const dp_netlist *nl, int32_t n_cells,
     cell_tab[3 * id + 2] = cc.n_in;
     std::copy(cc.code.begin(), cc.code.end(), code.begin() + (size_t)id * kCellMaxCode);
     tt[id] = truth_table(cc);
+    const std::vector<uint16_t> r = cell_rule(cc);
+    std::copy(r.begin(), r.end(), rule.begin() + (size_t)id * kCellRule);
   }
   std::vector<uint8_t> arity(std::max(G, 1), 0);
   for (int32_t gi = 0; gi < G; ++gi)
@@ -327,7 +330,7 @@ dp_status compile_design(dp_ctx *ctx, const dp_netlist *nl, int32_t n_cells,
   hipStream_t s = ctx->stream;
   dp_status st = DP_OK;
   if ((st = upload(d->code, code, s)) != DP_OK || (st = upload(d->cell, cell_tab, s)) != DP_OK ||
-      (st = upload(d->tt, tt, s)) != DP_OK || (st = upload(d->arity, arity, s)) != DP_OK ||
+      (st = upload(d->rule, rule, s)) != DP_OK || (st = upload(d->tt, tt, s)) != DP_OK || (st = upload(d->arity, arity, s)) != DP_OK ||
       (st = upload(d->op, d->h_op, s)) != DP_OK || (st = upload(d->in, in, s)) != DP_OK ||
       (st = upload(d->rev_ptr, rev_ptr, s)) != DP_OK ||
       (st = upload(d->rev_net, rev_net, s)) != DP_OK ||
@@ -347,7 +350,7 @@ dp_status compile_design(dp_ctx *ctx, const dp_netlist *nl, int32_t n_cells,
   }
   d->device_bytes = (int64_t)(d->op.bytes + d->in.bytes + d->rev_ptr.bytes + d->rev_net.bytes +
                               d->slot.bytes + d->int2ext.bytes + d->ext2int.bytes +
-                              d->code.bytes + d->cell.bytes + d->tt.bytes + d->arity.bytes + d->heavy.bytes +
+                              d->code.bytes + d->cell.bytes + d->rule.bytes + d->tt.bytes + d->arity.bytes + d->heavy.bytes +
                               d->heavy_pi.bytes);
   ctx_retain(ctx);
   *out = d;

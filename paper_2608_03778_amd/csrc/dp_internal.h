@@ -65,6 +65,8 @@ int fixed_op_of(const CellCode &cc);
 // Truth table of a compiled cell: bit m is the cell's output when input k
 // is bit k of m (m < 2^n_in; higher bits repeat the pattern).
 uint64_t truth_table(const CellCode &cc);
+// Its code as steps (see kCellRule).
+std::vector<uint16_t> cell_rule(const CellCode &c);
 
 }  // namespace dp
 
@@ -120,6 +122,7 @@ struct dp_design {
   dp::DevBuf slot;      // int32 [pins][n_gates] position of pin (g', j) in its source's fan-out list
   dp::DevBuf code;      // uint16: the library cells' stack code, concatenated
   dp::DevBuf cell;      // int32 [n_cells][3]: code offset, length, inputs
+  dp::DevBuf rule;      // uint16 [n_cells][kCellRule] the code as steps
   dp::DevBuf tt;        // uint64 [n_cells] truth tables (the simulation's cell function)
   dp::DevBuf arity;     // uint8 [n_gates] input count of each gate
   dp::DevBuf level_dev; // int32 [depth + 2] device copy of level_ptr
@@ -144,6 +147,7 @@ inline GraphView design_view(const dp_design *d) {
   g.slot = d->slot.as<int32_t>();
   g.code = d->code.as<uint16_t>();
   g.cell = d->cell.as<int32_t>();
+  g.rule = d->rule.as<uint16_t>();
   g.tt = d->tt.as<uint64_t>();
   g.arity = d->arity.as<uint8_t>();
   g.pins = d->pins;

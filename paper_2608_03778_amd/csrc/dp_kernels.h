@@ -17,6 +17,17 @@ constexpr int kCellMaxCode = 32;
 constexpr int kCellMaxStack = 8;
 enum : int { kCellIn = 0, kCellNot = 1, kCellAnd = 2, kCellOr = 3, kCellXor = 4,
              kCellZero = 5, kCellOne = 6 };
+// The same code as steps for the SP sweeps, kCellRule words per cell: the
+// number of steps, the most values that wait below the current one, two
+// zeros, then the steps.  A step takes an input or a constant as the new
+// current value, or combines the current value with an input, or the last
+// waiting value with the current one; NOTs ride along.
+constexpr int kCellRule = kCellMaxCode + 4;
+enum : int { kRuleInput = 7, kRuleInputNot = 8,  // input index, and whether it is complemented
+             kRuleOp = 4,                        // shift of the operation: kCellAnd.. less kCellAnd
+             kRulePush = 0, kRuleWithInput = 1 << 6, kRuleWithLast = 2 << 6, kRuleConst = 3 << 6,
+             kRuleKind = 3 << 6,
+             kRuleNot = 1 << 8 };  // the result (of an operation) is complemented; a constant: one
 
 struct GraphView {
   const uint8_t *op;        // [G]
@@ -26,6 +37,7 @@ struct GraphView {
   const int32_t *slot;      // [pins][G] fan-out position of each pin (-1: no such pin)
   const uint16_t *code;     // [n_cells][kCellMaxCode] library cells' stack code (op | arg << 8), padded
   const int32_t *cell;      // [n_cells][3]: code offset, length, inputs
+  const uint16_t *rule;     // [n_cells][kCellRule] the code as steps
   const uint64_t *tt;       // [n_cells] truth tables: bit m = output for input pattern m
   const uint8_t *arity;     // [G] input count of each gate
   int32_t pins;             // rows of in and slot (3, or the widest cell)
