@@ -643,13 +643,12 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
   return enqueue_forward_tail(ev, pl);
 }
 
-// The power terms (TR, beta) and their sum over nets, after a forward sweep.
-dp_status enqueue_forward_tail(dp_eval *ev, const ChunkPlan *pl) {
+// Arguments of the power terms (TR, beta) and their sum over nets, after a
+// forward sweep.
+dp::PowerArgs power_args(dp_eval *ev, const ChunkPlan *pl) {
   const dp_design *d = ev->d;
-  hipStream_t s = ev->stream();
-  float *sp = ev->sp.as<float>();
   dp::PowerArgs pa{};
-  pa.sp = sp;
+  pa.sp = ev->sp.as<float>();
   pa.tog = pl ? ev->tog.as<uint32_t>() : nullptr;
   pa.beta_frozen = ev->prm.mode == DP_FROZEN_BETA ? ev->beta_frozen.as<float>() : nullptr;
   pa.beta_shared = ev->beta_shared;
@@ -670,7 +669,10 @@ dp_status enqueue_forward_tail(dp_eval *ev, const ChunkPlan *pl) {
   pa.partial = ev->power_partial.as<double>();
   pa.n_chunks = dp::power_chunks(d->n_nets);
   pa.power = ev->power.as<float>();
-  DP_HIP_TRY(dp::launch_power(pa, s));
+  return pa;
+}
+dp_status enqueue_forward_tail(dp_eval *ev, const ChunkPlan *pl) {
+  DP_HIP_TRY(dp::launch_power(power_args(ev, pl), ev->stream()));
   return DP_OK;
 }
 
@@ -1943,6 +1945,22 @@ dp_status FlowTables::launch_reverse(const BwdFlowSeg *dev, hipStream_t s) const
   return DP_OK;
 }
 
+bool PowerTable::add(dp_eval *ev, float *host) {
+  const PowerArgs a = power_args(ev, nullptr);
+  if (!power_merges(a)) return false;
+  if ((int64_t)a.n_nets * a.B <= 0) return true;
+  segs.push_back(PowerSeg{a, host, blocks, cols});
+  blocks += power_blocks(a);
+  cols += a.B;
+  widest = std::max(widest, a.B);
+  return true;
+}
+dp_status PowerTable::launch(const void *dev, hipStream_t s) const {
+  DP_HIP_TRY(launch_power_multi(static_cast<const PowerSeg *>(dev), (int32_t)segs.size(), blocks, cols,
+                                widest, s));
+  return DP_OK;
+}
+
 }  // namespace dp
 
 struct GroupPool {
@@ -2002,7 +2020,8 @@ struct dp_group {
   dp::FlowTables flow;       // in place of tab where the evals' sweeps fit
   bool use_flow = false;
   dp::DevBuf tab_dev;
-  size_t tab_dev_bwd = 0;
+  size_t tab_dev_bwd = 0, tab_dev_power = 0;
+  dp::PowerTable power;  // empty: each eval's power by itself
   bool have_tables = false;
   uint64_t tables_key = 0;
   dp_ctx *ctx = nullptr;
@@ -2054,11 +2073,21 @@ dp_status build_merged_tables(dp_group *g, bool backward) {
   std::vector<dp::MergedTables::Lane> lanes;
   for (int32_t i : g->merged) lanes.push_back({g->evs[i], backward});
   std::vector<char> host;
+  g->power = dp::PowerTable{};
+  for (int32_t i : g->merged)
+    if (!g->power.add(g->evs[i], nullptr)) {  // (several size vectors)
+      g->power = dp::PowerTable{};
+      break;
+    }
   auto upload = [&](const auto &tab) -> dp_status {
     g->tab_dev_bwd = tab.bwd_offset();
-    DP_TRY(g->tab_dev.alloc(tab.bytes()));
-    host.resize(tab.bytes());
+    g->tab_dev_power = (tab.bytes() + 255) & ~(size_t)255;
+    host.resize(g->tab_dev_power + std::max<size_t>(g->power.bytes(), 256));
+    DP_TRY(g->tab_dev.alloc(host.size()));
     tab.pack(host.data());
+    if (!g->power.segs.empty())
+      std::memcpy(host.data() + g->tab_dev_power, g->power.segs.data(),
+                  g->power.segs.size() * sizeof(dp::PowerSeg));
     DP_HIP_TRY(hipMemcpy(g->tab_dev.ptr, host.data(), host.size(), hipMemcpyHostToDevice));
     return DP_OK;
   };
@@ -2084,13 +2113,16 @@ dp_status enqueue_merged(dp_group *g, hipStream_t origin, bool backward) {
     DP_TRY(g->flow.launch_forward(g->tab_dev.as<dp::SpFlowSeg>(), origin));
   else
     DP_TRY(g->tab.launch_forward(g->tab_dev.as<dp::SpSeg>(), origin));
-  for (int32_t i : g->merged) {
-    dp_eval *ev = g->evs[i];
-    ev->branch = origin;
-    const dp_status st = enqueue_forward_tail(ev, nullptr);
-    ev->branch = nullptr;
-    DP_TRY(st);
-  }
+  if (!g->power.segs.empty())
+    DP_TRY(g->power.launch((const char *)g->tab_dev.ptr + g->tab_dev_power, origin));
+  else
+    for (int32_t i : g->merged) {
+      dp_eval *ev = g->evs[i];
+      ev->branch = origin;
+      const dp_status st = enqueue_forward_tail(ev, nullptr);
+      ev->branch = nullptr;
+      DP_TRY(st);
+    }
   if (!backward) return DP_OK;
   if (g->use_flow)  // the PIs' adjoints included
     return g->flow.launch_reverse(reinterpret_cast<const dp::BwdFlowSeg *>(bwd_tab), origin);
@@ -2257,6 +2289,8 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
     mix((uint64_t)(uintptr_t)ev->sp.ptr);
     mix((uint64_t)(uintptr_t)ev->beta.ptr);
     mix((uint64_t)(uintptr_t)ev->cap.ptr);
+    mix((uint64_t)(uintptr_t)ev->power.ptr);
+    mix((uint64_t)(uintptr_t)ev->power_partial.ptr);
   }
   // modeled evals go into the merged level launches; the others (hybrid)
   // run on the branches
@@ -2442,74 +2476,34 @@ dp_status lane_create(dp_design *d, int32_t capacity, const dp_params *prm, hipS
   return DP_OK;
 }
 
-dp_status lane_run(dp_eval *ev, int32_t n, const float *p, const float *size, bool backward,
-                   float *power, float *dpi) {
-  const dp_design *d = ev->d;
-  hipStream_t s = ev->stream();
-  ev->B = n;
-  ev->S = size ? n : 0;
-  ev->paired_sizes = size != nullptr;
-  if (d->n_pi > 0) {
-    DP_HIP_TRY(hipMemcpyAsync(ev->p_stage.ptr, p, (size_t)n * d->n_pi * 4, hipMemcpyHostToDevice, s));
-    DP_HIP_TRY(launch_load_pi(ev->p_stage.as<float>(), ev->sp.as<float>(), d->n_pi, n, s));
-  }
-  if (size && d->n_gates > 0) {
-    DP_HIP_TRY(hipMemcpyAsync(ev->size_stage.ptr, size, (size_t)n * d->n_gates * 4,
-                              hipMemcpyHostToDevice, s));
-    DP_HIP_TRY(launch_import_sizes(ev->size_stage.as<float>(), d->int2ext.as<int32_t>(),
-                                   ev->size.as<float>(), d->n_pi, d->n_gates, n, s));
-  }
-  DP_TRY(enqueue_forward(ev, nullptr));
-  DP_HIP_TRY(hipMemcpyAsync(power, ev->power.ptr, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-  if (backward) {
-    const GraphView g = view(d);
-    const BwdArgs ba = backward_args(ev, nullptr, 0, n);
-    for (int32_t l = d->depth; l >= 1; --l)
-      DP_TRY(for_level_parts(d, l, [&](int32_t g0, int32_t n, bool cells) -> dp_status {
-        const HeavySpan hs = heavy_span(d, g0, n);
-        DP_HIP_TRY(launch_bwd_level(g, ba, g0, n, cells, s, hs.gates, hs.n));
-        return DP_OK;
-      }));
-    const HeavySpan hp = heavy_pis(d);
-    DP_HIP_TRY(launch_bwd_pi(g, ba, ev->pi_out.as<float>(), s, hp.gates, hp.n));
-    if (dpi && d->n_pi > 0)
-      DP_HIP_TRY(hipMemcpyAsync(dpi, ev->pi_out.ptr, (size_t)n * d->n_pi * 4,
-                                hipMemcpyDeviceToHost, s));
-  }
-  return DP_OK;
-}
-
 StepScratch::~StepScratch() {
   if (host) (void)hipHostFree(host);
 }
 
-namespace {
-
-// Stage one lane's inputs on `s` (the first half of lane_run).
-dp_status lane_stage(dp_eval *ev, int32_t n, const float *p, const float *size, hipStream_t s) {
-  const dp_design *d = ev->d;
-  ev->B = n;
-  ev->S = size ? n : 0;
-  ev->paired_sizes = size != nullptr;
-  if (d->n_pi > 0) {
-    DP_HIP_TRY(hipMemcpyAsync(ev->p_stage.ptr, p, (size_t)n * d->n_pi * 4, hipMemcpyHostToDevice, s));
-    DP_HIP_TRY(launch_load_pi(ev->p_stage.as<float>(), ev->sp.as<float>(), d->n_pi, n, s));
-  }
-  if (size && d->n_gates > 0) {
-    DP_HIP_TRY(hipMemcpyAsync(ev->size_stage.ptr, size, (size_t)n * d->n_gates * 4,
-                              hipMemcpyHostToDevice, s));
-    DP_HIP_TRY(launch_import_sizes(ev->size_stage.as<float>(), d->int2ext.as<int32_t>(),
-                                   ev->size.as<float>(), d->n_pi, d->n_gates, n, s));
-  }
-  return DP_OK;
-}
-
-}  // namespace
-
 dp_status lanes_run_merged(const LaneJob *jobs, int32_t n_jobs, hipStream_t s,
                            StepScratch *sc) {
-  for (int32_t j = 0; j < n_jobs; ++j)
-    DP_TRY(lane_stage(jobs[j].ev, jobs[j].n, jobs[j].p, jobs[j].size, s));
+  std::vector<LaneSeg> segs(n_jobs);
+  uint32_t stage = 0, import = 0, out = 0;
+  PowerTable power;
+  for (int32_t j = 0; j < n_jobs; ++j) {
+    const LaneJob &job = jobs[j];
+    dp_eval *ev = job.ev;
+    const dp_design *d = ev->d;
+    ev->B = job.n;
+    ev->S = job.size ? job.n : 0;
+    ev->paired_sizes = job.size != nullptr;
+    LaneSeg &l = segs[j];
+    l = LaneSeg{job.p, ev->sp.as<float>(), d->n_gates > 0 ? job.size : nullptr,
+                ev->size_stage.as<float>(), ev->size.as<float>(), d->int2ext.as<int32_t>(),
+                job.backward && job.dpi && d->n_pi > 0 ? ev->pi_out.as<float>() : nullptr, job.dpi,
+                d->n_pi, job.n, d->n_gates, stage, 0, import, out};
+    uint32_t n_stage, n_import, n_out;
+    lane_seg_blocks(l, n_stage, n_import, n_out);
+    stage += n_stage;
+    import += n_import;
+    out += n_out;
+    if (!power.add(ev, job.power)) return fail(DP_E_UNSUPPORTED, "a lane with several size vectors");
+  }
   // segment tables: forward over every lane, reverse over the lanes that
   // want gradients
   std::vector<MergedTables::Lane> lanes(n_jobs);
@@ -2525,7 +2519,8 @@ dp_status lanes_run_merged(const LaneJob *jobs, int32_t n_jobs, hipStream_t s,
     flow.build(lanes.data(), n_jobs);
   else
     tab.build(lanes.data(), n_jobs);
-  const size_t bytes = use_flow ? flow.bytes() : tab.bytes();
+  const size_t sweeps = ((use_flow ? flow.bytes() : tab.bytes()) + 255) & ~(size_t)255;
+  const size_t lanes_at = sweeps + power.bytes(), bytes = lanes_at + segs.size() * sizeof(LaneSeg);
   if (bytes > sc->cap) {
     if (sc->host) (void)hipHostFree(sc->host);
     sc->host = nullptr;
@@ -2534,40 +2529,33 @@ dp_status lanes_run_merged(const LaneJob *jobs, int32_t n_jobs, hipStream_t s,
     DP_TRY(sc->dev.alloc(bytes));
     sc->cap = bytes;
   }
-  use_flow ? flow.pack(sc->host) : tab.pack(sc->host);
+  char *host = static_cast<char *>(sc->host), *dev = static_cast<char *>(sc->dev.ptr);
+  use_flow ? flow.pack(host) : tab.pack(host);
+  std::memcpy(host + sweeps, power.segs.data(), power.segs.size() * sizeof(PowerSeg));
+  std::memcpy(host + lanes_at, segs.data(), segs.size() * sizeof(LaneSeg));
+  const auto *lane_tab = reinterpret_cast<const LaneSeg *>(dev + lanes_at);
   DP_HIP_TRY(hipMemcpyAsync(sc->dev.ptr, sc->host, bytes, hipMemcpyHostToDevice, s));
-  const char *bwd_tab =
-      (const char *)sc->dev.ptr + (use_flow ? flow.bwd_offset() : tab.bwd_offset());
+  const char *bwd_tab = dev + (use_flow ? flow.bwd_offset() : tab.bwd_offset());
+  DP_HIP_TRY(launch_lanes_stage(lane_tab, n_jobs, stage, import, s));
   if (use_flow)
     DP_TRY(flow.launch_forward(sc->dev.as<SpFlowSeg>(), s));
   else
     DP_TRY(tab.launch_forward(sc->dev.as<SpSeg>(), s));
-  for (int32_t j = 0; j < n_jobs; ++j) {
-    dp_eval *ev = jobs[j].ev;
-    ev->branch = s;
-    const dp_status st = enqueue_forward_tail(ev, nullptr);
-    ev->branch = nullptr;
-    DP_TRY(st);
-    DP_HIP_TRY(hipMemcpyAsync(jobs[j].power, ev->power.ptr, (size_t)jobs[j].n * 4,
-                              hipMemcpyDeviceToHost, s));
-  }
+  DP_TRY(power.launch(dev + sweeps, s));
   if (!any_backward) return DP_OK;
   if (use_flow)
     DP_TRY(flow.launch_reverse(reinterpret_cast<const BwdFlowSeg *>(bwd_tab), s));
   else
     DP_TRY(tab.launch_reverse(reinterpret_cast<const BwdSeg *>(bwd_tab), s));
-  for (int32_t j = 0; j < n_jobs; ++j) {
-    if (!jobs[j].backward) continue;
-    dp_eval *ev = jobs[j].ev;
-    const dp_design *d = ev->d;
-    const HeavySpan hp = heavy_pis(d);
-    if (!use_flow)  // (the dataflow sweep ends with the PIs)
-      DP_HIP_TRY(launch_bwd_pi(view(d), backward_args(ev, nullptr, 0, ev->B),
+  if (!use_flow)  // (the dataflow sweep ends with the PIs)
+    for (int32_t j = 0; j < n_jobs; ++j) {
+      if (!jobs[j].backward) continue;
+      dp_eval *ev = jobs[j].ev;
+      const HeavySpan hp = heavy_pis(ev->d);
+      DP_HIP_TRY(launch_bwd_pi(view(ev->d), backward_args(ev, nullptr, 0, ev->B),
                                ev->pi_out.as<float>(), s, hp.gates, hp.n));
-    if (jobs[j].dpi && d->n_pi > 0)
-      DP_HIP_TRY(hipMemcpyAsync(jobs[j].dpi, ev->pi_out.ptr, (size_t)jobs[j].n * d->n_pi * 4,
-                                hipMemcpyDeviceToHost, s));
-  }
+    }
+  DP_HIP_TRY(launch_lanes_out(lane_tab, n_jobs, out, s));
   return DP_OK;
 }
 

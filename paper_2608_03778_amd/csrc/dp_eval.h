@@ -107,11 +107,6 @@ dp_status lane_create(dp_design *d, int32_t capacity, const dp_params *prm, hipS
 // sweeps then run as merged level launches.
 size_t lane_flow_bytes(const dp_design *d, int32_t capacity);
 void lane_drop_flow(dp_eval *ev);
-// Enqueue one batch of n columns: p [n][n_pi] and sizes [n][n_gates] (caller
-// gate order, or null) in pinned host memory; outputs power [n] and, when
-// backward, dP/dp [n][n_pi] into pinned host memory.
-dp_status lane_run(dp_eval *ev, int32_t n, const float *p, const float *size, bool backward,
-                   float *power, float *dpi);
 // Device bytes a lane of `capacity` columns holds.
 size_t lane_bytes(const dp_design *d, int32_t capacity);
 
@@ -134,10 +129,10 @@ struct LaneJob {
   bool backward;
   float *power, *dpi;
 };
-// Enqueue one step over several lanes (of any designs) on `stream`: their
-// SP levels as merged launches (one per level index), each lane's finalize
-// and power, then the merged reverse levels of the lanes that want
-// gradients.  Each lane's results equal lane_run's bit for bit.
+// Enqueue one step over several lanes (of any designs) on `stream`, every
+// part as launches over all of them: staging, the SP sweep, power, and the
+// reverse sweep of the lanes that want gradients.  A lane's results do not
+// depend on the others of its step.
 dp_status lanes_run_merged(const LaneJob *jobs, int32_t n_jobs, hipStream_t stream,
                            StepScratch *scratch);
 // Segment tables of merged level launches over several evals (design groups
@@ -198,6 +193,18 @@ struct FlowTables {
   void pack(void *host) const;
   dp_status launch_forward(const SpFlowSeg *dev, hipStream_t s) const;
   dp_status launch_reverse(const BwdFlowSeg *dev, hipStream_t s) const;
+};
+
+// Segment table of the power of several evals.
+struct PowerTable {
+  std::vector<PowerSeg> segs;
+  uint32_t blocks = 0;
+  int32_t cols = 0, widest = 1;
+  // Appends an eval's power; host: pinned copy of it, or null.  False: the
+  // eval's form does not merge.
+  bool add(dp_eval *ev, float *host);
+  size_t bytes() const { return (segs.size() * sizeof(PowerSeg) + 255) & ~(size_t)255; }
+  dp_status launch(const void *dev, hipStream_t s) const;
 };
 
 // Whether a dataflow sweep of the eval gave up since the last check (its

@@ -182,6 +182,42 @@ int32_t power_chunks(int32_t n_nets);
 int32_t power_partial_doubles(int32_t n_nets, int32_t B, int32_t S, int32_t paired);
 hipError_t launch_power(const PowerArgs &a, hipStream_t s);
 
+// The power of several evals (design groups, serving steps) as one pair of
+// launches: per column one sum, as launch_power's with one or paired sizes.
+// A segment's blocks start at block0 (power_blocks each, a multiple of 8),
+// its columns at col0; host, where not null, receives the powers too.
+struct PowerSeg {
+  PowerArgs a;
+  float *host;
+  uint32_t block0;
+  int32_t col0;
+};
+inline bool power_merges(const PowerArgs &a) { return a.mode != 1 && (a.S == 0 || a.paired || !a.size); }
+uint32_t power_blocks(const PowerArgs &a);
+hipError_t launch_power_multi(const PowerSeg *segs /* device */, int32_t n_segs, uint32_t blocks,
+                              int32_t cols, int32_t widest /* B */, hipStream_t s);
+
+// A serving step's inputs out of its lanes' pinned host buffers, and their
+// gradients into them, each as one launch over all lanes.
+struct LaneSeg {
+  const float *p;        // pinned [B][n_pi]
+  float *sp;             // [n_nets][B]
+  const float *size;     // pinned [B][G], or null
+  float *size_stage;     // [B][G]
+  float *size_dev;       // [G][B]
+  const int32_t *int2ext;
+  const float *dpi;      // [B][n_pi], or null
+  float *dpi_host;       // pinned
+  int32_t n_pi, B, G;
+  uint32_t stage0, pi_blocks, import0, out0;  // first blocks of its three launches, and its PIs' share
+};
+// Blocks of a lane in the three launches (and of its PIs in the first).
+void lane_seg_blocks(LaneSeg &l, uint32_t &stage, uint32_t &import, uint32_t &out);
+hipError_t launch_lanes_stage(const LaneSeg *segs /* device */, int32_t n_segs, uint32_t stage_blocks,
+                              uint32_t import_blocks, hipStream_t s);
+hipError_t launch_lanes_out(const LaneSeg *segs /* device */, int32_t n_segs, uint32_t blocks,
+                            hipStream_t s);
+
 // Reverse sweep.  Columns c in [0, C); the SP column of c is c / cdiv.  The
 // local seed of net n in column c is computed where it is used:
 //   kappa C_n 2 (q - p) * (beta unless STE) * weight(n, c),

@@ -365,17 +365,17 @@ __global__ __launch_bounds__(kBlock) void k_import_cols(const float *__restrict_
 // gather from them (117K gates x 256: 368 us with groups of 32 anywhere).
 constexpr int32_t kSizeGates = 64, kSizeVecs = 8;
 constexpr int32_t kSizeXcds = 8;
-__global__ __launch_bounds__(kBlock) void k_import_sizes(const float *__restrict__ src,
-                                                          const int32_t *__restrict__ int2ext,
-                                                          float *__restrict__ dst, int32_t n_pi,
-                                                          int32_t G, int32_t S) {
+__device__ __forceinline__ void import_sizes(const float *__restrict__ src,
+                                             const int32_t *__restrict__ int2ext,
+                                             float *__restrict__ dst, int32_t n_pi, int32_t G,
+                                             int32_t S, int32_t block) {
   __shared__ float tile[kSizeGates][kSizeVecs + 1];
   const int32_t g_tiles = (G + kSizeGates - 1) / kSizeGates;
   const int32_t groups = (S + kSizeVecs - 1) / kSizeVecs;
   const int32_t ways = groups >= kSizeXcds ? kSizeXcds : 1;  // blocks go to the XCDs in turn
-  const int32_t slot = (int32_t)blockIdx.x / ways;
+  const int32_t slot = block / ways;
   const int32_t g0 = (slot % g_tiles) * kSizeGates;
-  const int32_t s0 = (slot / g_tiles * ways + (int32_t)blockIdx.x % ways) * kSizeVecs;
+  const int32_t s0 = (slot / g_tiles * ways + block % ways) * kSizeVecs;
   if (s0 >= S) return;
   const int32_t gl = (int32_t)threadIdx.x & 63, sl = (int32_t)threadIdx.x >> 6;
   if (g0 + gl < G) {
@@ -390,6 +390,58 @@ __global__ __launch_bounds__(kBlock) void k_import_sizes(const float *__restrict
   const int32_t ns = min(kSizeVecs, S - s0), ng = min(kSizeGates, G - g0);
   for (int32_t i = (int32_t)threadIdx.x; i < ng * ns; i += kBlock)
     dst[(int64_t)(g0 + i / ns) * S + s0 + i % ns] = tile[i / ns][i % ns];
+}
+__global__ __launch_bounds__(kBlock) void k_import_sizes(const float *__restrict__ src,
+                                                          const int32_t *__restrict__ int2ext,
+                                                          float *__restrict__ dst, int32_t n_pi,
+                                                          int32_t G, int32_t S) {
+  import_sizes(src, int2ext, dst, n_pi, G, S, (int32_t)blockIdx.x);
+}
+
+// ---------------------------------------------------------------- serving steps
+// A step's lanes staged by one launch that reads their pinned host buffers
+// itself, and one that orders the sizes; the gradients go back the same way.
+// (A copy and a launch per lane and array: with eight lanes of 10K to 117K
+// gates a step spent 290 us before its sweeps, half of it the copy engine's
+// latency.)
+template <class Seg>
+__device__ __forceinline__ int32_t seg_at(const Seg *segs, int32_t n, uint32_t Seg::*first) {
+  int32_t k = 0;
+  while (k + 1 < n && segs[k + 1].*first <= blockIdx.x) ++k;
+  return k;
+}
+constexpr int32_t kLaneCopy = 4 * 4 * kBlock;  // floats a block copies
+__device__ __forceinline__ void lane_copy(const float *src, float *dst, int64_t n, uint32_t block) {
+  const int64_t i0 = (int64_t)block * kLaneCopy + 4 * threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int64_t i = i0 + 4 * kBlock * k;
+    if (i + 4 <= n) {
+      *reinterpret_cast<float4 *>(dst + i) = *reinterpret_cast<const float4 *>(src + i);
+    } else {
+      for (int64_t j = i; j < n; ++j) dst[j] = src[j];
+    }
+  }
+}
+__global__ __launch_bounds__(kBlock) void k_lanes_stage(const LaneSeg *__restrict__ segs, int32_t n_segs) {
+  const LaneSeg l = segs[seg_at(segs, n_segs, &LaneSeg::stage0)];
+  const uint32_t block = blockIdx.x - l.stage0;
+  if (block >= l.pi_blocks) {
+    lane_copy(l.size, l.size_stage, (int64_t)l.B * l.G, block - l.pi_blocks);
+    return;
+  }
+  const int64_t i = (int64_t)block * kBlock + threadIdx.x;
+  if (i >= (int64_t)l.n_pi * l.B) return;
+  const int32_t b = (int32_t)(i / l.n_pi), pi = (int32_t)(i - (int64_t)b * l.n_pi);
+  l.sp[(int64_t)pi * l.B + b] = sp_pack(l.p[i]);
+}
+__global__ __launch_bounds__(kBlock) void k_lanes_import(const LaneSeg *__restrict__ segs, int32_t n_segs) {
+  const LaneSeg l = segs[seg_at(segs, n_segs, &LaneSeg::import0)];
+  import_sizes(l.size_stage, l.int2ext, l.size_dev, l.n_pi, l.G, l.B, (int32_t)(blockIdx.x - l.import0));
+}
+__global__ __launch_bounds__(kBlock) void k_lanes_out(const LaneSeg *__restrict__ segs, int32_t n_segs) {
+  const LaneSeg l = segs[seg_at(segs, n_segs, &LaneSeg::out0)];
+  lane_copy(l.dpi, l.dpi_host, (int64_t)l.B * l.n_pi, blockIdx.x - l.out0);
 }
 
 // ---------------------------------------------------------------- SP level
@@ -1166,12 +1218,11 @@ constexpr int32_t kXcds = 8;
 // round's eight terms is loaded (at a clamped, valid address) before the
 // first term is formed; a term past the chunk's end is dropped.
 template <int NQ, int MODE>
-__global__ __launch_bounds__(kPowerThreads) void k_power_sp(PowerArgs a, int32_t tb,
-                                                           int32_t col_tiles) {
+__device__ __forceinline__ void power_block(const PowerArgs &a, int32_t tb, int32_t col_tiles,
+                                            uint32_t block, double *lds) {
   constexpr int U = kPowerBatch / NQ;  // nets of each lane per round
   constexpr int32_t jper = kPowerLanes / NQ;
-  __shared__ double lds[kPowerLanes * kPowerCols];
-  const int32_t xcd = (int32_t)(blockIdx.x % kXcds), slot = (int32_t)(blockIdx.x / kXcds);
+  const int32_t xcd = (int32_t)(block % kXcds), slot = (int32_t)(block / kXcds);
   const int32_t chunk = (slot / col_tiles) * kXcds + xcd;
   const int32_t tile = slot - (slot / col_tiles) * col_tiles;
   if (chunk >= a.n_chunks) return;  // the grid's round-up to whole XCD rounds
@@ -1182,7 +1233,8 @@ __global__ __launch_bounds__(kPowerThreads) void k_power_sp(PowerArgs a, int32_t
   double acc[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
-  if (b < a.B) {
+  const bool mine = j0 < jper;  // (not in a workgroup sized for a wider segment)
+  if (mine && b < a.B) {
     for (int32_t i0 = 0; n_lo + i0 * kPowerLanes < n_hi; i0 += U) {
       // aux: the toggle count (hybrid) or the frozen beta's bits
       float v[kPowerBatch], cv[kPowerBatch], sv[kPowerBatch];
@@ -1216,14 +1268,38 @@ __global__ __launch_bounds__(kPowerThreads) void k_power_sp(PowerArgs a, int32_t
     }
   }
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) lds[(j0 + q * jper) * tb + c] = acc[q];
+  for (int q = 0; q < NQ; ++q)
+    if (mine) lds[(j0 + q * jper) * tb + c] = acc[q];
   __syncthreads();
   for (int32_t stride = kPowerLanes / 2; stride > 0; stride >>= 1) {
     for (int32_t e = threadIdx.x; e < stride * tb; e += blockDim.x)
       lds[e] += lds[e + stride * tb];
     __syncthreads();
   }
-  if (threadIdx.x < tb && b < a.B) a.partial[(int64_t)chunk * a.B + b] = lds[c];
+  if ((int32_t)threadIdx.x < tb && b < a.B) a.partial[(int64_t)chunk * a.B + b] = lds[c];
+}
+template <int NQ, int MODE>
+__global__ __launch_bounds__(kPowerThreads) void k_power_sp(PowerArgs a, int32_t tb,
+                                                           int32_t col_tiles) {
+  __shared__ double lds[kPowerLanes * kPowerCols];
+  power_block<NQ, MODE>(a, tb, col_tiles, blockIdx.x, lds);
+}
+// Several evals' nets in one launch, tiles of up to kPowerMulti columns.
+constexpr int32_t kPowerMulti = kPowerThreads / kPowerLanes;
+__host__ __device__ inline int32_t power_tile(int32_t B) {
+  int32_t tb = 1;
+  while (tb < B && tb < kPowerMulti) tb *= 2;
+  return tb;
+}
+__global__ __launch_bounds__(kPowerThreads) void k_power_multi(const PowerSeg *__restrict__ segs,
+                                                              int32_t n_segs) {
+  __shared__ double lds[kPowerLanes * kPowerMulti];
+  const PowerSeg &sg = segs[seg_at(segs, n_segs, &PowerSeg::block0)];
+  const int32_t tb = power_tile(sg.a.B), tiles = (sg.a.B + tb - 1) / tb;
+  if (sg.a.mode == 2)
+    power_block<1, 2>(sg.a, tb, tiles, blockIdx.x - sg.block0, lds);
+  else
+    power_block<1, 0>(sg.a, tb, tiles, blockIdx.x - sg.block0, lds);
 }
 
 __device__ __forceinline__ double block_sum_d(double v, double *lds) {
@@ -1349,14 +1425,27 @@ __global__ __launch_bounds__(kBlock) void k_power_slabs(const double *__restrict
 
 // One block per column: thread t sums chunks t, t + 256, ... in order, then
 // a fixed tree over the block.
-__global__ __launch_bounds__(kBlock) void k_power_final(PowerArgs a, int32_t n_cols) {
+__device__ __forceinline__ float power_column(const double *partial, int32_t n_chunks, int32_t n_cols,
+                                              int32_t col) {
   __shared__ double lds[kWavesPerBlock];
-  const int32_t col = blockIdx.x;
   double acc = 0.0;
-  for (int32_t k = threadIdx.x; k < a.n_chunks; k += kBlock)
-    acc += a.partial[(int64_t)k * n_cols + col];
-  const double r = block_sum_d(acc, lds);
-  if (threadIdx.x == 0) a.power[col] = (float)r;
+  for (int32_t k = threadIdx.x; k < n_chunks; k += kBlock) acc += partial[(int64_t)k * n_cols + col];
+  return (float)block_sum_d(acc, lds);
+}
+__global__ __launch_bounds__(kBlock) void k_power_final(PowerArgs a, int32_t n_cols) {
+  const float r = power_column(a.partial, a.n_chunks, n_cols, (int32_t)blockIdx.x);
+  if (threadIdx.x == 0) a.power[blockIdx.x] = r;
+}
+__global__ __launch_bounds__(kBlock) void k_power_final_multi(const PowerSeg *__restrict__ segs,
+                                                             int32_t n_segs) {
+  int32_t k = 0;
+  while (k + 1 < n_segs && segs[k + 1].col0 <= (int32_t)blockIdx.x) ++k;
+  const PowerSeg &sg = segs[k];
+  const int32_t col = (int32_t)blockIdx.x - sg.col0;
+  const float r = power_column(sg.a.partial, sg.a.n_chunks, sg.a.B, col);
+  if (threadIdx.x != 0) return;
+  sg.a.power[col] = r;
+  if (sg.host) sg.host[col] = r;
 }
 
 // ---------------------------------------------------------------- reverse sweep
@@ -3530,6 +3619,28 @@ hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, float *
   return hipGetLastError();
 }
 
+void lane_seg_blocks(LaneSeg &l, uint32_t &stage, uint32_t &import, uint32_t &out) {
+  const int64_t sizes = l.size ? (int64_t)l.B * l.G : 0;
+  l.pi_blocks = blocks_for((int64_t)l.n_pi * l.B);
+  stage = l.pi_blocks + (uint32_t)((sizes + kLaneCopy - 1) / kLaneCopy);
+  const int64_t groups = (l.B + kSizeVecs - 1) / kSizeVecs;
+  const int64_t rounds = groups >= kSizeXcds ? (groups + kSizeXcds - 1) / kSizeXcds * kSizeXcds : groups;
+  import = sizes ? (uint32_t)(((l.G + kSizeGates - 1) / kSizeGates) * rounds) : 0u;
+  out = l.dpi ? (uint32_t)(((int64_t)l.B * l.n_pi + kLaneCopy - 1) / kLaneCopy) : 0u;
+}
+hipError_t launch_lanes_stage(const LaneSeg *segs, int32_t n_segs, uint32_t stage_blocks,
+                              uint32_t import_blocks, hipStream_t s) {
+  if (stage_blocks) k_lanes_stage<<<stage_blocks, kBlock, 0, s>>>(segs, n_segs);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !import_blocks) return e;
+  k_lanes_import<<<import_blocks, kBlock, 0, s>>>(segs, n_segs);
+  return hipGetLastError();
+}
+hipError_t launch_lanes_out(const LaneSeg *segs, int32_t n_segs, uint32_t blocks, hipStream_t s) {
+  if (blocks) k_lanes_out<<<blocks, kBlock, 0, s>>>(segs, n_segs);
+  return hipGetLastError();
+}
+
 hipError_t launch_grad_lambda_export(const float *lam, const float *sp, const int32_t *int2ext,
                                      int32_t n_pi, int32_t n_nets, int32_t B, int32_t C,
                                      int32_t cdiv, float eps, float *lam_out, float *score,
@@ -3720,6 +3831,19 @@ int32_t power_partial_doubles(int32_t n_nets, int32_t B, int32_t S, int32_t pair
   return (int32_t)(slabs * cols);
 }
 
+uint32_t power_blocks(const PowerArgs &a) {
+  const int32_t tb = power_tile(a.B);
+  return (uint32_t)(kXcds * ((a.B + tb - 1) / tb) * ((a.n_chunks + kXcds - 1) / kXcds));
+}
+hipError_t launch_power_multi(const PowerSeg *segs, int32_t n_segs, uint32_t blocks, int32_t cols,
+                              int32_t widest, hipStream_t s) {
+  if (n_segs <= 0 || blocks == 0 || cols <= 0) return hipSuccess;
+  k_power_multi<<<blocks, (unsigned)(kPowerLanes * power_tile(widest)), 0, s>>>(segs, n_segs);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_power_final_multi<<<(unsigned)cols, kBlock, 0, s>>>(segs, n_segs);
+  return hipGetLastError();
+}
 hipError_t launch_power(const PowerArgs &a, hipStream_t s) {
   const int32_t Sp = (a.S > 0 && !a.paired) ? a.S : 1;
   const int32_t n_cols = a.B * Sp;

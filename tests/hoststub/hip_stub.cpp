@@ -501,6 +501,61 @@ int32_t power_partial_doubles(int32_t n_nets, int32_t B, int32_t S, int32_t pair
     slabs = std::max<int64_t>(slabs, (n_nets + power_slab(n_nets) - 1) / power_slab(n_nets));
   return (int32_t)(slabs * cols);
 }
+uint32_t power_blocks(const PowerArgs &a) { return 8u * (uint32_t)((a.n_chunks + 7) / 8); }
+hipError_t launch_power_multi(const PowerSeg *segs, int32_t n_segs, uint32_t blocks, int32_t cols,
+                              int32_t widest, hipStream_t stream_) {
+  uint32_t block = 0;
+  int32_t col = 0;
+  for (int32_t k = 0; k < n_segs; ++k) {
+    const PowerSeg &sg = segs[k];
+    if (sg.block0 != block || sg.col0 != col || sg.a.B > widest) fatal("power segments out of order");
+    if (!power_merges(sg.a)) fatal("power segment that does not merge");
+    block += power_blocks(sg.a);
+    col += sg.a.B;
+    launch_power(sg.a, stream_);
+    if (sg.host) std::fill(sg.host, sg.host + sg.a.B, 0.0f);
+  }
+  if (block != blocks || col != cols) fatal("power segments' totals");
+  return hipSuccess;
+}
+void lane_seg_blocks(LaneSeg &l, uint32_t &stage, uint32_t &import, uint32_t &out) {
+  l.pi_blocks = 1;
+  stage = l.size ? 2 : 1;
+  import = l.size ? 1 : 0;
+  out = l.dpi ? 1 : 0;
+}
+hipError_t launch_lanes_stage(const LaneSeg *segs, int32_t n_segs, uint32_t stage_blocks,
+                              uint32_t import_blocks, hipStream_t stream_) {
+  uint32_t stage = 0, import = 0;
+  for (int32_t k = 0; k < n_segs; ++k) {
+    const LaneSeg &l = segs[k];
+    if (l.stage0 != stage || l.import0 != import) fatal("lane segments out of order");
+    stage += l.size ? 2 : 1;
+    import += l.size ? 1 : 0;
+    Scope sc_(stream_);
+    wr(l.sp, (int64_t)l.n_pi * l.B);
+    if (!l.size) continue;
+    rd(l.int2ext, l.n_pi + l.G);
+    wr(l.size_stage, (int64_t)l.B * l.G);
+    wr(l.size_dev, (int64_t)l.B * l.G);
+  }
+  if (stage != stage_blocks || import != import_blocks) fatal("lane segments' totals");
+  return hipSuccess;
+}
+hipError_t launch_lanes_out(const LaneSeg *segs, int32_t n_segs, uint32_t blocks, hipStream_t stream_) {
+  uint32_t out = 0;
+  for (int32_t k = 0; k < n_segs; ++k) {
+    const LaneSeg &l = segs[k];
+    if (l.out0 != out) fatal("lane segments out of order");
+    if (!l.dpi) continue;
+    ++out;
+    Scope sc_(stream_);
+    rd(l.dpi, (int64_t)l.B * l.n_pi);
+    std::fill(l.dpi_host, l.dpi_host + (int64_t)l.B * l.n_pi, 0.0f);
+  }
+  if (out != blocks) fatal("lane segments' totals");
+  return hipSuccess;
+}
 hipError_t launch_power(const PowerArgs &a, hipStream_t stream_) {
   Scope sc_(stream_);
   const int64_t nb = (int64_t)a.n_nets * a.B;
