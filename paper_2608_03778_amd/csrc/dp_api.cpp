@@ -30,6 +30,29 @@ void ctx_release(dp_ctx *c) {
   }
   delete c;
 }
+
+constexpr size_t kReportPage = 4096;
+ReportWords::~ReportWords() {
+  for (uint32_t *p : pages_) (void)hipHostFree(p);
+}
+dp_status ReportWords::take(uint32_t **out) {
+  std::lock_guard<std::mutex> lock(mu_);
+  if (free_.empty()) {
+    void *p = nullptr;
+    DP_HIP_TRY(hipHostMalloc(&p, kReportPage));
+    pages_.push_back(static_cast<uint32_t *>(p));
+    for (size_t i = 0; i < kReportPage / sizeof(uint32_t); ++i) free_.push_back(pages_.back() + i);
+  }
+  *out = free_.back();
+  free_.pop_back();
+  **out = 0u;
+  return DP_OK;
+}
+void ReportWords::give(uint32_t *word) {
+  std::lock_guard<std::mutex> lock(mu_);
+  free_.push_back(word);
+}
+
 void design_retain(dp_design *d) { d->refs.fetch_add(1); }
 void design_release(dp_design *d) {
   if (d->refs.fetch_sub(1) != 1) return;
@@ -315,14 +338,10 @@ dp_status grid_barrier(dp_eval *ev, dp::GridBarrier *out) {
 // --- dataflow sweeps (launch_sp_flow, launch_bwd_flow)
 // Allocate what the eval's dataflow sweeps need (once; before any capture).
 dp_status ensure_flow(dp_eval *ev) {
-  DP_TRY(ev->flow.alloc(dp::kFlowWords * sizeof(uint32_t)));
-  if (!ev->flow_report) {
-    void *p = nullptr;
-    DP_HIP_TRY(hipHostMalloc(&p, sizeof(uint32_t)));
-    ev->flow_report = static_cast<uint32_t *>(p);
-    *ev->flow_report = 0u;
-  }
-  return DP_OK;
+  DP_TRY(ev->flow.alloc((dp::kFlowWords + dp::kSimWords) * sizeof(uint32_t)));
+  if (ev->flow_report) return DP_OK;
+  ev->reports = ev->d->ctx->reports;
+  return ev->reports->take(&ev->flow_report);
 }
 
 // Whether a sweep over C columns of the eval runs as one dataflow launch
@@ -440,9 +459,8 @@ dp_status ensure_forward_buffers(dp_eval *ev, const ChunkPlan *pl) {
     DP_TRY(ev->ones.alloc(nb * sizeof(uint32_t)));
     DP_TRY(ev->tog.alloc(nb * sizeof(uint32_t)));
     if (pl->tile) {
-      DP_TRY(ev->sim_ctl.alloc(dp::kSimWords * sizeof(uint32_t)));
-      DP_TRY(ev->words.alloc((size_t)pl->n_bufs * d->n_nets * pl->tile * sizeof(uint64_t)));
-      DP_TRY(ev->tiles.alloc((size_t)pl->n_tiles * nb * (2 * sizeof(uint64_t) + sizeof(uint32_t))));
+      DP_TRY(ev->words.alloc((size_t)pl->n_bufs * d->n_nets * pl->tile * sizeof(uint64_t) +
+                             (size_t)pl->n_tiles * nb * (2 * sizeof(uint64_t) + sizeof(uint32_t))));
       if (!ev->have_stim)
         DP_TRY(ev->mstim.alloc(std::max<size_t>((size_t)ev->B * d->n_pi * pl->T * sizeof(uint64_t), 16)));
       return DP_OK;
@@ -561,13 +579,13 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
     for (int32_t l = 1; l <= d->depth; ++l)
       bytes += sim_level_bytes(d, l, pl->T, ev->B, ev->B, false);
     SpanGuard sg(ev, SPAN_SIM, bytes, prof, 1);
-    uint64_t *edge = ev->tiles.as<uint64_t>();
+    uint64_t *edge = ev->words.as<uint64_t>() + (size_t)pl->n_bufs * d->n_nets * pl->tile;
     const size_t n = (size_t)pl->n_tiles * d->n_nets * ev->B;
     const dp::SimFlow t{g, d->level_dev.as<int32_t>(), stim, ev->words.as<uint64_t>(),
                         reinterpret_cast<uint32_t *>(edge + 2 * n), edge, pl->T, d->depth, ev->B,
                         pl->tile, pl->n_tiles, pl->n_bufs};
     dp::FlowCtl ctl = flow_ctl(ev);
-    ctl.words = ev->sim_ctl.as<uint32_t>();
+    ctl.words += dp::kFlowWords;
     DP_HIP_TRY(dp::launch_sim_flow(t, d->has_cell_gates, ctl, sp, ev->ones.as<uint32_t>(), ev->tog.as<uint32_t>(), s));
   } else if (pl) {
     const size_t nb = (size_t)d->n_nets * ev->B;
@@ -780,7 +798,6 @@ uint64_t graph_key(const dp_eval *ev, const ChunkPlan *pl) {
     mix((uint64_t)pl->Tc);
     mix((uint64_t)pl->tile);
     mix((uint64_t)pl->n_bufs);
-    mix((uint64_t)(uintptr_t)ev->tiles.ptr);
     mix((uint64_t)pl->cols);
     mix((uint64_t)pick_iters(ev, *pl));
     mix((uint64_t)n_sim_streams(ev));
@@ -964,7 +981,7 @@ dp_eval::~dp_eval() {
   if (graph_bwd) (void)hipGraphExecDestroy(graph_bwd);
   if (graph_fb) (void)hipGraphExecDestroy(graph_fb);
   if (capture_stream_owned) (void)hipStreamDestroy(capture_stream_owned);
-  if (flow_report) (void)hipHostFree(flow_report);
+  if (flow_report) reports->give(flow_report);
   if (coop_stream) {
     (void)hipStreamSynchronize(coop_stream);
     (void)hipStreamDestroy(coop_stream);
@@ -2412,7 +2429,7 @@ size_t lane_bytes(const dp_design *d, int32_t capacity) {
 
 size_t lane_flow_bytes(const dp_design *d, int32_t capacity) {
   return (size_t)capacity * 4 * ((size_t)d->n_nets + (size_t)d->pins * d->n_gates) +
-         kFlowWords * sizeof(uint32_t);
+         (kFlowWords + kSimWords) * sizeof(uint32_t);
 }
 
 void lane_drop_flow(dp_eval *ev) {

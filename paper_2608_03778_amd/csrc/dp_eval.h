@@ -36,9 +36,9 @@ struct dp_eval {
        have_stim = false, have_tau = false, have_streams = false, have_fixed = false;
   uint64_t inputs_version = 1, fwd_version = 0;
   // forward state
-  dp::DevBuf words;          // simulation chunk [n_nets][pitch], or the teams' tiles
-  dp::DevBuf sim_ctl;        // word tiles: control words (dp::kSimWords)
-  dp::DevBuf tiles;          // word tiles: first and last words, counts per (tile, net)
+  // simulation chunk [n_nets][pitch]; of word tiles: the teams' rows, then per
+  // (tile, net) the first and last words and the counts
+  dp::DevBuf words;
   dp::DevBuf ones, tog;      // [n_nets][B]
   dp::DevBuf beta;           // [n_nets][B] computed beta (hybrid mode only)
   dp::DevBuf power_partial;  // [chunks][B*S'] double
@@ -47,8 +47,9 @@ struct dp_eval {
   dp::DevBuf barrier;        // persistent sweeps: grid-barrier words (dp::kBarrierAlloc)
   bool barrier_pending = false;      // a persistent sweep ran since the report word was read
   double barrier_limit_us = 1000.0;  // a barrier wait gives up after this long without progress
-  dp::DevBuf flow;                   // dataflow sweeps: control words (dp::kFlowWords)
+  dp::DevBuf flow;                   // control words: dataflow sweeps (dp::kFlowWords), then word tiles
   uint32_t *flow_report = nullptr;   // pinned host word: a dataflow sweep's wait gave up
+  std::shared_ptr<dp::ReportWords> reports;  // where that word goes back to
   // reverse state
   dp::DevBuf w;              // [B*S'] upstream weights
   dp::DevBuf contrib;        // [n_edges][C] contributions, or [n_nets][C] adjoints

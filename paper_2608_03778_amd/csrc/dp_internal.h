@@ -6,6 +6,8 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdint>
+#include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -74,11 +76,28 @@ std::vector<uint16_t> cell_rule(const CellCode &c);
 // an eval (and a server lane) holds its design, a server holds its context
 // and its designs.  *_destroy drops the caller's reference, so handles may be
 // destroyed in any order.
+namespace dp {
+// Pinned host words, one per eval, that dataflow launches report in: cut from
+// pages that are given back with the last of the context and its evals (an
+// allocation of its own took a fresh eval's first forward 0.1 ms).
+class ReportWords {
+ public:
+  ~ReportWords();
+  dp_status take(uint32_t **out);  // zeroed
+  void give(uint32_t *word);
+
+ private:
+  std::mutex mu_;
+  std::vector<uint32_t *> pages_, free_;
+};
+}  // namespace dp
+
 struct dp_ctx {
   int device = 0;
   int32_t n_cu = 0;               // compute units of the device
   hipStream_t stream = nullptr;   // stream calls enqueue on
   hipStream_t owned = nullptr;    // stream created by the library, if any
+  std::shared_ptr<dp::ReportWords> reports = std::make_shared<dp::ReportWords>();
   std::atomic<int> refs{1};
 };
 
