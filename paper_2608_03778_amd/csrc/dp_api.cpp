@@ -104,8 +104,20 @@ dp_status check_params(const dp_params *p) {
 }
 
 // Validate a float array (host or device) against [lo, hi] (NaN rejected).
+// The eval's pinned words, once.
+dp_status ensure_reports(dp_eval *ev) {
+  if (!ev->reports) ev->reports = ev->d->ctx->reports;
+  if (!ev->flow_report) DP_TRY(ev->reports->take(&ev->flow_report));
+  if (!ev->check_report) DP_TRY(ev->reports->take(&ev->check_report));
+  return DP_OK;
+}
+
+// Refuse values outside [lo, hi] (and NaN).  Device values are checked on the
+// device; the kernel reports into a pinned word of the eval's (a device flag
+// took a fill and a copy to the host more, 20 to 30 us a call), and stores them
+// in `copy` on its way where that is not null.
 dp_status check_values(dp_eval *ev, const float *v, int64_t n, float lo, float hi, int on_device,
-                       const char *what) {
+                       const char *what, float *copy = nullptr) {
   if (!v) return fail(DP_E_INVALID, std::string(what) + ": NULL pointer");
   if (!on_device) {
     for (int64_t i = 0; i < n; ++i)
@@ -115,13 +127,12 @@ dp_status check_values(dp_eval *ev, const float *v, int64_t n, float lo, float h
     return DP_OK;
   }
   hipStream_t s = ev->stream();
-  DP_TRY(ev->flag.alloc(sizeof(int32_t)));
-  DP_HIP_TRY(dp::launch_fill_u32(ev->flag.as<uint32_t>(), 1, 0u, s));
-  DP_HIP_TRY(dp::launch_check_range(v, n, lo, hi, ev->flag.as<int32_t>(), s));
-  int32_t bad = 0;
-  DP_HIP_TRY(hipMemcpyAsync(&bad, ev->flag.ptr, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  DP_TRY(ensure_reports(ev));
+  volatile uint32_t *bad = ev->check_report;
+  *bad = 0u;
+  DP_HIP_TRY(dp::launch_check_range(v, n, lo, hi, copy, ev->check_report, s));
   DP_HIP_TRY(hipStreamSynchronize(s));
-  if (bad) return fail(DP_E_INVALID, std::string(what) + ": a value is NaN or out of range");
+  if (*bad) return fail(DP_E_INVALID, std::string(what) + ": a value is NaN or out of range");
   return DP_OK;
 }
 
@@ -131,6 +142,17 @@ dp_status stage_in(DevBuf &buf, const void *src, size_t bytes, int on_device, hi
   if (bytes)
     DP_HIP_TRY(hipMemcpyAsync(buf.ptr, src, bytes,
                               on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
+  return DP_OK;
+}
+
+// What an import kernel reads: a device array as it is, a host one's copy in
+// `stage`.
+dp_status import_from(DevBuf &stage, const float *src, size_t bytes, int on_device, hipStream_t s,
+                      const float **out) {
+  *out = src;
+  if (on_device) return DP_OK;
+  DP_TRY(stage_in(stage, src, bytes, 0, s));
+  *out = stage.as<float>();
   return DP_OK;
 }
 
@@ -339,9 +361,7 @@ dp_status grid_barrier(dp_eval *ev, dp::GridBarrier *out) {
 // Allocate what the eval's dataflow sweeps need (once; before any capture).
 dp_status ensure_flow(dp_eval *ev) {
   DP_TRY(ev->flow.alloc((dp::kFlowWords + dp::kSimWords) * sizeof(uint32_t)));
-  if (ev->flow_report) return DP_OK;
-  ev->reports = ev->d->ctx->reports;
-  return ev->reports->take(&ev->flow_report);
+  return ensure_reports(ev);
 }
 
 // Whether a sweep over C columns of the eval runs as one dataflow launch
@@ -982,6 +1002,7 @@ dp_eval::~dp_eval() {
   if (graph_fb) (void)hipGraphExecDestroy(graph_fb);
   if (capture_stream_owned) (void)hipStreamDestroy(capture_stream_owned);
   if (flow_report) reports->give(flow_report);
+  if (check_report) reports->give(check_report);
   if (coop_stream) {
     (void)hipStreamSynchronize(coop_stream);
     (void)hipStreamDestroy(coop_stream);
@@ -1176,8 +1197,9 @@ dp_status dp_set_pi_prob(dp_eval *ev, const float *p, int32_t on_device) {
   }
   DP_TRY(check_values(ev, p, n, 0.0f, 1.0f, on_device, "dp_set_pi_prob"));
   hipStream_t s = ev->stream();
-  DP_TRY(stage_in(ev->p_stage, p, n * sizeof(float), on_device, s));
-  DP_HIP_TRY(dp::launch_load_pi(ev->p_stage.as<float>(), ev->sp.as<float>(), d->n_pi, ev->B, s));
+  const float *src;
+  DP_TRY(import_from(ev->p_stage, p, n * sizeof(float), on_device, s, &src));
+  DP_HIP_TRY(dp::launch_load_pi(src, ev->sp.as<float>(), d->n_pi, ev->B, s));
   if (!on_device) DP_HIP_TRY(hipStreamSynchronize(s));
   ev->have_pi = true;
   ev->inputs_version++;
@@ -1189,8 +1211,9 @@ dp_status dp_set_caps(dp_eval *ev, const float *cap, int32_t on_device) {
   const dp_design *d = ev->d;
   DP_TRY(check_values(ev, cap, d->n_nets, 0.0f, 3.0e38f, on_device, "dp_set_caps"));
   hipStream_t s = ev->stream();
-  DP_TRY(stage_in(ev->cap_stage, cap, (size_t)d->n_nets * sizeof(float), on_device, s));
-  DP_HIP_TRY(dp::launch_gather_nets_f32(ev->cap_stage.as<float>(), d->int2ext.as<int32_t>(),
+  const float *src;
+  DP_TRY(import_from(ev->cap_stage, cap, (size_t)d->n_nets * sizeof(float), on_device, s, &src));
+  DP_HIP_TRY(dp::launch_gather_nets_f32(src, d->int2ext.as<int32_t>(),
                                         ev->cap.as<float>(), d->n_nets, s));
   if (!on_device) DP_HIP_TRY(hipStreamSynchronize(s));
   ev->have_cap = true;
@@ -1205,8 +1228,9 @@ dp_status dp_set_cell_sizes(dp_eval *ev, const float *size, int32_t on_device) {
   const int64_t n = (int64_t)ev->S * d->n_gates;
   DP_TRY(check_values(ev, size, n, 0.0f, 3.0e38f, on_device, "dp_set_cell_sizes"));
   hipStream_t s = ev->stream();
-  DP_TRY(stage_in(ev->size_stage, size, n * sizeof(float), on_device, s));
-  DP_HIP_TRY(dp::launch_import_sizes(ev->size_stage.as<float>(), d->int2ext.as<int32_t>(),
+  const float *src;
+  DP_TRY(import_from(ev->size_stage, size, n * sizeof(float), on_device, s, &src));
+  DP_HIP_TRY(dp::launch_import_sizes(src, d->int2ext.as<int32_t>(),
                                      ev->size.as<float>(), d->n_pi, d->n_gates, ev->S, s));
   if (!on_device) DP_HIP_TRY(hipStreamSynchronize(s));
   ev->have_size = true;
@@ -1221,8 +1245,9 @@ dp_status dp_set_beta(dp_eval *ev, const float *beta, int32_t on_device) {
   DP_TRY(check_values(ev, beta, n, 0.0f, 3.0e38f, on_device, "dp_set_beta"));
   hipStream_t s = ev->stream();
   DP_TRY(ev->beta_frozen.alloc(n * sizeof(float)));
-  DP_TRY(stage_in(ev->beta_stage, beta, n * sizeof(float), on_device, s));
-  DP_HIP_TRY(dp::launch_import_cols_f32(ev->beta_stage.as<float>(), d->int2ext.as<int32_t>(),
+  const float *src;
+  DP_TRY(import_from(ev->beta_stage, beta, n * sizeof(float), on_device, s, &src));
+  DP_HIP_TRY(dp::launch_import_cols_f32(src, d->int2ext.as<int32_t>(),
                                         ev->beta_frozen.as<float>(), d->n_nets, ev->B, s));
   if (!on_device) DP_HIP_TRY(hipStreamSynchronize(s));
   ev->have_beta = true;
@@ -1525,8 +1550,11 @@ static dp_status run_backward(dp_eval *ev, const float *grad_power, int per_colu
   const int32_t C = per_column ? cols : ev->B;
   const float *w = nullptr;
   if (grad_power) {
-    DP_TRY(check_values(ev, grad_power, cols, -3.0e38f, 3.0e38f, on_device, "dp_backward grad"));
-    DP_TRY(stage_in(ev->w, grad_power, (size_t)cols * sizeof(float), on_device, s));
+    DP_TRY(ev->w.alloc(std::max<size_t>((size_t)cols * sizeof(float), 16)));
+    DP_TRY(check_values(ev, grad_power, cols, -3.0e38f, 3.0e38f, on_device, "dp_backward grad",
+                        ev->w.as<float>()));
+    if (!on_device)
+      DP_TRY(stage_in(ev->w, grad_power, (size_t)cols * sizeof(float), 0, s));
     w = ev->w.as<float>();
   }
   if (dpi) {
@@ -2421,7 +2449,7 @@ size_t lane_bytes(const dp_design *d, int32_t capacity) {
   const size_t nn = d->n_nets, G = d->n_gates, np = d->n_pi;
   // SP per net (the frozen beta is one per net, shared by the columns);
   // contributions per edge; sizes (and their staging) per gate;
-  // probabilities (and staging, dP/dp)
+  // probabilities and dP/dp
   const size_t per_col = 4 * (nn + (size_t)d->n_edges + 2 * G + 2 * np) +
                          8 * (size_t)power_chunks(d->n_nets) + 16;
   return (size_t)capacity * per_col + 8 * nn;
@@ -2459,7 +2487,6 @@ dp_status lane_create(dp_design *d, int32_t capacity, const dp_params *prm, hipS
   A(ev->cap, nn * 4);
   A(ev->size, (size_t)capacity * d->n_gates * 4);
   A(ev->size_stage, (size_t)capacity * d->n_gates * 4);
-  A(ev->p_stage, (size_t)capacity * d->n_pi * 4);
   if (prm->mode == DP_HYBRID) A(ev->beta, nn * capacity * 4);
   A(ev->power_partial, (size_t)power_chunks(d->n_nets) * capacity * 8);
   A(ev->power, (size_t)capacity * 4);

@@ -43,13 +43,13 @@ struct dp_eval {
   dp::DevBuf beta;           // [n_nets][B] computed beta (hybrid mode only)
   dp::DevBuf power_partial;  // [chunks][B*S'] double
   dp::DevBuf power;          // [B*S']
-  dp::DevBuf flag;           // int32 validation flag
+  uint32_t *check_report = nullptr;  // pinned host word: a checked value was out of range
   dp::DevBuf barrier;        // persistent sweeps: grid-barrier words (dp::kBarrierAlloc)
   bool barrier_pending = false;      // a persistent sweep ran since the report word was read
   double barrier_limit_us = 1000.0;  // a barrier wait gives up after this long without progress
   dp::DevBuf flow;                   // control words: dataflow sweeps (dp::kFlowWords), then word tiles
   uint32_t *flow_report = nullptr;   // pinned host word: a dataflow sweep's wait gave up
-  std::shared_ptr<dp::ReportWords> reports;  // where that word goes back to
+  std::shared_ptr<dp::ReportWords> reports;  // where those words go back to
   // reverse state
   dp::DevBuf w;              // [B*S'] upstream weights
   dp::DevBuf contrib;        // [n_edges][C] contributions, or [n_nets][C] adjoints

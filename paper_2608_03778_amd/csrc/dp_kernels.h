@@ -89,9 +89,10 @@ hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t s);
 
 // PI probabilities [B][n_pi] (caller layout) -> stored SP [n_pi][B].
 hipError_t launch_load_pi(const float *p, float *sp, int32_t n_pi, int32_t B, hipStream_t s);
-// Check values are finite and inside [lo, hi]; sets *bad = 1 otherwise.
-hipError_t launch_check_range(const float *v, int64_t n, float lo, float hi, int32_t *bad,
-                              hipStream_t s);
+// Check values are finite and inside [lo, hi]; sets *bad = 1 otherwise (bad may
+// be pinned host memory).  copy: where not null, the values are stored there.
+hipError_t launch_check_range(const float *v, int64_t n, float lo, float hi, float *copy,
+                              uint32_t *bad, hipStream_t s);
 // Caller-numbered per-net array [n_nets] -> internal numbering.
 hipError_t launch_gather_nets_f32(const float *src_ext, const int32_t *int2ext, float *dst_int,
                                   int32_t n_nets, hipStream_t s);

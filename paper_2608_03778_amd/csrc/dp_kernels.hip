@@ -332,10 +332,12 @@ __global__ __launch_bounds__(kBlock) void k_load_pi(const float *__restrict__ p,
 }
 
 __global__ __launch_bounds__(kBlock) void k_check_range(const float *__restrict__ v, int64_t n,
-                                                         float lo, float hi, int32_t *bad) {
+                                                         float lo, float hi, float *copy,
+                                                         uint32_t *bad) {
   int64_t i = gidx();
   if (i >= n) return;
   float x = v[i];
+  if (copy) copy[i] = x;
   if (!(x >= lo && x <= hi)) *bad = 1;  // NaN fails both comparisons
 }
 
@@ -3584,11 +3586,11 @@ hipError_t launch_load_pi(const float *p, float *sp, int32_t n_pi, int32_t B, hi
   return hipGetLastError();
 }
 
-hipError_t launch_check_range(const float *v, int64_t n, float lo, float hi, int32_t *bad,
-                              hipStream_t s) {
+hipError_t launch_check_range(const float *v, int64_t n, float lo, float hi, float *copy,
+                              uint32_t *bad, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (too_big(n)) return hipErrorInvalidValue;
-  k_check_range<<<blocks_for(n), kBlock, 0, s>>>(v, n, lo, hi, bad);
+  k_check_range<<<blocks_for(n), kBlock, 0, s>>>(v, n, lo, hi, copy, bad);
   return hipGetLastError();
 }
 

@@ -356,13 +356,14 @@ hipError_t launch_load_pi(const float *p, float *sp, int32_t n_pi, int32_t B, hi
   wr(sp, (int64_t)n_pi * B);
   return hipSuccess;
 }
-hipError_t launch_check_range(const float *v, int64_t n, float lo, float hi, int32_t *bad,
-                              hipStream_t stream_) {
+hipError_t launch_check_range(const float *v, int64_t n, float lo, float hi, float *copy,
+                              uint32_t *bad, hipStream_t stream_) {
   Scope sc_(stream_);
-  int32_t b = 0;
+  if (copy) wr(copy, n);
+  uint32_t b = 0;
   for (int64_t i = 0; i < n; ++i)
     if (!(v[i] >= lo && v[i] <= hi)) b = 1;
-  *bad = b;
+  if (b) *bad = b;
   return hipSuccess;
 }
 hipError_t launch_gather_nets_f32(const float *src, const int32_t *int2ext, float *dst,
