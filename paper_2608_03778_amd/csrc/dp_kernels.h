@@ -372,6 +372,7 @@ struct FlowCtl {
   uint32_t *report;   // host-visible: set when a wait gave up
   uint32_t expected;  // workgroups a team's leader waits for (set by the launcher)
   int32_t n_cu;       // compute units of the device
+  int32_t shifts;     // levels in which the waves take turns (set by the launcher)
 };
 // Whether a sweep of C columns is one for these kernels: within their 32-bit
 // offsets and tables, and few enough (net, column) pairs that its levels are

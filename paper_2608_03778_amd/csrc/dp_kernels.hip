@@ -2477,13 +2477,15 @@ __device__ __forceinline__ int32_t flow_claim(const FlowCtl &ctl, const FlowSeat
 
 // A wave's walk over the 64-item blocks of a column's levels: block w, w + W,
 // ... of each level in turn, w counted across the members first, so a
-// level's blocks spread over as many CUs as there are.  The level table sits
+// level's blocks spread over as many CUs as there are, and from the shift on
+// whose turn the level is.  The level table sits
 // in LDS.
 __shared__ int32_t flow_lv[kFlowLevels];
 
 struct FlowWalk {
   int32_t w64, W64;   // 64 times this wave's index, 64 times the number of waves
   int32_t n_pi, depth;
+  int32_t shifts, shift;  // less one: levels until the waves' order is the first again; its step
 };
 
 // A block of the walk: its first item is `base` of the n of level l, whose
@@ -2494,13 +2496,14 @@ struct FlowBlock {
 
 // Loads the level table into LDS; every thread calls it, before any claim.
 __device__ __forceinline__ FlowWalk flow_walk(const FlowSeat &st, const int32_t *level_ptr,
-                                              int32_t depth, int32_t n_pi) {
+                                              int32_t depth, int32_t n_pi, int32_t shifts) {
   for (int32_t i = (int32_t)threadIdx.x; i < depth + 2; i += (int32_t)blockDim.x)
     flow_lv[i] = level_ptr[i];
   __syncthreads();
   const int32_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  return FlowWalk{64 * (wave * (int32_t)st.members + (int32_t)st.rank),
-                  (int32_t)(blockDim.x * st.members), n_pi, depth};
+  const int32_t all = (int32_t)(blockDim.x * st.members);
+  return FlowWalk{64 * (wave * (int32_t)st.members + (int32_t)st.rank), all, n_pi, depth,
+                  shifts - 1, all / shifts};
 }
 
 // The first block at or after `q` that has items, levels ascending (DIR 1,
@@ -2517,7 +2520,8 @@ __device__ __forceinline__ FlowBlock flow_settle(const FlowWalk &k, FlowBlock q)
     const int32_t b = __builtin_amdgcn_readfirstlane(flow_lv[q.l + 1]);
     q.net = q.l > 0 ? k.n_pi + a : 0;
     q.n = q.l > 0 ? b - a : k.n_pi;
-    q.base = k.w64;
+    q.base = k.w64 - (q.l & k.shifts) * k.shift;
+    if (q.base < 0) q.base += k.W64;
   }
   return q;
 }
@@ -2658,10 +2662,10 @@ __device__ __forceinline__ void sp_flow_column(const FlowCtl &ctl, const SpFlow 
     const SpFlowIn<CELLS> x = sp_flow_poll<CELLS>(ctl, t, col, i, f);
     const FlowItem it = i;
     const bool more = left != 0;
+    sp_flow_store<CELLS>(t, col, it, x);
     i = q.n ? flow_item(q) : i;  // (past the end: the same block again)
     f = sp_flow_fetch<CELLS>(t.g, i.net - n_pi);
     left = q.n;
-    sp_flow_store<CELLS>(t, col, it, x);
     if (q.n) q = flow_next<1>(k, q);
     return more;
   };
@@ -2673,7 +2677,7 @@ template <bool CELLS>
 __global__ __launch_bounds__(kFlowThreads) void k_sp_flow(FlowCtl ctl, SpFlow t) {
   const FlowSeat st = flow_join(ctl);
   if (st.members == 0) return;
-  const FlowWalk k = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi);
+  const FlowWalk k = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl.shifts);
   for (int32_t i = 0; i < kFlowSlots; ++i) {
     const int32_t col = flow_claim(ctl, st, i, t.B);
     if (col < 0) return;
@@ -2737,7 +2741,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_sp_flow_multi(FlowCtl ctl,
     if (job < 0) return;
     const int32_t k = seg_of_job(segs, n_segs, job);
     const SpFlow t = global_view(segs[k].t);
-    const FlowWalk w = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi);
+    const FlowWalk w = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl.shifts);
     if (t.depth > 0) sp_flow_column<CELLS>(ctl, t, w, job - segs[k].job0);
   }
 }
@@ -2790,51 +2794,78 @@ __device__ __forceinline__ BwdFlowFetch<N> bwd_flow_fetch(const BwdFlow &t, cons
   return f;
 }
 
-// The eight entries from e on, in two 16-byte loads past the L1 (entries
-// beyond the array read as zero), until none of the first m (any m <= 8, or
-// more for all) is armed; then their sum in entry order, as strand_fold.
+// The K strands of eight entries from e on, in 16-byte loads past the L1, until
+// none is armed; then the sum of the first m entries' strand sums in order, as
+// strand_fold (any m <= 8 K, or more for all).  A strand beyond m reads
+// nothing and entries beyond the array read as zero; the others' entries
+// belong to later nets, of this level or a deeper one, so that waiting for them
+// too, which takes half an instruction an entry in place of three, waits for
+// no net that waits for this one.
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 constexpr int kBufferSc1 = 16;  // cache policy of a buffer load: agent scope
-__device__ __forceinline__ float flow_strand(const FlowCtl &ctl, const BwdFlowCol &u, uint32_t e,
-                                             int32_t m, int32_t &ok) {
-  float v[kStrand];
+constexpr uint32_t kBeyond = ~15u;  // an offset past the end of every buffer
+template <int K>
+__device__ __forceinline__ float flow_strands(const FlowCtl &ctl, const BwdFlowCol &u, uint32_t e,
+                                              int32_t m, int32_t &ok) {
+  float v[K][kStrand];
   uint32_t polls = 0;
   for (;;) {
-    const u4 lo = __builtin_amdgcn_raw_buffer_load_b128(u.contrib_rsrc, (int)(4 * e), 0, kBufferSc1);
-    const u4 hi =
-        __builtin_amdgcn_raw_buffer_load_b128(u.contrib_rsrc, (int)(4 * e + 16), 0, kBufferSc1);
+    u4 w[K][2];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t at = 4 * e + 32u * k + 16u * h;
+        w[k][h] = __builtin_amdgcn_raw_buffer_load_b128(
+            u.contrib_rsrc, (int)(k == 0 || kStrand * k < m ? at : kBeyond), 0, kBufferSc1);
+      }
     asm volatile("" ::: "memory");  // each round loads again
     uint32_t worst = 0;
 #pragma unroll
-    for (int i = 0; i < kStrand; ++i) {
-      const uint32_t b = i < m ? (i < 4 ? lo[i] : hi[i - 4]) : 0u;
-      v[i] = __uint_as_float(b);
-      worst = max(worst, b);  // kArmed is the largest
-    }
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int i = 0; i < kStrand; ++i) {
+        const uint32_t b = w[k][i / 4][i % 4];
+        v[k][i] = __uint_as_float(b);
+        worst = max(worst, b);  // kArmed is the largest
+      }
     if (worst != kArmed) break;
     if (!flow_again(ctl, kFlowStop, polls)) {
       ok = 0;
       break;
     }
   }
-  return strand_fold(v, m);
+  // (x + -0 is x, bit for bit: an entry or a strand that is not there)
+  float acc = 0.0f;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    float sum = k == 0 || kStrand * k < m ? v[k][0] : -0.0f;
+#pragma unroll
+    for (int i = 1; i < kStrand; ++i) sum += kStrand * k + i < m ? v[k][i] : -0.0f;
+    acc = k == 0 ? sum : acc + sum;
+  }
+  return acc;
 }
 
 // The canonical sum of a net's contributions (strands of kStrand, their sums
-// in order).  Lane by lane while every net of the wave has at most
-// kFlowSerial entries left; the longer ranges (one net in a thousand) take
-// the whole wave, one strand per lane.  Every lane of the wave calls it.
-constexpr int32_t kFlowSerial = 32;
+// in order).  Lane by lane up to kFlowSerial entries, all of them polled in
+// one round (a strand after another, a wave took as many rounds as its
+// longest net has strands: reverse sweep of 1M gates 231 us against 222); the
+// longer ranges (one net in a thousand) take the whole wave, one strand per
+// lane.  Every lane of the wave calls it.
+constexpr int32_t kFlowSerial = 4 * kStrand;
 __device__ __forceinline__ float flow_pull(const FlowCtl &ctl, const BwdFlowCol &u, uint32_t e0,
                                            int32_t n, int lane, int32_t &ok) {
   float acc = 0.0f;
   const bool heavy = n > kFlowSerial;
   const int32_t mine = heavy ? 0 : n;
-  for (int32_t s = 0; __ballot(s < mine); s += kStrand)
-    if (s < mine) {
-      const float sum = flow_strand(ctl, u, e0 + (uint32_t)s, mine - s, ok);
-      acc = s == 0 ? sum : acc + sum;
-    }
+  if (__ballot(mine > 2 * kStrand)) {
+    if (mine > 0) acc = flow_strands<4>(ctl, u, e0, mine, ok);
+  } else if (__ballot(mine > kStrand)) {
+    if (mine > 0) acc = flow_strands<2>(ctl, u, e0, mine, ok);
+  } else if (mine > 0) {
+    acc = flow_strands<1>(ctl, u, e0, mine, ok);
+  }
   for (uint64_t hh = __ballot(heavy); hh; hh &= hh - 1) {
     const int h = __builtin_ctzll(hh);
     const uint32_t h0 = (uint32_t)__builtin_amdgcn_readlane((int)e0, h);
@@ -2844,7 +2875,8 @@ __device__ __forceinline__ float flow_pull(const FlowCtl &ctl, const BwdFlowCol 
     for (int32_t base = 0; base < strands; base += 64) {
       const int32_t j = base + lane;
       float v = 0.0f;
-      if (j < strands) v = flow_strand(ctl, u, h0 + (uint32_t)(j * kStrand), hn - j * kStrand, ok);
+      if (j < strands)
+        v = flow_strands<1>(ctl, u, h0 + (uint32_t)(j * kStrand), hn - j * kStrand, ok);
       const int32_t vb = __float_as_int(v), m = min(64, strands - base);
       for (int32_t t = 0; t < m; ++t) {
         const float x = __int_as_float(__builtin_amdgcn_readlane(vb, t));
@@ -2912,11 +2944,11 @@ __device__ __forceinline__ void bwd_flow_column(const FlowCtl &ctl, const BwdFlo
     const bool gate = gate_, more = left != 0;
     const FlowItem it = i;
     const Fetch f = fetched;
+    bwd_flow_store<N>(t, u, gate, ok, it, f, pulled);
     gate_ = q.n ? q.l > 0 : gate_;
     i = q.n ? flow_item(q) : i;  // (past the end: the same block again)
     fetched = bwd_flow_fetch<N>(t, u, i);
     left = q.n;
-    bwd_flow_store<N>(t, u, gate, ok, it, f, pulled);
     if (q.n) q = flow_next<-1>(k, q);
     return more;
   };
@@ -2928,7 +2960,7 @@ template <bool CELLS>
 __global__ __launch_bounds__(kFlowThreads) void k_bwd_flow(FlowCtl ctl, BwdFlow t) {
   const FlowSeat st = flow_join(ctl);
   if (st.members == 0) return;
-  const FlowWalk k = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi);
+  const FlowWalk k = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl.shifts);
   for (int32_t i = 0; i < kFlowSlots; ++i) {
     const int32_t c = flow_claim(ctl, st, i, t.a.C);
     if (c < 0) return;
@@ -2946,7 +2978,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_bwd_flow_multi(
     if (job < 0) return;
     const int32_t k = seg_of_job(segs, n_segs, job);
     const BwdFlow t = global_view(segs[k].t);
-    const FlowWalk w = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi);
+    const FlowWalk w = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl.shifts);
     bwd_flow_column<kFlowPins<CELLS>>(ctl, t, w, job - segs[k].job0);
   }
 }
@@ -4052,7 +4084,17 @@ hipError_t launch_bwd_persistent(const GraphView &g, const BwdArgs &a, const int
 // of their own while the waves stay resident together, and queue after that.
 // Blocks go to the XCDs in turn.
 constexpr int64_t kFlowWavesPerCu = 16;
-static void flow_shape(FlowCtl *ctl, int64_t widest, int32_t C, unsigned *grid, unsigned *threads) {
+// The waves of two shifts take the levels in turn: a wave alone on its SIMD is
+// bound by its instructions (a turn of the reverse sweep has some 400), and of
+// these only a poll that succeeds, the sum and the stores are on the way from
+// level to level; with one shift the next block's addresses and fetch were
+// too.  Reverse sweep, one column, us, by shifts 1 / 2 / 4: 2K gates 24 / 21 /
+// 24, 117K 78 / 64 / 73, 1M 209 / 202 / -; a whole pass with eight shifts is
+// slower than with one.  The SP sweep gains 2 us, and with library cells
+// loses (300K gates 274 / 292): one shift there.
+constexpr int32_t kFlowShifts = 2;
+static void flow_shape(FlowCtl *ctl, int64_t widest, int32_t C, int32_t shifts, unsigned *grid,
+                       unsigned *threads) {
   const int64_t cus = std::max<int64_t>(1, ctl->n_cu / kFlowDies);
   const int64_t waves = std::max<int64_t>(1, (widest + 63) / 64);
   int64_t m = std::min(waves, cus);
@@ -4063,6 +4105,10 @@ static void flow_shape(FlowCtl *ctl, int64_t widest, int32_t C, unsigned *grid, 
   }
   const int64_t fit = std::max<int64_t>(1, cus * kFlowWavesPerCu / (m * wpb));
   const int64_t teams = std::min<int64_t>({fit, kFlowTeams, (C + kFlowDies - 1) / kFlowDies});
+  if (m * wpb * shifts * teams > cus * kFlowWavesPerCu) shifts = 1;
+  if (wpb * shifts <= kFlowThreads / 64) wpb *= shifts;
+  else m *= shifts;
+  ctl->shifts = shifts;
   ctl->expected = (uint32_t)m;
   *grid = (unsigned)(m * kFlowDies * teams);
   *threads = (unsigned)(64 * wpb);
@@ -4089,7 +4135,7 @@ hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl c
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   unsigned grid, threads;
-  flow_shape(&ctl, widest, t.B, &grid, &threads);
+  flow_shape(&ctl, widest, t.B, cells ? 1 : kFlowShifts, &grid, &threads);
   if (cells)
     k_sp_flow<true><<<grid, threads, 0, s>>>(ctl, t);
   else
@@ -4111,7 +4157,7 @@ hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   unsigned grid, threads;
-  flow_shape(&ctl, widest, t.a.C, &grid, &threads);
+  flow_shape(&ctl, widest, t.a.C, kFlowShifts, &grid, &threads);
   if (cells)
     k_bwd_flow<true><<<grid, threads, 0, s>>>(ctl, t);
   else
@@ -4128,7 +4174,7 @@ hipError_t launch_sp_flow_multi(const SpFlowSeg *segs, int32_t n_segs, int32_t j
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   unsigned grid, threads;
-  flow_shape(&ctl, widest, jobs, &grid, &threads);
+  flow_shape(&ctl, widest, jobs, cells ? 1 : kFlowShifts, &grid, &threads);
   if (cells)
     k_sp_flow_multi<true><<<grid, threads, 0, s>>>(ctl, segs, n_segs, jobs);
   else
@@ -4148,7 +4194,7 @@ hipError_t launch_bwd_flow_multi(const BwdFlowSeg *segs, int32_t n_segs, int32_t
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   unsigned grid, threads;
-  flow_shape(&ctl, widest, jobs, &grid, &threads);
+  flow_shape(&ctl, widest, jobs, kFlowShifts, &grid, &threads);
   if (cells)
     k_bwd_flow_multi<true><<<grid, threads, 0, s>>>(ctl, segs, n_segs, jobs);
   else
