@@ -557,6 +557,60 @@ __global__ __launch_bounds__(kWideBlock) void k_sp_level_x2(GraphView g, SpLevel
   reinterpret_cast<f2 *>(lv.sp)[(int64_t)(g.n_pi + gi) * B2 + b / 2] = f2{r0, r1};
 }
 
+// A column of a lane's four.
+__device__ __forceinline__ float quad_elem(const float4 &v, int k) {
+  return k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w;
+}
+// f(integral_constant<OP>) of the fixed cell op.
+template <class F>
+__device__ __forceinline__ void with_cell(int op, const F &f) {
+  switch (op) {
+#define DP_CELL_CASE(OP) case OP: f(std::integral_constant<int, OP>{}); break
+    DP_CELL_CASE(INV);
+    DP_CELL_CASE(BUF);
+    DP_CELL_CASE(AND2);
+    DP_CELL_CASE(OR2);
+    DP_CELL_CASE(NAND2);
+    DP_CELL_CASE(NOR2);
+    DP_CELL_CASE(XOR2);
+    DP_CELL_CASE(AOI21);
+#undef DP_CELL_CASE
+    default: f(std::integral_constant<int, MUX2>{}); break;
+  }
+}
+// And four columns a lane, from kQuadItems (gate, column) pairs of a level on,
+// where there are waves enough all the same.  Forward and reverse, one column
+// or two a lane against four, us: 1M gates x 100 levels, 32 columns (320K
+// pairs a level) 914 / 984, 64 columns 1275 / 1197, 128 columns 2101 / 1618;
+// 117K gates x 60 levels, 128 columns (250K pairs) 450 / 492, 256 columns 675 /
+// 622.
+constexpr int64_t kQuadItems = 400000;
+__global__ __launch_bounds__(kWideBlock) void k_sp_level_x4(GraphView g, SpLevel lv) {
+  const uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t quads = (uint32_t)lv.B / 4;
+  const uint32_t gl = idx / quads;
+  if (gl >= (uint32_t)lv.n) return;
+  const int32_t b = 4 * (int32_t)(idx - gl * quads), gi = lv.g0 + (int32_t)gl;
+  const int op = g.op[gi];
+  const int32_t i0 = g.in[gi], i1 = pin_row(g.in, g, 1)[gi], i2 = pin_row(g.in, g, 2)[gi];
+  gathers_done(op, i0, i1, i2);
+  const auto row = [&](int32_t r) {
+    return reinterpret_cast<float4 *>(lv.sp + (int64_t)r * lv.B + b);
+  };
+  const int k = arity_of(op);
+  const float4 x0 = *row(i0), x1 = *row(k > 1 ? i1 : i0), x2 = *row(k > 2 ? i2 : i0);
+  const f2 z = f2{0.0f, 1.0f};
+  float r[4];
+  with_cell(op, [&](auto cell) {
+    constexpr int OP = decltype(cell)::value;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      r[j] = settle(sp_rule(OP, sp_load(quad_elem(x0, j)), kArity<OP> > 1 ? sp_load(quad_elem(x1, j)) : z,
+                            kArity<OP> > 2 ? sp_load(quad_elem(x2, j)) : z));
+  });
+  *row(g.n_pi + gi) = make_float4(r[0], r[1], r[2], r[3]);
+}
+
 // ---------------------------------------------------------------- simulation
 // Count ones / toggles of one word pair computed by this lane.  `prev` is the
 // word before the pair's first word.
@@ -1856,6 +1910,91 @@ __global__ __launch_bounds__(kWideBlock) void k_bwd_level(GraphView g, BwdArgs a
   }
   bwd_item<CELLS, WIDE, UNI>(g, a, g0, n, (blockIdx.x - heavy_blocks) * blockDim.x + threadIdx.x,
                              threadIdx.x & 63, n_heavy > 0);
+}
+
+// A reverse level of many columns, four columns a lane (a multiple of four
+// columns, each its own SP column): a level is bound by its instructions, of
+// which a lane's structure loads and addresses are most, and four columns
+// share them and move 16 bytes a load (from kQuadItems on).  A level of 10K
+// gates x 64 columns 8.3 -> 7.7 us, x 128 14 -> 10.
+// The sum is the canonical one: an entry that is not there adds -0, which
+// changes no bit.
+__global__ __launch_bounds__(kWideBlock) void k_bwd_quad(GraphView g, BwdArgs a, int32_t g0,
+                                                          int32_t n, const int32_t *heavy,
+                                                          int32_t n_heavy, uint32_t heavy_blocks) {
+  if (blockIdx.x < heavy_blocks) {
+    bwd_heavy(g, a, heavy, blockIdx.x);
+    return;
+  }
+  const uint32_t idx = (blockIdx.x - heavy_blocks) * blockDim.x + threadIdx.x;
+  const uint32_t quads = (uint32_t)a.C / 4;
+  const uint32_t gl = idx / quads;
+  if (gl >= (uint32_t)n) return;
+  const int32_t c = 4 * (int32_t)(idx - gl * quads), gi = g0 + (int32_t)gl, out = g.n_pi + gi;
+  const auto row = [&](const float *p, int32_t r) {
+    return *reinterpret_cast<const float4 *>(p + (int64_t)r * a.C + c);
+  };
+  const int32_t e0 = g.rev_ptr[out], e1 = g.rev_ptr[out + 1];
+  const int op = g.op[gi];
+  const int32_t i0 = g.in[gi], i1 = pin_row(g.in, g, 1)[gi], i2 = pin_row(g.in, g, 2)[gi];
+  const int32_t s0 = g.slot[gi], s1 = pin_row(g.slot, g, 1)[gi], s2 = pin_row(g.slot, g, 2)[gi];
+  const float4 own = row(a.sp, out);
+  float4 beta = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+  if (a.beta) {
+    if (a.beta_shared) {
+      const float x = a.beta[out];
+      beta = make_float4(x, x, x, x);
+    } else {
+      beta = row(a.beta, out);
+    }
+  }
+  const float cap = a.cap[out];
+  gathers_done(op, e0, e1, i0, i1, i2, s0, s1, s2);
+  if (n_heavy > 0 && e1 - e0 > kHeavyPull) return;
+  const float4 r0 = row(a.sp, i0), r1 = row(a.sp, i1), r2 = row(a.sp, i2);
+  const int32_t cnt = e1 - e0, last = max(e1 - 1, 0);
+  float acc[4], sum[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) acc[k] = sum[k] = -0.0f;
+  for (int32_t s = 0; __any(s < cnt); s += 4) {  // half a strand at a time
+    float4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = row(a.contrib, min(e0 + s + i, last));
+    if (s % kStrand == 0) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        acc[k] += sum[k];
+        sum[k] = -0.0f;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) sum[k] += s + i < cnt ? quad_elem(v[i], k) : -0.0f;
+  }
+  float lam[4], d[3][4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float pulled = cnt > 0 ? acc[k] + sum[k] : 0.0f, bk = quad_elem(beta, k);
+    lam[k] = seed_of(a, out, c + k, c + k, sp_load(quad_elem(own, k)), bk, cap) + pulled;
+    if (a.ste) lam[k] *= bk;
+    if (a.lam) a.lam[(int64_t)(c + k) * (a.n_pi + a.G) + out] = lam[k];
+  }
+  const f2 z = f2{0.0f, 1.0f};
+  with_cell(op, [&](auto cell) {
+    constexpr int OP = decltype(cell)::value;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      sp_partials(OP, sp_load(quad_elem(r0, k)), kArity<OP> > 1 ? sp_load(quad_elem(r1, k)) : z,
+                  kArity<OP> > 2 ? sp_load(quad_elem(r2, k)) : z, d[0][k], d[1][k], d[2][k]);
+  });
+  const int arity = arity_of(op);
+  const int32_t slot[3] = {s0, s1, s2};
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    if (j < arity)
+      *reinterpret_cast<float4 *>(a.contrib + (int64_t)slot[j] * a.C + c) =
+          make_float4(lam[0] * d[j][0], lam[1] * d[j][1], lam[2] * d[j][2], lam[3] * d[j][3]);
 }
 
 // skip_heavy: PIs with more than kHeavyPull fan-out entries are left to the
@@ -3747,6 +3886,8 @@ hipError_t launch_sp_level(const GraphView &g, const SpLevel &lv, bool cells, hi
   if (n >= (1ll << 31)) return hipErrorInvalidValue;
   if (cells)
     k_sp_cells<<<blocks_for(n), kBlock, 0, s>>>(g, lv);
+  else if (lv.B % 4 == 0 && n >= kQuadItems)
+    k_sp_level_x4<<<level_grid(n / 4), level_block(n / 4), 0, s>>>(g, lv);
   else if (lv.B % 2 == 0)
     k_sp_level_x2<<<level_grid(n / 2), level_block(n / 2), 0, s>>>(g, lv);
   else
@@ -3949,7 +4090,10 @@ hipError_t launch_bwd_level(const GraphView &g, const BwdArgs &a, int32_t g0, in
     const int64_t hb = (int64_t)n_heavy * ((a.C + 63) / 64);
     const int64_t blocks = hb + blocks_for(items);
     if (blocks > kMaxBlocks) return hipErrorInvalidValue;
-    if (a.C % 64 == 0)  // one gate per wave
+    if (a.C % 4 == 0 && a.C == a.B && a.cdiv == 1 && items >= kQuadItems)
+      k_bwd_quad<<<(unsigned)(hb + blocks_for(items / 4)), kWideBlock, 0, s>>>(
+          g, a, g0, n, heavy, n_heavy, (uint32_t)hb);
+    else if (a.C % 64 == 0)  // one gate per wave
       k_bwd_level<false, true, true><<<(unsigned)blocks, kWideBlock, 0, s>>>(
           g, a, g0, n, heavy, n_heavy, (uint32_t)hb);
     else
