@@ -825,9 +825,21 @@ uint64_t graph_key(const dp_eval *ev, const ChunkPlan *pl) {
   return k;
 }
 
+// Append a device copy to a list, which goes out when it is full.
+dp_status list_copy(dp::CopyList *l, const float *src, float *dst, int64_t count, hipStream_t s) {
+  if (l->add(src, dst, count)) return DP_OK;
+  DP_HIP_TRY(dp::launch_copies(*l, s));
+  *l = dp::CopyList{};
+  if (l->add(src, dst, count)) return DP_OK;
+  DP_HIP_TRY(hipMemcpyAsync(dst, src, (size_t)count * sizeof(float), hipMemcpyDeviceToDevice, s));
+  return DP_OK;
+}
+
 // Copy the last forward's results out (caller numbering), on the eval's
-// stream; host outputs are complete on return.
-dp_status export_forward(dp_eval *ev, const dp_fwd_out *out, const ChunkPlan *pl) {
+// stream; host outputs are complete on return.  copies: where not null, takes
+// the device copy of the powers instead.
+dp_status export_forward(dp_eval *ev, const dp_fwd_out *out, const ChunkPlan *pl,
+                         dp::CopyList *copies = nullptr) {
   const dp_design *d = ev->d;
   hipStream_t s = ev->stream();
   OutMap om{ev, out->on_device};
@@ -852,8 +864,10 @@ dp_status export_forward(dp_eval *ev, const dp_fwd_out *out, const ChunkPlan *pl
   if (ea.o_sp || ea.o_tr || ea.o_sp_acc || ea.o_tr_acc || ea.o_beta || ea.o_tr_hyb || ea.o_ones ||
       ea.o_tog)
     DP_HIP_TRY(dp::launch_export(ea, s));
-  if (out->power) {
-    const size_t bytes = (size_t)ev->B * s_prime(ev) * sizeof(float);
+  const size_t bytes = (size_t)ev->B * s_prime(ev) * sizeof(float);
+  if (out->power && out->on_device && copies) {
+    DP_TRY(list_copy(copies, ev->power.as<float>(), out->power, (int64_t)ev->B * s_prime(ev), s));
+  } else if (out->power) {
     DP_HIP_TRY(hipMemcpyAsync(out->power, ev->power.ptr, bytes,
                               out->on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
   }
@@ -2401,21 +2415,25 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
     DP_TRY(enqueue_group(g, s, backward != 0, plans, true, false));
   }
   bool host_out = false;
+  dp::CopyList copies{};
   for (size_t i = 0; i < n; ++i) {
     dp_eval *ev = g->evs[i];
     ev->fwd_version = ev->inputs_version;
     if (outs) {
-      DP_TRY(export_forward(ev, &outs[i], hybrid(ev) ? &plans[i] : nullptr));
+      DP_TRY(export_forward(ev, &outs[i], hybrid(ev) ? &plans[i] : nullptr, &copies));
       host_out = host_out || !outs[i].on_device;
     }
     if (backward && dpower_dpi && dpower_dpi[i] && ev->d->n_pi > 0) {
-      DP_HIP_TRY(hipMemcpyAsync(dpower_dpi[i], ev->pi_out.ptr,
-                                (size_t)ev->B * ev->d->n_pi * sizeof(float),
-                                on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
-                                ev->stream()));
+      const int64_t count = (int64_t)ev->B * ev->d->n_pi;
+      if (on_device)
+        DP_TRY(list_copy(&copies, ev->pi_out.as<float>(), dpower_dpi[i], count, s));
+      else
+        DP_HIP_TRY(hipMemcpyAsync(dpower_dpi[i], ev->pi_out.ptr, count * sizeof(float),
+                                  hipMemcpyDeviceToHost, ev->stream()));
       host_out = host_out || !on_device;
     }
   }
+  DP_HIP_TRY(dp::launch_copies(copies, s));
   if (host_out) {
     DP_HIP_TRY(hipStreamSynchronize(s));
     for (int32_t i : g->merged) DP_TRY(barrier_status(g->evs[i]));

@@ -425,6 +425,17 @@ __device__ __forceinline__ void lane_copy(const float *src, float *dst, int64_t 
     }
   }
 }
+constexpr int32_t kCopyPer = 4;  // floats a thread copies
+__global__ __launch_bounds__(kBlock) void k_copies(CopyList l) {
+  int32_t k = 0;
+  while (k + 1 < l.n && l.c[k + 1].block0 <= blockIdx.x) ++k;
+  const uint32_t i0 = (blockIdx.x - l.c[k].block0) * (kBlock * kCopyPer) + threadIdx.x;
+#pragma unroll
+  for (int j = 0; j < kCopyPer; ++j) {
+    const uint32_t i = i0 + j * kBlock;
+    if (i < l.c[k].n) l.c[k].dst[i] = l.c[k].src[i];
+  }
+}
 __global__ __launch_bounds__(kBlock) void k_lanes_stage(const LaneSeg *__restrict__ segs, int32_t n_segs) {
   const LaneSeg l = segs[seg_at(segs, n_segs, &LaneSeg::stage0)];
   const uint32_t block = blockIdx.x - l.stage0;
@@ -3792,6 +3803,16 @@ hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, float *
   return hipGetLastError();
 }
 
+bool CopyList::add(const float *src, float *dst, int64_t count) {
+  if (n == kMax || count > (1ll << 30)) return false;
+  c[n++] = Item{src, dst, (uint32_t)count, blocks};
+  blocks += (uint32_t)((count + kBlock * kCopyPer - 1) / (kBlock * kCopyPer));
+  return true;
+}
+hipError_t launch_copies(const CopyList &l, hipStream_t s) {
+  if (l.blocks) k_copies<<<l.blocks, kBlock, 0, s>>>(l);
+  return hipGetLastError();
+}
 void lane_seg_blocks(LaneSeg &l, uint32_t &stage, uint32_t &import, uint32_t &out) {
   const int64_t sizes = l.size ? (int64_t)l.B * l.G : 0;
   l.pi_blocks = blocks_for((int64_t)l.n_pi * l.B);

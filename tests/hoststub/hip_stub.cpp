@@ -519,6 +519,20 @@ hipError_t launch_power_multi(const PowerSeg *segs, int32_t n_segs, uint32_t blo
   if (block != blocks || col != cols) fatal("power segments' totals");
   return hipSuccess;
 }
+bool CopyList::add(const float *src, float *dst, int64_t count) {
+  if (n == kMax) return false;
+  c[n++] = Item{src, dst, (uint32_t)count, blocks++};
+  return true;
+}
+hipError_t launch_copies(const CopyList &l, hipStream_t stream_) {
+  Scope sc_(stream_);
+  for (int32_t k = 0; k < l.n; ++k) {
+    if (l.c[k].block0 != (uint32_t)k) fatal("copies out of order");
+    rd(l.c[k].src, l.c[k].n);
+    std::copy(l.c[k].src, l.c[k].src + l.c[k].n, l.c[k].dst);
+  }
+  return hipSuccess;
+}
 void lane_seg_blocks(LaneSeg &l, uint32_t &stage, uint32_t &import, uint32_t &out) {
   l.pi_blocks = 1;
   stage = l.size ? 2 : 1;

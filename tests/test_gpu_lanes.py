@@ -70,3 +70,26 @@ def test_group_power_is_each_evals_own(setup, cols, S):
     for _ in range(3):
         for r, w in zip(group.run(("power",)), want):
             np.testing.assert_array_equal(r["power"], w)
+
+
+def test_group_outputs_on_the_device(setup):
+    """More outputs than one list of copies holds (17 evals, power and
+    gradients), the arrays unaligned and of odd lengths."""
+    ctx, nls, caps = setup
+    say("group outputs on the device")
+    torch = pytest.importorskip("torch")
+    ctx = api.Context.for_torch(0)
+    evs = []
+    for k in range(17):
+        nl, cap = nls[k % 3], caps[k % 3]
+        ev = api.Eval(api.Design(ctx, nl), 1 + k % 4)
+        ev.set_pi_prob(synth.pi_probs(nl.n_pi, 90 + k, batch=1 + k % 4))
+        ev.set_caps(cap)
+        evs.append(ev)
+    group = api.Group(ctx, evs)
+    want = group.run(("power",), backward=True)
+    got = group.run(("power",), backward=True, device=True)
+    torch.cuda.synchronize()
+    for k, (r, w) in enumerate(zip(got, want)):
+        for f in ("power", "dpi"):
+            np.testing.assert_array_equal(r[f].cpu().numpy(), w[f], err_msg=f"eval {k}, {f}")
