@@ -389,6 +389,17 @@ struct FlowCtl {
   int32_t n_cu;       // compute units of the device
   int32_t shifts;     // levels in which the waves take turns (set by the launcher)
 };
+// The first block of level l that wave w of a team of `waves` takes, the next
+// ones `waves` further each: over all waves every block once, whatever the
+// team's size (it may close with fewer members than it was launched with), and
+// from `shift` waves on by turns of the level (shifts: 1 or 2).
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline int32_t flow_first_block(int32_t w, int32_t waves, int32_t shifts, int32_t l) {
+  const int32_t b = w - (l & (shifts - 1)) * (waves / shifts);
+  return b < 0 ? b + waves : b;
+}
 // Whether a sweep of C columns is one for these kernels: within their 32-bit
 // offsets and tables, and few enough (net, column) pairs that its levels are
 // bound by latency.  Forward / reverse sweep by level launches against

@@ -2506,9 +2506,9 @@ __global__ __launch_bounds__(kBlock) void k_bwd_persistent(GraphView g, BwdArgs 
 // poll through the one L2 that its CUs share in 180 ns (measured; across XCDs
 // 520 ns, and only with stores that write through).  So a column never leaves
 // its XCD; further columns go to other teams.  SP and reverse sweep of one
-// column, in us: 2K gates 36 and 72 by level launches, 17 and 25 (with 2 and 5
-// for arming) here; 117K gates 132 and 235 against 47 and 86 (2 and 6); 1M
-// gates 234 and 439 against 117 and 229 (5 and 16).
+// column, in us: 2K gates 36 and 72 by level launches, 17 and 21 (with 2 and 5
+// for arming) here; 117K gates 132 and 235 against 47 and 64 (2 and 6); 1M
+// gates 234 and 439 against 113 and 202 (5 and 15).
 //
 // Membership: the workgroups of a team register; the first (the leader)
 // waits until the expected number has come, or briefly, and closes the list;
@@ -2633,9 +2633,8 @@ __device__ __forceinline__ int32_t flow_claim(const FlowCtl &ctl, const FlowSeat
 __shared__ int32_t flow_lv[kFlowLevels];
 
 struct FlowWalk {
-  int32_t w64, W64;   // 64 times this wave's index, 64 times the number of waves
-  int32_t n_pi, depth;
-  int32_t shifts, shift;  // less one: levels until the waves' order is the first again; its step
+  int32_t w, waves;  // this wave's index, the team's waves
+  int32_t n_pi, depth, shifts;
 };
 
 // A block of the walk: its first item is `base` of the n of level l, whose
@@ -2651,9 +2650,8 @@ __device__ __forceinline__ FlowWalk flow_walk(const FlowSeat &st, const int32_t 
     flow_lv[i] = level_ptr[i];
   __syncthreads();
   const int32_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int32_t all = (int32_t)(blockDim.x * st.members);
-  return FlowWalk{64 * (wave * (int32_t)st.members + (int32_t)st.rank), all, n_pi, depth,
-                  shifts - 1, all / shifts};
+  return FlowWalk{wave * (int32_t)st.members + (int32_t)st.rank,
+                  (int32_t)((blockDim.x >> 6) * st.members), n_pi, depth, shifts};
 }
 
 // The first block at or after `q` that has items, levels ascending (DIR 1,
@@ -2670,14 +2668,13 @@ __device__ __forceinline__ FlowBlock flow_settle(const FlowWalk &k, FlowBlock q)
     const int32_t b = __builtin_amdgcn_readfirstlane(flow_lv[q.l + 1]);
     q.net = q.l > 0 ? k.n_pi + a : 0;
     q.n = q.l > 0 ? b - a : k.n_pi;
-    q.base = k.w64 - (q.l & k.shifts) * k.shift;
-    if (q.base < 0) q.base += k.W64;
+    q.base = 64 * flow_first_block(k.w, k.waves, k.shifts, q.l);
   }
   return q;
 }
 template <int DIR>
 __device__ __forceinline__ FlowBlock flow_next(const FlowWalk &k, FlowBlock q) {
-  q.base += k.W64;
+  q.base += 64 * k.waves;
   return flow_settle<DIR>(k, q);
 }
 

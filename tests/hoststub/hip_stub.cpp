@@ -708,10 +708,26 @@ static void flow_levels_ok(const GraphView &g, const int32_t *level_ptr, int32_t
       if (!cells && g.op[i] >= kCellBase) fatal("library cell in a fixed-cell sweep");
   }
 }
+// Every block of a level is some wave's, once, in teams of every size.
+static void flow_blocks_ok() {
+  static bool done = false;
+  if (done) return;
+  done = true;
+  for (int32_t waves = 1; waves <= 520; ++waves)
+    for (int32_t shifts = 1; shifts <= 2; ++shifts)
+      for (int32_t l = 0; l < 3; ++l) {
+        std::vector<int> hit(waves, 0);
+        for (int32_t w = 0; w < waves; ++w) {
+          const int32_t b = flow_first_block(w, waves, shifts, l);
+          if (b < 0 || b >= waves || hit[b]++) fatal("a block of a dataflow level is lost");
+        }
+      }
+}
 hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl ctl,
                           hipStream_t stream_) {
   Scope sc_(stream_);
   flow_ctl_ok(ctl);
+  flow_blocks_ok();
   if (!flow_fits(t.g, t.depth, t.B, 0)) fatal("dataflow sweep out of its range");
   flow_levels_ok(t.g, t.level_ptr, t.depth, widest, cells);
   wr(t.sp, (int64_t)t.g.n_nets * t.B);
