@@ -4253,7 +4253,8 @@ constexpr int64_t kFlowWavesPerCu = 16;
 // too.  Reverse sweep, one column, us, by shifts 1 / 2 / 4: 2K gates 24 / 21 /
 // 24, 117K 78 / 64 / 73, 1M 209 / 202 / -; a whole pass with eight shifts is
 // slower than with one.  The SP sweep gains 2 us, and with library cells
-// loses (300K gates 274 / 292): one shift there.
+// loses (300K gates 274 / 292): one shift there, and where several teams fill
+// a CU's SIMDs (forward, 117K gates x 32 columns 114 / 146, 50K x 64 100 / 129).
 constexpr int32_t kFlowShifts = 2;
 static void flow_shape(FlowCtl *ctl, int64_t widest, int32_t C, int32_t shifts, unsigned *grid,
                        unsigned *threads) {
@@ -4267,7 +4268,9 @@ static void flow_shape(FlowCtl *ctl, int64_t widest, int32_t C, int32_t shifts, 
   }
   const int64_t fit = std::max<int64_t>(1, cus * kFlowWavesPerCu / (m * wpb));
   const int64_t teams = std::min<int64_t>({fit, kFlowTeams, (C + kFlowDies - 1) / kFlowDies});
-  if (m * wpb * shifts * teams > cus * kFlowWavesPerCu) shifts = 1;
+  // (with several teams a CU's SIMDs have a wave each already)
+  if (m * wpb * shifts * teams > cus * kFlowWavesPerCu || (teams > 2 && m * wpb * teams > 3 * cus))
+    shifts = 1;
   if (wpb * shifts <= kFlowThreads / 64) wpb *= shifts;
   else m *= shifts;
   ctl->shifts = shifts;
