@@ -546,6 +546,7 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
   const dp::GraphView g = view(d);
   const bool prof = ev->profiling;
   float *sp = ev->sp.as<float>();
+  const dp::SpFlow sweep{g, sp, d->level_dev.as<int32_t>(), ev->B, d->depth};
   if (!pl || pl->tile) {  // modeled (or frozen-beta) sweep: one span over all level launches
     double bytes = 0.0;
     for (int32_t l = 1; l <= d->depth; ++l) bytes += sp_level_bytes(d, l, ev->B);
@@ -553,11 +554,10 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
                  ev->schedule == DP_SCHED_PERSISTENT || flows(ev, ev->B)
                      ? 1
                      : sp_sweep_launches(d, ev->B));
-    if (flows(ev, ev->B)) {
-      const dp::FlowCtl ctl = flow_ctl(ev);
-      DP_HIP_TRY(dp::launch_sp_flow(
-          dp::SpFlow{g, sp, d->level_dev.as<int32_t>(), ev->B, d->depth}, d->max_level_width,
-          d->has_cell_gates, ctl, s));
+    if (pl && ev->B <= dp::kRideColumns) {  // the sweep rides with the tiles
+      DP_HIP_TRY(dp::launch_sp_arm(sweep, flow_ctl(ev), s));
+    } else if (flows(ev, ev->B)) {
+      DP_HIP_TRY(dp::launch_sp_flow(sweep, d->max_level_width, d->has_cell_gates, flow_ctl(ev), s));
     } else if (ev->schedule == DP_SCHED_PERSISTENT) {
       dp::SpLevel lv{sp, ev->B, 0, 0};
       dp::GridBarrier bar;
@@ -606,7 +606,8 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
                         pl->tile, pl->n_tiles, pl->n_bufs};
     dp::FlowCtl ctl = flow_ctl(ev);
     ctl.words += dp::kFlowWords;
-    DP_HIP_TRY(dp::launch_sim_flow(t, d->has_cell_gates, ctl, sp, ev->ones.as<uint32_t>(), ev->tog.as<uint32_t>(), s));
+    DP_HIP_TRY(dp::launch_sim_flow(t, sweep, d->max_level_width, d->has_cell_gates, ctl, flow_ctl(ev),
+                                   ev->ones.as<uint32_t>(), ev->tog.as<uint32_t>(), s));
   } else if (pl) {
     const size_t nb = (size_t)d->n_nets * ev->B;
     DP_HIP_TRY(dp::launch_fill_u32(ev->ones.as<uint32_t>(), (int64_t)nb, 0u, s));

@@ -388,6 +388,7 @@ struct FlowCtl {
   uint32_t expected;  // workgroups a team's leader waits for (set by the launcher)
   int32_t n_cu;       // compute units of the device
   int32_t shifts;     // levels in which the waves take turns (set by the launcher)
+  int32_t per_block;  // waves of a workgroup that take items (set by the launcher)
 };
 // The first block of level l that wave w of a team of `waves` takes, the next
 // ones `waves` further each: over all waves every block once, whatever the
@@ -460,6 +461,9 @@ hipError_t launch_bwd_flow_multi(const BwdFlowSeg *segs, int32_t n_segs, int32_t
                                  uint32_t blocks, int64_t widest, bool cells, FlowCtl ctl,
                                  hipStream_t s);
 // widest: gates of the widest level; cells: the design holds library cells.
+// Arms the slots of an SP sweep and clears its control words (launch_sp_flow
+// does so itself).
+hipError_t launch_sp_arm(const SpFlow &t, FlowCtl ctl, hipStream_t s);
 hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl ctl, hipStream_t s);
 // The reverse levels and then the PI adjoints; widest also covers the PIs.
 hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl ctl,
@@ -500,10 +504,18 @@ inline bool sim_fits(const GraphView &g, int32_t depth, int32_t B, int32_t pitch
 hipError_t launch_stim_words(const float *sp /* stored SP [n_pi][B] */, const int32_t *stream,
                              int32_t n_pi, int32_t B, int64_t T, uint64_t seed, uint64_t *out,
                              hipStream_t s);
-// ctl.words: [kSimWords].  Writes ones and tog [n_nets][B]; a simulation that
-// gives up leaves NaN in sp.
-hipError_t launch_sim_flow(const SimFlow &t, bool cells, FlowCtl ctl, float *sp, uint32_t *ones,
-                           uint32_t *tog, hipStream_t s);
+// Whether the SP sweep of the simulated columns goes out with the tiles: with
+// one or two columns it holds one or two XCDs' CUs, and the other XCDs' teams
+// take up the tiles (300K gates half library cells 1030 -> 785 us a pass, 117K
+// gates x 257 words 416 -> 365).  Five columns gain nothing (50K gates x 64
+// words: 140 us one after the other, 147 together).
+constexpr int32_t kRideColumns = 2;
+// The simulation, and with sp.B <= kRideColumns the SP sweep of the same columns
+// (armed by launch_sp_arm), as one launch.  ctl.words: [kSimWords].  Writes ones
+// and tog [n_nets][B]; a simulation that gives up leaves NaN in sp.sp.
+hipError_t launch_sim_flow(const SimFlow &t, const SpFlow &sp, int64_t widest, bool cells,
+                           FlowCtl ctl, FlowCtl sp_ctl, uint32_t *ones, uint32_t *tog,
+                           hipStream_t s);
 
 // dcap[ext n] = sum_{b,s} w[b][s] x[n][b] size_s(n) and dsize[s][ext g] =
 // sum_b w[b][s] x[out g][b] C_out g, with x = kappa beta TR_model

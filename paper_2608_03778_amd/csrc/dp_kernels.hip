@@ -2645,13 +2645,13 @@ struct FlowBlock {
 
 // Loads the level table into LDS; every thread calls it, before any claim.
 __device__ __forceinline__ FlowWalk flow_walk(const FlowSeat &st, const int32_t *level_ptr,
-                                              int32_t depth, int32_t n_pi, int32_t shifts) {
+                                              int32_t depth, int32_t n_pi, const FlowCtl &ctl) {
   for (int32_t i = (int32_t)threadIdx.x; i < depth + 2; i += (int32_t)blockDim.x)
     flow_lv[i] = level_ptr[i];
   __syncthreads();
   const int32_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   return FlowWalk{wave * (int32_t)st.members + (int32_t)st.rank,
-                  (int32_t)((blockDim.x >> 6) * st.members), n_pi, depth, shifts};
+                  ctl.per_block * (int32_t)st.members, n_pi, depth, ctl.shifts};
 }
 
 // The first block at or after `q` that has items, levels ascending (DIR 1,
@@ -2821,15 +2821,20 @@ __device__ __forceinline__ void sp_flow_column(const FlowCtl &ctl, const SpFlow 
 }
 
 template <bool CELLS>
-__global__ __launch_bounds__(kFlowThreads) void k_sp_flow(FlowCtl ctl, SpFlow t) {
+__device__ __forceinline__ void sp_flow_team(const FlowCtl &ctl, const SpFlow &t) {
   const FlowSeat st = flow_join(ctl);
   if (st.members == 0) return;
-  const FlowWalk k = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl.shifts);
+  const FlowWalk k = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl);
+  const bool takes = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) < ctl.per_block;
   for (int32_t i = 0; i < kFlowSlots; ++i) {
     const int32_t col = flow_claim(ctl, st, i, t.B);
     if (col < 0) return;
-    sp_flow_column<CELLS>(ctl, t, k, col);
+    if (takes) sp_flow_column<CELLS>(ctl, t, k, col);
   }
+}
+template <bool CELLS>
+__global__ __launch_bounds__(kFlowThreads) void k_sp_flow(FlowCtl ctl, SpFlow t) {
+  sp_flow_team<CELLS>(ctl, t);
 }
 
 // A pointer read from a table, as one to global memory (loads through it are
@@ -2888,7 +2893,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_sp_flow_multi(FlowCtl ctl,
     if (job < 0) return;
     const int32_t k = seg_of_job(segs, n_segs, job);
     const SpFlow t = global_view(segs[k].t);
-    const FlowWalk w = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl.shifts);
+    const FlowWalk w = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl);
     if (t.depth > 0) sp_flow_column<CELLS>(ctl, t, w, job - segs[k].job0);
   }
 }
@@ -3107,7 +3112,7 @@ template <bool CELLS>
 __global__ __launch_bounds__(kFlowThreads) void k_bwd_flow(FlowCtl ctl, BwdFlow t) {
   const FlowSeat st = flow_join(ctl);
   if (st.members == 0) return;
-  const FlowWalk k = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl.shifts);
+  const FlowWalk k = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl);
   for (int32_t i = 0; i < kFlowSlots; ++i) {
     const int32_t c = flow_claim(ctl, st, i, t.a.C);
     if (c < 0) return;
@@ -3125,7 +3130,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_bwd_flow_multi(
     if (job < 0) return;
     const int32_t k = seg_of_job(segs, n_segs, job);
     const BwdFlow t = global_view(segs[k].t);
-    const FlowWalk w = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl.shifts);
+    const FlowWalk w = flow_walk(st, t.level_ptr, t.depth, t.g.n_pi, ctl);
     bwd_flow_column<kFlowPins<CELLS>>(ctl, t, w, job - segs[k].job0);
   }
 }
@@ -3255,24 +3260,31 @@ struct SimSeat {
   uint32_t buf, rank, members;  // members == 0: not a member
 };
 
-__device__ __forceinline__ SimSeat sim_join(const FlowCtl &ctl, uint32_t n_bufs) {
+__device__ __forceinline__ SimSeat sim_join(const FlowCtl &ctl, uint32_t n_bufs, uint32_t block) {
   __shared__ SimSeat seat;
   if (threadIdx.x == 0) {
     uint32_t x;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
-    const uint32_t sub = min(blockIdx.x / kFlowDies / ctl.expected, (uint32_t)kSimTeams - 1);
+    const uint32_t sub = min(block / kFlowDies / ctl.expected, (uint32_t)kSimTeams - 1);
     uint32_t *reg = ctl.words + kSimReg + ((x & (kFlowXcds - 1)) * kSimTeams + sub) * 32;
     uint32_t *open = reg + 16;
     const uint32_t r = __hip_atomic_fetch_add(reg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint32_t v = 0;  // members | (buffer + 1) << 8
     if (r == 0) {
-      const uint32_t buf = __hip_atomic_fetch_add(ctl.words + kSimNextBuf, 1u, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT);
       const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
       while (flow_load(reg) < ctl.expected && __builtin_amdgcn_s_memrealtime() - t0 < kFlowJoinTicks) {
       }
-      const uint32_t n = __hip_atomic_fetch_or(reg, kFlowClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      v = min(n, (uint32_t)kSimMembers) | (buf + 1) << 8;
+      const uint32_t n = min(__hip_atomic_fetch_or(reg, kFlowClosed, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT),
+                             (uint32_t)kSimMembers);
+      // a team that is far from whole (its CUs are taken) would hold a tile for
+      // many times a whole team's time: it leaves its tiles to the others; an
+      // XCD's first team always works
+      uint32_t buf = ~0u - 1;
+      if (sub == 0 || 4 * n >= 3 * ctl.expected)
+        buf = __hip_atomic_fetch_add(ctl.words + kSimNextBuf, 1u, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+      v = n | min(buf + 1, 0xffffffu) << 8;
       __hip_atomic_store(open, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else if (!(r & kFlowClosed)) {
       uint32_t polls = 0;
@@ -3485,9 +3497,17 @@ __device__ __forceinline__ w2 sim_cell(const w2 (&x)[N], const SimFlowFetch<N ==
   }
 }
 
+// The first sp_blocks workgroups take the SP sweep of the same columns, which
+// has few waves and long waits, beside the tiles.  Registers for six waves a SIMD: two or three teams of tiles and
+// the sweep's.
 template <int LPG, bool CELLS>
-__global__ __launch_bounds__(kFlowThreads) void k_sim_flow(FlowCtl ctl, SimFlow t) {
-  const SimSeat st = sim_join(ctl, (uint32_t)t.n_bufs);
+__global__ __launch_bounds__(kFlowThreads, 6) void k_sim_flow(FlowCtl ctl, SimFlow t, FlowCtl sp_ctl,
+                                                              SpFlow sp, uint32_t sp_blocks) {
+  if (blockIdx.x < sp_blocks) {
+    sp_flow_team<CELLS>(sp_ctl, sp);
+    return;
+  }
+  const SimSeat st = sim_join(ctl, (uint32_t)t.n_bufs, blockIdx.x - sp_blocks);
   if (st.members == 0) return;
   for (int32_t i = (int32_t)threadIdx.x; i < t.depth + 2; i += (int32_t)blockDim.x)
     flow_lv[i] = t.level_ptr[i];
@@ -4277,6 +4297,7 @@ static void flow_shape(FlowCtl *ctl, int64_t widest, int32_t C, int32_t shifts, 
   ctl->expected = (uint32_t)m;
   *grid = (unsigned)(m * kFlowDies * teams);
   *threads = (unsigned)(64 * wpb);
+  ctl->per_block = (int32_t)wpb;
 }
 
 static int64_t fill_blocks(int64_t slots, bool clears) {
@@ -4292,12 +4313,15 @@ uint32_t flow_arm_blocks(const BwdFlow &t, bool clears, uint32_t *arm_blocks,
   return *arm_blocks + *seed_blocks + blocks_for((int64_t)t.g.G * t.a.B);
 }
 
-hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl ctl, hipStream_t s) {
-  if (t.depth <= 0 || t.B <= 0) return hipSuccess;
+hipError_t launch_sp_arm(const SpFlow &t, FlowCtl ctl, hipStream_t s) {
   if (!ctl.words || !ctl.report || !flow_fits(t.g, t.depth, t.B, 0)) return hipErrorInvalidValue;
   k_flow_arm<<<flow_arm_blocks(t, true), kBlock, 0, s>>>(
       reinterpret_cast<uint32_t *>(t.sp + (int64_t)t.g.n_pi * t.B), (int64_t)t.g.G * t.B, ctl.words);
-  hipError_t e = hipGetLastError();
+  return hipGetLastError();
+}
+hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl ctl, hipStream_t s) {
+  if (t.depth <= 0 || t.B <= 0) return hipSuccess;
+  hipError_t e = launch_sp_arm(t, ctl, s);
   if (e != hipSuccess) return e;
   unsigned grid, threads;
   flow_shape(&ctl, widest, t.B, cells ? 1 : kFlowShifts, &grid, &threads);
@@ -4383,11 +4407,13 @@ hipError_t launch_stim_words(const float *sp, const int32_t *stream, int32_t n_p
   return hipGetLastError();
 }
 
-hipError_t launch_sim_flow(const SimFlow &t, bool cells, FlowCtl ctl, float *sp, uint32_t *ones,
-                           uint32_t *tog, hipStream_t s) {
+hipError_t launch_sim_flow(const SimFlow &t, const SpFlow &sp, int64_t widest, bool cells,
+                           FlowCtl ctl, FlowCtl sp_ctl, uint32_t *ones, uint32_t *tog,
+                           hipStream_t s) {
   const int64_t nb = (int64_t)t.g.n_nets * t.B;
   if (nb <= 0 || t.T <= 0) return hipSuccess;
-  if (!ctl.words || !ctl.report || !sim_fits(t.g, t.depth, t.B, t.pitch, t.T) ||
+  if (!ctl.words || !ctl.report || !sp_ctl.words || !sp_ctl.report ||
+      !flow_fits(sp.g, sp.depth, sp.B, 0) || !sim_fits(t.g, t.depth, t.B, t.pitch, t.T) ||
       t.n_chunks != (t.T + t.pitch - 1) / t.pitch || t.n_bufs < 1 || t.n_bufs > kSimBufs)
     return hipErrorInvalidValue;
   k_fill_u32<<<blocks_for(kSimWords), kBlock, 0, s>>>(ctl.words, kSimWords, 0u);
@@ -4396,14 +4422,21 @@ hipError_t launch_sim_flow(const SimFlow &t, bool cells, FlowCtl ctl, float *sp,
   const int64_t cus = std::min<int64_t>(kSimMembers, std::max<int64_t>(1, ctl.n_cu / kFlowDies));
   ctl.expected = (uint32_t)cus;
   const unsigned grid = (unsigned)(cus * kFlowDies * ((t.n_bufs + kFlowDies - 1) / kFlowDies));
-  using K = void (*)(FlowCtl, SimFlow);
+  // the sweep's workgroups: one a CU at most, so that the tiles' teams fit beside
+  unsigned sp_blocks = 0, sp_threads;
+  const int64_t sweep_widest = std::min<int64_t>(widest, cus * kFlowThreads);
+  const bool ride = sp.B <= kRideColumns;
+  if (ride) flow_shape(&sp_ctl, sweep_widest, sp.B, cells ? 1 : kFlowShifts, &sp_blocks, &sp_threads);
+  if (ride && (int64_t)sp_ctl.expected > cus)
+    flow_shape(&sp_ctl, sweep_widest, sp.B, 1, &sp_blocks, &sp_threads);
+  using K = void (*)(FlowCtl, SimFlow, FlowCtl, SpFlow, uint32_t);
   K kern = cells ? k_sim_flow<32, true> : k_sim_flow<32, false>;
   if (t.pitch == 16) kern = cells ? k_sim_flow<8, true> : k_sim_flow<8, false>;
   if (t.pitch == 32) kern = cells ? k_sim_flow<16, true> : k_sim_flow<16, false>;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kFlowThreads), 0, s, ctl, t);
+  hipLaunchKernelGGL(kern, dim3(sp_blocks + grid), dim3(kFlowThreads), 0, s, ctl, t, sp_ctl, sp, sp_blocks);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_sim_counts<<<blocks_for(nb), kBlock, 0, s>>>(t, ctl.words + kSimStop, sp, ones, tog);
+  k_sim_counts<<<blocks_for(nb), kBlock, 0, s>>>(t, ctl.words + kSimStop, sp.sp, ones, tog);
   return hipGetLastError();
 }
 

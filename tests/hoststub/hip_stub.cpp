@@ -733,9 +733,18 @@ hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl c
   wr(t.sp, (int64_t)t.g.n_nets * t.B);
   return hipSuccess;
 }
-hipError_t launch_sim_flow(const SimFlow &t, bool, FlowCtl ctl, float *sp, uint32_t *ones,
-                           uint32_t *tog, hipStream_t stream_) {
+hipError_t launch_sp_arm(const SpFlow &t, FlowCtl ctl, hipStream_t stream_) {
   Scope sc_(stream_);
+  flow_ctl_ok(ctl);
+  wr(t.sp + (int64_t)t.g.n_pi * t.B, (int64_t)t.g.G * t.B);
+  return hipSuccess;
+}
+hipError_t launch_sim_flow(const SimFlow &t, const SpFlow &sweep, int64_t widest, bool cells,
+                           FlowCtl ctl, FlowCtl sp_ctl, uint32_t *ones, uint32_t *tog,
+                           hipStream_t stream_) {
+  if (sweep.B <= kRideColumns) launch_sp_flow(sweep, widest, cells, sp_ctl, stream_);
+  Scope sc_(stream_);
+  float *sp = sweep.sp;
   if (!sim_fits(t.g, t.depth, t.B, t.pitch, t.T) || t.n_bufs < 1 || t.n_bufs > kSimBufs ||
       t.n_chunks != (t.T + t.pitch - 1) / t.pitch || !ctl.report || ctl.n_cu < 1)
     fatal("word tiles out of their range");
