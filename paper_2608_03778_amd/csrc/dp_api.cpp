@@ -472,8 +472,7 @@ dp_status ensure_forward_buffers(dp_eval *ev, const ChunkPlan *pl) {
   if (ev->prm.mode == DP_HYBRID) DP_TRY(ev->beta.alloc(nb * sizeof(float)));
   const int32_t cols = ev->B * s_prime(ev);
   DP_TRY(ev->power_partial.alloc(
-      (size_t)dp::power_partial_doubles(d->n_nets, ev->B, ev->S, ev->paired_sizes) *
-      sizeof(double)));
+      (size_t)dp::power_scratch(d->n_nets, ev->B, ev->S, ev->paired_sizes) * sizeof(double)));
   DP_TRY(ev->power.alloc((size_t)cols * sizeof(float)));
   if (pl) {
     DP_TRY(ev->ones.alloc(nb * sizeof(uint32_t)));

@@ -179,8 +179,18 @@ struct PowerArgs {
   float *power;                     // [B][S'] (device)
 };
 int32_t power_chunks(int32_t n_nets);
-// Doubles of partial-sum scratch launch_power needs.
-int32_t power_partial_doubles(int32_t n_nets, int32_t B, int32_t S, int32_t paired);
+// Nets of a slab of the (b, s) contraction: about 256 slabs (see k_power_mfma).
+inline int32_t power_slab_nets(int32_t n_nets) {
+  const int32_t n = (n_nets / 256 + 63) / 64 * 64;
+  return n < 64 ? 64 : n > 2048 ? 2048 : n;
+}
+// Doubles of PowerArgs::partial (more than 32 bits count: 16,448 nets with
+// 4,096 columns and as many size vectors have 257 slabs of 2^24 results).
+inline int64_t power_scratch(int32_t n_nets, int32_t B, int32_t S, int32_t paired) {
+  if (S <= 0 || paired || n_nets <= 0) return (int64_t)power_chunks(n_nets) * B;
+  const int32_t len = power_slab_nets(n_nets);
+  return (int64_t)((n_nets + len - 1) / len) * B * S;
+}
 hipError_t launch_power(const PowerArgs &a, hipStream_t s);
 
 // The power of several evals (design groups, serving steps) as one pair of

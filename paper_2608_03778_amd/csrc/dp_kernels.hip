@@ -1393,9 +1393,6 @@ __device__ __forceinline__ double block_sum_d(double v, double *lds) {
 // face still fills the chip (50K nets, 8 x 4: 330 us on 25 blocks of a 32 x 64
 // tile staged through LDS, vector FP64).
 typedef double d4 __attribute__((ext_vector_type(4)));
-inline int32_t power_slab(int32_t n_nets) {
-  return std::min(2048, std::max(64, (n_nets / 256 + 63) / 64 * 64));
-}
 
 template <int MB, int MS>
 __global__ __launch_bounds__(kBlock) void k_power_mfma(PowerArgs a, const float *beta,
@@ -4034,16 +4031,6 @@ int32_t power_chunks(int32_t n_nets) {
   return n_nets <= 0 ? 1 : (n_nets + kPowerChunk - 1) / kPowerChunk;
 }
 
-int32_t power_partial_doubles(int32_t n_nets, int32_t B, int32_t S, int32_t paired) {
-  const int64_t cols = (int64_t)B * ((S > 0 && !paired) ? S : 1);
-  int64_t slabs = power_chunks(n_nets);
-  if (S > 0 && !paired && n_nets > 0) {
-    const int32_t len = power_slab(n_nets);
-    slabs = std::max<int64_t>(slabs, (n_nets + len - 1) / len);
-  }
-  return (int32_t)(slabs * cols);
-}
-
 uint32_t power_blocks(const PowerArgs &a) {
   const int32_t tb = power_tile(a.B);
   return (uint32_t)(kXcds * ((a.B + tb - 1) / tb) * ((a.n_chunks + kXcds - 1) / kXcds));
@@ -4068,7 +4055,7 @@ hipError_t launch_power(const PowerArgs &a, hipStream_t s) {
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-    const int32_t len = power_slab(a.n_nets), n_slabs = (a.n_nets + len - 1) / len;
+    const int32_t len = power_slab_nets(a.n_nets), n_slabs = (a.n_nets + len - 1) / len;
     const float *beta = a.mode == 1 ? a.beta : a.mode == 2 ? a.beta_frozen : nullptr;
     const int32_t shared = a.mode == 2 ? a.beta_shared : 0;
     // two tiles a side where there are that many columns: each operand loaded

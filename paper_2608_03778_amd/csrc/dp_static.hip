@@ -18,7 +18,7 @@ namespace {
 //   frozen beta           float  [n]      4 n bytes (internal numbering)
 //   power partial sums    double [chunks]
 constexpr int64_t kMaxNets = int64_t(1) << 21;
-constexpr int64_t kPartBytes = 64 << 10;  // >= 8 * power_partial_doubles(kMaxNets, 1, 0, 0)
+constexpr int64_t kPartBytes = 64 << 10;  // >= 8 * power_scratch(kMaxNets, 1, 0, 0)
 constexpr int64_t kScratchBytes = 12 * kMaxNets + kPartBytes + 3 * 256;
 
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -79,7 +79,7 @@ extern "C" dp_status dp_forward_static(const dp_design *d, const dp_params *prm,
   float *capi = reinterpret_cast<float *>(s0 + up256(4 * (int64_t)nn));
   float *betai = reinterpret_cast<float *>(reinterpret_cast<char *>(capi) + up256(4 * (int64_t)nn));
   double *part = reinterpret_cast<double *>(reinterpret_cast<char *>(betai) + up256(4 * (int64_t)nn));
-  if ((int64_t)dp::power_partial_doubles(nn, 1, 0, 0) * 8 > kPartBytes)
+  if (dp::power_scratch(nn, 1, 0, 0) * 8 > kPartBytes)
     return fail(DP_E_INVALID, "dp_forward_static: power partials exceed the static scratch");
 
   hipStream_t s = d->ctx->stream;

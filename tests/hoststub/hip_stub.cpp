@@ -338,7 +338,6 @@ void rd_graph(const dp::GraphView &g, int32_t g0, int32_t n, bool cells) {
 
 namespace dp {
 constexpr int32_t kPowerChunk = 2048;
-static int32_t power_slab(int32_t n) { return std::min(2048, std::max(64, (n / 256 + 63) / 64 * 64)); }
 
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t stream_) {
   Scope sc_(stream_);
@@ -495,13 +494,6 @@ hipError_t launch_export(const ExportArgs &a, hipStream_t stream_) {
 int32_t power_chunks(int32_t n_nets) {
   return n_nets <= 0 ? 1 : (n_nets + kPowerChunk - 1) / kPowerChunk;
 }
-int32_t power_partial_doubles(int32_t n_nets, int32_t B, int32_t S, int32_t paired) {
-  const int64_t cols = (int64_t)B * ((S > 0 && !paired) ? S : 1);
-  int64_t slabs = power_chunks(n_nets);
-  if (S > 0 && !paired && n_nets > 0)
-    slabs = std::max<int64_t>(slabs, (n_nets + power_slab(n_nets) - 1) / power_slab(n_nets));
-  return (int32_t)(slabs * cols);
-}
 uint32_t power_blocks(const PowerArgs &a) { return 8u * (uint32_t)((a.n_chunks + 7) / 8); }
 hipError_t launch_power_multi(const PowerSeg *segs, int32_t n_segs, uint32_t blocks, int32_t cols,
                               int32_t widest, hipStream_t stream_) {
@@ -584,7 +576,7 @@ hipError_t launch_power(const PowerArgs &a, hipStream_t stream_) {
   rd(a.cap, a.n_nets);
   if (a.S > 0 && a.size) rd(a.size, (int64_t)a.S * a.G);
   if (a.n_chunks != power_chunks(a.n_nets)) fatal("power chunk count");
-  wr(a.partial, power_partial_doubles(a.n_nets, a.B, a.S, a.paired));
+  wr(a.partial, power_scratch(a.n_nets, a.B, a.S, a.paired));
   const int64_t Sp = (a.S > 0 && !a.paired) ? a.S : 1;
   wr(a.power, a.B * Sp);
   return hipSuccess;

@@ -267,9 +267,26 @@ def scenario_capture_order(ctx):
     return out
 
 
+def scenario_large_faces(ctx):
+    """Forward sweeps whose (b, s) results times slabs of nets are beyond 2^31
+    and 2^32 (the stand-in touches the last partial that the contraction
+    writes)."""
+    out = {}
+    for gates, B, S in ((16_384, 4096, 4096), (16_384, 2048, 4100)):
+        nl = synth.random_dag(synth.DagSpec(gates, 64, 8), 15)
+        ev = api.Eval(api.Design(ctx, nl), B, S)
+        ev.set_pi_prob(np.full((B, nl.n_pi), 0.5, np.float32))
+        ev.set_caps(synth.net_caps(nl.n_nets, 1))
+        ev.set_cell_sizes(np.ones((S, nl.n_gates), np.float32))
+        out[f"{B}x{S}"] = status_of(ev.forward, ("power",))[0]
+        ev.close()
+    return out
+
+
 if __name__ == "__main__":
     context = api.Context(0)
     result = {"compile": scenario_compile, "flows": scenario_flows,
               "group_serving": scenario_group_serving,
-              "capture_order": scenario_capture_order}[sys.argv[2]](context)
+              "capture_order": scenario_capture_order,
+              "large_faces": scenario_large_faces}[sys.argv[2]](context)
     print(json.dumps(result), flush=True)

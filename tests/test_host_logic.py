@@ -74,6 +74,11 @@ def test_groups_and_serving(stub_lib):
     assert r["unknown_ticket"] == "DP_E_NOTFOUND" and r["budget"] == "DP_E_BUDGET"
 
 
+def test_contraction_scratch_of_large_faces(stub_lib):
+    r = _run(stub_lib, "large_faces")
+    assert r == {"4096x4096": "OK", "2048x4100": "OK"}
+
+
 def test_capture_order_under_the_capture_model(stub_lib):
     """Groups and serving, then the autotuner and graph-captured multi-column
     hybrid sweeps and a captured hybrid design group, in one process, under
