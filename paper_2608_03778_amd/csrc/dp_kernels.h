@@ -184,12 +184,36 @@ inline int32_t power_slab_nets(int32_t n_nets) {
   const int32_t n = (n_nets / 256 + 63) / 64 * 64;
   return n < 64 ? 64 : n > 2048 ? 2048 : n;
 }
-// Doubles of PowerArgs::partial (more than 32 bits count: 16,448 nets with
-// 4,096 columns and as many size vectors have 257 slabs of 2^24 results).
+inline int32_t power_slabs(int32_t n_nets) {
+  const int32_t len = power_slab_nets(n_nets);
+  return (n_nets + len - 1) / len;
+}
+// The (b, s) results whose partials are held at once: the face in pieces of nb
+// columns x ns size vectors.  A result's slabs depend on the net count alone
+// (its bits do not depend on what shares the call), so the partials of a whole
+// face would take up to 32 times what slabs of 2,048 nets do (16,448 nets,
+// 4,096 x 4,096 results: 34 GB); a piece's take no more than those, or 64 MiB
+// (from which on a piece has a thousand waves of work or more).  Sides are whole
+// tiles of 32.
+struct PowerPiece {
+  int32_t nb, ns;
+};
+inline PowerPiece power_piece(int32_t n_nets, int32_t B, int32_t S) {
+  const int64_t face = (int64_t)B * S, whole = ((int64_t)n_nets + 2047) / 2048 * face;
+  const int64_t most = (whole > (1 << 23) ? whole : 1 << 23) / power_slabs(n_nets);
+  if (face <= most) return PowerPiece{B, S};
+  const auto side = [](int64_t fit, int32_t all) {
+    fit = fit < 32 ? 32 : fit / 32 * 32;
+    return fit < all ? (int32_t)fit : all;
+  };
+  const int32_t ns = side(most / (B < 32 ? B : 32), S);
+  return PowerPiece{side(most / ns, B), ns};
+}
+// Doubles of PowerArgs::partial.
 inline int64_t power_scratch(int32_t n_nets, int32_t B, int32_t S, int32_t paired) {
   if (S <= 0 || paired || n_nets <= 0) return (int64_t)power_chunks(n_nets) * B;
-  const int32_t len = power_slab_nets(n_nets);
-  return (int64_t)((n_nets + len - 1) / len) * B * S;
+  const PowerPiece p = power_piece(n_nets, B, S);
+  return (int64_t)power_slabs(n_nets) * p.nb * p.ns;
 }
 hipError_t launch_power(const PowerArgs &a, hipStream_t s);
 

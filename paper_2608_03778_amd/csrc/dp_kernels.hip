@@ -1388,7 +1388,8 @@ __device__ __forceinline__ double block_sum_d(double v, double *lds) {
 // columns b and 16 size vectors s; it loads both operands straight from
 // memory (16 consecutive b, or s, of four consecutive nets per load), sixteen
 // nets' loads in flight, so the operands need no LDS.  Partials
-// [slab][b][s] are summed over slabs in a fixed order.  The slab's length
+// [slab][b][s] are summed over slabs in a fixed order, a piece of the (b, s)
+// face (power_piece: b0, s0 on, whole tiles) at a time.  The slab's length
 // depends on the net count alone: about 256 slabs, so that a small (b, s)
 // face still fills the chip (50K nets, 8 x 4: 330 us on 25 blocks of a 32 x 64
 // tile staged through LDS, vector FP64).
@@ -1397,10 +1398,11 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 template <int MB, int MS>
 __global__ __launch_bounds__(kBlock) void k_power_mfma(PowerArgs a, const float *beta,
                                                        int32_t beta_shared, int32_t n_slabs,
-                                                       int32_t slab_nets) {
+                                                       int32_t slab_nets, int32_t b0, int32_t s0,
+                                                       PowerPiece pc) {
   constexpr int U = 4;  // steps of four nets in flight
-  const int32_t tiles_s = (a.S + 16 * MS - 1) / (16 * MS);
-  const int32_t tiles_b = (a.B + 16 * MB - 1) / (16 * MB);
+  const int32_t tiles_s = (pc.ns + 16 * MS - 1) / (16 * MS);
+  const int32_t tiles_b = (pc.nb + 16 * MB - 1) / (16 * MB);
   const int32_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t task = (int64_t)blockIdx.x * kWavesPerBlock + wave;
   if (task >= (int64_t)n_slabs * tiles_b * tiles_s) return;
@@ -1411,9 +1413,9 @@ __global__ __launch_bounds__(kBlock) void k_power_mfma(PowerArgs a, const float 
   const int32_t i = (int32_t)threadIdx.x & 15, kk = ((int32_t)threadIdx.x >> 4) & 3;
   int32_t b[MB], s[MS];
 #pragma unroll
-  for (int m = 0; m < MB; ++m) b[m] = tb * 16 * MB + 16 * m + i;
+  for (int m = 0; m < MB; ++m) b[m] = b0 + tb * 16 * MB + 16 * m + i;
 #pragma unroll
-  for (int m = 0; m < MS; ++m) s[m] = ts * 16 * MS + 16 * m + i;
+  for (int m = 0; m < MS; ++m) s[m] = s0 + ts * 16 * MS + 16 * m + i;
   const bool gates = a.G > 0;
   d4 acc[MB][MS];
 #pragma unroll
@@ -1464,15 +1466,17 @@ __global__ __launch_bounds__(kBlock) void k_power_mfma(PowerArgs a, const float 
       const int32_t bb = tb * 16 * MB + 16 * p + 4 * r + kk;
 #pragma unroll
       for (int q = 0; q < MS; ++q)
-        if (bb < a.B && s[q] < a.S) a.partial[((int64_t)slab * a.B + bb) * a.S + s[q]] = acc[p][q][r];
+        if (bb < pc.nb && s[q] - s0 < pc.ns)
+          a.partial[((int64_t)slab * pc.nb + bb) * pc.ns + s[q] - s0] = acc[p][q][r];
     }
 }
 
-// The slabs' partials of 16 (b, s) results per block: thread (k, c) sums
-// slabs k, k + 16, ... of result c in order, then a fixed order over k.
+// The slabs' partials of 16 (b, s) results of a piece per block: thread (k, c)
+// sums slabs k, k + 16, ... of result c in order, then a fixed order over k.
+// power: the piece's first result in rows of S.
 __global__ __launch_bounds__(kBlock) void k_power_slabs(const double *__restrict__ partial,
                                                         int32_t n_slabs, int32_t n_cols,
-                                                        float *power) {
+                                                        int32_t ns, int32_t S, float *power) {
   __shared__ double lds[16][16];
   const int32_t c = (int32_t)threadIdx.x & 15, k = (int32_t)threadIdx.x >> 4;
   const int32_t col = min((int32_t)blockIdx.x * 16 + c, n_cols - 1);
@@ -1484,7 +1488,7 @@ __global__ __launch_bounds__(kBlock) void k_power_slabs(const double *__restrict
   if (k != 0 || (int32_t)blockIdx.x * 16 + c >= n_cols) return;
   double r = lds[0][c];
   for (int32_t j = 1; j < 16; ++j) r += lds[j][c];
-  power[col] = (float)r;
+  power[(int64_t)(col / ns) * S + col % ns] = (float)r;
 }
 
 // One block per column: thread t sums chunks t, t + 256, ... in order, then
@@ -4055,26 +4059,34 @@ hipError_t launch_power(const PowerArgs &a, hipStream_t s) {
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-    const int32_t len = power_slab_nets(a.n_nets), n_slabs = (a.n_nets + len - 1) / len;
+    const int32_t len = power_slab_nets(a.n_nets), n_slabs = power_slabs(a.n_nets);
     const float *beta = a.mode == 1 ? a.beta : a.mode == 2 ? a.beta_frozen : nullptr;
     const int32_t shared = a.mode == 2 ? a.beta_shared : 0;
     // two tiles a side where there are that many columns: each operand loaded
     // feeds two products
     const int mb = a.B > 16 ? 2 : 1, ms = a.S > 16 ? 2 : 1;
-    const int64_t tasks = (int64_t)n_slabs * ((a.B + 16 * mb - 1) / (16 * mb)) *
-                          ((a.S + 16 * ms - 1) / (16 * ms));
-    const int64_t blocks = (tasks + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (blocks > kMaxBlocks) return hipErrorInvalidValue;
-    using K = void (*)(PowerArgs, const float *, int32_t, int32_t, int32_t);
+    using K = void (*)(PowerArgs, const float *, int32_t, int32_t, int32_t, int32_t, int32_t, PowerPiece);
     static const K table[2][2] = {{k_power_mfma<1, 1>, k_power_mfma<1, 2>},
                                   {k_power_mfma<2, 1>, k_power_mfma<2, 2>}};
-    hipLaunchKernelGGL(table[mb - 1][ms - 1], dim3((unsigned)blocks), dim3(kBlock), 0, s, a, beta,
-                       shared, n_slabs, len);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_power_slabs<<<(unsigned)((n_cols + 15) / 16), kBlock, 0, s>>>(a.partial, n_slabs, n_cols,
-                                                                   a.power);
-    return hipGetLastError();
+    const PowerPiece piece = power_piece(a.n_nets, a.B, a.S);
+    for (int32_t b0 = 0; b0 < a.B; b0 += piece.nb)
+      for (int32_t s0 = 0; s0 < a.S; s0 += piece.ns) {
+        const PowerPiece pc{std::min(piece.nb, a.B - b0), std::min(piece.ns, a.S - s0)};
+        const int64_t tasks = (int64_t)n_slabs * ((pc.nb + 16 * mb - 1) / (16 * mb)) *
+                              ((pc.ns + 16 * ms - 1) / (16 * ms));
+        const int64_t blocks = (tasks + kWavesPerBlock - 1) / kWavesPerBlock;
+        if (blocks > kMaxBlocks) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(table[mb - 1][ms - 1], dim3((unsigned)blocks), dim3(kBlock), 0, s, a,
+                           beta, shared, n_slabs, len, b0, s0, pc);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const int32_t n = pc.nb * pc.ns;
+        k_power_slabs<<<(unsigned)((n + 15) / 16), kBlock, 0, s>>>(
+            a.partial, n_slabs, n, pc.ns, a.S, a.power + (int64_t)b0 * a.S + s0);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+      }
+    return hipSuccess;
   }
   if (a.mode == 1 && !a.beta) return hipErrorInvalidValue;
   if (a.n_chunks != power_chunks(a.n_nets)) return hipErrorInvalidValue;

@@ -126,6 +126,13 @@ void stub_capture_counts(long *out) {
   out[1] = g_forks;
   out[2] = g_graph_launches;
 }
+// Bytes of all live allocations.
+long stub_live_bytes() {
+  std::lock_guard<std::mutex> l(g_mu);
+  size_t n = 0;
+  for (const auto &a : g_live) n += a.second;
+  return (long)n;
+}
 hipError_t hipMalloc(void **ptr, size_t size) {
   if (thread_captures()) fatal("hipMalloc while this thread captures a stream");
   *ptr = std::malloc(size ? size : 1);

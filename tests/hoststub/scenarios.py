@@ -270,7 +270,10 @@ def scenario_capture_order(ctx):
 def scenario_large_faces(ctx):
     """Forward sweeps whose (b, s) results times slabs of nets are beyond 2^31
     and 2^32 (the stand-in touches the last partial that the contraction
-    writes)."""
+    writes), and the device memory they take beside their inputs and powers."""
+    import ctypes
+    live = ctypes.CDLL(sys.argv[1]).stub_live_bytes
+    live.restype = ctypes.c_long
     out = {}
     for gates, B, S in ((16_384, 4096, 4096), (16_384, 2048, 4100)):
         nl = synth.random_dag(synth.DagSpec(gates, 64, 8), 15)
@@ -278,7 +281,9 @@ def scenario_large_faces(ctx):
         ev.set_pi_prob(np.full((B, nl.n_pi), 0.5, np.float32))
         ev.set_caps(synth.net_caps(nl.n_nets, 1))
         ev.set_cell_sizes(np.ones((S, nl.n_gates), np.float32))
+        before = live()
         out[f"{B}x{S}"] = status_of(ev.forward, ("power",))[0]
+        out[f"{B}x{S} bytes"] = live() - before - 4 * B * S
         ev.close()
     return out
 

@@ -50,6 +50,33 @@ def test_many_size_vectors(gates, pis, B, S, mode):
                           f"dP/dp {b} {s}")
 
 
+# 257 slabs of nets: faces whose partials take two pieces of columns, of size
+# vectors, and of both with a remainder in each
+@pytest.mark.parametrize("B,S", [(130, 300), (20, 2000), (97, 1100)])
+def test_size_contraction_in_pieces(B, S):
+    say(f"contraction in pieces: B={B}, S={S}")
+    nl = synth.random_dag(synth.DagSpec(16_384, 64, 8), 23)
+    p, cap = synth.pi_probs(nl.n_pi, 1, batch=B), synth.net_caps(nl.n_nets, 2)
+    size = np.random.default_rng(3).uniform(0.3, 4.0, (S, nl.n_gates)).astype(np.float32)
+    d = api.Design(api.Context(0), nl)
+
+    def run(bs, ss):
+        ev = api.Eval(d, len(bs), len(ss))
+        ev.set_pi_prob(p[bs])
+        ev.set_caps(cap)
+        ev.set_cell_sizes(size[ss])
+        return ev.forward(("power",))["power"]
+    power = run(np.arange(B), np.arange(S))
+    for bs in (np.arange(0, B, 2), np.arange(1, B, 2)):  # each small enough for one piece
+        for k in range(4):
+            ss = np.arange(k, S, 4)
+            np.testing.assert_array_equal(run(bs, ss), power[np.ix_(bs, ss)])
+    o = oracle.Netlist.of(nl)
+    for b, s in {(0, 0), (B - 1, S - 1), (B // 2, S // 2)}:
+        f, _ = oracle_column(o, p[b], cap, size[s])
+        assert_power_close(power[b, s], f["power"], f"power {b} {s}")
+
+
 def oracle_adjoint(o, f, cap, size, beta, mode, adj):
     """The adjoint with the beta in force (oracle_column's own for modeled and
     hybrid columns)."""
