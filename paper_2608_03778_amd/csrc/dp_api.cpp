@@ -2325,6 +2325,13 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
     if (hybrid(ev) && ev->have_stim &&
         ev->stim.bytes < (size_t)ev->B * d->n_pi * n_words(ev->prm) * sizeof(uint64_t))
       return fail(DP_E_STATE, "dp_group_run: an explicit stimulus is too short");
+    // planned, and its buffers made, for the schedule that the group runs it in
+    struct AsLevel {
+      dp_eval *ev;
+      const int32_t own = ev->schedule;
+      explicit AsLevel(dp_eval *e) : ev(e) { ev->schedule = DP_SCHED_LEVEL; }
+      ~AsLevel() { ev->schedule = own; }
+    } as_level(ev);
     DP_TRY(ensure_flow(ev));
     if (hybrid(ev)) plans[i] = plan_chunks(ev);
     DP_TRY(ensure_forward_buffers(ev, hybrid(ev) ? &plans[i] : nullptr));
@@ -2335,10 +2342,7 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
       cost[i] += d->depth + d->split_levels + 1;
     }
     launches += cost[i];
-    const int32_t sched = ev->schedule;
-    ev->schedule = DP_SCHED_LEVEL;
     mix(graph_key(ev, hybrid(ev) ? &plans[i] : nullptr));
-    ev->schedule = sched;
     mix((uint64_t)(uintptr_t)ev->contrib.ptr);
     mix((uint64_t)(uintptr_t)ev->part.ptr);
     mix((uint64_t)(uintptr_t)ev->seed.ptr);

@@ -267,6 +267,25 @@ def scenario_capture_order(ctx):
     return out
 
 
+def scenario_group_persistent(ctx):
+    """Groups of evals whose own schedule is the persistent one, which the group
+    does not use."""
+    nl = synth.random_dag(synth.SPECS["dag2k"], 13)
+    d = api.Design(ctx, nl)
+    evs = []
+    for mode in (L.DP_HYBRID, L.DP_MODELED, L.DP_HYBRID):
+        ev = api.Eval(d, 2, mode=mode, n_sim=64 * 20, seed=3)
+        ev.set_pi_prob(synth.pi_probs(nl.n_pi, 30, batch=2))
+        ev.set_caps(synth.net_caps(nl.n_nets, 14))
+        ev.set_schedule(L.DP_SCHED_PERSISTENT)
+        evs.append(ev)
+    grp = api.Group(ctx, evs)
+    for use_graph in (True, False):
+        grp.configure(use_graph=use_graph)
+        res = grp.run(("sp", "power"), backward=True)
+    return {"results": len(res), "schedules": [ev.get_schedule()["schedule"] for ev in evs]}
+
+
 def scenario_large_faces(ctx):
     """Forward sweeps whose (b, s) results times slabs of nets are beyond 2^31
     and 2^32 (the stand-in touches the last partial that the contraction
@@ -293,5 +312,6 @@ if __name__ == "__main__":
     result = {"compile": scenario_compile, "flows": scenario_flows,
               "group_serving": scenario_group_serving,
               "capture_order": scenario_capture_order,
+              "group_persistent": scenario_group_persistent,
               "large_faces": scenario_large_faces}[sys.argv[2]](context)
     print(json.dumps(result), flush=True)

@@ -214,3 +214,30 @@ def test_group_beyond_one_sweep(ctx):
                 for k in r:
                     np.testing.assert_array_equal(r[k], ref[k], err_msg=k)
             g.close()
+
+
+@pytest.mark.parametrize("graph", [True, False])
+def test_group_of_evals_with_the_persistent_schedule(ctx, graph):
+    """A group does not use its evals' own schedules: with the persistent one set
+    its results are those of the evals alone."""
+    say(f"group of evals with the persistent schedule, graph {graph}")
+    evs, want = [], []
+    for k, mode in enumerate((L.DP_HYBRID, L.DP_MODELED, L.DP_HYBRID)):
+        nl = synth.random_dag(synth.DagSpec(900 * (k + 1), 30 + k, 7 + 2 * k), 60 + k)
+        ev = api.Eval(api.Design(ctx, nl), 2, mode=mode, n_sim=64 * 20, seed=3)
+        ev.set_pi_prob(synth.pi_probs(nl.n_pi, 70 + k, batch=2))
+        ev.set_caps(synth.net_caps(nl.n_nets, 71))
+        r = ev.forward(("sp", "power"))
+        r.update(ev.backward(want=("dpi",)))
+        want.append(r)
+        fresh = api.Eval(api.Design(ctx, nl), 2, mode=mode, n_sim=64 * 20, seed=3)
+        fresh.set_pi_prob(synth.pi_probs(nl.n_pi, 70 + k, batch=2))
+        fresh.set_caps(synth.net_caps(nl.n_nets, 71))
+        fresh.set_schedule(L.DP_SCHED_PERSISTENT)
+        evs.append(fresh)
+    g = api.Group(ctx, evs)
+    g.configure(use_graph=graph)
+    for r, ref in zip(g.run(("sp", "power"), backward=True), want):
+        for k in ref:
+            np.testing.assert_array_equal(r[k], ref[k], err_msg=k)
+    g.close()

@@ -74,6 +74,11 @@ def test_groups_and_serving(stub_lib):
     assert r["unknown_ticket"] == "DP_E_NOTFOUND" and r["budget"] == "DP_E_BUDGET"
 
 
+def test_group_of_persistent_evals(stub_lib):
+    r = _run(stub_lib, "group_persistent")
+    assert r["results"] == 3 and len(set(r["schedules"])) == 1
+
+
 def test_contraction_scratch_of_large_faces(stub_lib):
     r = _run(stub_lib, "large_faces")
     for B, S in ((4096, 4096), (2048, 4100)):
