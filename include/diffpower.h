@@ -93,8 +93,8 @@ enum {
                              column) pairs and 64 columns as one launch whose
                              gates wait for their own inputs.  Bit for bit the
                              same results.  Should such a wait give up (after
-                             seconds; it cannot while the device makes
-                             progress), that sweep's outputs are NaN and the
+                             seconds, see dp_eval_set_barrier_timeout; it
+                             cannot while the device makes progress), that sweep's outputs are NaN and the
                              eval's next host synchronization returns
                              DP_E_HIP */
   DP_SCHED_GRAPH = 2,     /* the same launches captured once into HIP graphs,
@@ -427,15 +427,16 @@ dp_status dp_eval_get_schedule(const dp_eval *ev, int32_t *schedule,
                                int32_t *sim_pairs_per_lane,
                                int32_t *sim_streams);
 
-/* Block until the eval's stream is idle.  Returns DP_E_HIP if a persistent
- * sweep since the eval's last host synchronization had a grid-barrier wait
- * give up (its outputs are NaN). */
+/* Block until the eval's stream is idle.  Returns DP_E_HIP if a sweep since
+ * the eval's last host synchronization had a wait give up. */
 dp_status dp_eval_synchronize(dp_eval *ev);
 /* Time a grid-barrier wait of the persistent schedule may see no progress
  * before it gives up (microseconds, finite, >= 0; default 1000).  A guard
  * against a sweep whose blocks are not all resident, and a way for tests
  * to make the give-up path run: at 0 every wait that has to wait at all
- * gives up.  Errors: DP_E_INVALID. */
+ * gives up.  The waits of the other schedules' launches take their limit from
+ * it too: the same share of their own (seconds) as this is of 1000, and no
+ * more than all of it.  Errors: DP_E_INVALID. */
 dp_status dp_eval_set_barrier_timeout(dp_eval *ev, double microseconds);
 
 /* Kernel timing of the last forward/backward, accumulated with HIP events

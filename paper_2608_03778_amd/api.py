@@ -362,8 +362,8 @@ class Eval:
                     sim_streams=ns.value)
 
     def synchronize(self):
-        """Wait for the eval's stream; raises if a persistent sweep's grid
-        barrier gave up since the last host synchronization."""
+        """Wait for the eval's stream; raises if a wait of one of its sweeps
+        gave up since the last host synchronization."""
         check(self.lib.dp_eval_synchronize(self.handle))
 
     def set_barrier_timeout(self, microseconds: float):

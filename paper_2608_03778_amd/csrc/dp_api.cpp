@@ -397,8 +397,16 @@ dp_status ensure_reverse_buffers(dp_eval *ev, int32_t C, int per_column = 0) {
   return DP_OK;
 }
 
+// Polls after which a wait of the eval's dataflow launches gives up: the
+// default's share that dp_eval_set_barrier_timeout's limit is of its own.
+uint32_t flow_limit(const dp_eval *ev) {
+  return (uint32_t)(std::min(ev->barrier_limit_us / kBarrierLimitUs, 1.0) * dp::kFlowPolls);
+}
+
 dp::FlowCtl flow_ctl(const dp_eval *ev) {
-  return dp::FlowCtl{ev->flow.as<uint32_t>(), ev->flow_report, 0, ev->d->ctx->n_cu};
+  dp::FlowCtl ctl{ev->flow.as<uint32_t>(), ev->flow_report, 0, ev->d->ctx->n_cu};
+  dp::flow_set_limit(ctl, flow_limit(ev));
+  return ctl;
 }
 
 // At a host synchronization of the eval (its stream idle): whether a
@@ -814,6 +822,7 @@ uint64_t graph_key(const dp_eval *ev, const ChunkPlan *pl) {
   mix((uint64_t)ev->S);
   mix((uint64_t)ev->paired_sizes);
   mix((uint64_t)ev->beta_shared);
+  mix(flow_limit(ev));
   if (pl) {
     mix((uint64_t)pl->Tc);
     mix((uint64_t)pl->tile);
@@ -974,6 +983,7 @@ uint64_t reverse_key(const dp_eval *ev, const dp::BwdArgs &ba, const float *dst)
   uint32_t kb;
   std::memcpy(&kb, &ba.kappa, 4);
   mix(kb);
+  mix(flow_limit(ev));
   for (int32_t v : {ba.n_pi, ba.G, ba.B, ba.S, ba.C, ba.cdiv, ba.ste, ba.per_column, ba.paired,
                     ba.beta_shared})
     mix((uint64_t)(uint32_t)v);

@@ -6,6 +6,8 @@
 #include "dp_internal.h"
 #include "dp_kernels.h"
 
+constexpr double kBarrierLimitUs = 1000.0;
+
 struct dp_eval {
   dp_design *d = nullptr;
   int32_t B = 1, S = 0;      // query columns, size vectors (0 = none)
@@ -46,7 +48,7 @@ struct dp_eval {
   uint32_t *check_report = nullptr;  // pinned host word: a checked value was out of range
   dp::DevBuf barrier;        // persistent sweeps: grid-barrier words (dp::kBarrierAlloc)
   bool barrier_pending = false;      // a persistent sweep ran since the report word was read
-  double barrier_limit_us = 1000.0;  // a barrier wait gives up after this long without progress
+  double barrier_limit_us = kBarrierLimitUs;  // a barrier wait gives up after this long without progress
   dp::DevBuf flow;                   // control words: dataflow sweeps (dp::kFlowWords), then word tiles
   uint32_t *flow_report = nullptr;   // pinned host word: a dataflow sweep's wait gave up
   std::shared_ptr<dp::ReportWords> reports;  // where those words go back to

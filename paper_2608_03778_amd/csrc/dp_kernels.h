@@ -423,7 +423,17 @@ struct FlowCtl {
   int32_t n_cu;       // compute units of the device
   int32_t shifts;     // levels in which the waves take turns (set by the launcher)
   int32_t per_block;  // waves of a workgroup that take items (set by the launcher)
+  // a wait gives up after this many polls, and looks at its count and at the
+  // stop flag whenever polls & every is 0
+  uint32_t limit, every;
 };
+// Polls (a tenth of a microsecond each, so seconds) after which a wait gives up
+// by default.
+constexpr uint32_t kFlowPolls = 1u << 26;
+inline void flow_set_limit(FlowCtl &ctl, uint32_t polls) {
+  ctl.limit = polls;
+  ctl.every = polls < 64 ? 0 : 63;
+}
 // The first block of level l that wave w of a team of `waves` takes, the next
 // ones `waves` further each: over all waves every block once, whatever the
 // team's size (it may close with fewer members than it was launched with), and

@@ -2517,8 +2517,8 @@ __global__ __launch_bounds__(kBlock) void k_bwd_persistent(GraphView g, BwdArgs 
 // rank, every wave takes its items in level order, and only running
 // workgroups are members, so each wait is for work that a running wave will
 // reach: nothing depends on how many workgroups fit on the device beside
-// other streams' work.  As a guard a wait that polls kFlowPolls times (seconds)
-// gives up: it raises the launch's stop flag, which ends every other wait at
+// other streams' work.  As a guard a wait that polls ctl.limit times (seconds,
+// unless the host set less) gives up: it raises the launch's stop flag, which ends every other wait at
 // once, and the host-visible report word, and what it could not compute
 // stays NaN.
 //
@@ -2530,7 +2530,6 @@ __global__ __launch_bounds__(kBlock) void k_bwd_persistent(GraphView g, BwdArgs 
 // bases (launch_*_flow refuses larger arrays), and a column's seeds and
 // contributions are contiguous arrays of their own.
 constexpr uint32_t kArmed = 0xFFFFFFFFu;
-constexpr uint32_t kFlowPolls = 1u << 26;
 constexpr uint32_t kFlowClosed = 1u << 31;
 constexpr uint64_t kFlowJoinTicks = 500;  // 5 us of the 100 MHz counter
 constexpr int kFlowThreads = 512;         // threads per workgroup at most
@@ -2556,9 +2555,9 @@ __device__ __forceinline__ void flow_store(float *base, uint32_t bytes, float v)
 
 // One more poll of a wait: false when the wait has to end.
 __device__ __forceinline__ bool flow_again(const FlowCtl &ctl, int stop, uint32_t &polls) {
-  if ((++polls & 63u) != 0u) return true;
+  if ((++polls & ctl.every) != 0u) return true;
   if (flow_load(ctl.words + stop) != 0u) return false;
-  if (polls < kFlowPolls) return true;
+  if (polls < ctl.limit) return true;
   __hip_atomic_store(ctl.words + stop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(ctl.report, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   return false;

@@ -1,0 +1,67 @@
+"""The bounded waits of the dataflow sweeps and word tiles, forced from the
+host: at a limit of 0 a wait whose first look finds nothing gives up, the
+launch's other waits stop at once (every kernel exits normally), the failure
+is reported, and the next sweeps are whole again."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from paper_2608_03778_amd import _lib as L
+from paper_2608_03778_amd import api, synth
+from tests.gpu_helpers import say
+
+pytestmark = pytest.mark.gpu
+OFF, ON = 0.0, 1000.0
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    return api.Context(0)
+
+
+def _net(seed=17):
+    """Levels of several waves each, narrow and wide in turn: waves wait."""
+    return synth.random_dag(synth.DagSpec(6000, 300, 24), seed)
+
+
+def _eval(d, nl, B=2, mode=L.DP_MODELED, T=40, sched=L.DP_SCHED_AUTO):
+    ev = api.Eval(d, B, mode=mode, n_sim=64 * T, seed=5)
+    ev.set_pi_prob(synth.pi_probs(nl.n_pi, 6, batch=B))
+    ev.set_caps(synth.net_caps(nl.n_nets, 7))
+    ev.set_schedule(sched)
+    return ev
+
+
+def _pass(ev):
+    r = ev.forward(("sp", "beta", "power"))
+    r.update(ev.backward(want=("dpi", "dcap")))
+    return r
+
+
+@pytest.mark.parametrize("sched", [L.DP_SCHED_LEVEL, L.DP_SCHED_GRAPH])
+@pytest.mark.parametrize("mode", [L.DP_MODELED, L.DP_HYBRID])
+def test_give_up_is_reported_once(ctx, sched, mode):
+    say(f"give-up: schedule {sched}, mode {mode}")
+    nl = _net()
+    d = api.Design(ctx, nl)
+    want = _pass(_eval(d, nl, mode=mode))
+    ev = _eval(d, nl, mode=mode, sched=sched)
+    _pass(ev)  # (a captured graph of the default limit)
+    ev.set_barrier_timeout(OFF)
+    with pytest.raises(L.DiffPowerError, match="gave up"):
+        ev.forward(("sp", "power"))
+    ev.forward(("power",), device=True)
+    with pytest.raises(L.DiffPowerError, match="gave up"):
+        ev.synchronize()
+    ev.synchronize()  # reported once
+    ev.set_pi_prob(synth.pi_probs(nl.n_pi, 6, batch=2))
+    ev.set_barrier_timeout(ON)
+    ev.forward(("power",))
+    ev.set_barrier_timeout(OFF)
+    with pytest.raises(L.DiffPowerError, match="gave up"):
+        ev.backward(want=("dpi",))
+    ev.set_barrier_timeout(ON)
+    got = _pass(ev)
+    for k in want:
+        np.testing.assert_array_equal(got[k], want[k], err_msg=k)
