@@ -3156,7 +3156,8 @@ __global__ __launch_bounds__(kBlock) void k_flow_arm(uint32_t *p, int64_t n, uin
 
 // Before a reverse sweep, in three runs of blocks: arms the contributions,
 // writes every net's seed [C][n_nets], and every gate's partial derivatives
-// [B][pins][G].
+// [B][pins][G].  With the seeds the sweep's results become NaN, so that what a
+// sweep that gives up does not reach is no earlier sweep's.
 template <bool CELLS>
 __device__ __forceinline__ void bwd_arm(const BwdFlow &t, uint32_t *words, int32_t n_words,
                                         uint32_t block, uint32_t arm_blocks, uint32_t seed_blocks) {
@@ -3173,6 +3174,8 @@ __device__ __forceinline__ void bwd_arm(const BwdFlow &t, uint32_t *words, int32
     const int32_t b = c / a.cdiv;
     const float beta = a.beta ? a.beta[a.beta_shared ? (int64_t)net : (int64_t)net * a.B + b] : 1.0f;
     t.seed[idx] = seed_of(a, net, c, b, sp_load(a.sp[(int64_t)net * a.B + b]), beta, a.cap[net]);
+    if (a.lam) a.lam[idx] = __builtin_nanf("");
+    if (net < g.n_pi) t.pi_out[(int64_t)c * g.n_pi + net] = __builtin_nanf("");
     return;
   }
   const int64_t idx = (int64_t)(block - arm_blocks - seed_blocks) * kBlock + threadIdx.x;

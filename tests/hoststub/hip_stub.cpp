@@ -769,6 +769,7 @@ hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl
   flow_levels_ok(t.g, t.level_ptr, t.depth, widest, cells);
   wr(t.seed, (int64_t)t.g.n_nets * t.a.C);
   wr(t.part, (int64_t)t.a.B * t.g.pins * t.g.G);
+  wr(t.pi_out, (int64_t)t.a.C * t.g.n_pi);
   launch_bwd_level(t.g, t.a, 0, 0, false, stream_, nullptr, kNoHeavyCheck);  // its extents
   return launch_bwd_pi(t.g, t.a, t.pi_out, stream_, nullptr, kNoHeavyCheck);
 }

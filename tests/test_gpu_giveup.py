@@ -65,3 +65,30 @@ def test_give_up_is_reported_once(ctx, sched, mode):
     got = _pass(ev)
     for k in want:
         np.testing.assert_array_equal(got[k], want[k], err_msg=k)
+
+
+@pytest.mark.parametrize("sched", [L.DP_SCHED_LEVEL, L.DP_SCHED_GRAPH])
+def test_no_gradient_of_an_earlier_sweep_is_left(ctx, sched):
+    """What a reverse sweep that gives up does not reach is NaN, not what its
+    output held before: each gradient is NaN or the right one."""
+    import torch
+    say(f"give-up: gradients, schedule {sched}")
+    nl = _net()
+    B = 40
+    ev = _eval(api.Design(ctx, nl), nl, B, sched=sched)
+    ev.forward(("power",))
+    want = ev.backward(want=("dpi",))["dpi"]
+    out = torch.empty((B, nl.n_pi), dtype=torch.float32, device="cuda")
+    for _ in range(3):
+        out.fill_(7.0)
+        torch.cuda.synchronize()
+        ev.set_barrier_timeout(OFF)
+        api.check(ev.lib.dp_backward(ev.handle, None, out.data_ptr(), None, None, 1))
+        with pytest.raises(L.DiffPowerError, match="gave up"):
+            ev.synchronize()
+        ev.set_barrier_timeout(ON)
+        got = out.cpu().numpy()
+        bad = np.isnan(got)
+        assert bad.any()
+        np.testing.assert_array_equal(got[~bad], want[~bad])
+    np.testing.assert_array_equal(ev.backward(want=("dpi",))["dpi"], want)
