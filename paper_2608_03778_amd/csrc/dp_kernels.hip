@@ -3157,7 +3157,11 @@ __global__ __launch_bounds__(kBlock) void k_flow_arm(uint32_t *p, int64_t n, uin
 // Before a reverse sweep, in three runs of blocks: arms the contributions,
 // writes every net's seed [C][n_nets], and every gate's partial derivatives
 // [B][pins][G].  With the seeds the sweep's results become NaN, so that what a
-// sweep that gives up does not reach is no earlier sweep's.
+// sweep that gives up does not reach is no earlier sweep's.  A NaN among the
+// seeds and partials gets other bits than kArmed: the probabilities of an SP
+// sweep that gave up are kArmed, whose bits a product may hand on, and a
+// contribution of these bits would be waited for.
+__device__ __forceinline__ float disarmed(float v) { return v == v ? v : __builtin_nanf(""); }
 template <bool CELLS>
 __device__ __forceinline__ void bwd_arm(const BwdFlow &t, uint32_t *words, int32_t n_words,
                                         uint32_t block, uint32_t arm_blocks, uint32_t seed_blocks) {
@@ -3173,7 +3177,8 @@ __device__ __forceinline__ void bwd_arm(const BwdFlow &t, uint32_t *words, int32
     const int32_t c = (int32_t)(idx / g.n_nets), net = (int32_t)(idx - (int64_t)c * g.n_nets);
     const int32_t b = c / a.cdiv;
     const float beta = a.beta ? a.beta[a.beta_shared ? (int64_t)net : (int64_t)net * a.B + b] : 1.0f;
-    t.seed[idx] = seed_of(a, net, c, b, sp_load(a.sp[(int64_t)net * a.B + b]), beta, a.cap[net]);
+    t.seed[idx] =
+        disarmed(seed_of(a, net, c, b, sp_load(a.sp[(int64_t)net * a.B + b]), beta, a.cap[net]));
     if (a.lam) a.lam[idx] = __builtin_nanf("");
     if (net < g.n_pi) t.pi_out[(int64_t)c * g.n_pi + net] = __builtin_nanf("");
     return;
@@ -3197,7 +3202,7 @@ __device__ __forceinline__ void bwd_arm(const BwdFlow &t, uint32_t *words, int32
       cell_partials(lc, x, d);
 #pragma unroll
       for (int j = 0; j < kCellMaxIn; ++j)
-        if (j < lc.nin) part[(int64_t)j * g.G] = d[j];
+        if (j < lc.nin) part[(int64_t)j * g.G] = disarmed(d[j]);
       return;
     }
   }
@@ -3205,9 +3210,9 @@ __device__ __forceinline__ void bwd_arm(const BwdFlow &t, uint32_t *words, int32
   const f2 z = f2{0.0f, 1.0f};
   float d0, d1, d2;
   sp_partials(op, x[0], k > 1 ? x[1] : z, k > 2 ? x[2] : z, d0, d1, d2);
-  part[0] = d0;
-  if (k > 1) part[g.G] = d1;
-  if (k > 2) part[2 * (int64_t)g.G] = d2;
+  part[0] = disarmed(d0);
+  if (k > 1) part[g.G] = disarmed(d1);
+  if (k > 2) part[2 * (int64_t)g.G] = disarmed(d2);
 }
 template <bool CELLS>
 __global__ __launch_bounds__(kBlock) void k_bwd_arm(BwdFlow t, uint32_t *words, uint32_t arm_blocks,

@@ -92,3 +92,21 @@ def test_no_gradient_of_an_earlier_sweep_is_left(ctx, sched):
         assert bad.any()
         np.testing.assert_array_equal(got[~bad], want[~bad])
     np.testing.assert_array_equal(ev.backward(want=("dpi",))["dpi"], want)
+
+
+@pytest.mark.parametrize("cells", [False, True])
+def test_reverse_sweep_after_a_forward_that_gave_up(ctx, cells):
+    """It has nothing to wait for: NaN go through it as values do."""
+    import torch
+    say(f"give-up: the reverse sweep after it, library cells {cells}")
+    ops = tuple(range(9)) + (tuple(synth.CELL_BASE + c for c in range(9)) if cells else ())
+    nl = synth.random_dag(synth.DagSpec(6000, 300, 24, ops=ops, cells=synth.LIBRARY if cells else ()), 18)
+    ev = _eval(api.Design(ctx, nl), nl, 3)
+    ev.set_barrier_timeout(OFF)
+    ev.forward(("power",), device=True)
+    with pytest.raises(L.DiffPowerError, match="gave up"):
+        ev.synchronize()
+    ev.set_barrier_timeout(ON)
+    dpi = ev.backward(want=("dpi",), device=True)["dpi"]
+    ev.synchronize()  # no wait of this sweep gave up
+    assert torch.isnan(dpi).any()
