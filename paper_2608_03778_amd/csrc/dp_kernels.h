@@ -527,6 +527,9 @@ constexpr int kSimStop = kSimNextTile + 32;
 constexpr int kSimClaim = kSimStop + 32;
 constexpr int kSimFlags = kSimClaim + 32 * kSimBufs;
 constexpr int kSimWords = kSimFlags + 32 * kSimBufs * kSimMembers;
+// In the counts of a simulation that gave up (a count is 64 T at most); rates
+// and betas formed from it are NaN.
+constexpr uint32_t kNoCount = 0xFFFFFFFFu;
 struct SimFlow {
   GraphView g;
   const int32_t *level_ptr;
@@ -556,7 +559,8 @@ hipError_t launch_stim_words(const float *sp /* stored SP [n_pi][B] */, const in
 constexpr int32_t kRideColumns = 2;
 // The simulation, and with sp.B <= kRideColumns the SP sweep of the same columns
 // (armed by launch_sp_arm), as one launch.  ctl.words: [kSimWords].  Writes ones
-// and tog [n_nets][B]; a simulation that gives up leaves NaN in sp.sp.
+// and tog [n_nets][B]; a simulation that gives up leaves kNoCount
+// there and NaN as the gates' probabilities.
 hipError_t launch_sim_flow(const SimFlow &t, const SpFlow &sp, int64_t widest, bool cells,
                            FlowCtl ctl, FlowCtl sp_ctl, uint32_t *ones, uint32_t *tog,
                            hipStream_t s);

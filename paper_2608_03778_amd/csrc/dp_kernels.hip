@@ -1215,8 +1215,10 @@ __global__ __launch_bounds__(kBlock) void k_stimulus(int32_t n_pi, ChunkView c, 
 // ---------------------------------------------------------------- beta and terms
 // The hybrid beta of a net whose TR_model is tm and whose simulation counted
 // tog toggles: clip(TR_acc / TR_model) with TR_acc = toggles / (64 (T - 1))
-// (Eq. 4-5; 0/0 -> 1, x/0 -> beta_max).
+// (Eq. 4-5; 0/0 -> 1, x/0 -> beta_max).  NaN where a sweep that gave up left no
+// count or no probability (the clip alone would make beta_min of it).
 __device__ __forceinline__ float hybrid_beta(const PowerArgs &a, uint32_t tog, float tm) {
+  if (tog == kNoCount || tm != tm) return __builtin_nanf("");
   const float ta = (float)((double)tog / (64.0 * (double)(a.T - 1)));
   const float beta = tm == 0.0f ? (ta == 0.0f ? 1.0f : a.beta_max) : ta / tm;
   return fminf(fmaxf(beta, a.beta_min), a.beta_max);
@@ -1253,8 +1255,11 @@ __global__ __launch_bounds__(kBlock) void k_export(ExportArgs a) {
   const float beta = a.beta ? a.beta[idx] : 1.0f;
   if (a.o_beta) a.o_beta[o] = beta;
   if (a.o_tr_hyb) a.o_tr_hyb[o] = beta * tm;
-  if (a.o_sp_acc) a.o_sp_acc[o] = (float)((double)a.ones[idx] / (64.0 * (double)a.T));
-  if (a.o_tr_acc) a.o_tr_acc[o] = (float)((double)a.tog[idx] / (64.0 * (double)(a.T - 1)));
+  const auto rate = [](uint32_t count, int64_t words) {
+    return count == kNoCount ? __builtin_nanf("") : (float)((double)count / (64.0 * (double)words));
+  };
+  if (a.o_sp_acc) a.o_sp_acc[o] = rate(a.ones[idx], a.T);
+  if (a.o_tr_acc) a.o_tr_acc[o] = rate(a.tog[idx], a.T - 1);
   if (a.o_ones) a.o_ones[o] = a.ones[idx];
   if (a.o_tog) a.o_tog[o] = a.tog[idx];
 }
@@ -3588,8 +3593,9 @@ __global__ __launch_bounds__(kFlowThreads, 6) void k_sim_flow(FlowCtl ctl, SimFl
 }
 
 // Counts [n_nets][B] of all chunks, the toggles between chunks among them.  A
-// simulation that gave up (stop) leaves NaN probabilities, so that nothing
-// computed from its counts can pass for a result.
+// simulation that gave up (stop) leaves kNoCount and the gates' probabilities as
+// NaN, so that nothing computed from its counts can pass for a result; the PIs'
+// are inputs and stay.
 __global__ __launch_bounds__(kBlock) void k_sim_counts(SimFlow t, const uint32_t *stop, float *sp,
                                                        uint32_t *ones, uint32_t *tog) {
   const int64_t idx = gidx();
@@ -3608,9 +3614,10 @@ __global__ __launch_bounds__(kBlock) void k_sim_counts(SimFlow t, const uint32_t
     if (k) nt += __popcll(last ^ e.x);
     last = e.y;
   }
-  ones[o] = n1;
-  tog[o] = nt;
-  if (*stop) sp[o] = __builtin_nanf("");
+  const bool bad = *stop != 0u;
+  ones[o] = bad ? kNoCount : n1;
+  tog[o] = bad ? kNoCount : nt;
+  if (bad && net >= t.g.n_pi) sp[o] = __builtin_nanf("");
 }
 
 // Words [B][n_pi][T] of the independent stimulus: a wave takes 64 cycles of one

@@ -55,7 +55,6 @@ def test_give_up_is_reported_once(ctx, sched, mode):
     with pytest.raises(L.DiffPowerError, match="gave up"):
         ev.synchronize()
     ev.synchronize()  # reported once
-    ev.set_pi_prob(synth.pi_probs(nl.n_pi, 6, batch=2))
     ev.set_barrier_timeout(ON)
     ev.forward(("power",))
     ev.set_barrier_timeout(OFF)
@@ -110,3 +109,31 @@ def test_reverse_sweep_after_a_forward_that_gave_up(ctx, cells):
     dpi = ev.backward(want=("dpi",), device=True)["dpi"]
     ev.synchronize()  # no wait of this sweep gave up
     assert torch.isnan(dpi).any()
+
+
+@pytest.mark.parametrize("B,sched", [(1, L.DP_SCHED_LEVEL), (3, L.DP_SCHED_LEVEL), (3, L.DP_SCHED_GRAPH)])
+def test_simulation_that_gave_up(ctx, B, sched):
+    """Word tiles: no count, rate, beta or power of it can be taken for a result,
+    and its inputs are what they were."""
+    say(f"give-up: word tiles, B={B}, schedule {sched}")
+    nl = _net(19)
+    d = api.Design(ctx, nl)
+    names = ("sp", "tr", "sp_acc", "tr_acc", "beta", "tr_hyb", "ones", "toggles", "power")
+    want = _eval(d, nl, B, L.DP_HYBRID).forward(names)
+    ev = _eval(d, nl, B, L.DP_HYBRID, sched=sched)
+    ev.set_barrier_timeout(OFF)
+    r = {k: v.cpu().numpy() for k, v in ev.forward(names, device=True).items()}
+    with pytest.raises(L.DiffPowerError, match="gave up"):
+        ev.synchronize()
+    pi = np.arange(nl.n_nets) < nl.n_pi
+    for k in ("ones", "toggles"):
+        assert (r[k].view(np.uint32) == 0xFFFFFFFF).all(), k
+    for k in ("sp_acc", "tr_acc", "beta", "tr_hyb", "power"):
+        assert np.isnan(r[k]).all(), k
+    for k in ("sp", "tr"):
+        assert np.isnan(r[k][:, ~pi]).all(), k
+        np.testing.assert_array_equal(r[k][:, pi], want[k][:, pi])
+    ev.set_barrier_timeout(ON)
+    got = ev.forward(names)
+    for k in names:
+        np.testing.assert_array_equal(got[k], want[k], err_msg=k)
