@@ -1729,7 +1729,9 @@ dp_status dp_power_virus(dp_eval *ev, int32_t steps, double eta, uint8_t *v0, fl
   if (p_virus) DP_HIP_TRY(hipMemcpyAsync(p_virus, pv.ptr, (size_t)B * sizeof(double), k, s));
   DP_HIP_TRY(hipStreamSynchronize(s));  // the scratch buffers are freed on return
   ev->inputs_version++;  // the PI probabilities are now the ascended ones
-  return barrier_status(ev);
+  const dp_status st = barrier_status(ev);
+  if (st != DP_OK) ev->have_pi = false;  // or what NaN gradients made of them
+  return st;
 }
 
 dp_status dp_backward_columns(dp_eval *ev, float *dpower_dpi, int32_t on_device) {

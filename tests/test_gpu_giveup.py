@@ -137,3 +137,22 @@ def test_simulation_that_gave_up(ctx, B, sched):
     got = ev.forward(names)
     for k in names:
         np.testing.assert_array_equal(got[k], want[k], err_msg=k)
+
+
+def test_virus_ascent_that_gave_up(ctx):
+    """Its last probabilities are no start for anything: they have to be set
+    again."""
+    say("give-up: virus ascent")
+    nl = _net(20)
+    d = api.Design(ctx, nl)
+    want = _eval(d, nl).power_virus(5, 1e-3)
+    ev = _eval(d, nl)
+    ev.set_barrier_timeout(OFF)
+    with pytest.raises(L.DiffPowerError, match="gave up"):
+        ev.power_virus(5, 1e-3)
+    ev.set_barrier_timeout(ON)
+    with pytest.raises(L.DiffPowerError, match="probabilities not set"):
+        ev.forward(("power",))
+    ev.set_pi_prob(synth.pi_probs(nl.n_pi, 6, batch=2))
+    for a, b in zip(ev.power_virus(5, 1e-3), want):
+        np.testing.assert_array_equal(a, b)
