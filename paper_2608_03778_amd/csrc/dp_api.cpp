@@ -411,15 +411,15 @@ dp::FlowCtl flow_ctl(const dp_eval *ev) {
 
 // At a host synchronization of the eval (its stream idle): whether a
 // persistent or dataflow sweep since the last check had a wait give up.
-// Reads and clears the report words.
+// Reads and clears the report words, all of them.
 dp_status barrier_status(dp_eval *ev) {
-  DP_TRY(dp::flow_status(ev));
-  if (!ev->barrier_pending) return DP_OK;
+  const dp_status flow = dp::flow_status(ev);
+  if (!ev->barrier_pending) return flow;
   uint32_t rep = 0;
   uint32_t *w = ev->barrier.as<uint32_t>() + dp::kBarrierReport;
   DP_HIP_TRY(hipMemcpy(&rep, w, sizeof(uint32_t), hipMemcpyDeviceToHost));
   ev->barrier_pending = false;
-  if (rep == 0u) return DP_OK;
+  if (rep == 0u) return flow;
   DP_HIP_TRY(dp::launch_fill_u32(w, 1, 0u, ev->stream()));
   DP_HIP_TRY(hipStreamSynchronize(ev->stream()));
   return fail(DP_E_HIP, "a persistent sweep's grid barrier gave up waiting (no progress for " +
@@ -1010,9 +1010,40 @@ dp_status reverse_sweep(dp_eval *ev, const dp::BwdArgs &ba, float *dst) {
 }  // namespace
 
 namespace dp {
+// Takes note of failures that an eval's groups report and lets go of those
+// that are gone; done_only: looks at these alone (nothing of theirs is running).
+void note_shared(dp_eval *ev, bool done_only) {
+  for (size_t i = 0; i < ev->shared_reports.size();) {
+    dp_eval::Shared &r = ev->shared_reports[i];
+    std::unique_lock<std::mutex> lock(r.report->mu);
+    const bool done = r.report->done;
+    if (done || !done_only) {
+      const uint64_t n = r.report->count();
+      ev->shared_failed = ev->shared_failed || n != r.seen;
+      r.seen = n;
+    }
+    lock.unlock();
+    if (done) ev->shared_reports.erase(ev->shared_reports.begin() + i);
+    else ++i;
+  }
+}
+// Launches that concern the eval report there from now on.
+void join_shared(dp_eval *ev, const std::shared_ptr<SharedReport> &report) {
+  for (const dp_eval::Shared &r : ev->shared_reports)
+    if (r.report == report) return;
+  note_shared(ev, true);
+  std::lock_guard<std::mutex> lock(report->mu);
+  ev->shared_reports.push_back({report, report->failures});
+}
 dp_status flow_status(dp_eval *ev) {
-  if (!ev->flow_report || *static_cast<volatile uint32_t *>(ev->flow_report) == 0u) return DP_OK;
-  *ev->flow_report = 0u;
+  note_shared(ev, false);
+  bool bad = ev->shared_failed;
+  ev->shared_failed = false;
+  if (volatile uint32_t *own = ev->flow_report; own && *own != 0u) {
+    *own = 0u;
+    bad = true;
+  }
+  if (!bad) return DP_OK;
   return fail(DP_E_HIP, "a sweep's wait for its own results gave up; that sweep's outputs are NaN "
                         "and not a result");
 }
@@ -1965,6 +1996,8 @@ void FlowTables::build(const MergedTables::Lane *lanes, int32_t n) {
   f_widest = b_widest = 1;
   cells = false;
   ctl = flow_ctl(lanes[0].ev);
+  for (int32_t j = 1; j < n; ++j)
+    flow_set_limit(ctl, std::min(ctl.limit, flow_limit(lanes[j].ev)));
   std::vector<int32_t> order(n);
   for (int32_t j = 0; j < n; ++j) order[j] = j;
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
@@ -2106,7 +2139,12 @@ struct dp_group {
   hipStream_t capture = nullptr;
   hipGraphExec_t exec = nullptr;
   uint64_t key = 0;
+  std::shared_ptr<dp::SharedReport> report;  // of the merged dataflow sweeps
   ~dp_group() {
+    if (report) {
+      std::lock_guard<std::mutex> lock(report->mu);
+      report->done = true;
+    }
     if (exec) (void)hipGraphExecDestroy(exec);
     for (auto st : branch) {
       (void)hipStreamSynchronize(st);
@@ -2164,6 +2202,7 @@ dp_status build_merged_tables(dp_group *g, bool backward) {
   };
   if (g->use_flow) {
     g->flow.build(lanes.data(), (int32_t)lanes.size());
+    g->flow.ctl.report = g->report->word;
     DP_TRY(upload(g->flow));
   } else {
     for (auto &l : lanes) l.backward = true;
@@ -2308,6 +2347,12 @@ dp_status dp_group_create(dp_ctx *ctx, dp_eval *const *evals, int32_t n_evals, d
     delete g;
     return fail(DP_E_HIP, std::string("dp_group_create: ") + hipGetErrorString(e));
   }
+  g->report = std::make_shared<dp::SharedReport>();
+  g->report->words = ctx->reports;
+  if (const dp_status st = ctx->reports->take(&g->report->word); st != DP_OK) {
+    delete g;
+    return st;
+  }
   if (g->branch.size() > 1) g->pool.start((int)g->branch.size(), ctx->device);
   dp::ctx_retain(ctx);
   *out = g;
@@ -2381,6 +2426,8 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
     for (int32_t i : g->merged) lanes.push_back({g->evs[i], backward != 0});
     g->use_flow = dp::FlowTables::fits(lanes.data(), (int32_t)lanes.size());
     mix((uint64_t)g->use_flow);
+    if (g->use_flow)
+      for (const auto &l : lanes) dp::join_shared(l.ev, g->report);
     const int64_t per_sweep =
         g->use_flow ? 2 : dp::MergedTables::level_launches(lanes.data(), (int32_t)lanes.size());
     launches += per_sweep * (backward ? 2 : 1) + (int64_t)g->merged.size() * (backward ? 4 : 3);
@@ -2452,7 +2499,12 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
   DP_HIP_TRY(dp::launch_copies(copies, s));
   if (host_out) {
     DP_HIP_TRY(hipStreamSynchronize(s));
-    for (int32_t i : g->merged) DP_TRY(barrier_status(g->evs[i]));
+    dp_status st = DP_OK;  // every eval's words are read, whichever fails first
+    for (dp_eval *ev : g->evs) {
+      const dp_status one = barrier_status(ev);
+      if (st == DP_OK) st = one;
+    }
+    return st;
   }
   return DP_OK;
 }

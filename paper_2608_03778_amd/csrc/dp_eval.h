@@ -8,6 +8,31 @@
 
 constexpr double kBarrierLimitUs = 1000.0;
 
+namespace dp {
+// The pinned word that launches over several evals report in (a design group's
+// merged sweeps).  Every one of these evals tells of a failure at its own next
+// synchronization: whichever looks first clears the word and counts it.
+struct SharedReport {
+  std::mutex mu;
+  std::shared_ptr<ReportWords> words;
+  uint32_t *word = nullptr;
+  uint64_t failures = 0;
+  bool done = false;  // no more launches report here
+  ~SharedReport() {
+    if (word) words->give(word);
+  }
+  // Failures so far (the launches over).
+  uint64_t count() {
+    volatile uint32_t *w = word;
+    if (*w != 0u) {
+      *w = 0u;
+      ++failures;
+    }
+    return failures;
+  }
+};
+}  // namespace dp
+
 struct dp_eval {
   dp_design *d = nullptr;
   int32_t B = 1, S = 0;      // query columns, size vectors (0 = none)
@@ -52,6 +77,12 @@ struct dp_eval {
   dp::DevBuf flow;                   // control words: dataflow sweeps (dp::kFlowWords), then word tiles
   uint32_t *flow_report = nullptr;   // pinned host word: a dataflow sweep's wait gave up
   std::shared_ptr<dp::ReportWords> reports;  // where those words go back to
+  struct Shared {
+    std::shared_ptr<dp::SharedReport> report;
+    uint64_t seen = 0;  // of its failures
+  };
+  std::vector<Shared> shared_reports;  // of the groups it is in
+  bool shared_failed = false;          // a failure seen there and not told of yet
   // reverse state
   dp::DevBuf w;              // [B*S'] upstream weights
   dp::DevBuf contrib;        // [n_edges][C] contributions, or [n_nets][C] adjoints
@@ -184,7 +215,7 @@ struct FlowTables {
   uint32_t f_blocks = 0, b_blocks = 0;
   int64_t f_widest = 1, b_widest = 1;
   bool cells = false;
-  FlowCtl ctl{};  // the first eval's
+  FlowCtl ctl{};  // the first eval's words, the smallest limit
   // Whether these evals' sweeps go this way: each is one for the dataflow
   // kernels, its reverse buffers are there where it wants gradients, and
   // together they are within the launches' limits.
@@ -213,6 +244,7 @@ struct PowerTable {
 // Whether a dataflow sweep of the eval gave up since the last check (its
 // stream idle): a failure status, once.
 dp_status flow_status(dp_eval *ev);
+void join_shared(dp_eval *ev, const std::shared_ptr<SharedReport> &report);
 
 // Hybrid calibration at probability p_all for every PI: beta [n_nets] in
 // internal order into beta_int (device), on the context's stream.

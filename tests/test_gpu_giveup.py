@@ -156,3 +156,59 @@ def test_virus_ascent_that_gave_up(ctx):
     ev.set_pi_prob(synth.pi_probs(nl.n_pi, 6, batch=2))
     for a, b in zip(ev.power_virus(5, 1e-3), want):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.fixture(scope="module")
+def group_evals(ctx):
+    """Two modeled evals (merged sweeps) and two hybrid ones (on branches)."""
+    made = []
+    for k, mode in enumerate((L.DP_MODELED, L.DP_HYBRID, L.DP_MODELED, L.DP_HYBRID)):
+        nl = _net(21 + k)
+        d = api.Design(ctx, nl)
+        made.append((_eval(d, nl, mode=mode), _pass(_eval(d, nl, mode=mode))))
+    return made
+
+
+def _limits(evs, off):
+    for i, ev in enumerate(evs):
+        ev.set_barrier_timeout(OFF if i in off else ON)
+
+
+@pytest.mark.parametrize("graph", [True, False])
+@pytest.mark.parametrize("off", [(0, 2), (2,), (1,), (3,), (0, 1, 2, 3)])
+def test_group_with_a_sweep_that_gave_up(ctx, group_evals, graph, off):
+    """Host outputs: the run fails, whichever eval it was, and nothing is left to
+    report.  Device outputs: each eval whose outputs it concerns reports it,
+    once: all that share the merged sweeps, or the hybrid one."""
+    say(f"give-up: group, graph {graph}, evals {off}")
+    evs, want = [e for e, _ in group_evals], [w for _, w in group_evals]
+    g = api.Group(ctx, evs)
+    g.configure(use_graph=graph)
+    _limits(evs, off)
+    with pytest.raises(L.DiffPowerError, match="gave up"):
+        g.run(("power",), backward=True)
+    for ev in evs:
+        ev.synchronize()
+    g.run(("power",), backward=True, device=True)
+    hit = set(off) | ({0, 2} if {0, 2} & set(off) else set())
+    for again in (False, True):
+        for i, ev in enumerate(evs):
+            if i in hit and not again:
+                with pytest.raises(L.DiffPowerError, match="gave up"):
+                    ev.synchronize()
+            else:
+                ev.synchronize()
+    # a group that is gone when its evals look
+    g.run(("power",), device=True)
+    g.close()
+    g = api.Group(ctx, evs)
+    for i, ev in enumerate(evs):
+        if i in hit:
+            with pytest.raises(L.DiffPowerError, match="gave up"):
+                ev.synchronize()
+        ev.synchronize()
+    _limits(evs, ())
+    for r, w in zip(g.run(("sp", "power"), backward=True), want):
+        for k in r:
+            np.testing.assert_array_equal(r[k], w[k], err_msg=k)
+    g.close()
