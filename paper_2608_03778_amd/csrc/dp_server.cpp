@@ -125,10 +125,16 @@ Lane *make_lane(dp_server *s, int32_t design, int32_t cap) {
   // the dataflow sweeps' buffers come out of what the budget has left, and are
   // given back before any query waits for memory (trim_flow)
   const size_t base = dp::lane_bytes(d, cap), extra = dp::lane_flow_bytes(d, cap);
-  const bool flow = s->used + base + extra <= s->budget;
-  if (ok)
-    ok = dp::lane_create(de->d, cap, &de->prm, l->stream, de->cap_int.as<float>(),
-                         de->frozen ? de->beta_int.as<float>() : nullptr, flow, &l->ev) == DP_OK;
+  bool flow = s->used + base + extra <= s->budget;
+  auto create = [&] {
+    return dp::lane_create(de->d, cap, &de->prm, l->stream, de->cap_int.as<float>(),
+                           de->frozen ? de->beta_int.as<float>() : nullptr, flow, &l->ev) == DP_OK;
+  };
+  if (ok && !(ok = create()) && flow) {  // the device may hold less than the budget
+    (void)hipGetLastError();
+    flow = false;
+    ok = create();
+  }
   if (!ok) {
     (void)hipGetLastError();
     destroy_lane(l);

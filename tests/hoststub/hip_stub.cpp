@@ -133,8 +133,18 @@ long stub_live_bytes() {
   for (const auto &a : g_live) n += a.second;
   return (long)n;
 }
+// Device memory in all (host allocations are not counted against it); 0: no limit.
+static size_t g_limit = 0, g_host = 0;
+void stub_set_memory(long bytes) { g_limit = (size_t)bytes; }
+// Dataflow launches over several designs, and merged level launches.
+static long g_flow_multi = 0, g_level_multi = 0;
+void stub_multi_counts(long *out) {
+  out[0] = g_flow_multi;
+  out[1] = g_level_multi;
+}
 hipError_t hipMalloc(void **ptr, size_t size) {
   if (thread_captures()) fatal("hipMalloc while this thread captures a stream");
+  if (g_limit && (size_t)stub_live_bytes() - g_host + size > g_limit) return hipErrorOutOfMemory;
   *ptr = std::malloc(size ? size : 1);
   note_alloc(*ptr, size ? size : 1);
   return hipSuccess;
@@ -146,12 +156,26 @@ hipError_t hipFree(void *ptr) {
   std::free(ptr);
   return hipSuccess;
 }
-hipError_t hipHostMalloc(void **ptr, size_t size, unsigned int) { return hipMalloc(ptr, size); }
+hipError_t hipHostMalloc(void **ptr, size_t size, unsigned int) {
+  if (thread_captures()) fatal("hipHostMalloc while this thread captures a stream");
+  *ptr = std::malloc(size ? size : 1);
+  note_alloc(*ptr, size ? size : 1);
+  std::lock_guard<std::mutex> l(g_mu);
+  g_host += g_live[static_cast<const char *>(*ptr)];
+  return hipSuccess;
+}
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) {
   *v = 256;
   return hipSuccess;
 }
-hipError_t hipHostFree(void *ptr) { return hipFree(ptr); }
+hipError_t hipHostFree(void *ptr) {
+  if (ptr) {
+    std::lock_guard<std::mutex> l(g_mu);
+    auto it = g_live.find(static_cast<const char *>(ptr));
+    if (it != g_live.end()) g_host -= it->second;
+  }
+  return hipFree(ptr);
+}
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
   if (s && s->cap) {
     s->cap->extents.push_back({dst, n, "copy destination"});
@@ -785,6 +809,7 @@ hipError_t launch_sp_flow_multi(const SpFlowSeg *segs, int32_t n_segs, int32_t j
                                 uint32_t blocks, int64_t widest, bool cells, FlowCtl ctl,
                                 hipStream_t stream_) {
   Scope sc_(stream_);
+  ++g_flow_multi;
   int32_t job = 0;
   uint32_t block = 0;
   for (int32_t k = 0; k < n_segs; ++k) {
@@ -816,6 +841,7 @@ hipError_t launch_bwd_flow_multi(const BwdFlowSeg *segs, int32_t n_segs, int32_t
 hipError_t launch_sp_multi(const SpSeg *segs, int32_t n_segs, uint32_t blocks, bool cells,
                            hipStream_t st) {
   Scope sc_(st);
+  ++g_level_multi;
   for (int32_t k = 0; k < n_segs; ++k) {
     const uint32_t b0 = segs[k].block0, b1 = k + 1 < n_segs ? segs[k + 1].block0 : blocks;
     const int64_t items = ((int64_t)segs[k].lv.n + segs[k].lv2.n) * segs[k].lv.B;

@@ -286,6 +286,41 @@ def scenario_group_persistent(ctx):
     return {"results": len(res), "schedules": [ev.get_schedule()["schedule"] for ev in evs]}
 
 
+def scenario_lane_memory(ctx):
+    """Serving with a device that has less memory than the budget says: enough
+    for a lane, and not for its dataflow sweeps' buffers."""
+    import ctypes
+    import time
+    stub = ctypes.CDLL(sys.argv[1])
+    stub.stub_live_bytes.restype = ctypes.c_long
+    counts = (ctypes.c_long * 2)()
+    nl = synth.random_dag(synth.SPECS["dag2k"], 12)
+    d = api.Design(ctx, nl)
+    out = {}
+
+    def serve(limit):
+        srv = api.Server(ctx, hbm_budget_bytes=64 << 20, max_batch=8, max_inflight=2)
+        did = srv.add_design(d, synth.net_caps(nl.n_nets, 20))
+        stub.stub_set_memory(limit)
+        stub.stub_multi_counts(counts)
+        before = list(counts)
+        t = srv.submit(did, np.full(nl.n_pi, 0.5, np.float32), None, True)
+        end = time.time() + 5
+        while not srv.poll(t) and time.time() < end:
+            time.sleep(0.01)
+        done = srv.poll(t)
+        stub.stub_multi_counts(counts)
+        stub.stub_set_memory(0)
+        live = stub.stub_live_bytes()
+        if done:
+            srv.wait(t)
+        srv.close()
+        return [done, counts[0] > before[0], counts[1] > before[1], live]
+    out["all"] = serve(0)
+    out["less"] = serve(out["all"][3] - 100_000)
+    return out
+
+
 def scenario_large_faces(ctx):
     """Forward sweeps whose (b, s) results times slabs of nets are beyond 2^31
     and 2^32 (the stand-in touches the last partial that the contraction
@@ -313,5 +348,6 @@ if __name__ == "__main__":
               "group_serving": scenario_group_serving,
               "capture_order": scenario_capture_order,
               "group_persistent": scenario_group_persistent,
+              "lane_memory": scenario_lane_memory,
               "large_faces": scenario_large_faces}[sys.argv[2]](context)
     print(json.dumps(result), flush=True)

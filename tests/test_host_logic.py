@@ -79,6 +79,12 @@ def test_group_of_persistent_evals(stub_lib):
     assert r["results"] == 3 and len(set(r["schedules"])) == 1
 
 
+def test_lane_without_memory_for_its_dataflow_buffers(stub_lib):
+    r = _run(stub_lib, "lane_memory")
+    assert r["all"][:3] == [True, True, False]   # done, dataflow, merged levels
+    assert r["less"][:3] == [True, False, True]
+
+
 def test_contraction_scratch_of_large_faces(stub_lib):
     r = _run(stub_lib, "large_faces")
     for B, S in ((4096, 4096), (2048, 4100)):
