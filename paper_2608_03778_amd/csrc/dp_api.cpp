@@ -2552,6 +2552,16 @@ void lane_drop_flow(dp_eval *ev) {
   ev->flow.release();
 }
 
+dp_status lane_add_flow(dp_eval *ev, int32_t capacity) {
+  const dp_design *d = ev->d;
+  dp_status st = ev->seed.alloc(std::max<size_t>((size_t)d->n_nets * capacity * 4, 16));
+  if (st == DP_OK)
+    st = ev->part.alloc(std::max<size_t>((size_t)capacity * d->pins * d->n_gates * 4, 16));
+  if (st == DP_OK) st = ensure_flow(ev);
+  if (st != DP_OK) lane_drop_flow(ev);
+  return st;
+}
+
 dp_status lane_create(dp_design *d, int32_t capacity, const dp_params *prm, hipStream_t stream,
                       const float *cap_int, const float *beta_int, bool flow, dp_eval **out) {
   DP_TRY(check_params(prm));
@@ -2579,11 +2589,7 @@ dp_status lane_create(dp_design *d, int32_t capacity, const dp_params *prm, hipS
   A(ev->contrib, (size_t)d->n_edges * capacity * 4);
   A(ev->pi_out, (size_t)capacity * d->n_pi * 4);
   if (beta_int) A(ev->beta_frozen, nn * 4);
-  if (flow) {
-    A(ev->seed, nn * capacity * 4);
-    A(ev->part, (size_t)capacity * d->pins * d->n_gates * 4);
-    if (st == DP_OK) st = ensure_flow(ev);
-  }
+  if (flow && st == DP_OK) st = lane_add_flow(ev, capacity);
   if (st != DP_OK) {
     delete ev;
     return st;

@@ -137,10 +137,11 @@ namespace dp {
 //   flow:      also allocate what its dataflow sweeps need
 dp_status lane_create(dp_design *d, int32_t capacity, const dp_params *prm, hipStream_t stream,
                       const float *cap_int, const float *beta_int, bool flow, dp_eval **out);
-// Device bytes of what `flow` adds, and giving them back (the lane idle): its
-// sweeps then run as merged level launches.
+// Device bytes of what `flow` adds, giving them back (the lane idle; its sweeps
+// then run as merged level launches), and adding them again (all or none).
 size_t lane_flow_bytes(const dp_design *d, int32_t capacity);
 void lane_drop_flow(dp_eval *ev);
+dp_status lane_add_flow(dp_eval *ev, int32_t capacity);
 // Device bytes a lane of `capacity` columns holds.
 size_t lane_bytes(const dp_design *d, int32_t capacity);
 

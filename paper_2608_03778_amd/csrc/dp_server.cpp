@@ -62,7 +62,12 @@ struct Lane {
   float *pin_p = nullptr, *pin_size = nullptr, *pin_power = nullptr, *pin_dpi = nullptr;
   size_t bytes = 0;       // device bytes, those of flow_bytes included
   size_t flow_bytes = 0;  // of its dataflow sweeps' buffers (0: it has none)
+  Clock::time_point flow_retry;  // not before this are they asked for again
 };
+// A lane whose dataflow buffers were taken, or that the device had no memory for,
+// asks for them again after this long: under lasting pressure an allocation a
+// second at most.
+constexpr std::chrono::seconds kFlowRetry{1};
 
 // One device step in flight: its stream, completion event, the merged
 // launches' table scratch and the lanes it carries.
@@ -133,6 +138,7 @@ Lane *make_lane(dp_server *s, int32_t design, int32_t cap) {
   if (ok && !(ok = create()) && flow) {  // the device may hold less than the budget
     (void)hipGetLastError();
     flow = false;
+    l->flow_retry = Clock::now() + kFlowRetry;
     ok = create();
   }
   if (!ok) {
@@ -150,7 +156,8 @@ Lane *make_lane(dp_server *s, int32_t design, int32_t cap) {
 }
 
 // Give back idle lanes' dataflow buffers until `need` bytes fit (caller holds
-// mu): those lanes' sweeps run as merged level launches from then on.
+// mu): those lanes' sweeps, and those of the lanes that share a step with them,
+// run as merged level launches until there is room again (regain_flow).
 bool trim_flow(dp_server *s, size_t need) {
   for (Lane *l : s->lanes) {
     if (s->used + need <= s->budget) break;
@@ -159,8 +166,26 @@ bool trim_flow(dp_server *s, size_t need) {
     s->used -= l->flow_bytes;
     l->bytes -= l->flow_bytes;
     l->flow_bytes = 0;
+    l->flow_retry = Clock::now() + kFlowRetry;
   }
   return s->used + need <= s->budget;
+}
+
+// Dataflow buffers for a lane that has none, where the budget has room for them
+// (caller holds mu, the lane has no step in flight).
+void regain_flow(dp_server *s, Lane *l) {
+  if (l->flow_bytes > 0) return;
+  const size_t extra = dp::lane_flow_bytes(s->designs[l->design]->d, l->capacity);
+  if (s->used + extra > s->budget || Clock::now() < l->flow_retry) return;
+  if (dp::lane_add_flow(l->ev, l->capacity) != DP_OK) {
+    (void)hipGetLastError();
+    l->flow_retry = Clock::now() + kFlowRetry;
+    return;
+  }
+  l->flow_bytes = extra;
+  l->bytes += extra;
+  s->used += extra;
+  s->st.peak_slot_bytes = std::max<int64_t>(s->st.peak_slot_bytes, (int64_t)s->used);
 }
 
 // Free idle lanes of other designs until `need` bytes fit (caller holds mu).
@@ -309,6 +334,7 @@ void admit(dp_server *s) {
   Step *step = idle_step(s);
   if (!step) return;  // every step is in flight; queries wait and batch up
   std::vector<Lane *> ready;
+  bool waits = false;  // a query waits for memory
   int32_t carried = 0;  // queries in this step: at most max_batch
   for (size_t i = 0; i < s->pending.size() && carried < s->max_batch;) {
     Request *r = s->pending[i];
@@ -345,6 +371,7 @@ void admit(dp_server *s) {
       for (Lane *l : s->lanes) has_lane |= l->design == r->design;
       if (s->used + need > s->budget && (has_lane || !make_room(s, need, r->design))) {
         s->st.memory_waits++;
+        waits = true;
         ++i;  // no memory now; a running lane will free some
         continue;
       }
@@ -369,7 +396,10 @@ void admit(dp_server *s) {
     lane->busy = true;  // taken: not reused or freed while this pass goes on
     ready.push_back(lane);
   }
-  if (!ready.empty()) launch_step(s, step, ready);
+  if (ready.empty()) return;
+  if (!waits)
+    for (Lane *l : ready) regain_flow(s, l);
+  launch_step(s, step, ready);
 }
 
 void scheduler(dp_server *s) {

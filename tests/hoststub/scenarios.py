@@ -298,7 +298,7 @@ def scenario_lane_memory(ctx):
     d = api.Design(ctx, nl)
     out = {}
 
-    def serve(limit):
+    def serve(limit, later=False):
         srv = api.Server(ctx, hbm_budget_bytes=64 << 20, max_batch=8, max_inflight=2)
         did = srv.add_design(d, synth.net_caps(nl.n_nets, 20))
         stub.stub_set_memory(limit)
@@ -312,12 +312,20 @@ def scenario_lane_memory(ctx):
         stub.stub_multi_counts(counts)
         stub.stub_set_memory(0)
         live = stub.stub_live_bytes()
+        if done and later:  # the same lane, once there is memory and a second has passed
+            first = list(counts)
+            time.sleep(1.1)
+            srv.wait(srv.submit(did, np.full(nl.n_pi, 0.5, np.float32), None, True))
+            stub.stub_multi_counts(counts)
+            out["later"] = [counts[0] > first[0], counts[1] > first[1]]
+            out["lanes"] = srv.stats()["lanes_created"]
+            counts[0], counts[1] = first
         if done:
             srv.wait(t)
         srv.close()
         return [done, counts[0] > before[0], counts[1] > before[1], live]
     out["all"] = serve(0)
-    out["less"] = serve(out["all"][3] - 100_000)
+    out["less"] = serve(out["all"][3] - 100_000, later=True)
     return out
 
 

@@ -83,6 +83,7 @@ def test_lane_without_memory_for_its_dataflow_buffers(stub_lib):
     r = _run(stub_lib, "lane_memory")
     assert r["all"][:3] == [True, True, False]   # done, dataflow, merged levels
     assert r["less"][:3] == [True, False, True]
+    assert r["later"] == [True, False] and r["lanes"] == 1
 
 
 def test_contraction_scratch_of_large_faces(stub_lib):
