@@ -1420,7 +1420,9 @@ dp_status dp_eval_autotune(dp_eval *ev, int32_t reps, int32_t with_backward, dou
     // automatic chunks on one stream may be word tiles; whole rows in level
     // launches are then a chunk of T words
     ev->words_per_chunk = ev->sim_streams = 0;
+    ev->schedule = DP_SCHED_LEVEL;  // (as the candidates': the persistent one has no tiles)
     const bool tiles = plan_chunks(ev).tile > 0;
+    ev->schedule = s0;
     ev->words_per_chunk = c0;
     ev->sim_streams = l0;
     if (tiles)

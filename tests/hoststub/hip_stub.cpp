@@ -138,6 +138,12 @@ static size_t g_limit = 0, g_host = 0;
 void stub_set_memory(long bytes) { g_limit = (size_t)bytes; }
 // Dataflow launches over several designs, and merged level launches.
 static long g_flow_multi = 0, g_level_multi = 0;
+// Launches of word tiles, and of simulation levels.
+static long g_sim_flow = 0, g_sim_level = 0;
+void stub_sim_counts(long *out) {
+  out[0] = g_sim_flow;
+  out[1] = g_sim_level;
+}
 void stub_multi_counts(long *out) {
   out[0] = g_flow_multi;
   out[1] = g_level_multi;
@@ -487,6 +493,7 @@ hipError_t launch_sim_level(const GraphView &g, const ChunkView &c, const CountV
                             int32_t g0, int32_t n, const SpLevel *sp, bool cells,
                             const SimTune &, hipStream_t stream_, int cell_inputs) {
   Scope sc_(stream_);
+  ++g_sim_level;
   rd_graph(g, g0, n, cells);
   if (sp) rd_graph(g, sp->g0, sp->n, cells);  // the fused SP: gates of the same kind
   if (cells)  // every cell of the range within the instance's input count
@@ -765,6 +772,7 @@ hipError_t launch_sp_arm(const SpFlow &t, FlowCtl ctl, hipStream_t stream_) {
 hipError_t launch_sim_flow(const SimFlow &t, const SpFlow &sweep, int64_t widest, bool cells,
                            FlowCtl ctl, FlowCtl sp_ctl, uint32_t *ones, uint32_t *tog,
                            hipStream_t stream_) {
+  ++g_sim_flow;
   if (sweep.B <= kRideColumns) launch_sp_flow(sweep, widest, cells, sp_ctl, stream_);
   Scope sc_(stream_);
   float *sp = sweep.sp;

@@ -286,6 +286,29 @@ def scenario_group_persistent(ctx):
     return {"results": len(res), "schedules": [ev.get_schedule()["schedule"] for ev in evs]}
 
 
+def scenario_autotune(ctx):
+    """What the autotuner times (launches of word tiles and of simulation levels),
+    entered with each schedule."""
+    import ctypes
+    stub = ctypes.CDLL(sys.argv[1])
+    counts = (ctypes.c_long * 2)()
+    nl = synth.random_dag(synth.SPECS["dag2k"], 13)
+    d = api.Design(ctx, nl)
+    out = {}
+    for name, sched in (("level", L.DP_SCHED_LEVEL), ("persistent", L.DP_SCHED_PERSISTENT)):
+        ev = api.Eval(d, 1, mode=L.DP_HYBRID, n_sim=64 * 300, seed=8)
+        ev.set_pi_prob(synth.pi_probs(nl.n_pi, 13))
+        ev.set_caps(synth.net_caps(nl.n_nets, 14))
+        ev.set_schedule(sched)
+        stub.stub_sim_counts(counts)
+        before = list(counts)
+        ev.autotune(2)
+        stub.stub_sim_counts(counts)
+        out[name] = [counts[0] - before[0], counts[1] - before[1]]
+        ev.close()
+    return out
+
+
 def scenario_lane_memory(ctx):
     """Serving with a device that has less memory than the budget says: enough
     for a lane, and not for its dataflow sweeps' buffers."""
@@ -356,6 +379,7 @@ if __name__ == "__main__":
               "group_serving": scenario_group_serving,
               "capture_order": scenario_capture_order,
               "group_persistent": scenario_group_persistent,
+              "autotune": scenario_autotune,
               "lane_memory": scenario_lane_memory,
               "large_faces": scenario_large_faces}[sys.argv[2]](context)
     print(json.dumps(result), flush=True)

@@ -79,6 +79,11 @@ def test_group_of_persistent_evals(stub_lib):
     assert r["results"] == 3 and len(set(r["schedules"])) == 1
 
 
+def test_autotuner_times_the_same_from_any_schedule(stub_lib):
+    r = _run(stub_lib, "autotune")
+    assert r["level"][0] > 0 and r["persistent"] == r["level"]
+
+
 def test_lane_without_memory_for_its_dataflow_buffers(stub_lib):
     r = _run(stub_lib, "lane_memory")
     assert r["all"][:3] == [True, True, False]   # done, dataflow, merged levels
