@@ -472,6 +472,10 @@ int64_t forward_launches(const dp_eval *ev, const ChunkPlan *pl) {
          ev->d->cell_levels;  // the library cells' SP launches
 }
 
+// Kernel launches of one reverse sweep in level launches, the measure of whether
+// it is captured (a sweep in adjoints has two more, a dataflow sweep two in all).
+int64_t reverse_launches(const dp_design *d) { return (int64_t)d->depth + d->split_levels + 1; }
+
 // Allocate everything the forward sweep touches (before any capture).
 dp_status ensure_forward_buffers(dp_eval *ev, const ChunkPlan *pl) {
   const dp_design *d = ev->d;
@@ -995,8 +999,7 @@ uint64_t reverse_key(const dp_eval *ev, const dp::BwdArgs &ba, const float *dst)
 // replayed, otherwise enqueued launch by launch.
 dp_status reverse_sweep(dp_eval *ev, const dp::BwdArgs &ba, float *dst) {
   const dp_design *d = ev->d;
-  const int64_t launches = (int64_t)d->depth + d->split_levels + 3;
-  if (ev->schedule != DP_SCHED_GRAPH || ev->profiling || launches > kMaxGraphLaunches)
+  if (ev->schedule != DP_SCHED_GRAPH || ev->profiling || reverse_launches(d) > kMaxGraphLaunches)
     return enqueue_backward(ev, ba, dst);
   const uint64_t k = reverse_key(ev, ba, dst);
   if (!ev->graph_bwd || ev->graph_bwd_key != k) {
@@ -1785,7 +1788,7 @@ dp_status dp_forward_backward_columns(dp_eval *ev, float *power, float *dpower_d
   ChunkPlan plan;
   if (hyb) plan = plan_chunks(ev);
   const ChunkPlan *pl = hyb ? &plan : nullptr;
-  const int64_t launches = forward_launches(ev, pl) + d->depth + d->split_levels + 3;
+  const int64_t launches = forward_launches(ev, pl) + reverse_launches(d);
   if (ev->schedule != DP_SCHED_GRAPH || ev->profiling || launches > kMaxGraphLaunches) {
     DP_TRY(dp_forward(ev, nullptr));
     if (power) {

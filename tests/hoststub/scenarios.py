@@ -286,6 +286,29 @@ def scenario_group_persistent(ctx):
     return {"results": len(res), "schedules": [ev.get_schedule()["schedule"] for ev in evs]}
 
 
+def scenario_deep_graphs(ctx):
+    """Captures of the reverse sweep of chains whose level launches are about as
+    many as a graph takes (1,024)."""
+    import ctypes
+    stub = ctypes.CDLL(sys.argv[1])
+    counts = (ctypes.c_long * 3)()
+    out = {}
+    for depth in (1021, 1022, 1023, 1024):
+        nl = synth.from_gates(1, [(synth.INV, [i]) for i in range(depth)])
+        ev = api.Eval(api.Design(ctx, nl), 1)
+        ev.set_pi_prob(np.full((1, 1), 0.5, np.float32))
+        ev.set_caps(synth.net_caps(nl.n_nets, 14))
+        ev.set_schedule(L.DP_SCHED_GRAPH)
+        ev.forward(("power",))
+        stub.stub_capture_counts(counts)
+        before = counts[0]
+        ev.backward(want=("dpi",))
+        stub.stub_capture_counts(counts)
+        out[str(depth)] = counts[0] - before
+        ev.close()
+    return out
+
+
 def scenario_autotune(ctx):
     """What the autotuner times (launches of word tiles and of simulation levels),
     entered with each schedule."""
@@ -379,6 +402,7 @@ if __name__ == "__main__":
               "group_serving": scenario_group_serving,
               "capture_order": scenario_capture_order,
               "group_persistent": scenario_group_persistent,
+              "deep_graphs": scenario_deep_graphs,
               "autotune": scenario_autotune,
               "lane_memory": scenario_lane_memory,
               "large_faces": scenario_large_faces}[sys.argv[2]](context)

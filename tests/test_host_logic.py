@@ -79,6 +79,10 @@ def test_group_of_persistent_evals(stub_lib):
     assert r["results"] == 3 and len(set(r["schedules"])) == 1
 
 
+def test_reverse_graphs_of_deep_designs(stub_lib):
+    assert _run(stub_lib, "deep_graphs") == {"1021": 1, "1022": 1, "1023": 1, "1024": 0}
+
+
 def test_autotuner_times_the_same_from_any_schedule(stub_lib):
     r = _run(stub_lib, "autotune")
     assert r["level"][0] > 0 and r["persistent"] == r["level"]
