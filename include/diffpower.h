@@ -442,13 +442,16 @@ dp_status dp_eval_set_barrier_timeout(dp_eval *ev, double microseconds);
 /* Kernel timing of the last forward/backward, accumulated with HIP events
  * on the context's stream while profiling is enabled. */
 typedef struct {
-  double sim_ms;          /* simulation level kernels, summed per launch */
+  double sim_ms;          /* simulation kernels, summed per launch; with their
+                             levels' SP where one launch does both (hybrid
+                             level launches, short simulations of one or two
+                             columns), which is then not under sp_* */
   int64_t sim_launches;
   double sim_bytes;       /* algorithmic bytes moved by those launches */
-  double sp_ms;           /* SP level kernels (modeled sweeps) */
+  double sp_ms;           /* SP sweeps in launches of their own */
   int64_t sp_launches;
   double sp_bytes;
-  double bwd_ms;          /* reverse level kernels */
+  double bwd_ms;          /* reverse sweeps */
   int64_t bwd_launches;
   double bwd_bytes;
   double stim_ms;         /* stimulus generation */

@@ -558,16 +558,20 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
   const bool prof = ev->profiling;
   float *sp = ev->sp.as<float>();
   const dp::SpFlow sweep{g, sp, d->level_dev.as<int32_t>(), ev->B, d->depth};
-  if (!pl || pl->tile) {  // modeled (or frozen-beta) sweep: one span over all level launches
+  const bool rides = pl && pl->tile && ev->B <= dp::kRideColumns;  // the SP sweep, with the tiles
+  const auto sp_bytes = [&] {
     double bytes = 0.0;
     for (int32_t l = 1; l <= d->depth; ++l) bytes += sp_level_bytes(d, l, ev->B);
-    SpanGuard sg(ev, SPAN_SP, bytes, prof && d->depth > 0,
+    return bytes;
+  };
+  if (rides) {
+    DP_HIP_TRY(dp::launch_sp_arm(sweep, flow_ctl(ev), s));
+  } else if (!pl || pl->tile) {  // modeled (or frozen-beta) sweep: one span over all level launches
+    SpanGuard sg(ev, SPAN_SP, sp_bytes(), prof && d->depth > 0,
                  ev->schedule == DP_SCHED_PERSISTENT || flows(ev, ev->B)
                      ? 1
                      : sp_sweep_launches(d, ev->B));
-    if (pl && ev->B <= dp::kRideColumns) {  // the sweep rides with the tiles
-      DP_HIP_TRY(dp::launch_sp_arm(sweep, flow_ctl(ev), s));
-    } else if (flows(ev, ev->B)) {
+    if (flows(ev, ev->B)) {
       DP_HIP_TRY(dp::launch_sp_flow(sweep, d->max_level_width, d->has_cell_gates, flow_ctl(ev), s));
     } else if (ev->schedule == DP_SCHED_PERSISTENT) {
       dp::SpLevel lv{sp, ev->B, 0, 0};
@@ -606,7 +610,7 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
         DP_HIP_TRY(dp::launch_stim_words(sp, streams, d->n_pi, ev->B, pl->T, ev->prm.seed,
                                          ev->mstim.as<uint64_t>(), s));
     }
-    double bytes = 0.0;
+    double bytes = rides ? sp_bytes() : 0.0;
     for (int32_t l = 1; l <= d->depth; ++l)
       bytes += sim_level_bytes(d, l, pl->T, ev->B, ev->B, false);
     SpanGuard sg(ev, SPAN_SIM, bytes, prof, 1);

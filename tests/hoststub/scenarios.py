@@ -309,6 +309,24 @@ def scenario_deep_graphs(ctx):
     return out
 
 
+def scenario_profile(ctx):
+    """What the profile books a forward under (the stand-in's events are a
+    microsecond apart)."""
+    nl = synth.random_dag(synth.SPECS["dag2k"], 13)
+    d = api.Design(ctx, nl)
+    out = {}
+    for name, B, mode in (("modeled", 1, L.DP_MODELED), ("rides", 1, L.DP_HYBRID),
+                          ("rides2", 2, L.DP_HYBRID), ("apart", 3, L.DP_HYBRID)):
+        ev = api.Eval(d, B, mode=mode, n_sim=64 * 40, seed=8)
+        ev.set_pi_prob(synth.pi_probs(nl.n_pi, 13, batch=B))
+        ev.set_caps(synth.net_caps(nl.n_nets, 14))
+        ev.profile(True)
+        ev.forward(("power",))
+        out[name] = ev.get_profile()
+        ev.close()
+    return out
+
+
 def scenario_autotune(ctx):
     """What the autotuner times (launches of word tiles and of simulation levels),
     entered with each schedule."""
@@ -403,6 +421,7 @@ if __name__ == "__main__":
               "capture_order": scenario_capture_order,
               "group_persistent": scenario_group_persistent,
               "deep_graphs": scenario_deep_graphs,
+              "profile": scenario_profile,
               "autotune": scenario_autotune,
               "lane_memory": scenario_lane_memory,
               "large_faces": scenario_large_faces}[sys.argv[2]](context)

@@ -83,6 +83,19 @@ def test_reverse_graphs_of_deep_designs(stub_lib):
     assert _run(stub_lib, "deep_graphs") == {"1021": 1, "1022": 1, "1023": 1, "1024": 0}
 
 
+def test_profile_books_a_joint_launch_as_simulation(stub_lib):
+    r = _run(stub_lib, "profile")
+    assert r["modeled"]["sp_launches"] == 1 and r["modeled"]["sim_launches"] == 0
+    for k in ("rides", "rides2"):  # the SP sweep goes out with the tiles
+        assert r[k]["sp_launches"] == 0 and r[k]["sp_ms"] == 0 and r[k]["sp_bytes"] == 0, k
+        assert r[k]["sim_launches"] == 1
+    assert r["apart"]["sp_launches"] == 1 and r["apart"]["sim_launches"] == 1
+    # a column of SP bytes went to the simulation's
+    sim1, sim2, sim3 = (r[k]["sim_bytes"] for k in ("rides", "rides2", "apart"))
+    assert r["modeled"]["sp_bytes"] > 0
+    assert sim1 + sim2 > sim3 and sim2 > sim1
+
+
 def test_autotuner_times_the_same_from_any_schedule(stub_lib):
     r = _run(stub_lib, "autotune")
     assert r["level"][0] > 0 and r["persistent"] == r["level"]
