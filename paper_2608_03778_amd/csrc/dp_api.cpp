@@ -250,7 +250,7 @@ constexpr int32_t kTileTeams = 24, kTileWide = 8192;
 void plan_tiles(const dp_eval *ev, ChunkPlan *c) {
   const dp_design *d = ev->d;
   if (ev->words_per_chunk > 0 || ev->sim_streams > 1 || ev->sim_cols > 0 ||
-      d->depth < 1 || !flows(ev, ev->B) || c->T > kTileMaxWords / d->n_nets / ev->B)
+      std::chrono::steady_clock::now() < ev->tiles_retry || d->depth < 1 || !flows(ev, ev->B) || c->T > kTileMaxWords / d->n_nets / ev->B)
     return;
   for (int32_t pitch : {16, 32, 64}) {
     const int64_t tiles = (c->T + pitch - 1) / pitch * ev->B;
@@ -545,6 +545,24 @@ double bwd_level_bytes(const dp_design *d, int32_t l, int32_t C) {
   // structure: fan-out offsets and edge ids, fan-in indices, cell
   const double structure = 8.0 * n + 4.0 * fo + 4.0 * pins + n;
   return (double)C * per_col + structure;
+}
+
+// Plan a forward and make its buffers (*pl: null unless hybrid).  Tiles take up
+// to a few times the words of the level launches in their place: where the device
+// has no memory for them, level launches, and tiles again after a second.
+dp_status plan_forward(dp_eval *ev, ChunkPlan *plan, const ChunkPlan **pl) {
+  *pl = nullptr;
+  DP_TRY(ensure_flow(ev));
+  if (!hybrid(ev)) return ensure_forward_buffers(ev, nullptr);
+  *pl = plan;
+  *plan = plan_chunks(ev);
+  const dp_status st = ensure_forward_buffers(ev, plan);
+  if (st != DP_E_OOM || !plan->tile) return st;
+  ev->words.release();
+  if (!markov(ev)) ev->mstim.release();
+  ev->tiles_retry = std::chrono::steady_clock::now() + std::chrono::seconds(1);
+  *plan = plan_chunks(ev);
+  return ensure_forward_buffers(ev, plan);
 }
 
 // Enqueue the whole forward sweep (no host sync, no allocation).
@@ -1579,11 +1597,9 @@ dp_status dp_forward(dp_eval *ev, const dp_fwd_out *out) {
     return fail(DP_E_STATE, "dp_forward: the explicit stimulus is shorter than n_sim/64 words");
   DP_HIP_TRY(hipSetDevice(d->ctx->device));
   hipStream_t s = ev->stream();
-  DP_TRY(ensure_flow(ev));
   ChunkPlan plan;
-  if (hyb) plan = plan_chunks(ev);
-  const ChunkPlan *pl = hyb ? &plan : nullptr;
-  DP_TRY(ensure_forward_buffers(ev, pl));
+  const ChunkPlan *pl;
+  DP_TRY(plan_forward(ev, &plan, &pl));
   if (ev->schedule == DP_SCHED_GRAPH && forward_launches(ev, pl) > kMaxGraphLaunches)
     return fail(DP_E_UNSUPPORTED, "dp_forward: the sweep has " +
                 std::to_string(forward_launches(ev, pl)) + " launches, more than the " +
@@ -1822,7 +1838,7 @@ dp_status dp_forward_backward_columns(dp_eval *ev, float *power, float *dpower_d
                             "n_sim/64 words");
   DP_HIP_TRY(hipSetDevice(d->ctx->device));
   hipStream_t s = ev->stream();
-  DP_TRY(ensure_forward_buffers(ev, pl));
+  DP_TRY(plan_forward(ev, &plan, &pl));
   const int32_t C = ev->B * s_prime(ev);
   DP_TRY(ensure_reverse_buffers(ev, C, 1));
   const size_t dpi_bytes = (size_t)C * d->n_pi * sizeof(float);
@@ -2398,9 +2414,8 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
       explicit AsLevel(dp_eval *e) : ev(e) { ev->schedule = DP_SCHED_LEVEL; }
       ~AsLevel() { ev->schedule = own; }
     } as_level(ev);
-    DP_TRY(ensure_flow(ev));
-    if (hybrid(ev)) plans[i] = plan_chunks(ev);
-    DP_TRY(ensure_forward_buffers(ev, hybrid(ev) ? &plans[i] : nullptr));
+    const ChunkPlan *pl;
+    DP_TRY(plan_forward(ev, &plans[i], &pl));
     cost[i] = forward_launches(ev, hybrid(ev) ? &plans[i] : nullptr);
     if (backward) {
       DP_TRY(ensure_reverse_buffers(ev, ev->B));

@@ -327,6 +327,46 @@ def scenario_profile(ctx):
     return out
 
 
+def scenario_tile_memory(ctx):
+    """A short simulation on a device that holds the level launches' words and not
+    the tiles', and a second after there is memory."""
+    import ctypes
+    import time
+    stub = ctypes.CDLL(sys.argv[1])
+    stub.stub_live_bytes.restype = ctypes.c_long
+    counts = (ctypes.c_long * 2)()
+    nl = synth.random_dag(synth.SPECS["dag2k"], 13)
+    d = api.Design(ctx, nl)
+    out = {}
+
+    def sims(ev):
+        stub.stub_sim_counts(counts)
+        before = list(counts)
+        st = status_of(ev.forward, ("power",))[0]
+        stub.stub_sim_counts(counts)
+        return [st, counts[0] > before[0], counts[1] > before[1]]
+    for sched in (L.DP_SCHED_LEVEL, L.DP_SCHED_GRAPH):
+        def make():
+            ev = api.Eval(d, 1, mode=L.DP_HYBRID, n_sim=64 * 1280, seed=8)
+            ev.set_pi_prob(synth.pi_probs(nl.n_pi, 13))
+            ev.set_caps(synth.net_caps(nl.n_nets, 14))
+            ev.set_schedule(sched)
+            return ev
+        ev = make()
+        out[f"{sched} all"] = sims(ev)
+        live = stub.stub_live_bytes()
+        ev.close()
+        ev = make()
+        stub.stub_set_memory(live - 100_000)
+        out[f"{sched} less"] = sims(ev)
+        out[f"{sched} again"] = sims(ev)
+        stub.stub_set_memory(0)
+        time.sleep(1.1)
+        out[f"{sched} later"] = sims(ev)
+        ev.close()
+    return out
+
+
 def scenario_autotune(ctx):
     """What the autotuner times (launches of word tiles and of simulation levels),
     entered with each schedule."""
@@ -422,6 +462,7 @@ if __name__ == "__main__":
               "group_persistent": scenario_group_persistent,
               "deep_graphs": scenario_deep_graphs,
               "profile": scenario_profile,
+              "tile_memory": scenario_tile_memory,
               "autotune": scenario_autotune,
               "lane_memory": scenario_lane_memory,
               "large_faces": scenario_large_faces}[sys.argv[2]](context)

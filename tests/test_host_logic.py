@@ -96,6 +96,15 @@ def test_profile_books_a_joint_launch_as_simulation(stub_lib):
     assert sim1 + sim2 > sim3 and sim2 > sim1
 
 
+def test_simulation_without_memory_for_tiles(stub_lib):
+    r = _run(stub_lib, "tile_memory")
+    for sched in (1, 2):  # status, tiles, level launches (a replayed graph makes none)
+        assert r[f"{sched} all"] == ["OK", True, False]
+        assert r[f"{sched} less"] == ["OK", False, True]
+        assert r[f"{sched} again"] == ["OK", False, sched == 1]
+        assert r[f"{sched} later"] == ["OK", True, False]
+
+
 def test_autotuner_times_the_same_from_any_schedule(stub_lib):
     r = _run(stub_lib, "autotune")
     assert r["level"][0] > 0 and r["persistent"] == r["level"]
