@@ -138,6 +138,9 @@ static size_t g_limit = 0, g_host = 0;
 void stub_set_memory(long bytes) { g_limit = (size_t)bytes; }
 // Dataflow launches over several designs, and merged level launches.
 static long g_flow_multi = 0, g_level_multi = 0;
+// The next n dataflow launches over several designs report a wait that gave up.
+static long g_fail_flows = 0;
+void stub_fail_flows(long n) { g_fail_flows = n; }
 // Launches of word tiles, and of simulation levels.
 static long g_sim_flow = 0, g_sim_level = 0;
 void stub_sim_counts(long *out) {
@@ -818,6 +821,7 @@ hipError_t launch_sp_flow_multi(const SpFlowSeg *segs, int32_t n_segs, int32_t j
                                 hipStream_t stream_) {
   Scope sc_(stream_);
   ++g_flow_multi;
+  if (g_fail_flows > 0 && g_fail_flows-- > 0) *ctl.report = 1u;
   int32_t job = 0;
   uint32_t block = 0;
   for (int32_t k = 0; k < n_segs; ++k) {

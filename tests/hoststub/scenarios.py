@@ -390,6 +390,24 @@ def scenario_autotune(ctx):
     return out
 
 
+def scenario_server_give_up(ctx):
+    """A serving step whose sweep gives up, and the steps after it."""
+    import ctypes
+    stub = ctypes.CDLL(sys.argv[1])
+    nls = [synth.random_dag(synth.SPECS["dag2k"], 12), synth.random_dag(synth.DagSpec(900, 30, 9), 13)]
+    srv = api.Server(ctx, hbm_budget_bytes=64 << 20, max_batch=8, max_inflight=1)
+    ids = [srv.add_design(api.Design(ctx, nl), synth.net_caps(nl.n_nets, 20)) for nl in nls]
+
+    def query(i):
+        return status_of(srv.wait, srv.submit(ids[i], np.full(nls[i].n_pi, 0.5, np.float32), None, True))
+    out = {"before": [query(i)[0] for i in (0, 1)]}
+    stub.stub_fail_flows(1)
+    out["failed"] = query(0)
+    out["after"] = [query(i)[0] for i in (0, 1, 0)]
+    srv.close()
+    return out
+
+
 def scenario_lane_memory(ctx):
     """Serving with a device that has less memory than the budget says: enough
     for a lane, and not for its dataflow sweeps' buffers."""
@@ -464,6 +482,7 @@ if __name__ == "__main__":
               "profile": scenario_profile,
               "tile_memory": scenario_tile_memory,
               "autotune": scenario_autotune,
+              "server_give_up": scenario_server_give_up,
               "lane_memory": scenario_lane_memory,
               "large_faces": scenario_large_faces}[sys.argv[2]](context)
     print(json.dumps(result), flush=True)

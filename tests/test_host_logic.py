@@ -110,6 +110,12 @@ def test_autotuner_times_the_same_from_any_schedule(stub_lib):
     assert r["level"][0] > 0 and r["persistent"] == r["level"]
 
 
+def test_server_step_that_gave_up(stub_lib):
+    r = _run(stub_lib, "server_give_up")
+    assert r["before"] == ["OK"] * 2 and r["after"] == ["OK"] * 3
+    assert r["failed"][0] == "DP_E_HIP" and "gave up" in r["failed"][1]
+
+
 def test_lane_without_memory_for_its_dataflow_buffers(stub_lib):
     r = _run(stub_lib, "lane_memory")
     assert r["all"][:3] == [True, True, False]   # done, dataflow, merged levels
