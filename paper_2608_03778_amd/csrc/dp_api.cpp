@@ -232,7 +232,7 @@ struct ChunkPlan {
 
 int32_t n_sim_streams(const dp_eval *ev) { return ev->sim_streams > 0 ? ev->sim_streams : 1; }
 
-bool flows(const dp_eval *ev, int32_t C);
+bool flow_ready(const dp_eval *ev, int32_t C);
 
 // Whether the simulation runs in word tiles, and in which: with chunks, streams
 // and columns left automatic and the SP sweep a dataflow launch of its own.  Up to 24 tiles are a round of the teams; of the pitches
@@ -250,7 +250,8 @@ constexpr int32_t kTileTeams = 24, kTileWide = 8192;
 void plan_tiles(const dp_eval *ev, ChunkPlan *c) {
   const dp_design *d = ev->d;
   if (ev->words_per_chunk > 0 || ev->sim_streams > 1 || ev->sim_cols > 0 ||
-      std::chrono::steady_clock::now() < ev->tiles_retry || d->depth < 1 || !flows(ev, ev->B) || c->T > kTileMaxWords / d->n_nets / ev->B)
+      std::chrono::steady_clock::now() < ev->tiles_retry || d->depth < 1 ||
+      !flow_ready(ev, ev->B) || c->T > kTileMaxWords / d->n_nets / ev->B)
     return;
   for (int32_t pitch : {16, 32, 64}) {
     const int64_t tiles = (c->T + pitch - 1) / pitch * ev->B;
@@ -364,13 +365,71 @@ dp_status ensure_flow(dp_eval *ev) {
   return ensure_reports(ev);
 }
 
-// Whether a sweep over C columns of the eval runs as one dataflow launch
+// Whether a sweep over C columns of the eval can run as one dataflow launch
 // (once ensure_flow has run).
-bool flows(const dp_eval *ev, int32_t C) {
+bool flow_ready(const dp_eval *ev, int32_t C) {
   const dp_design *d = ev->d;
   return ev->flow.ptr && ev->schedule != DP_SCHED_PERSISTENT &&
          dp::flow_fits(view(d), d->depth, std::max(C, ev->B), d->n_edges);
 }
+
+// What a sweep takes, in us, of G million gates and N million (net, column)
+// pairs over D levels: base + |(level D, gates G rounds + pairs N + far N log2 N)|
+// + over N.  A level's latency and its work overlap, hence the root of squares.
+// A dataflow sweep keeps a column in one XCD: its latency per level is a
+// fraction of a launch's, its work goes by rounds of eight columns, and columns
+// share lines that every XCD fetches; level launches have the whole chip for each
+// level.  So few levels of many gates are faster in level launches (1M gates,
+// one column, forward / gradient in us, levels against dataflow: 8 levels 46 /
+// 117 against 71 / 153, 25 levels 83 / 144 against 80 / 143, 100 levels 233 / 401
+// against 125 / 214; 117K gates, 16 columns: 3 levels 25 / 29 against 83 / 150, 60
+// levels 128 / 245 against 84 / 124).  Fitted to 334 (design, columns) of 2K to
+// 3.5M gates, 2 to 400 levels, 1 to 64 columns and 94 with library cells in half
+// of the gates; over the former the choice is 0.1 % (forward) and 0.4 % (gradient)
+// slower than the better of the two on average and at most 2 % slower than level
+// launches (the bases lean that way by 2 and 3 us).
+struct SweepCost {
+  double base, level, gates, pairs, far, over;
+};
+constexpr SweepCost kSpFlow{20.5, 0.72, 31.6, 26.8, 0.0, 0.0}, kSpLevels{12.7, 1.82, 16.7, 0.0, 0.0, 7.9};
+constexpr SweepCost kBwdFlow{13.4, 0.80, 118.6, 24.1, 7.3, 0.0}, kBwdLevels{5.1, 3.81, 123.0, 0.0, 0.0, 4.9};
+// (level launches of one or two columns pull with whole waves)
+constexpr SweepCost kBwdFlowFew{11.6, 0.74, 87.8, 61.4, 0.0, 0.0},
+    kBwdLevelsFew{22.0, 2.80, 19.0, 0.0, 0.0, 71.5};
+// every level with library cells
+constexpr SweepCost kSpFlowCells{15.3, 5.6, 86.6, 20.4, 0.0, 0.0},
+    kSpLevelsCells{10.4, 8.3, 17.1, 6.5, 0.0, 4.2};
+constexpr SweepCost kBwdFlowCells{40.1, 0.93, 163.2, 85.5, 0.0, 0.0},
+    kBwdLevelsCells{18.9, 28.7, 265.0, 0.0, 0.0, 43.6};
+// gates: a column's, with the rounds of columns that follow one another; pairs:
+// of all columns; both in millions.
+double sweep_us(const SweepCost &c, double depth, double gates, double pairs) {
+  const double work = c.gates * gates + c.pairs * pairs +
+                      (pairs > 1.0 ? c.far * pairs * std::log2(pairs) : 0.0);
+  return c.base + std::hypot(c.level * depth, work) + c.over * pairs;
+}
+// The same with library cells in `cells` of the levels.
+double sweep_us(const SweepCost &fixed, const SweepCost &lib, const dp_design *d, double gates,
+                double pairs) {
+  const double us = sweep_us(fixed, d->depth, gates, pairs);
+  if (d->cell_levels == 0) return us;
+  const double part = (double)d->cell_levels / d->depth;
+  return (1.0 - part) * us + part * sweep_us(lib, d->depth, gates, pairs);
+}
+bool flow_pays(const dp_design *d, int32_t C, bool reverse) {
+  const double G = d->n_gates * 1e-6, N = (double)d->n_nets * C * 1e-6, rounds = (C + 7) / 8;
+  if (!reverse)
+    return sweep_us(kSpFlow, kSpFlowCells, d, G * rounds, N) <
+           sweep_us(kSpLevels, kSpLevelsCells, d, G, N);
+  const bool few = C < 3;
+  return sweep_us(few ? kBwdFlowFew : kBwdFlow, kBwdFlowCells, d, G * rounds, N) <
+         sweep_us(few ? kBwdLevelsFew : kBwdLevels, kBwdLevelsCells, d, G, N);
+}
+
+// Whether the eval's SP sweep, and a reverse sweep over C columns, run as one
+// dataflow launch.
+bool sp_flows(const dp_eval *ev) { return flow_ready(ev, ev->B) && flow_pays(ev->d, ev->B, false); }
+bool bwd_flows(const dp_eval *ev, int32_t C) { return flow_ready(ev, C) && flow_pays(ev->d, C, true); }
 
 // Whether the per-(b, s) reverse sweep over C columns runs in adjoints
 // (launch_bwd_wide_level): from 16 size vectors, which then share an entry's
@@ -378,7 +437,7 @@ bool flows(const dp_eval *ev, int32_t C) {
 constexpr int32_t kWideSizes = 16;
 bool wide_reverse(const dp_eval *ev, int32_t C, int per_column) {
   return per_column && s_prime(ev) >= kWideSizes && ev->schedule != DP_SCHED_PERSISTENT &&
-         !flows(ev, C);
+         !bwd_flows(ev, C);
 }
 
 // Every buffer of a reverse sweep over C columns (before any capture).
@@ -390,7 +449,7 @@ dp_status ensure_reverse_buffers(dp_eval *ev, int32_t C, int per_column = 0) {
     return ev->part.alloc(std::max<size_t>((size_t)d->n_edges * ev->B * sizeof(float), 16));
   }
   DP_TRY(ev->contrib.alloc(std::max<size_t>((size_t)d->n_edges * C * sizeof(float), 16)));
-  if (flows(ev, C)) {
+  if (bwd_flows(ev, C)) {
     DP_TRY(ev->seed.alloc(std::max<size_t>((size_t)d->n_nets * C * sizeof(float), 16)));
     DP_TRY(ev->part.alloc(std::max<size_t>((size_t)ev->B * d->pins * d->n_gates * sizeof(float), 16)));
   }
@@ -586,10 +645,10 @@ dp_status enqueue_forward(dp_eval *ev, const ChunkPlan *pl) {
     DP_HIP_TRY(dp::launch_sp_arm(sweep, flow_ctl(ev), s));
   } else if (!pl || pl->tile) {  // modeled (or frozen-beta) sweep: one span over all level launches
     SpanGuard sg(ev, SPAN_SP, sp_bytes(), prof && d->depth > 0,
-                 ev->schedule == DP_SCHED_PERSISTENT || flows(ev, ev->B)
+                 ev->schedule == DP_SCHED_PERSISTENT || sp_flows(ev)
                      ? 1
                      : sp_sweep_launches(d, ev->B));
-    if (flows(ev, ev->B)) {
+    if (sp_flows(ev)) {
       DP_HIP_TRY(dp::launch_sp_flow(sweep, d->max_level_width, d->has_cell_gates, flow_ctl(ev), s));
     } else if (ev->schedule == DP_SCHED_PERSISTENT) {
       dp::SpLevel lv{sp, ev->B, 0, 0};
@@ -949,7 +1008,7 @@ dp_status enqueue_backward(dp_eval *ev, const dp::BwdArgs &ba, float *dst) {
   const dp::GraphView g = view(d);
   double bwd_bytes = 0.0;
   for (int32_t l = d->depth; l >= 1; --l) bwd_bytes += bwd_level_bytes(d, l, ba.C);
-  if (flows(ev, ba.C)) {
+  if (bwd_flows(ev, ba.C)) {
     const dp::FlowCtl ctl = flow_ctl(ev);
     SpanGuard sg(ev, SPAN_BWD, bwd_bytes, ev->profiling && d->depth > 0, 1);
     DP_HIP_TRY(dp::launch_bwd_flow(
@@ -2006,7 +2065,7 @@ bool FlowTables::fits(const MergedTables::Lane *lanes, int32_t n) {
   int64_t jobs = 0, items = 0;
   for (int32_t j = 0; j < n; ++j) {
     const dp_eval *ev = lanes[j].ev;
-    if (!flows(ev, ev->B) || (lanes[j].backward && !ev->part.ptr)) return false;
+    if (!flow_ready(ev, ev->B) || (lanes[j].backward && !ev->part.ptr)) return false;
     jobs += ev->B;
     items += (int64_t)ev->d->n_nets * ev->B;
   }

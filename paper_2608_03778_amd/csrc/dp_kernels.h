@@ -447,14 +447,12 @@ inline int32_t flow_first_block(int32_t w, int32_t waves, int32_t shifts, int32_
 }
 // Whether a sweep of C columns is one for these kernels: within their 32-bit
 // offsets and tables, and few enough (net, column) pairs that its levels are
-// bound by latency.  Forward / reverse sweep by level launches against
-// dataflow, in us: 1M gates, 1 column 222 / 394 against 123 / 214, 4 columns
-// 233 / 515 against 183 / 301; 117K gates, 1 column 127 / 212 against 55 / 87,
-// 16 columns 133 / 263 against 88 / 142, 32 columns 143 / 261 against 114 /
-// 268; 50K gates, 64 columns 121 / 179 against 100 / 157; 20K gates, 64 columns
-// 93 / 144 against 73 / 73.  Beyond: 1M gates, 8 columns 238 / 526 against 243 /
-// 521, 16 columns 245 / 546 against 487 / 1243; 117K gates, 64 columns 156 / 269
-// against 237 / 463.
+// bound by latency at the depths designs have (forward / reverse sweep by level
+// launches against dataflow, in us: 1M gates x 100 levels, 4 columns 233 / 515
+// against 183 / 301, 8 columns 238 / 526 against 243 / 521; 117K gates x 60
+// levels, 32 columns 143 / 261 against 114 / 268, 64 columns 156 / 269 against
+// 237 / 463).  Which of the two a sweep within these limits takes depends on
+// its depth too (the eval's rule).
 constexpr int64_t kFlowMaxItems = 1 << 22;
 // Jobs and (net, column) pairs of a sweep over several designs.
 constexpr int32_t kFlowMaxJobs = kFlowMaxCols;

@@ -138,6 +138,10 @@ static size_t g_limit = 0, g_host = 0;
 void stub_set_memory(long bytes) { g_limit = (size_t)bytes; }
 // Dataflow launches over several designs, and merged level launches.
 static long g_flow_multi = 0, g_level_multi = 0;
+// Modeled SP and reverse sweeps: dataflow launches, level launches, and those of
+// the reverse sweep in adjoints.
+static long g_sweeps[5] = {};
+void stub_sweep_counts(long *out) { std::copy(g_sweeps, g_sweeps + 5, out); }
 // The next n dataflow launches over several designs report a wait that gave up.
 static long g_fail_flows = 0;
 void stub_fail_flows(long n) { g_fail_flows = n; }
@@ -428,12 +432,14 @@ hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, float *
 }
 hipError_t launch_sp_level(const GraphView &g, const SpLevel &lv, bool cells, hipStream_t stream_) {
   Scope sc_(stream_);
+  ++g_sweeps[1];
   rd_graph(g, lv.g0, lv.n, cells);
   wr(lv.sp + (int64_t)(g.n_pi + lv.g0) * lv.B, (int64_t)lv.n * lv.B);
   return hipSuccess;
 }
 hipError_t launch_sp_pair(const GraphView &g, const SpLevel &a, const SpLevel &b, hipStream_t stream_) {
   Scope sc_(stream_);
+  ++g_sweeps[1];
   if (a.B != b.B || a.sp != b.sp || b.g0 != a.g0 + a.n) fatal("level pair not adjacent");
   rd_graph(g, a.g0, a.n, false);
   rd_graph(g, b.g0, b.n, false);
@@ -627,6 +633,7 @@ hipError_t launch_bwd_level(const GraphView &g, const BwdArgs &a, int32_t g0, in
                             bool cells, hipStream_t stream_, const int32_t *heavy,
                             int32_t n_heavy) {
   Scope sc_(stream_);
+  if (n > 0) ++g_sweeps[3];
   rd_graph(g, g0, n, cells);
   // the heavy list: every gate of the range whose fan-out range is longer
   // than kHeavyPull, ascending, and nothing else
@@ -665,6 +672,7 @@ hipError_t launch_bwd_wide_level(const GraphView &g, const BwdArgs &a, const flo
                                  int32_t net0, int32_t n, hipStream_t stream_, const int32_t *heavy,
                                  int32_t n_heavy) {
   Scope sc_(stream_);
+  ++g_sweeps[4];
   if (!a.per_column || a.lam || net0 < 0 || net0 + n > g.n_nets) fatal("wide reverse range");
   if (net0 != 0 && net0 < g.n_pi) fatal("wide reverse range over PIs and gates");
   int32_t k = 0;  // the heavy list: gates, or PIs, of the range
@@ -759,6 +767,7 @@ static void flow_blocks_ok() {
 hipError_t launch_sp_flow(const SpFlow &t, int64_t widest, bool cells, FlowCtl ctl,
                           hipStream_t stream_) {
   Scope sc_(stream_);
+  ++g_sweeps[0];
   flow_ctl_ok(ctl);
   flow_blocks_ok();
   if (!flow_fits(t.g, t.depth, t.B, 0)) fatal("dataflow sweep out of its range");
@@ -797,6 +806,7 @@ hipError_t launch_sim_flow(const SimFlow &t, const SpFlow &sweep, int64_t widest
 hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl ctl,
                            hipStream_t stream_) {
   Scope sc_(stream_);
+  ++g_sweeps[2];
   flow_ctl_ok(ctl);
   if (!flow_fits(t.g, t.depth, t.a.C, t.n_edges)) fatal("dataflow sweep out of its range");
   if (t.g.n_pi > widest) fatal("startpoints wider than their sweep");

@@ -408,6 +408,37 @@ def scenario_server_give_up(ctx):
     return out
 
 
+def scenario_sweep_routes(ctx):
+    """Whether the SP and the reverse sweep of a shape go out as dataflow launches."""
+    import ctypes
+    stub = ctypes.CDLL(sys.argv[1])
+    counts = (ctypes.c_long * 5)()
+    out = {}
+    lib = tuple(range(9)) + tuple(synth.CELL_BASE + c for c in range(len(synth.LIBRARY)))
+    for gates, pis, depth, ops, cells in ((2000, 64, 20, tuple(range(9)), ()), (20_000, 500, 2, tuple(range(9)), ()),
+                                          (20_000, 500, 60, tuple(range(9)), ()),
+                                          (117_000, 2000, 3, tuple(range(9)), ()),
+                                          (117_000, 2000, 60, tuple(range(9)), ()),
+                                          (20_000, 500, 2, lib, synth.LIBRARY),
+                                          (20_000, 500, 60, lib, synth.LIBRARY)):
+        nl = synth.random_dag(synth.DagSpec(gates, pis, depth, ops=ops, cells=cells), 13)
+        d = api.Design(ctx, nl)
+        for B in (1, 16, 64):
+            ev = api.Eval(d, B)
+            ev.set_pi_prob(np.full((B, nl.n_pi), 0.5, np.float32))
+            ev.set_caps(synth.net_caps(nl.n_nets, 14))
+            stub.stub_sweep_counts(counts)
+            c0 = list(counts)
+            ev.forward(("power",))
+            ev.backward(want=("dpi",))
+            stub.stub_sweep_counts(counts)
+            got = [counts[k] - c0[k] for k in range(5)]
+            assert (got[0] > 0) != (got[1] > 0) and (got[2] > 0) != (got[3] > 0), got
+            out[f"{gates} {depth} {'cells' if cells else 'fixed'} {B}"] = [got[0] > 0, got[2] > 0]
+            ev.close()
+    return out
+
+
 def scenario_lane_memory(ctx):
     """Serving with a device that has less memory than the budget says: enough
     for a lane, and not for its dataflow sweeps' buffers."""
@@ -483,6 +514,7 @@ if __name__ == "__main__":
               "tile_memory": scenario_tile_memory,
               "autotune": scenario_autotune,
               "server_give_up": scenario_server_give_up,
+              "sweep_routes": scenario_sweep_routes,
               "lane_memory": scenario_lane_memory,
               "large_faces": scenario_large_faces}[sys.argv[2]](context)
     print(json.dumps(result), flush=True)

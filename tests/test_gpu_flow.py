@@ -241,3 +241,43 @@ def test_group_of_evals_with_the_persistent_schedule(ctx, graph):
         for k in ref:
             np.testing.assert_array_equal(r[k], ref[k], err_msg=k)
     g.close()
+
+
+def _with_chain(nl, levels):
+    """The netlist with a chain of inverters from its last gate: designs of few
+    levels take level launches."""
+    ptr, fan = nl.fanin_ptr, nl.fanin
+    gates = [(int(nl.op[g]), fan[ptr[g]:ptr[g + 1]].tolist()) for g in range(nl.n_gates)]
+    last = nl.n_nets - 1
+    gates += [(synth.INV, [last + i]) for i in range(levels)]
+    return synth.from_gates(nl.n_pi, gates)
+
+
+@pytest.mark.parametrize("gates,pis,depth,B", [
+    (5, 3, 5, 1), (63, 4, 1, 1), (64 * 4, 70, 4, 2), (65 * 3, 9, 3, 9), (40_000, 90, 1, 1),
+    (70_000, 40_000, 2, 3), (20_000, 500, 2, 40)])
+@pytest.mark.parametrize("mode,ste", [(L.DP_MODELED, False), (L.DP_HYBRID, True)])
+def test_flow_of_wide_levels_in_deep_designs(ctx, gates, pis, depth, B, mode, ste):
+    say(f"dataflow sweep, deep: {gates} gates, {pis} PIs, depth {depth}, B={B}, mode {mode}, ste {ste}")
+    nl = _with_chain(synth.random_dag(synth.DagSpec(gates, pis, depth), 11), 200)
+    d = api.Design(ctx, nl)
+    fixed = (np.arange(pis) % 5 == 0).astype(np.uint8)
+    ref = _run(d, nl, L.DP_SCHED_PERSISTENT, B, mode, ste, fixed)
+    for sched in (L.DP_SCHED_AUTO, L.DP_SCHED_GRAPH):
+        r = _run(d, nl, sched, B, mode, ste, fixed)
+        for k in ref:
+            np.testing.assert_array_equal(r[k], ref[k], err_msg=f"{k}, schedule {sched}")
+
+
+@pytest.mark.parametrize("readers", [32, 33, 64, 65, 256, 257, 600, 1300])
+def test_flow_long_fanout_ranges_in_deep_designs(ctx, readers):
+    say(f"dataflow sweep, deep: {readers} readers")
+    gates = [(synth.AND2, [0, 1])]
+    gates += [(synth.XOR2 if i % 2 else synth.OR2, [3, 0 if i % 3 else 2]) for i in range(readers)]
+    gates += [(synth.MUX2, [4 + i, 3, 4 + (i * 7) % readers]) for i in range(readers)]
+    nl = _with_chain(synth.from_gates(3, gates), 200)
+    d = api.Design(ctx, nl)
+    ref = _run(d, nl, L.DP_SCHED_PERSISTENT, 2, L.DP_MODELED)
+    r = _run(d, nl, L.DP_SCHED_AUTO, 2, L.DP_MODELED)
+    for k in ref:
+        np.testing.assert_array_equal(r[k], ref[k], err_msg=k)

@@ -116,6 +116,21 @@ def test_server_step_that_gave_up(stub_lib):
     assert r["failed"][0] == "DP_E_HIP" and "gave up" in r["failed"][1]
 
 
+def test_dataflow_sweeps_where_they_pay(stub_lib):
+    """Forward and reverse of shapes measured well on either side of the line."""
+    r = _run(stub_lib, "sweep_routes")
+    want = {"2000 20 fixed": {1: [True, True], 16: [True, True], 64: [True, True]},
+            "20000 2 fixed": {1: [False, True], 16: [False, False], 64: [False, False]},
+            "20000 60 fixed": {1: [True, True], 16: [True, True], 64: [True, True]},
+            "117000 3 fixed": {1: [False, True], 16: [False, False], 64: [False, False]},
+            "117000 60 fixed": {1: [True, True], 16: [True, True], 64: [False, False]},
+            "20000 2 cells": {64: [False, False]},
+            "20000 60 cells": {1: [True, True], 16: [True, True], 64: [True, True]}}
+    for shape, by_columns in want.items():
+        for columns, route in by_columns.items():
+            assert r[f"{shape} {columns}"] == route, (shape, columns)
+
+
 def test_lane_without_memory_for_its_dataflow_buffers(stub_lib):
     r = _run(stub_lib, "lane_memory")
     assert r["all"][:3] == [True, True, False]   # done, dataflow, merged levels
