@@ -390,3 +390,42 @@ def test_pin_list_errors(ctx):
     for bad in ("I0,I1", "I0,I1,S,T", "I0,I0,S", "I0,I1,X", "I0;I1;S"):
         with pytest.raises(L.DiffPowerError, match="INVALID"):
             api.Design(ctx, dataclasses.replace(nl, pins=(bad,)))
+
+
+def _cell(k):
+    """The k-th of a family of different cells: 2 to 6 inputs, NOTs anywhere,
+    balanced and chained forms (up to three values wait)."""
+    r = np.random.default_rng(k)
+    names = "ABCDEF"[:2 + k % 5]
+    terms = [("!" if r.integers(2) else "") + n for n in names]
+    while len(terms) > 1:
+        i = int(r.integers(len(terms) - 1))
+        a, b = terms[i], terms.pop(i + 1)
+        terms[i] = f"{'!' if r.integers(2) else ''}({a}{'&|^'[r.integers(3)]}{b})"
+    return terms[0]
+
+
+@pytest.mark.parametrize("n_cells", [1, 4, 5, 6, 20, 64, 150])
+def test_sp_level_of_many_different_cells(n_cells):
+    """One-column level launches (the forward without allocation) of waves with
+    few and many different cells: bit for bit the sweeps of more columns, whose
+    waves hold fewer, and the oracle's."""
+    say(f"levels of {n_cells} different cells")
+    import torch
+    cells = tuple(dict.fromkeys(_cell(k) for k in range(4 * n_cells)))[:n_cells]
+    assert len(cells) == n_cells
+    ops = tuple(synth.CELL_BASE + c for c in range(n_cells)) + ((0,) if n_cells > 1 else ())
+    nl = synth.random_dag(synth.DagSpec(700, 40, 7, ops=ops, cells=cells), 51)
+    d = api.Design(api.Context(0), nl)
+    p, cap = synth.pi_probs(nl.n_pi, 52, batch=70), synth.net_caps(nl.n_nets, 53)
+    ev = api.Eval(d, 70)
+    ev.set_pi_prob(p)
+    ev.set_caps(cap)
+    want = ev.forward(("sp",))["sp"]
+    power, sp = torch.empty(1, device="cuda"), torch.empty(nl.n_nets, device="cuda")
+    for b in (0, 69):
+        d.forward_static(torch.from_numpy(p[b]).cuda(), torch.from_numpy(cap).cuda(), out_power=power, out_sp=sp)
+        d.ctx.synchronize()
+        np.testing.assert_array_equal(sp.cpu().numpy(), want[b])
+        f, _ = oracle_column(oracle.Netlist.of(nl), p[b], cap)
+        assert np.abs(want[b] - f["sp"]).max() <= SP_ABS
