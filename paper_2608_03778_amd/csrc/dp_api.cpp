@@ -384,8 +384,10 @@ bool flow_ready(const dp_eval *ev, int32_t C) {
 // 117 against 71 / 153, 25 levels 83 / 144 against 80 / 143, 100 levels 233 / 401
 // against 125 / 214; 117K gates, 16 columns: 3 levels 25 / 29 against 83 / 150, 60
 // levels 128 / 245 against 84 / 124).  Fitted to 334 (design, columns) of 2K to
-// 3.5M gates, 2 to 400 levels, 1 to 64 columns and 94 with library cells in half
-// of the gates; over the former the choice is 0.1 % (forward) and 0.4 % (gradient)
+// 3.5M gates, 2 to 400 levels, 1 to 64 columns and 113 with 9 to 200 library
+// cells in half of the gates or all (20K gates x 2 levels of nine cells, 32
+// columns, 33 / 98 against 48 / 117; 117K x 12, one column, 107 / 367 against 66 /
+// 67); over the former the choice is 0.1 % (forward) and 0.4 % (gradient)
 // slower than the better of the two on average and at most 2 % slower than level
 // launches (the bases lean that way by 2 and 3 us).
 struct SweepCost {
@@ -397,10 +399,10 @@ constexpr SweepCost kBwdFlow{13.4, 0.80, 118.6, 24.1, 7.3, 0.0}, kBwdLevels{5.1,
 constexpr SweepCost kBwdFlowFew{11.6, 0.74, 87.8, 61.4, 0.0, 0.0},
     kBwdLevelsFew{22.0, 2.80, 19.0, 0.0, 0.0, 71.5};
 // every level with library cells
-constexpr SweepCost kSpFlowCells{15.3, 5.6, 86.6, 20.4, 0.0, 0.0},
-    kSpLevelsCells{10.4, 8.3, 17.1, 6.5, 0.0, 4.2};
-constexpr SweepCost kBwdFlowCells{40.1, 0.93, 163.2, 85.5, 0.0, 0.0},
-    kBwdLevelsCells{18.9, 28.7, 265.0, 0.0, 0.0, 43.6};
+constexpr SweepCost kSpFlowCells{16.9, 3.79, 89.4, 25.5, 0.0, 0.0},
+    kSpLevelsCells{10.6, 7.61, 24.1, 0.0, 0.0, 6.9};
+constexpr SweepCost kBwdFlowCells{39.9, 1.64, 151.0, 92.4, 0.0, 0.0},
+    kBwdLevelsCells{7.2, 34.9, 237.6, 0.0, 0.0, 39.9};
 // gates: a column's, with the rounds of columns that follow one another; pairs:
 // of all columns; both in millions.
 double sweep_us(const SweepCost &c, double depth, double gates, double pairs) {
