@@ -235,18 +235,37 @@ int32_t n_sim_streams(const dp_eval *ev) { return ev->sim_streams > 0 ? ev->sim_
 bool flow_ready(const dp_eval *ev, int32_t C);
 
 // Whether the simulation runs in word tiles, and in which: with chunks, streams
-// and columns left automatic and the SP sweep a dataflow launch of its own.  Up to 24 tiles are a round of the teams; of the pitches
-// that stay within it the narrowest (a level's turns grow with the pitch),
-// and 64 words up to 32 tiles.  Beyond, and beyond 2^28 words over all nets
-// and columns, the level launches' longer rows are the faster ones (forward,
+// and columns left automatic.  Up to 24 tiles are a round of the teams; of the
+// pitches that stay within it the narrowest (a level's turns grow with the
+// pitch), and 64 words up to 32 tiles.  Beyond, and beyond 2^28 words over all
+// nets and columns, the level launches' longer rows are the faster ones (forward,
 // us, tiles against levels: 2K gates x 1280 words 105 / 123, x 5120 184 / 167;
 // 117K x 257 271 / 424, x 1024 638 / 691; 300K x 1024 1516 / 1368; 1M x 257
 // 1670 / 1966), as they are where fewer than 16 tiles leave XCDs without work
 // in levels of more than 8192 gates (1M x 64: 899 / 817).  Half library cells,
 // 300K x 256, with the reverse sweep: 1074 / 1914.  (Their kernel's registers
 // leave room for 24 teams.)
+// A level saves its launch, 3.4 us (11 with library cells); level launches read
+// rows shorter than a wave's 128 words at 2 us more per million (net, column) and
+// word short, and rows of an odd number of words at 1.5 us more per million words
+// (117K gates x 3 levels: 256 words 150, 257 words 199).  A tile's rows cost 12 us
+// per million words of one tile more, and what the columns' last tiles leave
+// empty, beyond a sixteenth, 4 us per million words (300K gates x 20 levels, 5
+// columns of 100 words: 935 / 828).  So with few levels of many gates level launches win (forward, us, tiles
+// against levels: 117K gates x 3 levels x 1024 words 505 / 414, x 12 567 / 493, x 60
+// 629 / 720; 1M x 256 words, 8 levels 1279 / 1065, 50 1383 / 1260, 100 1390 / 1461).
+// Over 390 (design, columns, words) within the limits above the choice is at most
+// 6 us slower than level launches (designs of two or three levels), or 2 %.
 constexpr int64_t kTileMaxWords = 1ll << 28;
 constexpr int32_t kTileTeams = 24, kTileWide = 8192;
+bool tiles_pay(const dp_design *d, int32_t B, int64_t T, int64_t tiles, int32_t pitch) {
+  const double n = d->n_nets * 1e-6, words = (double)(B * T), held = (double)(tiles * pitch);
+  const double saved = 3.4 * d->depth + 8.0 * d->cell_levels +
+                       2.0 * n * B * (double)std::max<int64_t>(0, 128 - T) +
+                       (T % 2 != 0 ? 1.5 * n * words : 0.0);
+  return saved > 8.0 + std::max(0.0, 12.0 * n * pitch - 25.0) +
+                     4.0 * n * std::max(0.0, held * (15.0 / 16.0) - words);
+}
 void plan_tiles(const dp_eval *ev, ChunkPlan *c) {
   const dp_design *d = ev->d;
   if (ev->words_per_chunk > 0 || ev->sim_streams > 1 || ev->sim_cols > 0 ||
@@ -258,6 +277,7 @@ void plan_tiles(const dp_eval *ev, ChunkPlan *c) {
     if (tiles > (pitch < 64 ? kTileTeams : dp::kSimBufs)) continue;
     if (tiles < 16 && d->max_level_width > kTileWide) return;
     if (!dp::sim_fits(view(d), d->depth, ev->B, pitch, c->T)) return;
+    if (!tiles_pay(d, ev->B, c->T, tiles, pitch)) return;
     c->n_chunks = 1;  // of the level launches in its place
     c->tile = pitch;
     c->n_tiles = (int32_t)(tiles / ev->B);

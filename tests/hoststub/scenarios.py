@@ -439,6 +439,28 @@ def scenario_sweep_routes(ctx):
     return out
 
 
+def scenario_tile_routes(ctx):
+    """Whether the simulation of a shape goes out in word tiles."""
+    import ctypes
+    stub = ctypes.CDLL(sys.argv[1])
+    counts = (ctypes.c_long * 2)()
+    out = {}
+    for gates, pis, depth in ((2000, 64, 20), (20_000, 500, 30), (117_000, 2000, 3), (117_000, 2000, 60)):
+        nl = synth.random_dag(synth.DagSpec(gates, pis, depth), 13)
+        d = api.Design(ctx, nl)
+        for B, T in ((1, 16), (1, 1024), (4, 96)):
+            ev = api.Eval(d, B, mode=L.DP_HYBRID, n_sim=64 * T, seed=8)
+            ev.set_pi_prob(np.full((B, nl.n_pi), 0.5, np.float32))
+            ev.set_caps(synth.net_caps(nl.n_nets, 14))
+            stub.stub_sim_counts(counts)
+            c0 = list(counts)
+            ev.forward(("power",))
+            stub.stub_sim_counts(counts)
+            out[f"{gates} {depth} {B}x{T}"] = counts[0] > c0[0]
+            ev.close()
+    return out
+
+
 def scenario_lane_memory(ctx):
     """Serving with a device that has less memory than the budget says: enough
     for a lane, and not for its dataflow sweeps' buffers."""
@@ -515,6 +537,7 @@ if __name__ == "__main__":
               "autotune": scenario_autotune,
               "server_give_up": scenario_server_give_up,
               "sweep_routes": scenario_sweep_routes,
+              "tile_routes": scenario_tile_routes,
               "lane_memory": scenario_lane_memory,
               "large_faces": scenario_large_faces}[sys.argv[2]](context)
     print(json.dumps(result), flush=True)

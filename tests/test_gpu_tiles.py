@@ -109,3 +109,35 @@ def test_tiles_of_library_cells(ctx, pis, gates, depth, B, T):
         np.testing.assert_array_equal(want["ones"][b].astype(np.uint64), f["ones"])
         np.testing.assert_array_equal(want["toggles"][b].astype(np.uint64), f["toggles"])
         np.testing.assert_allclose(want["sp"][b], f["sp"], atol=SP_ABS, rtol=0)
+
+
+def _with_chain(nl, levels):
+    """The netlist with a chain of inverters from its last gate: designs of few
+    levels take level launches."""
+    ptr, fan = nl.fanin_ptr, nl.fanin
+    gates = [(int(nl.op[g]), fan[ptr[g]:ptr[g + 1]].tolist()) for g in range(nl.n_gates)]
+    gates += [(synth.INV, [nl.n_nets - 1 + i]) for i in range(levels)]
+    return synth.from_gates(nl.n_pi, gates, cells=nl.cells) if nl.cells else synth.from_gates(nl.n_pi, gates)
+
+
+@pytest.mark.parametrize("gates,pis,depth,B,T,cells", [
+    (5, 3, 5, 1, 2, False), (64, 9, 1, 2, 3, False), (700, 33, 7, 3, 16, False), (700, 33, 7, 25, 7, False),
+    (6500, 2100, 3, 1, 33, False), (9000, 50, 1, 1, 250, False), (9000, 50, 1, 1, 2000, False),
+    (900, 40, 1, 1, 16, True), (4000, 30, 12, 2, 70, True)])
+def test_tiles_of_wide_levels_in_deep_designs(ctx, gates, pis, depth, B, T, cells):
+    say(f"word tiles, deep: {gates} gates, {pis} PIs, depth {depth}, B={B}, T={T}, library cells {cells}")
+    ops = tuple(range(9)) + (tuple(synth.CELL_BASE + c for c in range(len(ODD_CELLS))) if cells else ())
+    nl = _with_chain(synth.random_dag(synth.DagSpec(gates, pis, depth, ops=ops,
+                                                    cells=ODD_CELLS if cells else ()), 43), 60)
+    d = api.Design(ctx, nl)
+    ref = _eval(d, nl, B, T)
+    ref.set_schedule(L.DP_SCHED_LEVEL, T)  # a chunk that is set: level launches
+    want = ref.forward(FIELDS)
+    ev = _eval(d, nl, B, T)
+    for _ in range(2):
+        _same(ev.forward(FIELDS), want, "tiles")
+    p, cap = synth.pi_probs(pis, 41, batch=B), synth.net_caps(nl.n_nets, 42)
+    f = oracle.Netlist.of(nl).forward(p[B - 1], cap, hybrid=True, n_words=T,
+                                      pi_words=oracle.stimulus_model(p[B - 1], 9, T))
+    np.testing.assert_array_equal(want["ones"][B - 1].astype(np.uint64), f["ones"])
+    np.testing.assert_array_equal(want["toggles"][B - 1].astype(np.uint64), f["toggles"])

@@ -131,6 +131,13 @@ def test_dataflow_sweeps_where_they_pay(stub_lib):
             assert r[f"{shape} {columns}"] == route, (shape, columns)
 
 
+def test_word_tiles_where_they_pay(stub_lib):
+    r = _run(stub_lib, "tile_routes")
+    for shape in ("2000 20", "20000 30", "117000 60"):
+        assert all(r[f"{shape} {k}"] for k in ("1x16", "1x1024", "4x96")), shape
+    assert not r["117000 3 1x16"] and not r["117000 3 1x1024"] and r["117000 3 4x96"]
+
+
 def test_lane_without_memory_for_its_dataflow_buffers(stub_lib):
     r = _run(stub_lib, "lane_memory")
     assert r["all"][:3] == [True, True, False]   # done, dataflow, merged levels
