@@ -455,11 +455,21 @@ bool bwd_flows(const dp_eval *ev, int32_t C) { return flow_ready(ev, C) && flow_
 
 // Whether the per-(b, s) reverse sweep over C columns runs in adjoints
 // (launch_bwd_wide_level): from 16 size vectors, which then share an entry's
-// partial derivative.
+// partial derivative, and where there are pairs enough.  A wave of that sweep
+// pulls a net's whole fan-out range, 0.9 us a strand in a row, so that a level
+// takes its longest range's time however few its columns; contributions take 8
+// us per million (gate, column), adjoints 2, and 33 us more a level with library
+// cells.  Sweep by contributions / in adjoints, us: 117K gates, 4 x 32 columns
+// 274 / 342, 16 x 16 422 / 361, 32 x 64 2077 / 812; 300K (ranges up to 220) 4 x 16
+// 391 / 948, 20 x 16 1049 / 1387; 1M, 2 x 16 608 / 1587, 16 x 16 2427 / 2443, 32 x 16
+// 4482 / 2864; 2M, 8 x 16 2572 / 2671, 16 x 16 4627 / 3519; half library cells, 117K,
+// 2 x 40 2224 / 397.
 constexpr int32_t kWideSizes = 16;
 bool wide_reverse(const dp_eval *ev, int32_t C, int per_column) {
+  const dp_design *d = ev->d;
   return per_column && s_prime(ev) >= kWideSizes && ev->schedule != DP_SCHED_PERSISTENT &&
-         !bwd_flows(ev, C);
+         !bwd_flows(ev, C) &&
+         (int64_t)d->n_gates * C + 5400000ll * d->cell_levels >= 130000 * d->pull_strands;
 }
 
 // Every buffer of a reverse sweep over C columns (before any capture).

@@ -286,6 +286,12 @@ dp_status compile_design(dp_ctx *ctx, const dp_netlist *nl, int32_t n_cells,
       d->lvl_read[l] += rev_ptr[n_pi + gi + 1] > rev_ptr[n_pi + gi];
     }
   d->lvl_fanout[0] = rev_ptr[n_pi] - rev_ptr[0];
+  for (int32_t l = 0; l <= depth; ++l) {
+    int32_t longest = 0;
+    const int32_t first = l ? n_pi + d->level_ptr[l] : 0, last = l ? n_pi + d->level_ptr[l + 1] : n_pi;
+    for (int32_t n = first; n < last; ++n) longest = std::max(longest, rev_ptr[n + 1] - rev_ptr[n]);
+    d->pull_strands += (longest + 7) / 8;
+  }
   // gates whose fan-out range the many-column reverse levels pull with
   // whole workgroups (ascending internal id)
   for (int32_t gi = 0; gi < G; ++gi)

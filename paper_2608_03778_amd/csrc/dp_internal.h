@@ -127,6 +127,7 @@ struct dp_design {
   std::vector<int32_t> lvl_small_cells;
   int32_t split_levels = 0;           // levels holding both kinds (one launch more each)
   int32_t cell_levels = 0;            // levels holding library cells
+  int64_t pull_strands = 0;           // over levels (and the PIs): strands of eight of the longest fan-out range
   bool has_cell_gates = false;
   // device arrays
   int32_t pins = 3;      // rows of `in` and `slot`: 3, or the widest library cell

@@ -461,6 +461,40 @@ def scenario_tile_routes(ctx):
     return out
 
 
+def scenario_wide_routes(ctx):
+    """Whether a sizing sweep's gradients go in adjoints: gates times columns at
+    and below 130,000 a strand, from the design's own fan-out."""
+    import ctypes
+    stub = ctypes.CDLL(sys.argv[1])
+    counts = (ctypes.c_long * 5)()
+    out = {}
+    lib = tuple(range(9)) + tuple(synth.CELL_BASE + c for c in range(len(synth.LIBRARY)))
+    for name, spec in (("fixed", synth.DagSpec(3000, 90, 9)), ("far", synth.DagSpec(3000, 90, 9, fo_mean=3.0, fo_cap=256)),
+                       ("cells", synth.DagSpec(3000, 90, 9, ops=lib, cells=synth.LIBRARY))):
+        nl = synth.random_dag(spec, 22)
+        lv = oracle.Netlist.of(nl).levels()
+        longest = np.zeros(int(lv.max()) + 1, np.int64)
+        np.maximum.at(longest, lv, np.bincount(nl.fanin, minlength=nl.n_nets))
+        line = int(130_000 * (-(-longest // 8)).sum() / nl.n_gates)  # columns
+        d = api.Design(ctx, nl)
+        for what, B, S in (("below", line // 32 - 1, 32), ("above", line // 32 + 2, 32), ("few sizes", 2 * line // 15, 15),
+                           ("small", 5, 16)):
+            ev = api.Eval(d, B, S)
+            ev.set_pi_prob(np.full((B, nl.n_pi), 0.5, np.float32))
+            ev.set_caps(synth.net_caps(nl.n_nets, 14))
+            ev.set_cell_sizes(np.ones((S, nl.n_gates), np.float32))
+            ev.forward(("power",))
+            stub.stub_sweep_counts(counts)
+            c0 = list(counts)
+            ev.backward_columns()
+            stub.stub_sweep_counts(counts)
+            got = [counts[k] - c0[k] for k in range(5)]
+            assert sum(x > 0 for x in got[2:]) == 1, got
+            out[f"{name} {what}"] = got[4] > 0
+            ev.close()
+    return out
+
+
 def scenario_lane_memory(ctx):
     """Serving with a device that has less memory than the budget says: enough
     for a lane, and not for its dataflow sweeps' buffers."""
@@ -538,6 +572,7 @@ if __name__ == "__main__":
               "server_give_up": scenario_server_give_up,
               "sweep_routes": scenario_sweep_routes,
               "tile_routes": scenario_tile_routes,
+              "wide_routes": scenario_wide_routes,
               "lane_memory": scenario_lane_memory,
               "large_faces": scenario_large_faces}[sys.argv[2]](context)
     print(json.dumps(result), flush=True)

@@ -133,3 +133,14 @@ def test_reverse_of_many_size_vectors(gates, pis, depth, B, S, mode, cells, ste)
     o = oracle.Netlist.of(nl)
     f, adj = oracle_column(o, p[B - 1], cap, size[S - 1], mode=mode, n_words=8, seed=2, ste=ste)
     assert_grad_close(dpi[B - 1, S - 1], np.where(fixed, 0.0, adj["dpi"]), "dP/dp")
+
+
+# columns enough for the sweep in adjoints (the ones above are in contributions
+# but for the library cells), four columns a lane and one, with hybrid beta, STE
+# and library cells
+@pytest.mark.parametrize("gates,pis,depth,B,S,mode,cells,ste", [
+    (3000, 90, 9, 24, 256, "modeled", False, False), (3000, 90, 9, 40, 129, "hybrid", False, True),
+    (12_000, 300, 6, 8, 256, "hybrid", False, False), (300, 70, 3, 64, 256, "modeled", False, False),
+    (300, 70, 3, 150, 65, "modeled", False, False), (3000, 90, 9, 24, 256, "hybrid", True, True)])
+def test_reverse_of_very_many_size_vectors(gates, pis, depth, B, S, mode, cells, ste):
+    test_reverse_of_many_size_vectors(gates, pis, depth, B, S, mode, cells, ste)

@@ -138,6 +138,15 @@ def test_word_tiles_where_they_pay(stub_lib):
     assert not r["117000 3 1x16"] and not r["117000 3 1x1024"] and r["117000 3 4x96"]
 
 
+def test_reverse_sweep_in_adjoints_where_it_pays(stub_lib):
+    r = _run(stub_lib, "wide_routes")
+    for name in ("fixed", "far"):
+        assert not r[f"{name} below"] and r[f"{name} above"], name
+    assert r["cells below"] and r["cells above"] and r["cells small"]
+    assert not any(r[f"{name} few sizes"] for name in ("fixed", "far", "cells"))
+    assert not r["fixed small"] and not r["far small"]
+
+
 def test_lane_without_memory_for_its_dataflow_buffers(stub_lib):
     r = _run(stub_lib, "lane_memory")
     assert r["all"][:3] == [True, True, False]   # done, dataflow, merged levels
