@@ -2138,6 +2138,7 @@ void FlowTables::build(const MergedTables::Lane *lanes, int32_t n) {
                   d->n_edges, d->depth};
     b.job0 = b_jobs;
     b.block0 = b_blocks;
+    ctl.sized = ctl.sized || staged_sizes(b.t.a);
     b_jobs += ev->B;
     b_blocks += flow_arm_blocks(b.t, bs.empty(), &b.arm_blocks, &b.seed_blocks);
     b_widest = std::max<int64_t>(b_widest, std::max(d->max_level_width, d->n_pi));

@@ -426,10 +426,17 @@ struct FlowCtl {
   // a wait gives up after this many polls, and looks at its count and at the
   // stop flag whenever polls & every is 0
   uint32_t limit, every;
+  int32_t sized;      // several designs: staged_sizes of one of them
 };
 // Polls (a tenth of a microsecond each, so seconds) after which a wait gives up
 // by default.
 constexpr uint32_t kFlowPolls = 1u << 26;
+// Whether the seeds of a reverse sweep take several size vectors' weights
+// through LDS (from this many on; fewer are read directly).
+constexpr int32_t kStagedSizes = 4;
+constexpr bool staged_sizes(const BwdArgs &a) {
+  return a.size && !a.per_column && !a.paired && a.S >= kStagedSizes;
+}
 inline void flow_set_limit(FlowCtl &ctl, uint32_t polls) {
   ctl.limit = polls;
   ctl.every = polls < 64 ? 0 : 63;

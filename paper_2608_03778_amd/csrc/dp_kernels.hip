@@ -1523,14 +1523,59 @@ __global__ __launch_bounds__(kBlock) void k_power_final_multi(const PowerSeg *__
 }
 
 // ---------------------------------------------------------------- reverse sweep
+// The weights of a net over several size vectors, ws[k] = sum over s of
+// w[k][s] size_s(n) in order of s (a PI's sizes are 1) for cols columns' rows
+// w, for one net per thread of the workgroup.  Sizes come through LDS
+// kSizeChunk vectors at a time: neighbouring nets' rows are one run of memory,
+// while a wave's threads, each along its own row, read 64 lines an instruction
+// (dP/dC of 1M gates x 4 columns x 32 vectors: 2,197 us read directly).
+// net_of(thread): its net, or -1.  Every thread of the workgroup calls it;
+// fresh: the chunk in LDS is not this one's.
+constexpr int32_t kSizeChunk = 16;
+template <int ROWS, int COLS, class NetOf>
+__device__ __forceinline__ void staged_weights(const float *size, int32_t n_pi, int32_t S, const float *w,
+                                               int32_t cols, float (&lds)[ROWS][kSizeChunk + 1],
+                                               const NetOf &net_of, bool fresh, float (&ws)[COLS]) {
+#pragma unroll
+  for (int k = 0; k < COLS; ++k) ws[k] = 0.0f;
+  for (int32_t s0 = 0; s0 < S; s0 += kSizeChunk) {
+    const int32_t m = min(kSizeChunk, S - s0);
+    if (fresh || S > kSizeChunk) {
+      __syncthreads();
+      float v[kSizeChunk];
+#pragma unroll
+      for (int k = 0; k < kSizeChunk; ++k) {
+        const int32_t e = (int32_t)threadIdx.x + k * ROWS, row = e / kSizeChunk, col = e % kSizeChunk;
+        const int32_t net = net_of(row);
+        v[k] = 1.0f;
+        if (net >= n_pi && col < m) v[k] = size[(int64_t)(net - n_pi) * S + s0 + col];
+      }
+#pragma unroll
+      for (int k = 0; k < kSizeChunk; ++k) {
+        const int32_t e = (int32_t)threadIdx.x + k * ROWS;
+        lds[e / kSizeChunk][e % kSizeChunk] = v[k];
+      }
+      __syncthreads();
+    }
+    for (int32_t s = 0; s < m; ++s) {
+      const float sz = lds[threadIdx.x][s];
+#pragma unroll
+      for (int k = 0; k < COLS; ++k)
+        if (k < cols) ws[k] = fmaf(w ? w[(int64_t)k * S + s0 + s] : 1.0f, sz, ws[k]);
+    }
+  }
+}
+
 // Local adjoint seed of net n in reverse column c (SP column b): the
 // derivative of the net's own power term, kappa C 2 (1 - 2P) (Eq. 2 and
 // Eq. 7), times beta (unless STE), the upstream weight and the driver's size
 // factor (per column, paired, or summed over the size vectors).  Rounded as it
 // stands (no product of it is fused into the sum that the caller adds it to),
 // so that a sweep which stores seeds has the same bits.
+// staged: ws is the net's weight over the size vectors, from staged_weights.
 __device__ __forceinline__ float seed_of(const BwdArgs &a, int32_t n, int32_t c, int32_t b,
-                                         f2 pq, float beta, float cap) {
+                                         f2 pq, float beta, float cap, bool staged = false,
+                                         float ws = 0.0f) {
 #pragma clang fp contract(off)
   const float local = a.kappa * cap * 2.0f * (pq.y - pq.x);
   const float base = a.ste ? local : beta * local;
@@ -1548,11 +1593,13 @@ __device__ __forceinline__ float seed_of(const BwdArgs &a, int32_t n, int32_t c,
     return base * (w * sz);
   }
   const int32_t Sp = a.S > 0 ? a.S : 1;
-  float ws = 0.0f;
-  for (int32_t s = 0; s < Sp; ++s) {
-    const float w = a.w ? a.w[(int64_t)b * Sp + s] : 1.0f;
-    const float sz = gate ? a.size[g * a.S + s] : 1.0f;
-    ws = fmaf(w, sz, ws);
+  if (!staged) {
+    ws = 0.0f;
+    for (int32_t s = 0; s < Sp; ++s) {
+      const float w = a.w ? a.w[(int64_t)b * Sp + s] : 1.0f;
+      const float sz = gate ? a.size[g * a.S + s] : 1.0f;
+      ws = fmaf(w, sz, ws);
+    }
   }
   return base * ws;
 }
@@ -3168,7 +3215,7 @@ __global__ __launch_bounds__(kBlock) void k_flow_arm(uint32_t *p, int64_t n, uin
 // sweep that gave up are kArmed, whose bits a product may hand on, and a
 // contribution of these bits would be waited for.
 __device__ __forceinline__ float disarmed(float v) { return v == v ? v : __builtin_nanf(""); }
-template <bool CELLS>
+template <bool CELLS, bool SIZED>
 __device__ __forceinline__ void bwd_arm(const BwdFlow &t, uint32_t *words, int32_t n_words,
                                         uint32_t block, uint32_t arm_blocks, uint32_t seed_blocks) {
   const GraphView &g = t.g;
@@ -3178,13 +3225,29 @@ __device__ __forceinline__ void bwd_arm(const BwdFlow &t, uint32_t *words, int32
     return;
   }
   if (block < arm_blocks + seed_blocks) {
-    const int64_t idx = (int64_t)(block - arm_blocks) * kBlock + threadIdx.x;
-    if (idx >= (int64_t)g.n_nets * a.C) return;
+    const int64_t first = (int64_t)(block - arm_blocks) * kBlock, idx = first + threadIdx.x;
     const int32_t c = (int32_t)(idx / g.n_nets), net = (int32_t)(idx - (int64_t)c * g.n_nets);
     const int32_t b = c / a.cdiv;
+    const bool in = idx < (int64_t)g.n_nets * a.C;
+    const bool staged = SIZED && staged_sizes(a);
+    float ws[1] = {0.0f};
+    if constexpr (SIZED)
+      if (staged) {
+        __shared__ float lds[kBlock][kSizeChunk + 1];
+        const int32_t net0 = (int32_t)(first % g.n_nets);
+        staged_weights<kBlock>(
+            a.size, g.n_pi, a.S, a.w && in ? a.w + (int64_t)b * a.S : nullptr, 1, lds,
+            [&](int32_t row) {  // (on into the next columns)
+              const uint32_t n = (uint32_t)(net0 + row), all = (uint32_t)g.n_nets;
+              return (int32_t)(n < all ? n : n % all);
+            },
+            true, ws);
+      }
+    if (!in) return;
     const float beta = a.beta ? a.beta[a.beta_shared ? (int64_t)net : (int64_t)net * a.B + b] : 1.0f;
     t.seed[idx] =
-        disarmed(seed_of(a, net, c, b, sp_load(a.sp[(int64_t)net * a.B + b]), beta, a.cap[net]));
+        disarmed(seed_of(a, net, c, b, sp_load(a.sp[(int64_t)net * a.B + b]), beta, a.cap[net],
+                         staged, ws[0]));
     if (a.lam) a.lam[idx] = __builtin_nanf("");
     if (net < g.n_pi) t.pi_out[(int64_t)c * g.n_pi + net] = __builtin_nanf("");
     return;
@@ -3220,10 +3283,10 @@ __device__ __forceinline__ void bwd_arm(const BwdFlow &t, uint32_t *words, int32
   if (k > 1) part[g.G] = disarmed(d1);
   if (k > 2) part[2 * (int64_t)g.G] = disarmed(d2);
 }
-template <bool CELLS>
+template <bool CELLS, bool SIZED>
 __global__ __launch_bounds__(kBlock) void k_bwd_arm(BwdFlow t, uint32_t *words, uint32_t arm_blocks,
                                                     uint32_t seed_blocks) {
-  bwd_arm<CELLS>(t, words, kFlowWords, blockIdx.x, arm_blocks, seed_blocks);
+  bwd_arm<CELLS, SIZED>(t, words, kFlowWords, blockIdx.x, arm_blocks, seed_blocks);
 }
 
 // The same for the segments of a sweep over several designs; the first
@@ -3235,12 +3298,12 @@ __global__ __launch_bounds__(kBlock) void k_flow_arm_multi(const SpFlowSeg *__re
   flow_arm(reinterpret_cast<uint32_t *>(t.sp + (int64_t)t.g.n_pi * t.B), (int64_t)t.g.G * t.B, words,
            k == 0 ? kFlowWords : 0, blockIdx.x - segs[k].block0);
 }
-template <bool CELLS>
+template <bool CELLS, bool SIZED>
 __global__ __launch_bounds__(kBlock) void k_bwd_arm_multi(const BwdFlowSeg *__restrict__ segs,
                                                           int32_t n_segs, uint32_t *words) {
   const int32_t k = seg_of(segs, n_segs);
   const BwdFlow t = global_view(segs[k].t);
-  bwd_arm<CELLS>(t, words, k == 0 ? kFlowWords : 0, blockIdx.x - segs[k].block0,
+  bwd_arm<CELLS, SIZED>(t, words, k == 0 ? kFlowWords : 0, blockIdx.x - segs[k].block0,
                  segs[k].arm_blocks, segs[k].seed_blocks);
 }
 
@@ -3672,8 +3735,9 @@ __device__ __forceinline__ float x_of(const GradExportArgs &a, int64_t n, int32_
 // sixteen go out before the first store), then lane r sums its net's
 // columns in order.
 constexpr int32_t kCapRows = 64, kCapCols = 32, kCapBatch = 16;
+constexpr int32_t kCapSized = 4;  // columns whose weights one pass over the sizes forms
 
-template <bool BETA>  // BETA: a beta array is present
+template <bool BETA, bool SIZED>  // BETA: a beta array is present; SIZED: weights through LDS
 __global__ __launch_bounds__(kCapRows) void k_grad_cap(GradExportArgs a) {
   __shared__ float xs[kCapRows][kCapCols + 1];
   __shared__ float wcol[kCapCols];  // without sizes a column's weight is the net's
@@ -3693,6 +3757,8 @@ __global__ __launch_bounds__(kCapRows) void k_grad_cap(GradExportArgs a) {
     }
     return ws;
   };
+  __shared__ float lds[SIZED ? kCapRows : 1][kSizeChunk + 1];
+  const auto net_of = [&](int32_t row) { return row < rows ? (int32_t)(n0 + row) : -1; };
   double acc = 0.0;
   for (int32_t b0 = 0; b0 < a.B; b0 += kCapCols) {
     const int32_t tw = min(kCapCols, a.B - b0), total = rows * tw;
@@ -3724,7 +3790,17 @@ __global__ __launch_bounds__(kCapRows) void k_grad_cap(GradExportArgs a) {
     // lane per column forms it (as weight() would), the row loop reads it
     if (!a.size && r < tw) wcol[r] = weight(b0 + r);
     __syncthreads();
-    if (r < rows) {
+    if constexpr (SIZED) {
+      for (int32_t cc = 0; cc < tw; cc += kCapSized) {
+        const float *w = a.w ? a.w + (int64_t)(b0 + cc) * Sp : nullptr;
+        const int32_t cols = min(kCapSized, tw - cc);
+        float ws[kCapSized];
+        staged_weights(a.size, a.n_pi, Sp, w, cols, lds, net_of, b0 + cc == 0, ws);
+#pragma unroll
+        for (int k = 0; k < kCapSized; ++k)
+          if (r < rows && k < cols) acc += (double)xs[r][cc + k] * (double)ws[k];
+      }
+    } else if (r < rows) {
       if (!a.size)
         for (int32_t cc = 0; cc < tw; ++cc) acc += (double)xs[r][cc] * (double)wcol[cc];
       else
@@ -3740,12 +3816,31 @@ __global__ __launch_bounds__(kCapRows) void k_grad_cap(GradExportArgs a) {
 // columns are already whole lines, and no LDS pass is needed.
 constexpr int32_t kCapRowsMinCols = 16;  // from this many columns k_grad_cap stages rows
 
+template <bool SIZED>
 __global__ __launch_bounds__(kBlock) void k_grad_cap_narrow(GradExportArgs a) {
   const int64_t n = gidx();
-  if (n >= a.n_nets) return;
   const int32_t Sp = (a.S > 0 && !a.paired) ? a.S : 1;
   const bool gate = n >= a.n_pi && a.size;
   double acc = 0.0;
+  if constexpr (SIZED) {
+    __shared__ float lds[kBlock][kSizeChunk + 1];
+    const auto net_of = [&](int32_t row) {
+      const int64_t m = (int64_t)blockIdx.x * kBlock + row;
+      return m < a.n_nets ? (int32_t)m : -1;
+    };
+    for (int32_t b = 0; b < a.B; b += kCapSized) {
+      const int32_t cols = min(kCapSized, a.B - b);
+      float ws[kCapSized];
+      staged_weights(a.size, a.n_pi, Sp, a.w ? a.w + (int64_t)b * Sp : nullptr, cols, lds, net_of,
+                     b == 0, ws);
+#pragma unroll
+      for (int k = 0; k < kCapSized; ++k)
+        if (n < a.n_nets && k < cols) acc += (double)x_of(a, n, b + k) * (double)ws[k];
+    }
+    if (n < a.n_nets) a.dcap[a.int2ext[n]] = (float)acc;
+    return;
+  }
+  if (n >= a.n_nets) return;
   for (int32_t b = 0; b < a.B; ++b) {
     float ws = 0.0f;
     for (int32_t s = 0; s < Sp; ++s) {
@@ -4353,10 +4448,10 @@ hipError_t launch_bwd_flow(const BwdFlow &t, int64_t widest, bool cells, FlowCtl
     return hipErrorInvalidValue;
   uint32_t ab, sb;
   const uint32_t blocks = flow_arm_blocks(t, true, &ab, &sb);
-  if (cells)
-    k_bwd_arm<true><<<blocks, kBlock, 0, s>>>(t, ctl.words, ab, sb);
-  else
-    k_bwd_arm<false><<<blocks, kBlock, 0, s>>>(t, ctl.words, ab, sb);
+  const bool sized = staged_sizes(t.a);
+  const auto arm = cells ? (sized ? k_bwd_arm<true, true> : k_bwd_arm<true, false>)
+                         : (sized ? k_bwd_arm<false, true> : k_bwd_arm<false, false>);
+  hipLaunchKernelGGL(arm, dim3(blocks), dim3(kBlock), 0, s, t, ctl.words, ab, sb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   unsigned grid, threads;
@@ -4390,10 +4485,9 @@ hipError_t launch_bwd_flow_multi(const BwdFlowSeg *segs, int32_t n_segs, int32_t
                                  hipStream_t s) {
   if (n_segs <= 0 || jobs <= 0) return hipSuccess;
   if (!ctl.words || !ctl.report || jobs > kFlowMaxJobs || blocks == 0) return hipErrorInvalidValue;
-  if (cells)
-    k_bwd_arm_multi<true><<<blocks, kBlock, 0, s>>>(segs, n_segs, ctl.words);
-  else
-    k_bwd_arm_multi<false><<<blocks, kBlock, 0, s>>>(segs, n_segs, ctl.words);
+  const auto arm = cells ? (ctl.sized ? k_bwd_arm_multi<true, true> : k_bwd_arm_multi<true, false>)
+                         : (ctl.sized ? k_bwd_arm_multi<false, true> : k_bwd_arm_multi<false, false>);
+  hipLaunchKernelGGL(arm, dim3(blocks), dim3(kBlock), 0, s, segs, n_segs, ctl.words);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   unsigned grid, threads;
@@ -4457,12 +4551,15 @@ hipError_t launch_sim_flow(const SimFlow &t, const SpFlow &sp, int64_t widest, b
 hipError_t launch_grad_export(const GradExportArgs &a, hipStream_t s) {
   if (a.dcap && a.n_nets > 0) {
     const unsigned blocks = (unsigned)((a.n_nets + kCapRows - 1) / kCapRows);
-    if (a.B < kCapRowsMinCols)
-      k_grad_cap_narrow<<<blocks_for(a.n_nets), kBlock, 0, s>>>(a);
-    else if (a.beta)
-      k_grad_cap<true><<<blocks, kCapRows, 0, s>>>(a);
-    else
-      k_grad_cap<false><<<blocks, kCapRows, 0, s>>>(a);
+    const bool sized = a.size && !a.paired && a.S >= kStagedSizes;
+    if (a.B < kCapRowsMinCols) {
+      const auto kern = sized ? k_grad_cap_narrow<true> : k_grad_cap_narrow<false>;
+      hipLaunchKernelGGL(kern, dim3(blocks_for(a.n_nets)), dim3(kBlock), 0, s, a);
+    } else {
+      const auto kern = a.beta ? (sized ? k_grad_cap<true, true> : k_grad_cap<true, false>)
+                               : (sized ? k_grad_cap<false, true> : k_grad_cap<false, false>);
+      hipLaunchKernelGGL(kern, dim3(blocks), dim3(kCapRows), 0, s, a);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -144,3 +144,69 @@ def test_reverse_of_many_size_vectors(gates, pis, depth, B, S, mode, cells, ste)
     (300, 70, 3, 150, 65, "modeled", False, False), (3000, 90, 9, 24, 256, "hybrid", True, True)])
 def test_reverse_of_very_many_size_vectors(gates, pis, depth, B, S, mode, cells, ste):
     test_reverse_of_many_size_vectors(gates, pis, depth, B, S, mode, cells, ste)
+
+
+def weighted_adjoints(o, p, cap, size, w, mode, ste):
+    """dP/dp [B][n_pi] and dP/dC [nets] of sum over (b, s) of w power, in FP64."""
+    dpi, dcap = [], 0.0
+    for b in range(len(p)):
+        adj = [oracle_column(o, p[b], cap, size[s], mode=mode, n_words=8, seed=2, ste=ste)[1]
+               for s in range(len(size))]
+        dpi.append(sum(w[b, s] * a["dpi"] for s, a in enumerate(adj)))
+        dcap = dcap + sum(w[b, s] * a["dcap"] for s, a in enumerate(adj))
+    return np.stack(dpi), dcap
+
+
+# size vectors around a staged chunk (16) and the fewest that are staged (4);
+# columns around the row kernel's fewest (16) and its tile (32); blocks of nets
+# that end in the next column, and in the second next of a small design
+@pytest.mark.parametrize("gates,pis,B,S,mode,cells,ste,weighted", [
+    (700, 30, 3, 3, "modeled", False, False, True), (700, 30, 3, 4, "modeled", False, False, True),
+    (60, 5, 9, 5, "modeled", False, False, True), (700, 30, 15, 16, "modeled", False, False, False),
+    (700, 300, 16, 17, "hybrid", False, False, True), (226, 30, 33, 15, "hybrid", False, False, True),
+    (700, 30, 2, 33, "modeled", True, False, True), (700, 30, 17, 48, "hybrid", True, True, False)])
+def test_gradients_weighted_over_size_vectors(gates, pis, B, S, mode, cells, ste, weighted):
+    say(f"gradients over sizes: {gates} gates, B={B}, S={S}, {mode}, cells {cells}")
+    ops = tuple(range(9)) + (tuple(synth.CELL_BASE + c for c in range(9)) if cells else ())
+    nl = synth.random_dag(synth.DagSpec(gates, pis, 6, ops=ops, fo_mean=3.0, fo_cap=64,
+                                        cells=synth.LIBRARY if cells else ()), 25)
+    ctx = api.Context(0)
+    d = api.Design(ctx, nl)
+    p, cap = synth.pi_probs(pis, 1, batch=B), synth.net_caps(nl.n_nets, 2)
+    rng = np.random.default_rng(3)
+    size = rng.uniform(0.3, 4.0, (S, nl.n_gates)).astype(np.float32)
+    w = rng.uniform(0.2, 1.8, (B, S)).astype(np.float32) if weighted else None
+
+    def make(bs, sched):
+        ev = api.Eval(d, len(bs), S, n_sim=64 * 8, seed=2,
+                      mode=L.DP_HYBRID if mode == "hybrid" else L.DP_MODELED,
+                      beta_grad=L.DP_BETA_STE if ste else L.DP_BETA_LOCAL)
+        ev.set_pi_prob(p[bs])
+        ev.set_caps(cap)
+        ev.set_cell_sizes(size)
+        ev.set_schedule(sched)
+        return ev
+
+    def run(bs, sched):
+        ev = make(bs, sched)
+        ev.forward(("power",))
+        return ev.backward(None if w is None else w[bs], want=("dpi", "dcap"))
+    every = list(range(B))
+    g = run(every, L.DP_SCHED_AUTO)
+    for sched in (L.DP_SCHED_LEVEL,) if cells else (L.DP_SCHED_LEVEL, L.DP_SCHED_PERSISTENT):
+        ref = run(every, sched)
+        for k in ref:
+            np.testing.assert_array_equal(g[k], ref[k], err_msg=f"{k}, schedule {sched}")
+    np.testing.assert_array_equal(run([B - 1], L.DP_SCHED_AUTO)["dpi"][0], g["dpi"][B - 1])
+    dpi, dcap = weighted_adjoints(oracle.Netlist.of(nl), p, cap, size,
+                                  np.ones((B, S)) if w is None else w, mode, ste)
+    for b in (0, B - 1):
+        assert_grad_close(g["dpi"][b], dpi[b], f"dP/dp {b}")
+    assert_grad_close(g["dcap"], dcap, "dP/dC")
+    if w is None:  # (a group's gradients are of the sum)
+        evs = [make(every, L.DP_SCHED_AUTO), make([0], L.DP_SCHED_AUTO)]
+        grp = api.Group(ctx, evs)
+        for _ in range(2):
+            r = grp.run(("power",), backward=True)
+            np.testing.assert_array_equal(r[0]["dpi"], g["dpi"])
+            np.testing.assert_array_equal(r[1]["dpi"][0], g["dpi"][0])
