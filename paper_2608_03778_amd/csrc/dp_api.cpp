@@ -1401,7 +1401,7 @@ dp_status dp_set_cell_sizes(dp_eval *ev, const float *size, int32_t on_device) {
   hipStream_t s = ev->stream();
   const float *src;
   DP_TRY(import_from(ev->size_stage, size, n * sizeof(float), on_device, s, &src));
-  DP_HIP_TRY(dp::launch_import_sizes(src, d->int2ext.as<int32_t>(),
+  DP_HIP_TRY(dp::launch_import_sizes(src, d->int2ext.as<int32_t>(), d->ext2int.as<int32_t>(),
                                      ev->size.as<float>(), d->n_pi, d->n_gates, ev->S, s));
   if (!on_device) DP_HIP_TRY(hipStreamSynchronize(s));
   ev->have_size = true;

@@ -100,8 +100,8 @@ hipError_t launch_gather_nets_f32(const float *src_ext, const int32_t *int2ext, 
 hipError_t launch_import_cols_f32(const float *src, const int32_t *int2ext, float *dst,
                                   int32_t n_nets, int32_t B, hipStream_t s);
 // Sizes [S][G] caller gate numbering -> [G][S] internal gate order.
-hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, float *dst, int32_t n_pi,
-                               int32_t G, int32_t S, hipStream_t s);
+hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, const int32_t *ext2int,
+                               float *dst, int32_t n_pi, int32_t G, int32_t S, hipStream_t s);
 
 // One SP level (modeled sweep).
 // cells: the range holds library cells only (every launch below that takes

@@ -401,6 +401,40 @@ __global__ __launch_bounds__(kBlock) void k_import_sizes(const float *__restrict
   import_sizes(src, int2ext, dst, n_pi, G, S, (int32_t)blockIdx.x);
 }
 
+// The same from the caller's side: a block reads 64 of the caller's gates x 32
+// size vectors, whole lines, and writes each gate's run of the result.  The
+// gathers above fetch a line for every float once a row is past an L2
+// (dp_set_cell_sizes, us, gathered / in runs: 117K gates x 32 43 / 25, x 256
+// 209 / 89; 300K x 32 134 / 39; 1M x 2 35 / 30, x 8 144 / 39, x 32 562 / 87).
+// One vector has runs of a single float (1M 25 / 28), and small arrays are the
+// launches alone (117K x 4 16.6 / 17.5, x 6 17.6 / 17.7, x 8 19.4 / 17.7;
+// 300K x 2 17.4 / 18.5, x 3 19.6 / 19.8, x 4 22.9 / 20.2; 50K x 12 17.5 / 17.1).
+constexpr int32_t kSizeRuns = 32;
+constexpr int64_t kSizeRunsMin = 800'000;
+__global__ __launch_bounds__(kBlock) void k_import_size_runs(const float *__restrict__ src,
+                                                              const int32_t *__restrict__ ext2int,
+                                                              float *__restrict__ dst, int32_t n_pi,
+                                                              int32_t G, int32_t S) {
+  __shared__ float tile[kSizeGates][kSizeRuns + 1];
+  __shared__ int32_t row[kSizeGates];
+  const int32_t g_tiles = (G + kSizeGates - 1) / kSizeGates;
+  const int32_t g0 = ((int32_t)blockIdx.x % g_tiles) * kSizeGates;
+  const int32_t s0 = ((int32_t)blockIdx.x / g_tiles) * kSizeRuns;
+  const int32_t gl = (int32_t)threadIdx.x & 63, sl = (int32_t)threadIdx.x >> 6;
+  const int32_t ns = min(kSizeRuns, S - s0), ng = min(kSizeGates, G - g0);
+  if (gl < ng) {
+    if (sl == 0) row[gl] = ext2int[n_pi + g0 + gl] - n_pi;
+#pragma unroll
+    for (int k = 0; k < kSizeRuns / kWavesPerBlock; ++k) {
+      const int32_t s = sl + k * kWavesPerBlock;
+      if (s < ns) tile[gl][s] = src[(int64_t)(s0 + s) * G + g0 + gl];
+    }
+  }
+  __syncthreads();
+  for (int32_t i = (int32_t)threadIdx.x; i < ng * ns; i += kBlock)
+    dst[(int64_t)row[i / ns] * S + s0 + i % ns] = tile[i / ns][i % ns];
+}
+
 // ---------------------------------------------------------------- serving steps
 // A step's lanes staged by one launch that reads their pinned host buffers
 // itself, and one that orders the sizes; the gradients go back the same way.
@@ -3920,9 +3954,15 @@ hipError_t launch_import_cols_f32(const float *src, const int32_t *int2ext, floa
   return hipGetLastError();
 }
 
-hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, float *dst, int32_t n_pi,
-                               int32_t G, int32_t S, hipStream_t s) {
+hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, const int32_t *ext2int,
+                               float *dst, int32_t n_pi, int32_t G, int32_t S, hipStream_t s) {
   if ((int64_t)G * S <= 0) return hipSuccess;
+  if (S >= 2 && (int64_t)G * S >= kSizeRunsMin) {
+    const int64_t blocks = (int64_t)((G + kSizeGates - 1) / kSizeGates) * ((S + kSizeRuns - 1) / kSizeRuns);
+    if (blocks > kMaxBlocks) return hipErrorInvalidValue;
+    k_import_size_runs<<<(unsigned)blocks, kBlock, 0, s>>>(src, ext2int, dst, n_pi, G, S);
+    return hipGetLastError();
+  }
   const int64_t groups = (S + kSizeVecs - 1) / kSizeVecs;
   const int64_t rounds = groups >= kSizeXcds ? (groups + kSizeXcds - 1) / kSizeXcds * kSizeXcds : groups;
   const int64_t blocks = (int64_t)((G + kSizeGates - 1) / kSizeGates) * rounds;

@@ -422,9 +422,10 @@ hipError_t launch_import_cols_f32(const float *src, const int32_t *int2ext, floa
     for (int32_t b = 0; b < B; ++b) dst[(int64_t)i * B + b] = src[(int64_t)b * n_nets + int2ext[i]];
   return hipSuccess;
 }
-hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, float *dst, int32_t n_pi,
-                               int32_t G, int32_t S, hipStream_t stream_) {
+hipError_t launch_import_sizes(const float *src, const int32_t *int2ext, const int32_t *ext2int,
+                               float *dst, int32_t n_pi, int32_t G, int32_t S, hipStream_t stream_) {
   Scope sc_(stream_);
+  rd(ext2int, n_pi + G);
   rd(int2ext, n_pi + G);
   rd(src, (int64_t)S * G);
   wr(dst, (int64_t)S * G);

@@ -210,3 +210,31 @@ def test_gradients_weighted_over_size_vectors(gates, pis, B, S, mode, cells, ste
             r = grp.run(("power",), backward=True)
             np.testing.assert_array_equal(r[0]["dpi"], g["dpi"])
             np.testing.assert_array_equal(r[1]["dpi"][0], g["dpi"][0])
+
+
+# gates that end within a block, vectors around one block's 32; two vectors,
+# and faces just below and above the size from which whole runs are written
+@pytest.mark.parametrize("gates,S", [(400_001, 2), (50_003, 15), (50_003, 16), (25_027, 33),
+                                     (12_700, 65), (800_000, 1)])
+def test_order_of_large_size_arrays(gates, S):
+    say(f"size arrays: {gates} gates x {S}")
+    import torch
+    nl = synth.random_dag(synth.DagSpec(gates, 500, 6), 26)
+    d = api.Design(api.Context(0, torch.cuda.current_stream().cuda_stream), nl)
+    size = np.random.default_rng(5).uniform(0.3, 4.0, (S, gates)).astype(np.float32)
+    cap = synth.net_caps(nl.n_nets, 2)
+
+    def power(sizes):
+        ev = api.Eval(d, 1, len(sizes))
+        ev.set_pi_prob(synth.pi_probs(nl.n_pi, 1, batch=1))
+        ev.set_caps(cap)
+        ev.set_cell_sizes(sizes)
+        return ev.forward(("power", "sp"))
+    r = power(size)
+    np.testing.assert_array_equal(power(torch.from_numpy(size).cuda())["power"], r["power"])
+    for s in range(S):  # a vector by itself is gathered below 800K gates
+        np.testing.assert_array_equal(power(size[s:s + 1])["power"][0, 0], r["power"][0, s])
+    p = r["sp"][0].astype(np.float64)
+    term = 0.5 * cap.astype(np.float64) * 2 * p * (1 - p)
+    ref = term[:nl.n_pi].sum() + size.astype(np.float64) @ term[nl.n_pi:]
+    assert_power_close(r["power"][0], ref, "power")
