@@ -472,6 +472,21 @@ bool wide_reverse(const dp_eval *ev, int32_t C, int per_column) {
          (int64_t)d->n_gates * C + 5400000ll * d->cell_levels >= 130000 * d->pull_strands;
 }
 
+// What a dataflow reverse sweep over C columns takes besides contributions.
+size_t seed_bytes(const dp_eval *ev, int32_t C) {
+  return std::max<size_t>((size_t)ev->d->n_nets * C * sizeof(float), 16);
+}
+size_t part_bytes(const dp_eval *ev) {
+  return std::max<size_t>((size_t)ev->B * ev->d->pins * ev->d->n_gates * sizeof(float), 16);
+}
+dp_status ensure_flow_scratch(dp_eval *ev, int32_t C) {
+  DP_TRY(ev->seed.alloc(seed_bytes(ev, C)));
+  return ev->part.alloc(part_bytes(ev));
+}
+// (part alone may be there in another sweep's size)
+bool have_flow_scratch(const dp_eval *ev, int32_t C) {
+  return ev->seed.bytes >= seed_bytes(ev, C) && ev->part.bytes >= part_bytes(ev);
+}
 // Every buffer of a reverse sweep over C columns (before any capture).
 dp_status ensure_reverse_buffers(dp_eval *ev, int32_t C, int per_column = 0) {
   const dp_design *d = ev->d;
@@ -481,11 +496,7 @@ dp_status ensure_reverse_buffers(dp_eval *ev, int32_t C, int per_column = 0) {
     return ev->part.alloc(std::max<size_t>((size_t)d->n_edges * ev->B * sizeof(float), 16));
   }
   DP_TRY(ev->contrib.alloc(std::max<size_t>((size_t)d->n_edges * C * sizeof(float), 16)));
-  if (bwd_flows(ev, C)) {
-    DP_TRY(ev->seed.alloc(std::max<size_t>((size_t)d->n_nets * C * sizeof(float), 16)));
-    DP_TRY(ev->part.alloc(std::max<size_t>((size_t)ev->B * d->pins * d->n_gates * sizeof(float), 16)));
-  }
-  return DP_OK;
+  return bwd_flows(ev, C) ? ensure_flow_scratch(ev, C) : DP_OK;
 }
 
 // Polls after which a wait of the eval's dataflow launches gives up: the
@@ -2097,7 +2108,7 @@ bool FlowTables::fits(const MergedTables::Lane *lanes, int32_t n) {
   int64_t jobs = 0, items = 0;
   for (int32_t j = 0; j < n; ++j) {
     const dp_eval *ev = lanes[j].ev;
-    if (!flow_ready(ev, ev->B) || (lanes[j].backward && !ev->part.ptr)) return false;
+    if (!flow_ready(ev, ev->B) || (lanes[j].backward && !have_flow_scratch(ev, ev->B))) return false;
     jobs += ev->B;
     items += (int64_t)ev->d->n_nets * ev->B;
   }
@@ -2511,6 +2522,8 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
     cost[i] = forward_launches(ev, hybrid(ev) ? &plans[i] : nullptr);
     if (backward) {
       DP_TRY(ensure_reverse_buffers(ev, ev->B));
+      // (whatever its own route: a dataflow sweep is of every eval or of none)
+      if (!hybrid(ev) && flow_ready(ev, ev->B)) DP_TRY(ensure_flow_scratch(ev, ev->B));
       DP_TRY(ev->pi_out.alloc(std::max<size_t>((size_t)ev->B * d->n_pi * sizeof(float), 16)));
       cost[i] += d->depth + d->split_levels + 1;
     }

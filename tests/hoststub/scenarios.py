@@ -286,6 +286,40 @@ def scenario_group_persistent(ctx):
     return {"results": len(res), "schedules": [ev.get_schedule()["schedule"] for ev in evs]}
 
 
+def scenario_group_after_columns(ctx):
+    """Groups of evals whose reverse sweep alone goes by level launches: one
+    that has made the smaller scratch of a sweep over (b, s) columns before,
+    beside a fresh one, and each by itself."""
+    import ctypes
+    stub = ctypes.CDLL(sys.argv[1])
+    counts = (ctypes.c_long * 5)()
+    n_pi = 1500  # two levels, up to four readers a net
+    first = [(synth.AND2, [i, (i * 7 + 1) % n_pi]) for i in range(n_pi)]
+    nl = synth.from_gates(n_pi, first + [(synth.MUX2, [n_pi + i, n_pi + (i * 5 + 2) % n_pi, i])
+                                         for i in range(n_pi)])
+    d = api.Design(ctx, nl)
+
+    def make(S):
+        ev = api.Eval(d, 4, S)
+        ev.set_pi_prob(synth.pi_probs(nl.n_pi, 30, batch=4))
+        ev.set_caps(synth.net_caps(nl.n_nets, 14))
+        ev.set_cell_sizes(synth.cell_sizes(nl.n_gates, 3, n_size=S))
+        return ev
+    used, fresh = make(64), make(2)
+    used.forward(("power",))
+    used.backward_columns()
+    stub.stub_sweep_counts(counts)
+    n, wide = 0, counts[4] > 0
+    for evs in ([used], [used, fresh], [fresh], [used, make(64)]):
+        grp = api.Group(ctx, evs)
+        for use_graph in (True, False):
+            grp.configure(use_graph=use_graph)
+            n += len(grp.run(("power",), backward=True))
+        grp.close()
+        used.backward_columns()
+    return {"results": n, "wide": wide}
+
+
 def scenario_deep_graphs(ctx):
     """Captures of the reverse sweep of chains whose level launches are about as
     many as a graph takes (1,024)."""
@@ -565,6 +599,7 @@ if __name__ == "__main__":
               "group_serving": scenario_group_serving,
               "capture_order": scenario_capture_order,
               "group_persistent": scenario_group_persistent,
+              "group_after_columns": scenario_group_after_columns,
               "deep_graphs": scenario_deep_graphs,
               "profile": scenario_profile,
               "tile_memory": scenario_tile_memory,

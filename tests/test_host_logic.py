@@ -79,6 +79,10 @@ def test_group_of_persistent_evals(stub_lib):
     assert r["results"] == 3 and len(set(r["schedules"])) == 1
 
 
+def test_groups_of_evals_with_other_scratch(stub_lib):
+    assert _run(stub_lib, "group_after_columns") == {"results": 12, "wide": True}
+
+
 def test_reverse_graphs_of_deep_designs(stub_lib):
     assert _run(stub_lib, "deep_graphs") == {"1021": 1, "1022": 1, "1023": 1, "1024": 0}
 
