@@ -1993,7 +1993,7 @@ void level_part(const dp_design *d, int32_t l, int k, int32_t *g0, int32_t *n) {
 }
 }  // namespace
 
-void MergedTables::build(const Lane *lanes, int32_t n) {
+void MergedTables::build(const Lane *lanes, int32_t n, bool forward, bool reverse) {
   D = 0;
   for (int32_t j = 0; j < n; ++j) D = std::max(D, lanes[j].ev->d->depth);
   fs.clear();
@@ -2006,7 +2006,7 @@ void MergedTables::build(const Lane *lanes, int32_t n) {
   // forward: level indices l and l + 1 share a launch when every design that
   // has level l holds fixed cells only there and pairs it with l + 1 (or
   // ends at l)
-  for (int32_t l = 1; l <= D;) {
+  for (int32_t l = 1; forward && l <= D;) {
     bool pair = l + 1 <= D;
     for (int32_t j = 0; j < n && pair; ++j) {
       const dp_eval *ev = lanes[j].ev;
@@ -2039,7 +2039,7 @@ void MergedTables::build(const Lane *lanes, int32_t n) {
     }
     l += pair ? 2 : 1;
   }
-  for (int32_t l = 1; l <= D; ++l)
+  for (int32_t l = 1; reverse && l <= D; ++l)
     for (int k = 0; k < 2; ++k) {
       const size_t i = 2 * (size_t)l + k;
       b_off[i] = (int32_t)bs.size();
@@ -2077,18 +2077,6 @@ int64_t MergedTables::level_launches(const Lane *lanes, int32_t n) {
   return c;
 }
 
-size_t MergedTables::bwd_offset() const { return (fs.size() * sizeof(SpSeg) + 255) & ~(size_t)255; }
-
-size_t MergedTables::bytes() const {
-  return std::max<size_t>(bwd_offset() + bs.size() * sizeof(BwdSeg), 256);
-}
-
-void MergedTables::pack(void *host) const {
-  if (!fs.empty()) std::memcpy(host, fs.data(), fs.size() * sizeof(SpSeg));
-  if (!bs.empty())
-    std::memcpy((char *)host + bwd_offset(), bs.data(), bs.size() * sizeof(BwdSeg));
-}
-
 dp_status MergedTables::launch_forward(const SpSeg *dev, hipStream_t s) const {
   for (const FwdLaunch &fl : f_launch)
     DP_HIP_TRY(launch_sp_multi(dev + fl.off, fl.cnt, fl.blocks, fl.cells, s));
@@ -2104,24 +2092,13 @@ dp_status MergedTables::launch_reverse(const BwdSeg *dev, hipStream_t s) const {
   return DP_OK;
 }
 
-bool FlowTables::fits(const MergedTables::Lane *lanes, int32_t n) {
-  int64_t jobs = 0, items = 0;
-  for (int32_t j = 0; j < n; ++j) {
-    const dp_eval *ev = lanes[j].ev;
-    if (!flow_ready(ev, ev->B) || (lanes[j].backward && !have_flow_scratch(ev, ev->B))) return false;
-    jobs += ev->B;
-    items += (int64_t)ev->d->n_nets * ev->B;
-  }
-  return n > 0 && jobs <= kFlowMaxJobs && items <= kFlowMultiItems;
-}
-
 void FlowTables::build(const MergedTables::Lane *lanes, int32_t n) {
   fs.clear();
   bs.clear();
   f_jobs = b_jobs = 0;
   f_blocks = b_blocks = 0;
   f_widest = b_widest = 1;
-  cells = false;
+  f_cells = b_cells = false;
   ctl = flow_ctl(lanes[0].ev);
   for (int32_t j = 1; j < n; ++j)
     flow_set_limit(ctl, std::min(ctl.limit, flow_limit(lanes[j].ev)));
@@ -2133,7 +2110,7 @@ void FlowTables::build(const MergedTables::Lane *lanes, int32_t n) {
   for (int32_t j : order) {
     dp_eval *ev = lanes[j].ev;
     const dp_design *d = ev->d;
-    cells = cells || d->has_cell_gates;
+    f_cells = f_cells || d->has_cell_gates;
     SpFlowSeg f{};
     f.t = SpFlow{view(d), ev->sp.as<float>(), d->level_dev.as<int32_t>(), ev->B, d->depth};
     f.job0 = f_jobs;
@@ -2143,6 +2120,7 @@ void FlowTables::build(const MergedTables::Lane *lanes, int32_t n) {
     f_widest = std::max<int64_t>(f_widest, d->max_level_width);
     fs.push_back(f);
     if (!lanes[j].backward) continue;
+    b_cells = b_cells || d->has_cell_gates;
     BwdFlowSeg b{};
     b.t = BwdFlow{view(d), backward_args(ev, nullptr, 0, ev->B), ev->pi_out.as<float>(),
                   ev->seed.as<float>(), ev->part.as<float>(), d->level_dev.as<int32_t>(),
@@ -2157,23 +2135,131 @@ void FlowTables::build(const MergedTables::Lane *lanes, int32_t n) {
   }
 }
 
-size_t FlowTables::bwd_offset() const {
-  return (fs.size() * sizeof(SpFlowSeg) + 255) & ~(size_t)255;
-}
-size_t FlowTables::bytes() const {
-  return std::max<size_t>(bwd_offset() + bs.size() * sizeof(BwdFlowSeg), 256);
-}
-void FlowTables::pack(void *host) const {
-  if (!fs.empty()) std::memcpy(host, fs.data(), fs.size() * sizeof(SpFlowSeg));
-  if (!bs.empty())
-    std::memcpy((char *)host + bwd_offset(), bs.data(), bs.size() * sizeof(BwdFlowSeg));
-}
 dp_status FlowTables::launch_forward(const SpFlowSeg *dev, hipStream_t s) const {
-  DP_HIP_TRY(launch_sp_flow_multi(dev, (int32_t)fs.size(), f_jobs, f_blocks, f_widest, cells, ctl, s));
+  DP_HIP_TRY(launch_sp_flow_multi(dev, (int32_t)fs.size(), f_jobs, f_blocks, f_widest, f_cells, ctl, s));
   return DP_OK;
 }
 dp_status FlowTables::launch_reverse(const BwdFlowSeg *dev, hipStream_t s) const {
-  DP_HIP_TRY(launch_bwd_flow_multi(dev, (int32_t)bs.size(), b_jobs, b_blocks, b_widest, cells, ctl, s));
+  DP_HIP_TRY(launch_bwd_flow_multi(dev, (int32_t)bs.size(), b_jobs, b_blocks, b_widest, b_cells, ctl, s));
+  return DP_OK;
+}
+
+// The same choice for the sweeps of n evals together: depth is the deepest
+// one's, pairs (net, column) pairs in millions, turns the gates that the fullest
+// XCD's columns walk (all columns share the eight), gates the evals' gates times
+// their rounds of eight columns, since the columns of a design share its lines.
+//   us = base + |(level D, turns T + pairs N + gates G)| + over N + each n
+// So one launch for many levels or for many designs of few columns, and launches
+// level by level for few levels of many pairs (forward / reverse in us, levels
+// against dataflow: 4 x 117K gates x 3 levels, 8 columns each 49 / 71 against 127 /
+// 220; 8 x 50K x 12, 8 columns 70 / 146 against 97 / 105; 8 x 1M x 8, one column 188 /
+// 863 against 102 / 369; 4 x 117K x 60, 4 columns 176 / 346 against 89 / 100).
+// Fitted to 250 sets of 2 to 16 designs of 2K to 1M gates, 2 to 100 levels, 1 to 16
+// columns, 30 of them with library cells: the choice is 0.5 % (forward) and 0.4 %
+// (reverse) slower than the better of the two on average.  Level by level each
+// eval's startpoints are a launch of their own, by whole waves and one after
+// another with one or two columns (about 50 us each), where dataflow was faster
+// in every set.
+namespace {
+struct MultiCost {
+  double base, level, turns, pairs, gates, over, each;
+};
+constexpr MultiCost kSpFlowMulti{23.3, 0.60, 63.8, 13.5, -14.8, 0.0, 0.0},
+    kSpLevelsMulti{20.6, 2.15, 0.0, 0.0, 17.9, 4.0, 0.0};
+constexpr MultiCost kBwdFlowMulti{8.3, 0.98, 171.0, 16.9, -4.4, 0.0, 0.0},
+    kBwdLevelsMulti{-6.0, 5.4, 0.0, 0.0, 0.0, 27.6, 2.0};
+// library cells in one of the designs
+constexpr MultiCost kSpFlowMultiCells{23.8, 3.47, 203.0, 15.1, -34.3, 0.0, 0.0},
+    kSpLevelsMultiCells{11.2, 7.8, 0.0, 0.0, 0.0, 7.1, 0.0};
+constexpr MultiCost kBwdFlowMultiCells{31.4, 1.13, 251.0, 71.5, -20.9, 0.0, 0.0},
+    kBwdLevelsMultiCells{0.0, 34.7, 0.0, 0.0, 0.0, 69.4, 0.0};
+struct MultiSize {
+  double depth = 0, pairs = 0, largest = 0, gates = 0, n = 0;
+  bool cells = false, few = false;
+  void add(const dp_eval *ev) {
+    const dp_design *d = ev->d;
+    const double rounds = (ev->B + 7) / 8, g = d->n_gates * 1e-6 * rounds;
+    depth = std::max(depth, (double)d->depth);
+    pairs += (double)d->n_nets * ev->B * 1e-6;
+    largest = std::max(largest, g);
+    gates += g;
+    n += 1;
+    cells = cells || d->has_cell_gates;
+    few = few || ev->B < 3;
+  }
+  double us(const MultiCost &c) const {
+    const double work = c.turns * std::max(largest, pairs / 8) + c.pairs * pairs + c.gates * gates;
+    return c.base + std::hypot(c.level * depth, std::max(work, 0.0)) + c.over * pairs + c.each * n;
+  }
+};
+}  // namespace
+
+void SweepTables::choose(const MergedTables::Lane *lanes, int32_t n) {
+  int64_t jobs = 0, items = 0;
+  MultiSize f, b;
+  bool ready = n > 0, b_ready = true;
+  for (int32_t j = 0; j < n; ++j) {
+    const dp_eval *ev = lanes[j].ev;
+    ready = ready && flow_ready(ev, ev->B);
+    jobs += ev->B;
+    items += (int64_t)ev->d->n_nets * ev->B;
+    f.add(ev);
+    if (!lanes[j].backward) continue;
+    b_ready = b_ready && have_flow_scratch(ev, ev->B);
+    b.add(ev);
+  }
+  ready = ready && jobs <= kFlowMaxJobs && items <= kFlowMultiItems;
+  flow_forward = ready && (f.cells ? f.us(kSpFlowMultiCells) < f.us(kSpLevelsMultiCells)
+                                   : f.us(kSpFlowMulti) < f.us(kSpLevelsMulti));
+  flow_reverse = ready && b_ready &&
+                 (b.few || (b.cells ? b.us(kBwdFlowMultiCells) < b.us(kBwdLevelsMultiCells)
+                                    : b.us(kBwdFlowMulti) < b.us(kBwdLevelsMulti)));
+}
+
+void SweepTables::build(const MergedTables::Lane *lanes, int32_t n) {
+  choose(lanes, n);
+  if (!flow_forward || !flow_reverse) levels.build(lanes, n, !flow_forward, !flow_reverse);
+  if (flow_forward || flow_reverse) flow.build(lanes, n);
+}
+
+namespace {
+template <class T>
+size_t bytes_of(const std::vector<T> &v) {
+  return v.size() * sizeof(T);
+}
+template <class T>
+void copy_to(void *dst, const std::vector<T> &v) {
+  if (!v.empty()) std::memcpy(dst, v.data(), bytes_of(v));
+}
+}  // namespace
+
+size_t SweepTables::bwd_offset() const {
+  return ((flow_forward ? bytes_of(flow.fs) : bytes_of(levels.fs)) + 255) & ~(size_t)255;
+}
+size_t SweepTables::bytes() const {
+  return std::max<size_t>(bwd_offset() + (flow_reverse ? bytes_of(flow.bs) : bytes_of(levels.bs)), 256);
+}
+void SweepTables::pack(void *host) const {
+  flow_forward ? copy_to(host, flow.fs) : copy_to(host, levels.fs);
+  char *bwd = (char *)host + bwd_offset();
+  flow_reverse ? copy_to(bwd, flow.bs) : copy_to(bwd, levels.bs);
+}
+dp_status SweepTables::launch_forward(const void *dev, hipStream_t s) const {
+  return flow_forward ? flow.launch_forward(static_cast<const SpFlowSeg *>(dev), s)
+                      : levels.launch_forward(static_cast<const SpSeg *>(dev), s);
+}
+dp_status SweepTables::launch_reverse(const void *dev, const MergedTables::Lane *lanes, int32_t n,
+                                      hipStream_t s) const {
+  const void *bwd = static_cast<const char *>(dev) + bwd_offset();
+  if (flow_reverse) return flow.launch_reverse(static_cast<const BwdFlowSeg *>(bwd), s);
+  DP_TRY(levels.launch_reverse(static_cast<const BwdSeg *>(bwd), s));
+  for (int32_t j = 0; j < n; ++j) {
+    if (!lanes[j].backward) continue;
+    dp_eval *ev = lanes[j].ev;
+    const HeavySpan hp = heavy_pis(ev->d);
+    DP_HIP_TRY(launch_bwd_pi(view(ev->d), backward_args(ev, nullptr, 0, ev->B),
+                             ev->pi_out.as<float>(), s, hp.gates, hp.n));
+  }
   return DP_OK;
 }
 
@@ -2246,13 +2332,11 @@ struct dp_group {
   GroupPool pool;
   // Merged level launches of the group's modeled evals (one launch per level
   // index and kind covers that level of every such eval): host tables and
-  // their device copy (forward segments, then reverse at tab_dev_bwd).
+  // their device copy, the power's segments at tab_dev_power.
   std::vector<int32_t> merged;      // eval indices
-  dp::MergedTables tab;
-  dp::FlowTables flow;       // in place of tab where the evals' sweeps fit
-  bool use_flow = false;
+  dp::SweepTables tab;
   dp::DevBuf tab_dev;
-  size_t tab_dev_bwd = 0, tab_dev_power = 0;
+  size_t tab_dev_power = 0;
   dp::PowerTable power;  // empty: each eval's power by itself
   bool have_tables = false;
   uint64_t tables_key = 0;
@@ -2316,27 +2400,16 @@ dp_status build_merged_tables(dp_group *g, bool backward) {
       g->power = dp::PowerTable{};
       break;
     }
-  auto upload = [&](const auto &tab) -> dp_status {
-    g->tab_dev_bwd = tab.bwd_offset();
-    g->tab_dev_power = (tab.bytes() + 255) & ~(size_t)255;
-    host.resize(g->tab_dev_power + std::max<size_t>(g->power.bytes(), 256));
-    DP_TRY(g->tab_dev.alloc(host.size()));
-    tab.pack(host.data());
-    if (!g->power.segs.empty())
-      std::memcpy(host.data() + g->tab_dev_power, g->power.segs.data(),
-                  g->power.segs.size() * sizeof(dp::PowerSeg));
-    DP_HIP_TRY(hipMemcpy(g->tab_dev.ptr, host.data(), host.size(), hipMemcpyHostToDevice));
-    return DP_OK;
-  };
-  if (g->use_flow) {
-    g->flow.build(lanes.data(), (int32_t)lanes.size());
-    g->flow.ctl.report = g->report->word;
-    DP_TRY(upload(g->flow));
-  } else {
-    for (auto &l : lanes) l.backward = true;
-    g->tab.build(lanes.data(), (int32_t)lanes.size());
-    DP_TRY(upload(g->tab));
-  }
+  g->tab.build(lanes.data(), (int32_t)lanes.size());
+  g->tab.flow.ctl.report = g->report->word;
+  g->tab_dev_power = (g->tab.bytes() + 255) & ~(size_t)255;
+  host.resize(g->tab_dev_power + std::max<size_t>(g->power.bytes(), 256));
+  DP_TRY(g->tab_dev.alloc(host.size()));
+  g->tab.pack(host.data());
+  if (!g->power.segs.empty())
+    std::memcpy(host.data() + g->tab_dev_power, g->power.segs.data(),
+                g->power.segs.size() * sizeof(dp::PowerSeg));
+  DP_HIP_TRY(hipMemcpy(g->tab_dev.ptr, host.data(), host.size(), hipMemcpyHostToDevice));
   g->have_tables = true;
   return DP_OK;
 }
@@ -2346,11 +2419,7 @@ dp_status build_merged_tables(dp_group *g, bool backward) {
 // eval's PI adjoints.
 dp_status enqueue_merged(dp_group *g, hipStream_t origin, bool backward) {
   if (g->merged.empty()) return DP_OK;
-  const char *bwd_tab = (const char *)g->tab_dev.ptr + g->tab_dev_bwd;
-  if (g->use_flow)
-    DP_TRY(g->flow.launch_forward(g->tab_dev.as<dp::SpFlowSeg>(), origin));
-  else
-    DP_TRY(g->tab.launch_forward(g->tab_dev.as<dp::SpSeg>(), origin));
+  DP_TRY(g->tab.launch_forward(g->tab_dev.ptr, origin));
   if (!g->power.segs.empty())
     DP_TRY(g->power.launch((const char *)g->tab_dev.ptr + g->tab_dev_power, origin));
   else
@@ -2362,16 +2431,9 @@ dp_status enqueue_merged(dp_group *g, hipStream_t origin, bool backward) {
       DP_TRY(st);
     }
   if (!backward) return DP_OK;
-  if (g->use_flow)  // the PIs' adjoints included
-    return g->flow.launch_reverse(reinterpret_cast<const dp::BwdFlowSeg *>(bwd_tab), origin);
-  DP_TRY(g->tab.launch_reverse(reinterpret_cast<const dp::BwdSeg *>(bwd_tab), origin));
-  for (int32_t i : g->merged) {
-    dp_eval *ev = g->evs[i];
-    const dp::HeavySpan hp = dp::heavy_pis(ev->d);
-    DP_HIP_TRY(dp::launch_bwd_pi(view(ev->d), backward_args(ev, nullptr, 0, ev->B),
-                                 ev->pi_out.as<float>(), origin, hp.gates, hp.n));
-  }
-  return DP_OK;
+  std::vector<dp::MergedTables::Lane> lanes;
+  for (int32_t i : g->merged) lanes.push_back({g->evs[i], true});
+  return g->tab.launch_reverse(g->tab_dev.ptr, lanes.data(), (int32_t)lanes.size(), origin);
 }
 
 // `threads`: enqueue the branches from the group's worker threads, one
@@ -2553,13 +2615,14 @@ dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
   if (!g->merged.empty()) {
     std::vector<dp::MergedTables::Lane> lanes;
     for (int32_t i : g->merged) lanes.push_back({g->evs[i], backward != 0});
-    g->use_flow = dp::FlowTables::fits(lanes.data(), (int32_t)lanes.size());
-    mix((uint64_t)g->use_flow);
-    if (g->use_flow)
+    dp::SweepTables route;
+    route.choose(lanes.data(), (int32_t)lanes.size());
+    mix((uint64_t)route.flow_forward + 2 * (uint64_t)route.flow_reverse);
+    if (route.flow_forward || route.flow_reverse)
       for (const auto &l : lanes) dp::join_shared(l.ev, g->report);
-    const int64_t per_sweep =
-        g->use_flow ? 2 : dp::MergedTables::level_launches(lanes.data(), (int32_t)lanes.size());
-    launches += per_sweep * (backward ? 2 : 1) + (int64_t)g->merged.size() * (backward ? 4 : 3);
+    const int64_t levels = dp::MergedTables::level_launches(lanes.data(), (int32_t)lanes.size());
+    launches += (route.flow_forward ? 2 : levels) + (int64_t)g->merged.size() * (backward ? 4 : 3);
+    if (backward) launches += route.flow_reverse ? 2 : levels;
   }
   const int32_t want = g->max_branches > 0 ? g->max_branches : kGroupBranches;
   const int32_t nb = std::max<int32_t>(1, std::min<int32_t>({want, (int32_t)g->branch.size(), (int32_t)n}));
@@ -2777,14 +2840,9 @@ dp_status lanes_run_merged(const LaneJob *jobs, int32_t n_jobs, hipStream_t s,
     lanes[j] = {jobs[j].ev, jobs[j].backward};
     any_backward = any_backward || jobs[j].backward;
   }
-  MergedTables tab;
-  FlowTables flow;
-  const bool use_flow = FlowTables::fits(lanes.data(), n_jobs);
-  if (use_flow)
-    flow.build(lanes.data(), n_jobs);
-  else
-    tab.build(lanes.data(), n_jobs);
-  const size_t sweeps = ((use_flow ? flow.bytes() : tab.bytes()) + 255) & ~(size_t)255;
+  SweepTables tab;
+  tab.build(lanes.data(), n_jobs);
+  const size_t sweeps = (tab.bytes() + 255) & ~(size_t)255;
   const size_t lanes_at = sweeps + power.bytes(), bytes = lanes_at + segs.size() * sizeof(LaneSeg);
   if (bytes > sc->cap) {
     if (sc->host) (void)hipHostFree(sc->host);
@@ -2795,31 +2853,16 @@ dp_status lanes_run_merged(const LaneJob *jobs, int32_t n_jobs, hipStream_t s,
     sc->cap = bytes;
   }
   char *host = static_cast<char *>(sc->host), *dev = static_cast<char *>(sc->dev.ptr);
-  use_flow ? flow.pack(host) : tab.pack(host);
+  tab.pack(host);
   std::memcpy(host + sweeps, power.segs.data(), power.segs.size() * sizeof(PowerSeg));
   std::memcpy(host + lanes_at, segs.data(), segs.size() * sizeof(LaneSeg));
   const auto *lane_tab = reinterpret_cast<const LaneSeg *>(dev + lanes_at);
   DP_HIP_TRY(hipMemcpyAsync(sc->dev.ptr, sc->host, bytes, hipMemcpyHostToDevice, s));
-  const char *bwd_tab = dev + (use_flow ? flow.bwd_offset() : tab.bwd_offset());
   DP_HIP_TRY(launch_lanes_stage(lane_tab, n_jobs, stage, import, s));
-  if (use_flow)
-    DP_TRY(flow.launch_forward(sc->dev.as<SpFlowSeg>(), s));
-  else
-    DP_TRY(tab.launch_forward(sc->dev.as<SpSeg>(), s));
+  DP_TRY(tab.launch_forward(dev, s));
   DP_TRY(power.launch(dev + sweeps, s));
   if (!any_backward) return DP_OK;
-  if (use_flow)
-    DP_TRY(flow.launch_reverse(reinterpret_cast<const BwdFlowSeg *>(bwd_tab), s));
-  else
-    DP_TRY(tab.launch_reverse(reinterpret_cast<const BwdSeg *>(bwd_tab), s));
-  if (!use_flow)  // (the dataflow sweep ends with the PIs)
-    for (int32_t j = 0; j < n_jobs; ++j) {
-      if (!jobs[j].backward) continue;
-      dp_eval *ev = jobs[j].ev;
-      const HeavySpan hp = heavy_pis(ev->d);
-      DP_HIP_TRY(launch_bwd_pi(view(ev->d), backward_args(ev, nullptr, 0, ev->B),
-                               ev->pi_out.as<float>(), s, hp.gates, hp.n));
-    }
+  DP_TRY(tab.launch_reverse(dev, lanes.data(), n_jobs, s));
   DP_HIP_TRY(launch_lanes_out(lane_tab, n_jobs, out, s));
   return DP_OK;
 }

@@ -197,14 +197,10 @@ struct MergedTables {
   // reverse, [2 (D + 1)], index 2 l + k: first segment, segment count, blocks
   std::vector<int32_t> b_off, b_cnt;
   std::vector<uint32_t> b_blk;
-  void build(const Lane *lanes, int32_t n);
+  void build(const Lane *lanes, int32_t n, bool forward, bool reverse);
   // Launches of one merged sweep over these lanes (the reverse; the
   // forward's are at most as many).
   static int64_t level_launches(const Lane *lanes, int32_t n);
-  // Packed layout: forward segments, then the reverse ones at bwd_offset().
-  size_t bwd_offset() const;
-  size_t bytes() const;
-  void pack(void *host) const;
   dp_status launch_forward(const SpSeg *dev, hipStream_t s) const;
   dp_status launch_reverse(const BwdSeg *dev, hipStream_t s) const;
 };
@@ -217,19 +213,30 @@ struct FlowTables {
   int32_t f_jobs = 0, b_jobs = 0;
   uint32_t f_blocks = 0, b_blocks = 0;
   int64_t f_widest = 1, b_widest = 1;
-  bool cells = false;
+  bool f_cells = false, b_cells = false;
   FlowCtl ctl{};  // the first eval's words, the smallest limit
-  // Whether these evals' sweeps go this way: each is one for the dataflow
-  // kernels, its reverse buffers are there where it wants gradients, and
-  // together they are within the launches' limits.
-  static bool fits(const MergedTables::Lane *lanes, int32_t n);
+  void build(const MergedTables::Lane *lanes, int32_t n);
+  dp_status launch_forward(const SpFlowSeg *dev, hipStream_t s) const;
+  dp_status launch_reverse(const BwdFlowSeg *dev, hipStream_t s) const;
+};
+
+// The sweeps of several evals (design groups and serving steps), forward and
+// reverse each as merged level launches or as one dataflow launch.
+struct SweepTables {
+  MergedTables levels;
+  FlowTables flow;
+  bool flow_forward = false, flow_reverse = false;
+  // Chooses; the tables stay as they are.
+  void choose(const MergedTables::Lane *lanes, int32_t n);
   void build(const MergedTables::Lane *lanes, int32_t n);
   // Packed layout: forward segments, then the reverse ones at bwd_offset().
   size_t bwd_offset() const;
   size_t bytes() const;
   void pack(void *host) const;
-  dp_status launch_forward(const SpFlowSeg *dev, hipStream_t s) const;
-  dp_status launch_reverse(const BwdFlowSeg *dev, hipStream_t s) const;
+  // dev: the packed tables.  The reverse ends with the PIs' adjoints.
+  dp_status launch_forward(const void *dev, hipStream_t s) const;
+  dp_status launch_reverse(const void *dev, const MergedTables::Lane *lanes, int32_t n,
+                           hipStream_t s) const;
 };
 
 // Segment table of the power of several evals.

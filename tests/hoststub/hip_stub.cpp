@@ -137,7 +137,7 @@ long stub_live_bytes() {
 static size_t g_limit = 0, g_host = 0;
 void stub_set_memory(long bytes) { g_limit = (size_t)bytes; }
 // Dataflow launches over several designs, and merged level launches.
-static long g_flow_multi = 0, g_level_multi = 0;
+static long g_flow_multi = 0, g_level_multi = 0, g_flow_multi_bwd = 0, g_level_multi_bwd = 0;
 // Modeled SP and reverse sweeps: dataflow launches, level launches, and those of
 // the reverse sweep in adjoints.
 static long g_sweeps[5] = {};
@@ -154,6 +154,10 @@ void stub_sim_counts(long *out) {
 void stub_multi_counts(long *out) {
   out[0] = g_flow_multi;
   out[1] = g_level_multi;
+}
+void stub_multi_reverse_counts(long *out) {
+  out[0] = g_flow_multi_bwd;
+  out[1] = g_level_multi_bwd;
 }
 hipError_t hipMalloc(void **ptr, size_t size) {
   if (thread_captures()) fatal("hipMalloc while this thread captures a stream");
@@ -848,6 +852,7 @@ hipError_t launch_bwd_flow_multi(const BwdFlowSeg *segs, int32_t n_segs, int32_t
                                  uint32_t blocks, int64_t widest, bool cells, FlowCtl ctl,
                                  hipStream_t stream_) {
   Scope sc_(stream_);
+  ++g_flow_multi_bwd;
   int32_t job = 0;
   uint32_t block = 0;
   for (int32_t k = 0; k < n_segs; ++k) {
@@ -884,6 +889,7 @@ hipError_t launch_sp_multi(const SpSeg *segs, int32_t n_segs, uint32_t blocks, b
 hipError_t launch_bwd_multi(const BwdSeg *segs, int32_t n_segs, uint32_t blocks, bool cells,
                             hipStream_t st) {
   Scope sc_(st);
+  ++g_level_multi_bwd;
   for (int32_t k = 0; k < n_segs; ++k) {
     const uint32_t b0 = segs[k].block0, b1 = k + 1 < n_segs ? segs[k + 1].block0 : blocks;
     if (b1 < b0 || (int64_t)(b1 - b0) * kMergedBlock < (int64_t)segs[k].n * segs[k].a.C) {

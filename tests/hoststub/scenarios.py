@@ -320,6 +320,50 @@ def scenario_group_after_columns(ctx):
     return {"results": n, "wide": wide}
 
 
+def scenario_group_routes(ctx):
+    """Which way groups' forward and reverse sweeps go: [forward, reverse], "flow"
+    or "levels", launched as they are and recorded into a graph."""
+    import ctypes
+    stub = ctypes.CDLL(sys.argv[1])
+    f, b = (ctypes.c_long * 2)(), (ctypes.c_long * 2)()
+
+    def counts():
+        stub.stub_multi_counts(f)
+        stub.stub_multi_reverse_counts(b)
+        return list(f), list(b)
+    out = {}
+    lib = tuple(range(9)) + tuple(synth.CELL_BASE + c for c in range(3))
+    for name, gates, depth, n, B, cells in (
+            ("deep", 2000, 40, 3, 2, False), ("shallow", 20_000, 2, 4, 8, False),
+            ("middle", 20_000, 4, 2, 16, False), ("shallow, one column", 20_000, 2, 4, 1, False),
+            ("shallow cells", 20_000, 2, 4, 16, True), ("deep cells", 2000, 20, 3, 4, True)):
+        nl = synth.random_dag(synth.DagSpec(gates, 500, depth, ops=lib if cells else tuple(range(9)),
+                                            cells=synth.LIBRARY[:3] if cells else ()), 13)
+        d = api.Design(ctx, nl)
+        evs = []
+        for i in range(n):
+            ev = api.Eval(d, B)
+            ev.set_pi_prob(synth.pi_probs(nl.n_pi, 30 + i, batch=B))
+            ev.set_caps(synth.net_caps(nl.n_nets, 14))
+            evs.append(ev)
+        grp = api.Group(ctx, evs)
+        for use_graph in (False, True):
+            grp.configure(use_graph=use_graph)
+            for backward in (True, False, True):
+                f0, b0 = counts()
+                grp.run(("power",), backward=backward)
+                f1, b1 = counts()
+                got = ["flow" if x1[0] > x0[0] else "levels" if x1[1] > x0[1] else "-"
+                       for x0, x1 in ((f0, f1), (b0, b1))]
+                out.setdefault(name, got if backward else None)
+                want = out[name] if backward else [out[name][0], "-"]
+                assert got == want, (name, use_graph, backward, got, want)
+        grp.close()
+        for ev in evs:
+            ev.close()
+    return out
+
+
 def scenario_deep_graphs(ctx):
     """Captures of the reverse sweep of chains whose level launches are about as
     many as a graph takes (1,024)."""
@@ -599,6 +643,7 @@ if __name__ == "__main__":
               "group_serving": scenario_group_serving,
               "capture_order": scenario_capture_order,
               "group_persistent": scenario_group_persistent,
+              "group_routes": scenario_group_routes,
               "group_after_columns": scenario_group_after_columns,
               "deep_graphs": scenario_deep_graphs,
               "profile": scenario_profile,

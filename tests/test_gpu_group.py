@@ -125,3 +125,39 @@ def test_merged_level_launches_match_alone():
             for g, w in zip(got, want):
                 _check(g, w)
     grp.close()
+
+
+# both sweeps level by level; the forward alone; neither, though the designs are
+# as shallow; and the like with library cells
+@pytest.mark.parametrize("gates,depth,n,B,cells", [
+    (20_000, 2, 4, 8, False), (20_000, 4, 2, 16, False), (20_000, 2, 4, 1, False),
+    (20_000, 2, 4, 16, True), (20_000, 4, 3, 5, True)])
+def test_group_routes_agree(gates, depth, n, B, cells):
+    say(f"group: {n} x {gates} gates x {depth} levels, {B} columns, cells {cells}")
+    ops = tuple(range(9)) + (tuple(synth.CELL_BASE + c for c in range(3)) if cells else ())
+    nl = synth.random_dag(synth.DagSpec(gates, 500, depth, ops=ops,
+                                        cells=synth.LIBRARY[:3] if cells else ()), 13)
+    ctx = api.Context(0)
+    d = api.Design(ctx, nl)
+
+    def make(i):
+        ev = api.Eval(d, B)
+        ev.set_pi_prob(synth.pi_probs(nl.n_pi, 30 + i, batch=B))
+        ev.set_caps(synth.net_caps(nl.n_nets, 14))
+        return ev
+    ref = []
+    for i in range(n):
+        ev = make(i)
+        ev.set_schedule(L.DP_SCHED_LEVEL)
+        r = ev.forward(("power", "sp"))
+        r.update(ev.backward(want=("dpi",)))
+        ref.append(r)
+    grp = api.Group(ctx, [make(i) for i in range(n)])
+    for use_graph in (True, False):
+        grp.configure(use_graph=use_graph)
+        for backward in (True, False, True):
+            res = grp.run(("power", "sp"), backward=backward)
+            for i in range(n):
+                for k in res[i]:
+                    np.testing.assert_array_equal(res[i][k], ref[i][k], err_msg=f"{k} of {i}")
+    grp.close()

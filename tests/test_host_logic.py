@@ -83,6 +83,15 @@ def test_groups_of_evals_with_other_scratch(stub_lib):
     assert _run(stub_lib, "group_after_columns") == {"results": 12, "wide": True}
 
 
+def test_routes_of_groups(stub_lib):
+    """Few levels of many pairs go level by level, forward and reverse by
+    themselves; a reverse sweep of one column does not."""
+    assert _run(stub_lib, "group_routes") == {
+        "deep": ["flow", "flow"], "shallow": ["levels", "levels"], "middle": ["levels", "flow"],
+        "shallow, one column": ["flow", "flow"], "shallow cells": ["levels", "levels"],
+        "deep cells": ["flow", "flow"]}
+
+
 def test_reverse_graphs_of_deep_designs(stub_lib):
     assert _run(stub_lib, "deep_graphs") == {"1021": 1, "1022": 1, "1023": 1, "1024": 0}
 
