@@ -103,7 +103,6 @@ dp_status check_params(const dp_params *p) {
   return DP_OK;
 }
 
-// Validate a float array (host or device) against [lo, hi] (NaN rejected).
 // The eval's pinned words, once.
 dp_status ensure_reports(dp_eval *ev) {
   if (!ev->reports) ev->reports = ev->d->ctx->reports;
@@ -112,10 +111,10 @@ dp_status ensure_reports(dp_eval *ev) {
   return DP_OK;
 }
 
-// Refuse values outside [lo, hi] (and NaN).  Device values are checked on the
-// device; the kernel reports into a pinned word of the eval's (a device flag
-// took a fill and a copy to the host more, 20 to 30 us a call), and stores them
-// in `copy` on its way where that is not null.
+// Refuse a float array (host or device) with values outside [lo, hi] or NaN.
+// Device values are checked on the device; the kernel reports into a pinned word
+// of the eval's (a device flag took a fill and a copy to the host more, 20 to 30
+// us a call), and stores them in `copy` on its way where that is not null.
 dp_status check_values(dp_eval *ev, const float *v, int64_t n, float lo, float hi, int on_device,
                        const char *what, float *copy = nullptr) {
   if (!v) return fail(DP_E_INVALID, std::string(what) + ": NULL pointer");
@@ -529,10 +528,9 @@ dp_status barrier_status(dp_eval *ev) {
                             " us); that sweep's outputs are NaN and not a result");
 }
 
-// Synchronize the eval's stream when a persistent sweep is unchecked, then
-// report it (host-output calls end here).
+// Synchronize the eval's stream, then report a sweep of it that gave up
+// (host-output calls end here).
 dp_status sync_and_check(dp_eval *ev) {
-  if (!ev->barrier_pending && !ev->flow_report) return DP_OK;
   DP_HIP_TRY(hipStreamSynchronize(ev->stream()));
   return barrier_status(ev);
 }
@@ -1776,7 +1774,6 @@ static dp_status run_backward(dp_eval *ev, const float *grad_power, int per_colu
     DP_TRY(om.flush(s));
   }
   if (!on_device) DP_TRY(sync_and_check(ev));
-  if (!on_device) DP_HIP_TRY(hipStreamSynchronize(s));
   return DP_OK;
 }
 
@@ -1920,10 +1917,7 @@ dp_status dp_forward_backward_columns(dp_eval *ev, float *power, float *dpower_d
                                 ev->stream()));
     }
     if (dpower_dpi) return run_backward(ev, nullptr, 1, dpower_dpi, nullptr, nullptr, on_device);
-    if (!on_device) {
-      DP_TRY(sync_and_check(ev));
-      DP_HIP_TRY(hipStreamSynchronize(ev->stream()));
-    }
+    if (!on_device) DP_TRY(sync_and_check(ev));
     return DP_OK;
   }
   // the checks of dp_forward and dp_backward, then every buffer before the
@@ -1968,7 +1962,6 @@ dp_status dp_forward_backward_columns(dp_eval *ev, float *power, float *dpower_d
     DP_HIP_TRY(hipMemcpyAsync(dpower_dpi, dst, dpi_bytes, hipMemcpyDeviceToHost, s));
   if (!on_device) {
     DP_TRY(sync_and_check(ev));
-    DP_HIP_TRY(hipStreamSynchronize(s));
   }
   return DP_OK;
 }
