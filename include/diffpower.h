@@ -84,19 +84,24 @@ enum {
 /* Sweep schedules (see dp_eval_set_schedule). */
 enum {
   DP_SCHED_AUTO = 0,      /* the autotuned choice (default) */
-  DP_SCHED_LEVEL = 1,     /* launches in stream order: a simulation, and a
-                             sweep of many (net, column) pairs, one launch per
-                             level (an SP-only forward with few columns: one
-                             per two levels of fixed cells, the second level
-                             recomputing the pins the first drives); an
-                             SP-only or reverse sweep of at most 2^22 (net,
-                             column) pairs and 64 columns as one launch whose
-                             gates wait for their own inputs.  Bit for bit the
-                             same results.  Should such a wait give up (after
-                             seconds, see dp_eval_set_barrier_timeout; it
-                             cannot while the device makes progress), that sweep's outputs are NaN and the
-                             eval's next host synchronization returns
-                             DP_E_HIP */
+  DP_SCHED_LEVEL = 1,     /* launches in stream order.  A sweep is one launch
+                             per level (an SP-only forward with few columns:
+                             one per two levels of fixed cells, the second
+                             level recomputing the pins the first drives), or
+                             one launch whose gates wait for their own inputs:
+                             an SP-only or reverse sweep of at most 2^22 (net,
+                             column) pairs and 64 columns, and a short
+                             simulation, where that is the faster way at the
+                             design's depth.  Bit for bit the same results.
+
+                             Should such a wait give up (after seconds, see
+                             dp_eval_set_barrier_timeout; it cannot while the
+                             device makes progress), nothing of the sweep is a
+                             result: what it did not reach is NaN, as are the
+                             rates, beta and power that need it, and a
+                             simulation's counts are 0xFFFFFFFF.  The eval's
+                             next host synchronization returns DP_E_HIP, once;
+                             later sweeps are not affected */
   DP_SCHED_GRAPH = 2,     /* the same launches captured once into HIP graphs,
                              one per forward sweep and one per reverse sweep
                              of dp_backward / dp_backward_columns (forward
@@ -377,7 +382,8 @@ dp_status dp_power_gradients(dp_eval *ev, float *dpower_dsp, float *score,
  * level) comes from a two-cycle bit-parallel simulation of the pair.
  * Outputs (host or device memory as on_device; each may be NULL): v0
  * [B][n_pi] bytes (0/1), p_final [B][n_pi], p_virus [B] (double).  The
- * eval's PI probabilities are left at p_final.  Returns after the results
+ * eval's PI probabilities are left at p_final (after a sweep that gave up,
+ * DP_E_HIP, they have to be set again).  Returns after the results
  * are written.  Needs DP_MODELED or DP_FROZEN_BETA and S = 0.
  * Errors: DP_E_STATE, DP_E_UNSUPPORTED, DP_E_INVALID, DP_E_HIP, DP_E_OOM. */
 dp_status dp_power_virus(dp_eval *ev, int32_t steps, double eta, uint8_t *v0,
@@ -387,9 +393,10 @@ dp_status dp_power_virus(dp_eval *ev, int32_t steps, double eta, uint8_t *v0,
  * held on the device at once (0 = automatic; otherwise a multiple of 2 that
  * splits the n_sim/64 words into chunks carrying a two-word halo), and the
  * word pairs each simulation lane handles per wave (1, 2, 4 or 8; 0 =
- * automatic).  With words_per_chunk 0, short simulations of designs without
- * library cells run all their levels in one launch (sim_pairs_per_lane then
- * has no effect); a chunk of all n_sim/64 words keeps level launches.
+ * automatic).  With words_per_chunk 0, short simulations run all their levels
+ * in one launch where that is the faster way and the device has the memory for
+ * it (sim_pairs_per_lane then has no effect); a chunk of all n_sim/64 words
+ * keeps level launches.
  * Results are bitwise independent of all three.  Choosing
  * DP_SCHED_PERSISTENT the first time allocates the eval's two barrier words
  * (8 bytes of device memory, zeroed on the eval's stream).
@@ -464,7 +471,7 @@ dp_status dp_eval_get_profile(dp_eval *ev, dp_profile *out);
 /* For callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  The same
  * forward as dp_forward on a one-column eval in DP_MODELED or DP_FROZEN_BETA
- * (the same launches: one per level, or one per two levels of fixed cells;
+ * (level launches only: one per level, or one per two levels of fixed cells;
  * bit for bit the same results), without an eval: the
  * SP, the internal capacitances and beta and the power partial sums
  * live in a static device array of the library
@@ -497,7 +504,9 @@ dp_status dp_forward_static(const dp_design *design, const dp_params *params,
  * the context's stream.  Up to 1024 launches in total the whole unit is
  * captured once into a HIP graph, recorded on one stream (no branches), and
  * each run is one graph launch; larger units, and use_graph = 0, are
- * enqueued directly on the branches.  Results are bitwise
+ * enqueued directly on the branches.  The modeled and frozen-beta evals sweep
+ * together, on the context's stream: one launch per level over all of them, or
+ * one for all levels, whichever is the faster way for the set.  Results are bitwise
  * those of dp_forward and dp_backward on each eval alone (per-level
  * launches, grad_power = 1).
  *
@@ -512,6 +521,9 @@ dp_status dp_group_create(dp_ctx *ctx, dp_eval *const *evals, int32_t n_evals,
  * sweep.  outs: NULL, or n_evals output descriptors (as dp_forward; each
  * with its own on_device).  dpower_dpi: NULL, or n_evals pointers (each
  * NULL or [B_i][n_pi_i], host or device as on_device) for dPower/dp.
+ * A wait that gave up in a joint sweep is reported to each of its evals: by this
+ * call if it returns host outputs, else by each eval's next host
+ * synchronization.
  * Errors: DP_E_STATE (an eval's inputs are missing), DP_E_INVALID, DP_E_HIP,
  * DP_E_OOM. */
 dp_status dp_group_run(dp_group *g, int32_t backward, const dp_fwd_out *outs,
