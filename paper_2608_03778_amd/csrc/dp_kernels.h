@@ -423,14 +423,15 @@ struct FlowCtl {
   int32_t n_cu;       // compute units of the device
   int32_t shifts;     // levels in which the waves take turns (set by the launcher)
   int32_t per_block;  // waves of a workgroup that take items (set by the launcher)
-  // a wait gives up after this many polls, and looks at its count and at the
-  // stop flag whenever polls & every is 0
-  uint32_t limit, every;
+  // a wait counts its polls from start and gives up at limit; it looks at that
+  // and at the stop flag once in kFlowRound polls
+  uint32_t limit, start;
   int32_t sized;      // several designs: staged_sizes of one of them
 };
 // Polls (a tenth of a microsecond each, so seconds) after which a wait gives up
 // by default.
 constexpr uint32_t kFlowPolls = 1u << 26;
+constexpr uint32_t kFlowRound = 64;
 // Whether the seeds of a reverse sweep take several size vectors' weights
 // through LDS (from this many on; fewer are read directly).
 constexpr int32_t kStagedSizes = 4;
@@ -439,7 +440,7 @@ constexpr bool staged_sizes(const BwdArgs &a) {
 }
 inline void flow_set_limit(FlowCtl &ctl, uint32_t polls) {
   ctl.limit = polls;
-  ctl.every = polls < 64 ? 0 : 63;
+  ctl.start = polls < kFlowRound ? kFlowRound - 1 : 0;  // (a small one: at the first poll)
 }
 // The first block of level l that wave w of a team of `waves` takes, the next
 // ones `waves` further each: over all waves every block once, whatever the

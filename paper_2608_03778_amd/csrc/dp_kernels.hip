@@ -2642,7 +2642,7 @@ __device__ __forceinline__ void flow_store(float *base, uint32_t bytes, float v)
 
 // One more poll of a wait: false when the wait has to end.
 __device__ __forceinline__ bool flow_again(const FlowCtl &ctl, int stop, uint32_t &polls) {
-  if ((++polls & ctl.every) != 0u) return true;
+  if ((++polls & (kFlowRound - 1)) != 0u) return true;
   if (flow_load(ctl.words + stop) != 0u) return false;
   if (polls < ctl.limit) return true;
   __hip_atomic_store(ctl.words + stop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2675,7 +2675,7 @@ __device__ __forceinline__ FlowSeat flow_join(const FlowCtl &ctl) {
       n = __hip_atomic_fetch_or(reg, kFlowClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(open, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else if (!(r & kFlowClosed)) {
-      uint32_t polls = 0;
+      uint32_t polls = ctl.start;
       while ((n = flow_load(open)) == 0u && flow_again(ctl, kFlowStop, polls)) {
       }
     }
@@ -2702,7 +2702,7 @@ __device__ __forceinline__ int32_t flow_claim(const FlowCtl &ctl, const FlowSeat
       v = t < (uint32_t)n_cols ? t + 2u : 1u;  // 1: none left
       __hip_atomic_store(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
-      uint32_t polls = 0;
+      uint32_t polls = ctl.start;
       while ((v = flow_load(slot)) == 0u && flow_again(ctl, kFlowStop, polls)) {
       }
     }
@@ -2835,7 +2835,7 @@ __device__ __forceinline__ SpFlowIn<CELLS> sp_flow_poll(const FlowCtl &ctl, cons
   for (int j = 0; j < N; ++j) at[j] = flow_off(f.pin[j], t.B, col);
 #pragma unroll
   for (int j = 0; j < N; ++j) x.v[j] = j < n ? flow_poll(t.sp, at[j]) : 0.0f;
-  uint32_t polls = 0;
+  uint32_t polls = ctl.start;
   for (;;) {
     bool wait = false;
 #pragma unroll
@@ -3047,7 +3047,7 @@ template <int K>
 __device__ __forceinline__ float flow_strands(const FlowCtl &ctl, const BwdFlowCol &u, uint32_t e,
                                               int32_t m, int32_t &ok) {
   float v[K][kStrand];
-  uint32_t polls = 0;
+  uint32_t polls = ctl.start;
   for (;;) {
     u4 w[K][2];
 #pragma unroll
@@ -3398,7 +3398,7 @@ __device__ __forceinline__ SimSeat sim_join(const FlowCtl &ctl, uint32_t n_bufs,
       v = n | min(buf + 1, 0xffffffu) << 8;
       __hip_atomic_store(open, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else if (!(r & kFlowClosed)) {
-      uint32_t polls = 0;
+      uint32_t polls = ctl.start;
       while ((v = flow_load(open)) == 0u && flow_again(ctl, kSimStop, polls)) {
       }
     }
@@ -3427,7 +3427,7 @@ __device__ __forceinline__ bool sim_wait(const FlowCtl &ctl, const SimSeat &st, 
   __shared__ int32_t go;
   if (threadIdx.x < 64) {
     const uint32_t *flags = ctl.words + kSimFlags + st.buf * kSimMembers * 32;
-    uint32_t polls = 0;
+    uint32_t polls = ctl.start;
     int32_t ok = 1;
     for (;;) {
       const uint32_t v = threadIdx.x < st.members ? flow_load(flags + threadIdx.x * 32) : epoch;
@@ -3459,7 +3459,7 @@ __device__ __forceinline__ int32_t sim_claim(const FlowCtl &ctl, const SimSeat &
       v = (k + 1) << 16 | (t < (uint32_t)n_tiles ? t + 1 : 0u);
       __hip_atomic_store(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
-      uint32_t polls = 0;
+      uint32_t polls = ctl.start;
       while ((v = flow_load(slot)) >> 16 != k + 1)
         if (!flow_again(ctl, kSimStop, polls)) {
           v = 0;
