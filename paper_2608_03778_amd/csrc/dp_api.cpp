@@ -406,12 +406,16 @@ bool flow_ready(const dp_eval *ev, int32_t C) {
 // 3.5M gates, 2 to 400 levels, 1 to 64 columns and 113 with 9 to 200 library
 // cells in half of the gates or all (20K gates x 2 levels of nine cells, 32
 // columns, 33 / 98 against 48 / 117; 117K x 12, one column, 107 / 367 against 66 /
-// 67); over the former the choice is 0.1 % (forward) and 0.4 % (gradient)
-// slower than the better of the two on average and at most 2 % slower than level
-// launches (the bases lean that way by 2 and 3 us).
+// 67).  Dataflow is taken up to kFlowLean times the levels' fitted cost, as the
+// fit errs that way in the middle (50K gates x 25 levels, 32 columns 62 us
+// against 71, fitted 74 against 71; 20K x 20, 56 columns 61 against 69): over the
+// 280 of the former that fit a dataflow sweep the choice is then 0.05 % (forward)
+// and 0.3 % (gradient) slower than the better of the two on average and at most
+// 5 % slower than level launches.
 struct SweepCost {
   double base, level, gates, pairs, far, over;
 };
+constexpr double kFlowLean = 1.06;
 constexpr SweepCost kSpFlow{20.5, 0.72, 31.6, 26.8, 0.0, 0.0}, kSpLevels{12.7, 1.82, 16.7, 0.0, 0.0, 7.9};
 constexpr SweepCost kBwdFlow{13.4, 0.80, 118.6, 24.1, 7.3, 0.0}, kBwdLevels{5.1, 3.81, 123.0, 0.0, 0.0, 4.9};
 // (level launches of one or two columns pull with whole waves)
@@ -441,10 +445,10 @@ bool flow_pays(const dp_design *d, int32_t C, bool reverse) {
   const double G = d->n_gates * 1e-6, N = (double)d->n_nets * C * 1e-6, rounds = (C + 7) / 8;
   if (!reverse)
     return sweep_us(kSpFlow, kSpFlowCells, d, G * rounds, N) <
-           sweep_us(kSpLevels, kSpLevelsCells, d, G, N);
+           kFlowLean * sweep_us(kSpLevels, kSpLevelsCells, d, G, N);
   const bool few = C < 3;
   return sweep_us(few ? kBwdFlowFew : kBwdFlow, kBwdFlowCells, d, G * rounds, N) <
-         sweep_us(few ? kBwdLevelsFew : kBwdLevels, kBwdLevelsCells, d, G, N);
+         kFlowLean * sweep_us(few ? kBwdLevelsFew : kBwdLevels, kBwdLevelsCells, d, G, N);
 }
 
 // Whether the eval's SP sweep, and a reverse sweep over C columns, run as one
