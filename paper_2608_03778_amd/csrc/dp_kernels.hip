@@ -3609,8 +3609,9 @@ __device__ __forceinline__ w2 sim_cell(const w2 (&x)[N], const SimFlowFetch<N ==
 }
 
 // The first sp_blocks workgroups take the SP sweep of the same columns, which
-// has few waves and long waits, beside the tiles.  Registers for six waves a SIMD: two or three teams of tiles and
-// the sweep's.
+// has few waves and long waits, beside the tiles.  Registers for six waves a
+// SIMD: two or three teams of tiles and the sweep's (library cells spill one of
+// them, 8 bytes of scratch).
 template <int LPG, bool CELLS>
 __global__ __launch_bounds__(kFlowThreads, 6) void k_sim_flow(FlowCtl ctl, SimFlow t, FlowCtl sp_ctl,
                                                               SpFlow sp, uint32_t sp_blocks) {

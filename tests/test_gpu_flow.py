@@ -141,8 +141,8 @@ def test_flow_on_several_streams(ctx):
 
 
 def test_flow_library_cells(ctx):
-    """Fixed and library cells in one sweep, against the same gates written as
-    fixed cells where they have one (so that the two share no level shape)."""
+    """Fixed and library cells in one sweep, launched and replayed from a graph,
+    against the oracle (test_gpu_reuse.py has the bits against level launches)."""
     say("dataflow sweep: library cells")
     ops = tuple(range(9)) + tuple(synth.CELL_BASE + c for c in range(len(synth.LIBRARY)))
     nl = synth.random_dag(synth.DagSpec(5000, 100, 15, ops=ops, cells=synth.LIBRARY), 14)
