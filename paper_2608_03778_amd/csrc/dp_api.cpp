@@ -482,13 +482,21 @@ size_t seed_bytes(const dp_eval *ev, int32_t C) {
 size_t part_bytes(const dp_eval *ev) {
   return std::max<size_t>((size_t)ev->B * ev->d->pins * ev->d->n_gates * sizeof(float), 16);
 }
-dp_status ensure_flow_scratch(dp_eval *ev, int32_t C) {
-  DP_TRY(ev->seed.alloc(seed_bytes(ev, C)));
-  return ev->part.alloc(part_bytes(ev));
-}
 // (part alone may be there in another sweep's size)
 bool have_flow_scratch(const dp_eval *ev, int32_t C) {
   return ev->seed.bytes >= seed_bytes(ev, C) && ev->part.bytes >= part_bytes(ev);
+}
+dp_status ensure_flow_scratch(dp_eval *ev, int32_t C) {
+  if (have_flow_scratch(ev, C)) return DP_OK;
+  if (std::chrono::steady_clock::now() < ev->scratch_retry) return DP_OK;
+  dp_status st = ev->seed.alloc(seed_bytes(ev, C));
+  if (st == DP_OK) st = ev->part.alloc(part_bytes(ev));
+  if (st != DP_E_OOM) return st;
+  // level by level where the device has no memory for it, and again in a second
+  ev->seed.release();
+  ev->part.release();
+  ev->scratch_retry = std::chrono::steady_clock::now() + std::chrono::seconds(1);
+  return DP_OK;
 }
 // Every buffer of a reverse sweep over C columns (before any capture).
 dp_status ensure_reverse_buffers(dp_eval *ev, int32_t C, int per_column = 0) {
@@ -1053,7 +1061,7 @@ dp_status enqueue_backward(dp_eval *ev, const dp::BwdArgs &ba, float *dst) {
   const dp::GraphView g = view(d);
   double bwd_bytes = 0.0;
   for (int32_t l = d->depth; l >= 1; --l) bwd_bytes += bwd_level_bytes(d, l, ba.C);
-  if (bwd_flows(ev, ba.C)) {
+  if (bwd_flows(ev, ba.C) && have_flow_scratch(ev, ba.C)) {
     const dp::FlowCtl ctl = flow_ctl(ev);
     SpanGuard sg(ev, SPAN_BWD, bwd_bytes, ev->profiling && d->depth > 0, 1);
     DP_HIP_TRY(dp::launch_bwd_flow(
@@ -1110,6 +1118,7 @@ uint64_t reverse_key(const dp_eval *ev, const dp::BwdArgs &ba, const float *dst)
                           (const void *)ev->part.ptr, (const void *)ev->seed.ptr,
                           (const void *)ev->stream()})
     mix((uint64_t)(uintptr_t)ptr);
+  mix((uint64_t)have_flow_scratch(ev, ba.C));
   uint32_t kb;
   std::memcpy(&kb, &ba.kappa, 4);
   mix(kb);

@@ -44,6 +44,7 @@ struct dp_eval {
   int32_t sim_iters = 0;
   int32_t sim_streams = 0;                 // 0 = automatic (1)
   std::chrono::steady_clock::time_point tiles_retry;  // no word tiles before this
+  std::chrono::steady_clock::time_point scratch_retry;  // no dataflow reverse scratch before this
   int32_t sim_cols = 0;                    // columns per simulation launch, 0 = what the budget holds
   std::vector<hipStream_t> lane_streams;   // extra simulation streams (owned)
   std::vector<hipEvent_t> lane_events;     // fork + one join per extra stream

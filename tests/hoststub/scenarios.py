@@ -445,6 +445,72 @@ def scenario_tile_memory(ctx):
     return out
 
 
+def scenario_scratch_memory(ctx):
+    """Reverse sweeps on a device that holds the level launches' buffers and not
+    the dataflow sweep's, alone and in a group, and a second after there is
+    memory."""
+    import ctypes
+    import time
+    stub = ctypes.CDLL(sys.argv[1])
+    stub.stub_live_bytes.restype = ctypes.c_long
+    counts = (ctypes.c_long * 5)()
+    multi = (ctypes.c_long * 2)()
+    nl = synth.random_dag(synth.SPECS["dag2k"], 13)
+    d = api.Design(ctx, nl)
+    out = {}
+
+    def flows(call):
+        stub.stub_sweep_counts(counts)
+        before = counts[2]
+        st = status_of(call)[0]
+        stub.stub_sweep_counts(counts)
+        return [st, counts[2] > before]
+    for sched in (L.DP_SCHED_LEVEL, L.DP_SCHED_GRAPH):
+        def make():
+            ev = api.Eval(d, 16)
+            ev.set_pi_prob(synth.pi_probs(nl.n_pi, 13, batch=16))
+            ev.set_caps(synth.net_caps(nl.n_nets, 14))
+            ev.set_schedule(sched)
+            ev.forward(("power",))
+            return ev
+        ev = make()
+        out[f"{sched} all"] = flows(ev.backward)
+        live = stub.stub_live_bytes()
+        ev.close()
+        ev = make()
+        stub.stub_set_memory(live - 100_000)
+        out[f"{sched} less"] = flows(ev.backward)
+        out[f"{sched} again"] = flows(ev.backward)
+        stub.stub_set_memory(0)
+        time.sleep(1.1)
+        out[f"{sched} later"] = flows(ev.backward)
+        ev.close()
+    evs = []
+    for i in range(2):
+        ev = api.Eval(d, 16)
+        ev.set_pi_prob(synth.pi_probs(nl.n_pi, 13 + i, batch=16))
+        ev.set_caps(synth.net_caps(nl.n_nets, 14))
+        evs.append(ev)
+    grp = api.Group(ctx, evs)
+    grp.configure(use_graph=False)
+    grp.run(("power",))
+
+    def group():
+        stub.stub_multi_reverse_counts(multi)
+        before = list(multi)
+        st = status_of(grp.run, ("power",), True)[0]
+        stub.stub_multi_reverse_counts(multi)
+        return [st, multi[0] > before[0], multi[1] > before[1]]
+    live = stub.stub_live_bytes()
+    edges = len(nl.fanin)
+    stub.stub_set_memory(live + 2 * 16 * 4 * (edges + nl.n_pi) + 150_000)  # the contributions
+    out["group less"] = group()
+    stub.stub_set_memory(0)
+    time.sleep(1.1)
+    out["group later"] = group()
+    return out
+
+
 def scenario_autotune(ctx):
     """What the autotuner times (launches of word tiles and of simulation levels),
     entered with each schedule."""
@@ -643,6 +709,7 @@ if __name__ == "__main__":
               "group_serving": scenario_group_serving,
               "capture_order": scenario_capture_order,
               "group_persistent": scenario_group_persistent,
+              "scratch_memory": scenario_scratch_memory,
               "group_routes": scenario_group_routes,
               "group_after_columns": scenario_group_after_columns,
               "deep_graphs": scenario_deep_graphs,

@@ -109,6 +109,16 @@ def test_profile_books_a_joint_launch_as_simulation(stub_lib):
     assert sim1 + sim2 > sim3 and sim2 > sim1
 
 
+def test_reverse_without_memory_for_its_scratch(stub_lib):
+    r = _run(stub_lib, "scratch_memory")
+    for sched in (1, 2):  # status, a dataflow sweep (a replayed graph makes none)
+        assert r[f"{sched} all"] == ["OK", True]
+        assert r[f"{sched} less"] == r[f"{sched} again"] == ["OK", False]
+        assert r[f"{sched} later"] == ["OK", True]
+    assert r["group less"] == ["OK", False, True]  # status, dataflow, level launches
+    assert r["group later"] == ["OK", True, False]
+
+
 def test_simulation_without_memory_for_tiles(stub_lib):
     r = _run(stub_lib, "tile_memory")
     for sched in (1, 2):  # status, tiles, level launches (a replayed graph makes none)
