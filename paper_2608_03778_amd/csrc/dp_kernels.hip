@@ -2605,9 +2605,9 @@ __global__ __launch_bounds__(kBlock) void k_bwd_persistent(GraphView g, BwdArgs 
 // workgroups are members, so each wait is for work that a running wave will
 // reach: nothing depends on how many workgroups fit on the device beside
 // other streams' work.  As a guard a wait that polls ctl.limit times (seconds,
-// unless the host set less) gives up: it raises the launch's stop flag, which ends every other wait at
-// once, and the host-visible report word, and what it could not compute
-// stays NaN.
+// unless the host set less) gives up: it raises the launch's stop flag, which
+// ends every other wait at once, and the host-visible report word, and what it
+// could not compute stays NaN.
 //
 // Polls are agent-scope loads: they go past the L1, which other CUs' stores
 // do not reach, to the L2, where plain stores of the same XCD land.
